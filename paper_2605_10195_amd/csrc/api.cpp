@@ -948,6 +948,7 @@ static spex_status_t decode_attention_impl(spex_tree_t *t, const spex_node_t *le
   m.qt_ids = fused ? dp.merge_qt : nullptr;
   m.n_qtok = fused ? static_cast<int32_t>(pl.merge_qt.size())
                    : static_cast<int32_t>(pl.qt_limit.size());
+  m.avg_pieces = static_cast<int32_t>((pl.part_base.size() + pl.qt_limit.size() - 1) / pl.qt_limit.size());
   HIP_TRY(bracket(2, true));
   HIP_TRY(spex::launch_merge(t->shape, m, stream));
   HIP_TRY(bracket(2, false));

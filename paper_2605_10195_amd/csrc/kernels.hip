@@ -1608,46 +1608,101 @@ __global__ __launch_bounds__(64) void spex_generic_attn_kernel(AttnArgs p, Shape
 }
 
 // ---- merge -----------------------------------------------------------------------------------
-// Thread = (query token, query head, VEC consecutive dims).
+// One row (query token, query head) per group of slices * D / VEC threads: slice s folds pieces
+// e0 + s, e0 + s + slices, .. of the row, thread c of a slice VEC consecutive dims, and the slices
+// are folded through LDS.  Bound by latency, not bytes: a piece is a chain of two dependent reads
+// (its slot, then m, l and o), so four pieces of a slice are requested together and the row's
+// pieces are spread over the slices.
+constexpr int kMergeBatch = 4;
+
 template <int VEC>
-__global__ __launch_bounds__(256) void spex_lse_merge_kernel(MergeArgs a, Shape sh) {
-  const int dv = sh.D / VEC;
-  const int64_t tid = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-  const int64_t row = tid / dv;
-  const int c = static_cast<int>(tid % dv);
-  if (row >= static_cast<int64_t>(a.n_qtok) * sh.Hq) return;
-  const int qt = a.qt_ids ? a.qt_ids[row / sh.Hq] : static_cast<int>(row / sh.Hq);
-  const int h = static_cast<int>(row % sh.Hq);
-  const int g = h / sh.G, hh = h % sh.G;
-  const int e0 = a.part_indptr[qt], e1 = a.part_indptr[qt + 1];
-  float m = kNegInf;
-  for (int e = e0; e < e1; ++e) {
-    const int64_t slot = static_cast<int64_t>(a.part_base[e]) + static_cast<int64_t>(g) * a.part_hstride[e] + hh;
-    m = fmaxf(m, a.part_ml[slot * 2]);
-  }
-  float l = 0.f;
-  float acc[VEC];
+__global__ __launch_bounds__(256) void spex_lse_merge_kernel(MergeArgs a, Shape sh, int slices) {
+  __shared__ __attribute__((aligned(16))) float lds_o[256 * VEC];
+  __shared__ float lds_ml[256][2];
+  const int dv = sh.D / VEC, per = dv * slices, rpw = 256 / per;
+  const int r = static_cast<int>(threadIdx.x) / per, rem = static_cast<int>(threadIdx.x) % per;
+  const int s = rem / dv, c = rem % dv;
+  const int64_t row = static_cast<int64_t>(blockIdx.x) * rpw + r;
+  const bool live = r < rpw && row < static_cast<int64_t>(a.n_qtok) * sh.Hq;
+  float m = kNegInf, l = 0.f, acc[VEC];
 #pragma unroll
   for (int i = 0; i < VEC; ++i) acc[i] = 0.f;
-  for (int e = e0; e < e1; ++e) {
-    const int64_t slot = static_cast<int64_t>(a.part_base[e]) + static_cast<int64_t>(g) * a.part_hstride[e] + hh;
-    const float mj = a.part_ml[slot * 2];
-    const float lj = a.part_ml[slot * 2 + 1];
-    if (lj == 0.f) continue;
-    const float f = fast_exp2(mj - m);
-    l += lj * f;
-    const float *op = a.part_o + slot * sh.D + c * VEC;
-    if (VEC == 4) {
-      const f32x4 o = *reinterpret_cast<const f32x4 *>(op);
+  int64_t orow = 0;
+  if (live) {
+    const int qt = a.qt_ids ? a.qt_ids[row / sh.Hq] : static_cast<int>(row / sh.Hq);
+    const int h = static_cast<int>(row % sh.Hq);
+    const int g = h / sh.G, hh = h % sh.G;
+    orow = static_cast<int64_t>(qt) * sh.Hq + h;
+    const int e0 = a.part_indptr[qt], e1 = a.part_indptr[qt + 1];
+    for (int e = e0 + s; e < e1; e += kMergeBatch * slices) {
+      // entries past the row's last one repeat it (a valid read) and count nothing
+      float mj[kMergeBatch], lj[kMergeBatch], oj[kMergeBatch][VEC];
+      int64_t slot[kMergeBatch];
 #pragma unroll
-      for (int i = 0; i < VEC; ++i) acc[i] += o[i] * f;
-    } else {
+      for (int k = 0; k < kMergeBatch; ++k) {
+        const int ek = e + k * slices < e1 ? e + k * slices : e1 - 1;
+        slot[k] = static_cast<int64_t>(a.part_base[ek]) + static_cast<int64_t>(g) * a.part_hstride[ek] + hh;
+      }
 #pragma unroll
-      for (int i = 0; i < VEC; ++i) acc[i] += op[i] * f;
+      for (int k = 0; k < kMergeBatch; ++k) {
+        const f32x2 ml = *reinterpret_cast<const f32x2 *>(a.part_ml + slot[k] * 2);
+        const bool use = e + k * slices < e1 && ml[1] != 0.f;
+        mj[k] = use ? ml[0] : kNegInf;
+        lj[k] = use ? ml[1] : 0.f;
+        const float *op = a.part_o + slot[k] * sh.D + c * VEC;
+        if (VEC == 4) {
+          const f32x4 o = *reinterpret_cast<const f32x4 *>(op);
+#pragma unroll
+          for (int i = 0; i < VEC; ++i) oj[k][i] = o[i];
+        } else {
+#pragma unroll
+          for (int i = 0; i < VEC; ++i) oj[k][i] = op[i];
+        }
+      }
+      float m_new = m;
+#pragma unroll
+      for (int k = 0; k < kMergeBatch; ++k) m_new = fmaxf(m_new, mj[k]);
+      if (m_new == kNegInf) continue;  // nothing seen so far
+      const float fa = fast_exp2(m - m_new);
+      l *= fa;
+#pragma unroll
+      for (int i = 0; i < VEC; ++i) acc[i] *= fa;
+#pragma unroll
+      for (int k = 0; k < kMergeBatch; ++k) {
+        const float f = fast_exp2(mj[k] - m_new);
+        l += lj[k] * f;
+        if (lj[k] != 0.f) {
+#pragma unroll
+          for (int i = 0; i < VEC; ++i) acc[i] += oj[k][i] * f;
+        }
+      }
+      m = m_new;
     }
   }
+  if (slices > 1) {
+#pragma unroll
+    for (int i = 0; i < VEC; ++i) lds_o[threadIdx.x * VEC + i] = acc[i];
+    lds_ml[threadIdx.x][0] = m;
+    lds_ml[threadIdx.x][1] = l;
+    __syncthreads();
+    if (!live || s != 0) return;
+    float m_all = m;
+    for (int k = 1; k < slices; ++k) m_all = fmaxf(m_all, lds_ml[threadIdx.x + k * dv][0]);
+    const float f0 = fast_exp2(m - m_all);
+    l *= f0;
+#pragma unroll
+    for (int i = 0; i < VEC; ++i) acc[i] *= f0;
+    for (int k = 1; k < slices; ++k) {
+      const int t = threadIdx.x + k * dv;
+      const float f = fast_exp2(lds_ml[t][0] - m_all);
+      l += lds_ml[t][1] * f;
+#pragma unroll
+      for (int i = 0; i < VEC; ++i) acc[i] += lds_o[t * VEC + i] * f;
+    }
+    m = m_all;
+  }
+  if (!live) return;
   const float inv = 1.0f / l;
-  const int64_t orow = static_cast<int64_t>(qt) * sh.Hq + h;
   float *out = a.out + orow * sh.D + c * VEC;
   if (VEC == 4) {
     *reinterpret_cast<f32x4 *>(out) = f32x4{acc[0] * inv, acc[1] * inv, acc[2] * inv, acc[3] * inv};
@@ -2007,12 +2062,18 @@ hipError_t launch_patch(int32_t *blob, const int32_t *pairs, int32_t n, hipStrea
 hipError_t launch_merge(const Shape &sh, const MergeArgs &a, hipStream_t stream) {
   if (a.n_qtok <= 0) return hipSuccess;
   const int vec = (sh.D % 4 == 0) ? 4 : 1;
-  const int64_t threads = static_cast<int64_t>(a.n_qtok) * sh.Hq * (sh.D / vec);
-  const dim3 grid(static_cast<unsigned>((threads + 255) / 256)), block(256);
+  // Slices per row: one per kMergeBatch pieces of the average row, so that a slice runs one or two
+  // rounds, as many as 256 threads hold.
+  const int dv = sh.D / vec;
+  int slices = 1;
+  while (slices < 8 && slices * 2 * dv <= 256 && slices * kMergeBatch < a.avg_pieces) slices *= 2;
+  const int64_t rpw = 256 / (dv * slices);
+  const int64_t rows = static_cast<int64_t>(a.n_qtok) * sh.Hq;
+  const dim3 grid(static_cast<unsigned>((rows + rpw - 1) / rpw)), block(256);
   if (vec == 4)
-    hipLaunchKernelGGL(spex_lse_merge_kernel<4>, grid, block, 0, stream, a, sh);
+    hipLaunchKernelGGL(spex_lse_merge_kernel<4>, grid, block, 0, stream, a, sh, slices);
   else
-    hipLaunchKernelGGL(spex_lse_merge_kernel<1>, grid, block, 0, stream, a, sh);
+    hipLaunchKernelGGL(spex_lse_merge_kernel<1>, grid, block, 0, stream, a, sh, slices);
   return hipGetLastError();
 }
 

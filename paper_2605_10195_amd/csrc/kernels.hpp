@@ -66,6 +66,7 @@ struct MergeArgs {
   float *out, *lse;
   const int32_t *qt_ids;  // query tokens to merge, or null for 0 .. n_qtok-1
   int32_t n_qtok;         // number of query tokens handled by the launch
+  int32_t avg_pieces;     // pieces of an average query token (a hint for the launch shape)
 };
 
 constexpr int kMaxPagesPerScatter = 64;
