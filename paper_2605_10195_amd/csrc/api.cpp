@@ -909,7 +909,18 @@ static spex_status_t decode_attention_impl(spex_tree_t *t, const spex_node_t *le
   int32_t n_coop_items = 0;
   for (int c = 0; c < 3; ++c)
     n_coop_items += static_cast<int32_t>(pl.coop_items[c].size() / spex::Plan::kItemInts);
-  if (n_prefix_items + n_coop_items > 0) {
+  const bool rowmajor = !generic && spex::has_rowmajor_kernel(t->shape, a);
+  if (rowmajor) {
+    // shared and private items in one launch; every row is finished by the merge kernel
+    spex::ItemList lists[4] = {{dp.prefix_items, n_prefix_items, 16 * pl.prefix_row_tiles},
+                               {dp.suffix_items, n_suffix_items, 16 * pl.suffix_row_tiles}};
+    for (int c = 0; c < 2; ++c)
+      lists[2 + c] = {dp.coop_items[c], static_cast<int32_t>(pl.coop_items[c].size() / spex::Plan::kItemInts), 64 << c};
+    HIP_TRY(bracket(0, true));
+    HIP_TRY(spex::launch_rowmajor(t->shape, a, lists, 4, stream));
+    HIP_TRY(bracket(0, false));
+  }
+  if (!rowmajor && n_prefix_items + n_coop_items > 0) {
     HIP_TRY(bracket(0, true));
     if (n_prefix_items > 0) {
       a.items = dp.prefix_items;
@@ -927,7 +938,7 @@ static spex_status_t decode_attention_impl(spex_tree_t *t, const spex_node_t *le
     }
     HIP_TRY(bracket(0, false));
   }
-  if (n_suffix_items > 0) {
+  if (!rowmajor && n_suffix_items > 0) {
     a.items = dp.suffix_items;
     a.n_items = n_suffix_items;
     HIP_TRY(bracket(1, true));

@@ -17,8 +17,11 @@
 //       online softmax per row and emits the partial state (m, l, o).  The shared-prefix kernel
 //       stacks the rows of all branches below a node, so the node's pages are read once for all
 //       of them; the suffix kernel has the few rows of one branch and is bound by HBM bandwidth.
+//   spex_rowmajor_attn_kernel
+//       Same contract for row-major pools (fp32 KV, other page sizes and head dims): all items of a
+//       launch -- shared and private -- in one grid, scores and weighted sums as fp32 MFMAs.
 //   spex_generic_attn_kernel
-//       Same contract without matrix cores, for fp32 KV and shapes the MFMA kernels do not cover.
+//       Same contract without matrix cores, for rows that are not 16-byte aligned and as a cross-check.
 //   spex_lse_merge_kernel
 //       Combines the partial states of every query row (log-sum-exp rule) and normalises.
 //   spex_scatter_kv_kernel / spex_scatter_quant_kernel / spex_append_tokens_kernel / spex_gather_kv_kernel
@@ -1607,6 +1610,306 @@ __global__ __launch_bounds__(64) void spex_generic_attn_kernel(AttnArgs p, Shape
   }
 }
 
+// ---- row-major pools on the matrix cores --------------------------------------------------------
+// One workgroup (four wavefronts) per work item and group of up to 64 of its rows.  A wavefront
+// holds one tile of 16 rows; an item with up to 16 (32) rows has its tokens split between four
+// (two) wavefronts, which fold their softmax states through LDS at the end.
+//
+// A row-major tile is an operand as it lies in memory, because a contraction may take its index in
+// any order as long as both operands agree:
+//   S^T = K Q^T: lane (token m16, group jj) loads 16 bytes of its token's row at a time; every
+//     element (fp32) or octet (16-bit, widened fp8) of the load is one MFMA operand whose
+//     contraction index is the dim the lane holds, and Q is loaded with the same dims.
+//   The result leaves tokens 4 jj .. 4 jj + 3 of row m16 in the lane: P^T as the B operand of four
+//   MFMA 16x16x4, one per r, whose contraction runs over tokens {4 jj + r}.
+//   O^T += V^T P^T: lane (m16, jj) loads VE consecutive dims VE m16 .. of token 4 jj + r; element i
+//     is the A operand of the tile of dims {VE m + i}.
+// All products with the softmax weights are fp32 MFMAs on fp32 weights, so fp32 pools lose nothing
+// and 16-bit and fp8 values (exact in fp32) meet unrounded weights; Q K^T of 16-bit values runs on
+// the bf16 MFMA, whose products are exact in fp32.
+//
+// Why this shape: a lane per token on the vector ALU read 4 bytes per lane at a row's stride and
+// every row read K and V again.  Per 16 tokens and row tile at D = 128 a wavefront issues 32 + 4
+// (bf16) or 64 (fp32) MFMAs, about 1100 or 2050 cycles for 8 or 16 KiB of K and V, three times
+// what memory needs to deliver them, so 16 rows stay memory-bound.
+// Measured against the generic kernel (one launch each for shared and private items): fp32, one
+// tree of 4 branches, 8 heads of 64: 107.7 -> 13.5 us a call; bf16 pages of 32 tokens, 128
+// branches, 32 heads of 128: 1010 -> 55 us.  Error against 64 bits 3.5e-7 (generic 4.7e-7).
+// A wavefront's K loads for the next 16 tokens are issued right after the score MFMAs, its V loads
+// right after the PV MFMAs, page records two steps ahead.
+struct SplitLists {
+  static constexpr int kLists = 4;
+  const int32_t *items[kLists];
+  int32_t wg_end[kLists];   // workgroups of lists 0 .. k
+  int32_t n_items[kLists];
+  int32_t span[kLists];     // rows an item of the list covers from its first row on
+};
+
+template <int KV>
+struct RowMajorTraits {};
+template <>
+struct RowMajorTraits<kF32> { static constexpr int kEsz = 4; };
+template <>
+struct RowMajorTraits<kBF16> { static constexpr int kEsz = 2; };
+template <>
+struct RowMajorTraits<kFP8> { static constexpr int kEsz = 1; };
+
+template <int KV, int DP>
+__global__ __launch_bounds__(256, DP <= 128 ? 2 : 1) void spex_rowmajor_attn_kernel(AttnArgs p, Shape sh, SplitLists ls) {
+  constexpr int ESZ = RowMajorTraits<KV>::kEsz;
+  constexpr int CH = 16 / ESZ;             // elements per 16-byte load
+  constexpr int NK = DP / (4 * CH);        // K loads per lane and step
+  constexpr int VE = DP / 16 < CH ? DP / 16 : CH;  // V elements per lane and load
+  constexpr int NC = DP / (16 * VE);       // V loads per token
+  constexpr int NO = DP / 16;              // output tiles
+  constexpr int NQ = KV == kF32 ? DP / 4 : DP / 8;  // Q registers
+  constexpr int kFold = NO * 4 + 2;        // floats per lane a wavefront hands over
+  __shared__ float fold[3 * 64 * kFold];
+
+  const int lane = threadIdx.x & 63, m16 = lane & 15, jj = lane >> 4;
+  const int w = uniform(threadIdx.x >> 6);
+  int k = 0;
+#pragma unroll
+  for (int i = 0; i + 1 < SplitLists::kLists; ++i) k += static_cast<int>(blockIdx.x) >= ls.wg_end[i] ? 1 : 0;
+  const int32_t *list = ls.items[0];
+  int first_wg = 0, n_items = ls.n_items[0], span = ls.span[0];
+#pragma unroll
+  for (int i = 1; i < SplitLists::kLists; ++i) {
+    list = k == i ? ls.items[i] : list;
+    first_wg = k == i ? ls.wg_end[i - 1] : first_wg;
+    n_items = k == i ? ls.n_items[i] : n_items;
+    span = k == i ? ls.span[i] : span;
+  }
+  const int local = static_cast<int>(blockIdx.x) - first_wg;
+  const int group = local / n_items;       // 64 rows each
+  const Item it = load_item(list, local - group * n_items);
+  if (it.pg_count == 0) return;            // padding item
+  const int D = sh.D, G = sh.G, rows = it.qt_count * G;
+  const int row_end = min(rows, it.row0 + span);
+  const int row_lo = it.row0 + group * 64;
+  if (row_lo >= row_end) return;           // whole workgroup
+  const int here = row_end - row_lo;
+  const int ks_log = here <= 16 ? 2 : (here <= 32 ? 1 : 0);  // log2 of the wavefronts per row tile
+  const int rt = w >> ks_log, ks = w & ((1 << ks_log) - 1);
+  const int row_base = row_lo + rt * 16;
+  const bool has_rows = row_base < row_end;
+
+  const int logp = 31 - __builtin_clz(sh.P);
+  const int n_slots = it.pg_count << logp;
+  const int n_steps = (n_slots + 15) >> 4;
+  const int step0 = (n_steps * ks) >> ks_log, step1 = (n_steps * (ks + 1)) >> ks_log;
+
+  // ---- rows
+  const int row = row_base + m16;
+  const bool row_ok = row < row_end;
+  int limit = 0, qt = 0, d_base = 0;
+  uint32_t d_mask = 0;
+  u32x4 q[NQ / 4];
+#pragma unroll
+  for (int i = 0; i < NQ / 4; ++i) q[i] = u32x4{0, 0, 0, 0};
+  if (row_ok) {
+    const int2 qr = *reinterpret_cast<const int2 *>(p.qt_rec + 2 * (it.qt_begin + row / G));
+    qt = qr.x;
+    limit = qr.y;
+    if (p.qt_mask) {
+      const int2 dm = *reinterpret_cast<const int2 *>(p.qt_mask + 2 * qt);
+      d_base = limit - 1 - dm.x;
+      d_mask = static_cast<uint32_t>(dm.y);
+    }
+    const int64_t qrow = (static_cast<int64_t>(qt) * sh.Hq + it.g * G + row % G) * D;
+#pragma unroll
+    for (int i = 0; i < NQ / 4; ++i) {
+      // fp32: load i covers dims 16 i + 4 jj ..; bf16: 32 i + 8 jj ..; against fp8 K two octets per load
+      const int d = KV == kF32 ? 16 * i + 4 * jj : (KV == kBF16 ? 32 * i + 8 * jj : 64 * (i >> 1) + 16 * jj + 8 * (i & 1));
+      if (d < D)
+        q[i] = *reinterpret_cast<const u32x4 *>(static_cast<const char *>(p.q) + (qrow + d) * (KV == kF32 ? 4 : 2));
+    }
+  }
+
+  f32x4 o[NO];
+#pragma unroll
+  for (int i = 0; i < NO; ++i) o[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+  float m = kWalkMInit, l = 0.f;
+
+  const int64_t tile_bytes = static_cast<int64_t>(D) * ESZ << logp;
+  const char *kpool = static_cast<const char *>(p.k_pool), *vpool = static_cast<const char *>(p.v_pool);
+  // Page record of the token whose K row the lane loads (token m16 of the step) and of the four
+  // tokens whose V rows it loads and whose scores it gets (4 jj .. 4 jj + 3: one page, P >= 4).
+  struct Rec {
+    int2 k, v;
+  };
+  auto rec_of = [&](int step) {
+    const int last = it.pg_count - 1;
+    const int s = min(step, step1 - 1) << 4;
+    Rec r;
+    r.k = *reinterpret_cast<const int2 *>(p.pg_rec + 2 * (it.pg_begin + min((s + m16) >> logp, last)));
+    r.v = *reinterpret_cast<const int2 *>(p.pg_rec + 2 * (it.pg_begin + min((s + 4 * jj) >> logp, last)));
+    return r;
+  };
+  // Dims past D (D < DP) are read from the start of the row instead, so that no load is
+  // conditional: in K they meet zeros of Q, in V they make output dims that are not written.
+  u32x4 kr[NK];
+  auto load_k = [&](const Rec &r, int step) {
+    const int slot = ((step << 4) + m16) & (sh.P - 1);
+    const char *src = kpool + (static_cast<int64_t>(r.k.x) * sh.page_tiles + it.g) * tile_bytes +
+                      static_cast<int64_t>(slot) * D * ESZ;
+#pragma unroll
+    for (int i = 0; i < NK; ++i)
+      kr[i] = *reinterpret_cast<const u32x4 *>(src + (4 * CH * i + CH * jj < D ? 64 * i + 16 * jj : 0));
+  };
+  struct VReg {
+    uint32_t w[VE * ESZ / 4];
+  };
+  VReg vr[4][NC];
+  int v_off[NC];
+#pragma unroll
+  for (int c = 0; c < NC; ++c) v_off[c] = 16 * VE * c + VE * m16 < D ? 16 * VE * c : -VE * m16;
+  auto load_v = [&](const Rec &r, int step) {
+    const int slot = ((step << 4) + 4 * jj) & (sh.P - 1);
+    const char *src = vpool + (static_cast<int64_t>(r.v.x) * sh.page_tiles + it.g) * tile_bytes +
+                      (static_cast<int64_t>(slot) * D + VE * m16) * ESZ;
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+#pragma unroll
+      for (int c = 0; c < NC; ++c)
+        __builtin_memcpy(&vr[t][c], __builtin_assume_aligned(src + (t * D + v_off[c]) * ESZ, VE * ESZ), VE * ESZ);
+  };
+
+  if (has_rows && step0 < step1) {
+    Rec cur = rec_of(step0), nxt = rec_of(step0 + 1);
+    load_k(cur, step0);
+    load_v(cur, step0);
+    for (int st = step0; st < step1; ++st) {
+      const Rec nxt2 = rec_of(st + 2);
+      float ks_l = 1.f, vs_l = 1.f;
+      if (KV == kFP8) {
+        ks_l = p.k_scale[static_cast<int64_t>(cur.v.x) * sh.Hkv + it.g];
+        vs_l = p.v_scale[static_cast<int64_t>(cur.v.x) * sh.Hkv + it.g];
+      }
+      f32x4 sa = {0.f, 0.f, 0.f, 0.f}, sb = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int i = 0; i < NK; ++i) {
+        if (KV == kF32) {
+          const f32x4 kv = __builtin_bit_cast(f32x4, kr[i]), qv = __builtin_bit_cast(f32x4, q[i]);
+          sa = __builtin_amdgcn_mfma_f32_16x16x4f32(kv[0], qv[0], sa, 0, 0, 0);
+          sb = __builtin_amdgcn_mfma_f32_16x16x4f32(kv[1], qv[1], sb, 0, 0, 0);
+          sa = __builtin_amdgcn_mfma_f32_16x16x4f32(kv[2], qv[2], sa, 0, 0, 0);
+          sb = __builtin_amdgcn_mfma_f32_16x16x4f32(kv[3], qv[3], sb, 0, 0, 0);
+        } else if (KV == kBF16) {
+          f32x4 &acc = (i & 1) ? sb : sa;
+          acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kr[i]), __builtin_bit_cast(bf16x8, q[i]), acc, 0, 0, 0);
+        } else {
+          sa = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fp8x8_to_bf16x8(kr[i][0], kr[i][1]), __builtin_bit_cast(bf16x8, q[2 * i]), sa, 0, 0, 0);
+          sb = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fp8x8_to_bf16x8(kr[i][2], kr[i][3]), __builtin_bit_cast(bf16x8, q[2 * i + 1]), sb, 0, 0, 0);
+        }
+      }
+      load_k(nxt, min(st + 1, step1 - 1));
+      // ---- what the row sees of the lane's four tokens
+      const int slot = ((st << 4) + 4 * jj) & (sh.P - 1);
+      const int pos = (cur.v.y >> 7) + slot;
+      int have = (st << 4) + 4 * jj < n_slots ? (cur.v.y & 127) - slot : 0;
+      uint32_t vm = 0xfu;
+      if (p.qt_mask) {
+        const int shift = pos - d_base + 32;
+        const uint64_t bits = (static_cast<uint64_t>(d_mask) << 32) | 0xffffffffull;
+        vm = shift <= 0 ? 0xfu : (shift >= 64 ? 0u : static_cast<uint32_t>(bits >> shift) & 0xfu);
+      } else {
+        have = min(have, limit - pos);
+      }
+      const float c = p.scale_log2 * ks_l;
+      float x[4];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        x[r] = (sa[r] + sb[r]) * c;
+        x[r] = (r < have && ((vm >> r) & 1u)) ? x[r] : kNegInf;
+      }
+      // softmax reference as in the tree-walk kernel: moves only when a score exceeds it by 2^8 in weight
+      const float mx = fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3]));
+      if (__any(mx > m + 8.f)) {
+        const float rmax = row_group_max(mx);
+        const float m_new = rmax > m + 8.f ? rmax : m;
+        const float alpha = fast_exp2(m - m_new);
+        m = m_new;
+        l *= alpha;
+#pragma unroll
+        for (int i = 0; i < NO; ++i) o[i] *= alpha;
+      }
+      float pr[4];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        pr[r] = fast_exp2(x[r] - m);
+        l += pr[r];
+        if (KV == kFP8) pr[r] *= vs_l;
+      }
+#pragma unroll
+      for (int t = 0; t < 4; ++t)
+#pragma unroll
+        for (int cc = 0; cc < NC; ++cc)
+#pragma unroll
+          for (int i = 0; i < VE; ++i) {
+            float v;
+            if (KV == kF32) {
+              v = __builtin_bit_cast(float, vr[t][cc].w[i]);
+            } else if (KV == kBF16) {
+              const uint32_t wd = vr[t][cc].w[i / 2];
+              v = __builtin_bit_cast(float, (i & 1) ? wd & 0xffff0000u : wd << 16);
+            } else {
+              const int wd = static_cast<int>(vr[t][cc].w[i / 4]);
+              const f32x2 two = (i & 2) ? __builtin_amdgcn_cvt_pk_f32_fp8(wd, true) : __builtin_amdgcn_cvt_pk_f32_fp8(wd, false);
+              v = two[i & 1];
+            }
+            o[cc * VE + i] = __builtin_amdgcn_mfma_f32_16x16x4f32(v, pr[t], o[cc * VE + i], 0, 0, 0);
+          }
+      load_v(nxt, min(st + 1, step1 - 1));
+      cur = nxt;
+      nxt = nxt2;
+    }
+  }
+  l += __shfl_xor(l, 16);  // the row sum is spread over the four lane groups
+  l += __shfl_xor(l, 32);
+
+  // ---- the wavefronts of one row tile fold their states
+  if (ks_log > 0) {
+    if (ks > 0) {
+      float *f = fold + static_cast<int>(w - rt - 1) * (64 * kFold) + lane;
+#pragma unroll
+      for (int i = 0; i < NO; ++i)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) f[(i * 4 + r) * 64] = o[i][r];
+      f[NO * 4 * 64] = m;
+      f[(NO * 4 + 1) * 64] = l;
+    }
+    __syncthreads();
+    if (ks > 0) return;
+    for (int j = 1; j < (1 << ks_log); ++j) {
+      const float *f = fold + static_cast<int>(w + j - rt - 1) * (64 * kFold) + lane;
+      const float mj = f[NO * 4 * 64], m_new = fmaxf(m, mj);
+      const float fa = fast_exp2(m - m_new), fb = fast_exp2(mj - m_new);
+      m = m_new;
+      l = l * fa + f[(NO * 4 + 1) * 64] * fb;
+#pragma unroll
+      for (int i = 0; i < NO; ++i)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) o[i][r] = o[i][r] * fa + f[(i * 4 + r) * 64] * fb;
+    }
+  }
+  if (!row_ok) return;
+  const int64_t slot = static_cast<int64_t>(it.pbase) + static_cast<int64_t>(it.g) * rows + row;
+  if (jj == 0) *reinterpret_cast<f32x2 *>(p.part_ml + slot * 2) = f32x2{m, l};
+  // the lane holds dims 16 VE c + 4 VE jj .. + 4 VE - 1 of its row
+#pragma unroll
+  for (int c = 0; c < NC; ++c)
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+#pragma unroll
+      for (int h = 0; h < VE / 4; ++h) {
+        const int d = 16 * VE * c + 4 * VE * jj + VE * r + 4 * h;
+        if (d < D)
+          *reinterpret_cast<f32x4 *>(p.part_o + slot * D + d) =
+              f32x4{o[c * VE + 4 * h][r], o[c * VE + 4 * h + 1][r], o[c * VE + 4 * h + 2][r], o[c * VE + 4 * h + 3][r]};
+      }
+}
+
 // ---- merge -----------------------------------------------------------------------------------
 // One row (query token, query head) per group of slices * D / VEC threads: slice s folds pieces
 // e0 + s, e0 + s + slices, .. of the row, thread c of a slice VEC consecutive dims, and the slices
@@ -1970,6 +2273,46 @@ hipError_t launch_attention(const Shape &sh, const AttnArgs &a, bool prefix, int
   if (sh.kv_dtype == kBF16 && sh.q_dtype == kBF16) return launch_generic<kBF16, kBF16>(sh, a, rows_per_item, stream);
   if (sh.kv_dtype == kFP8 && sh.q_dtype == kBF16) return launch_generic<kFP8, kBF16>(sh, a, rows_per_item, stream);
   return hipErrorInvalidValue;
+}
+
+bool has_rowmajor_kernel(const Shape &sh, const AttnArgs &a) {
+  // 16-byte loads of whole rows: rows and buffers must be 16-byte aligned; four tokens of a lane
+  // must share a page.  Anything else goes to the generic kernel.
+  const int ch = sh.kv_dtype == kF32 ? 4 : (sh.kv_dtype == kBF16 ? 8 : 16);
+  const bool types = sh.kv_dtype == kF32 ? sh.q_dtype == kF32 : sh.q_dtype == kBF16;
+  auto aligned = [](const void *x) { return (reinterpret_cast<uintptr_t>(x) & 15) == 0; };
+  return sh.layout == kRowMajor && types && sh.P >= 4 && sh.D % ch == 0 && sh.D <= 256 && aligned(a.k_pool) &&
+         aligned(a.v_pool) && aligned(a.q);
+}
+
+template <int KV>
+static hipError_t launch_rowmajor_kv(const Shape &sh, const AttnArgs &a, const SplitLists &ls, int n_wg, hipStream_t stream) {
+  const dim3 grid(n_wg), block(256);
+  if (sh.D <= 64)
+    hipLaunchKernelGGL((spex_rowmajor_attn_kernel<KV, 64>), grid, block, 0, stream, a, sh, ls);
+  else if (sh.D <= 128)
+    hipLaunchKernelGGL((spex_rowmajor_attn_kernel<KV, 128>), grid, block, 0, stream, a, sh, ls);
+  else
+    hipLaunchKernelGGL((spex_rowmajor_attn_kernel<KV, 256>), grid, block, 0, stream, a, sh, ls);
+  return hipGetLastError();
+}
+
+hipError_t launch_rowmajor(const Shape &sh, const AttnArgs &a, const ItemList *lists, int n_lists, hipStream_t stream) {
+  if (!has_rowmajor_kernel(sh, a) || n_lists > SplitLists::kLists) return hipErrorInvalidValue;
+  SplitLists ls{};
+  int64_t n_wg = 0;
+  for (int k = 0; k < SplitLists::kLists; ++k) {
+    ls.items[k] = k < n_lists ? lists[k].items : nullptr;
+    ls.n_items[k] = k < n_lists && lists[k].n_items > 0 ? lists[k].n_items : 1;  // a divisor
+    ls.span[k] = k < n_lists ? lists[k].rows_per_item : 0;
+    if (k < n_lists) n_wg += static_cast<int64_t>(lists[k].n_items) * ((lists[k].rows_per_item + 63) / 64);
+    if (n_wg > INT32_MAX) return hipErrorInvalidValue;
+    ls.wg_end[k] = static_cast<int32_t>(n_wg);
+  }
+  if (n_wg == 0) return hipSuccess;
+  if (sh.kv_dtype == kF32) return launch_rowmajor_kv<kF32>(sh, a, ls, static_cast<int>(n_wg), stream);
+  if (sh.kv_dtype == kBF16) return launch_rowmajor_kv<kBF16>(sh, a, ls, static_cast<int>(n_wg), stream);
+  return launch_rowmajor_kv<kFP8>(sh, a, ls, static_cast<int>(n_wg), stream);
 }
 
 template <int KV, int D>

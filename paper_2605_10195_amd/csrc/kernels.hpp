@@ -113,6 +113,14 @@ struct GatherArgs {
 // number of 16-row MFMA tiles per wavefront the item list was built for.
 hipError_t launch_attention(const Shape &sh, const AttnArgs &a, bool prefix, int row_tiles,
                             bool force_generic, hipStream_t stream);
+// Row-major pools: every item of all lists in one launch (n_lists <= 4).  rows_per_item: rows an item
+// of the list covers from its first row on.
+struct ItemList {
+  const int32_t *items;
+  int32_t n_items, rows_per_item;
+};
+bool has_rowmajor_kernel(const Shape &sh, const AttnArgs &a);
+hipError_t launch_rowmajor(const Shape &sh, const AttnArgs &a, const ItemList *lists, int n_lists, hipStream_t stream);
 hipError_t launch_merge(const Shape &sh, const MergeArgs &a, hipStream_t stream);
 hipError_t launch_scatter(const Shape &sh, const ScatterArgs &a, hipStream_t stream);
 // fp8 pools: k_src / v_src hold bf16 values; page scales are computed (started pages) or reused.
