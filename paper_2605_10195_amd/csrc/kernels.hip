@@ -24,9 +24,13 @@
 //       Same contract without matrix cores, for rows that are not 16-byte aligned and as a cross-check.
 //   spex_lse_merge_kernel
 //       Combines the partial states of every query row (log-sum-exp rule) and normalises.
-//   spex_scatter_kv_kernel / spex_scatter_quant_kernel / spex_append_tokens_kernel / spex_gather_kv_kernel
-//       Write appended tokens into (a run for one node, the same quantised to e4m3 on the way, one
-//       token for each of many nodes) / read tokens out of the paged pool.
+//   spex_write_tiles_kernel / spex_write_rows_kernel / spex_read_pages_kernel
+//       Write a run of one node's tokens into the paged pool (quantised to e4m3 on the way where asked
+//       for) / read tokens out of it, a page and kv head per workgroup, 16 bytes at a time.
+//   spex_scatter_kv_kernel / spex_scatter_quant_kernel / spex_gather_kv_kernel
+//       The same element by element, for rows or buffers that are not 16-byte aligned.
+//   spex_append_tokens_kernel
+//       One token for each of many nodes.
 //   spex_patch_plan_kernel
 //       Applies {index, value} patches to the device copy of the cached launch lists.
 #include "kernels.hpp"
@@ -2139,6 +2143,288 @@ __global__ __launch_bounds__(256) void spex_scatter_quant_kernel(ScatterArgs a, 
   }
 }
 
+// ---- whole pages in and out ---------------------------------------------------------------------
+// One workgroup per (page, kv head).  Both sides are bound by memory, and by the launch for a step
+// of a few pages, so every access of a tile or of a token's row is 16 bytes (8 where an fp8 chunk
+// has to be put together), V crosses LDS because a tile holds it token-minor, and one launch takes
+// up to kMaxPagesPerScatter pages.  The element kernels above moved 2 bytes per access and
+// 64 pages per launch; they remain for rows or buffers that are not 16-byte aligned.
+// Slots [lo, fill) of the page are written: tokens up to hi, zeros from there to the end of a page
+// the append starts.
+struct PageSpan {
+  int pi, g, lo, hi, fill, tok0;  // token of slot s: s - tok0
+  bool is_new;
+};
+__device__ __forceinline__ PageSpan page_span(const ScatterArgs &a, const Shape &sh) {
+  PageSpan s;
+  s.g = static_cast<int>(blockIdx.x) % sh.Hkv;
+  s.pi = static_cast<int>(blockIdx.x) / sh.Hkv;
+  s.is_new = s.pi > 0 || a.first_page_is_new;
+  s.tok0 = a.first_slot - s.pi * sh.P;
+  s.lo = s.pi == 0 ? a.first_slot : 0;
+  s.hi = min(sh.P, s.tok0 + a.n_tokens);
+  s.fill = s.is_new ? sh.P : s.hi;
+  return s;
+}
+
+__device__ __forceinline__ uint16_t half_word(const u32x4 &v, int i) {
+  return static_cast<uint16_t>(v[i >> 1] >> (16 * (i & 1)));
+}
+
+// Page scales of a quantising append: from the largest magnitudes of the workgroup's tokens for a
+// page it starts, else the page's own.  Also writes the scales of a started page.
+struct Scales {
+  float k, v;
+};
+__device__ __forceinline__ Scales quant_scales(const ScatterArgs &a, bool is_new, int sidx, float ka, float va) {
+  __shared__ float red[2][4];
+  Scales s;
+  if (is_new) {  // uniform over the workgroup
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) {
+      ka = fmaxf(ka, __shfl_xor(ka, o));
+      va = fmaxf(va, __shfl_xor(va, o));
+    }
+    if ((threadIdx.x & 63) == 0) {
+      red[0][threadIdx.x >> 6] = ka;
+      red[1][threadIdx.x >> 6] = va;
+    }
+    __syncthreads();
+    ka = fmaxf(fmaxf(red[0][0], red[0][1]), fmaxf(red[0][2], red[0][3]));
+    va = fmaxf(fmaxf(red[1][0], red[1][1]), fmaxf(red[1][2], red[1][3]));
+    s.k = fmaxf(ka / 448.0f, 0x1p-40f);
+    s.v = fmaxf(va / 448.0f, 0x1p-40f);
+    if (threadIdx.x == 0) {
+      a.k_scale[sidx] = s.k;
+      a.v_scale[sidx] = s.v;
+    }
+  } else {
+    s.k = a.k_scale[sidx];
+    s.v = a.v_scale[sidx];
+  }
+  return s;
+}
+__device__ __forceinline__ float abs_max8(const u32x4 &x) {
+  float m = 0.f;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) m = fmaxf(m, __builtin_fabsf(bf16_bits_to_float(half_word(x, i))));
+  return m;
+}
+__device__ __forceinline__ u32x2 encode8(const u32x4 &x, float inv) {
+  u32x2 r = {0, 0};
+#pragma unroll
+  for (int i = 0; i < 8; ++i) r[i >> 2] |= encode_e4m3(bf16_bits_to_float(half_word(x, i)) * inv) << (8 * (i & 3));
+  return r;
+}
+
+// Tiled pools.  bf16: K chunks of 8 dims of a token go straight to their place, V through LDS as
+// fp16.  fp8: K and V codes (given, or encoded here with QUANT) through LDS.
+template <int KV, int D, bool QUANT>
+__global__ __launch_bounds__(256) void spex_write_tiles_kernel(ScatterArgs a, Shape sh) {
+  constexpr bool FP8 = KV == kFP8;
+  constexpr int CH = (FP8 && !QUANT) ? 16 : 8;       // elements per 16-byte piece of a source row
+  constexpr int ESZ = FP8 ? 1 : 2, SSZ = (FP8 && !QUANT) ? 1 : 2;
+  constexpr int N = 16 * D / CH;                      // source pieces of a page, <= 256
+  constexpr int ROW = D * ESZ + 16;                   // LDS bytes per token
+  __shared__ __attribute__((aligned(16))) char ldsk[FP8 ? 16 * ROW : 16];
+  __shared__ __attribute__((aligned(16))) char ldsv[16 * ROW];
+  const PageSpan ps = page_span(a, sh);
+  const int page = a.page_ids[ps.pi], H = sh.Hkv, tid = threadIdx.x;
+  char *kt = static_cast<char *>(a.k_pool) + (static_cast<int64_t>(page) * sh.page_tiles + ps.g) * (16 * D * ESZ);
+  char *vt = static_cast<char *>(a.v_pool) + (static_cast<int64_t>(page) * sh.page_tiles + ps.g) * (16 * D * ESZ);
+  const int slot = tid / (D / CH), d = tid % (D / CH) * CH;
+  u32x4 kx = {0, 0, 0, 0}, vx = {0, 0, 0, 0};
+  if (tid < N && slot >= ps.lo && slot < ps.hi) {
+    const int64_t src = ((static_cast<int64_t>(slot - ps.tok0) * H + ps.g) * D + d) * SSZ;
+    kx = *reinterpret_cast<const u32x4 *>(static_cast<const char *>(a.k_src) + src);
+    vx = *reinterpret_cast<const u32x4 *>(static_cast<const char *>(a.v_src) + src);
+  }
+  const int sidx = page * H + ps.g;
+  if (QUANT) {
+    const Scales s = quant_scales(a, ps.is_new, sidx, abs_max8(kx), abs_max8(vx));
+    if (tid < N) {  // zeros of unused slots encode to zero codes
+      *reinterpret_cast<u32x2 *>(ldsk + slot * ROW + d) = encode8(kx, 1.0f / s.k);
+      *reinterpret_cast<u32x2 *>(ldsv + slot * ROW + d) = encode8(vx, 1.0f / s.v);
+    }
+  } else if (FP8) {
+    if (tid < N) {
+      *reinterpret_cast<u32x4 *>(ldsk + slot * ROW + d) = kx;
+      *reinterpret_cast<u32x4 *>(ldsv + slot * ROW + d) = vx;
+    }
+    if (ps.is_new && tid == 0) {
+      const int idx_new = ps.pi - (a.first_page_is_new ? 0 : 1);
+      a.k_scale[sidx] = a.k_scale_src[idx_new * H + ps.g];
+      a.v_scale[sidx] = a.v_scale_src[idx_new * H + ps.g];
+    }
+  } else if (tid < N) {
+    if (slot >= ps.lo && slot < ps.fill)
+      *reinterpret_cast<u32x4 *>(kt + 2 * k_offset<KV, kMfmaTiled>(slot, d, D)) = kx;
+    u32x4 h;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      h[i] = bf16_bits_to_f16_bits(half_word(vx, 2 * i)) | static_cast<uint32_t>(bf16_bits_to_f16_bits(half_word(vx, 2 * i + 1))) << 16;
+    *reinterpret_cast<u32x4 *>(ldsv + slot * ROW + 2 * d) = h;
+  }
+  __syncthreads();
+  // 16-byte pieces of the tiles, in memory order
+  constexpr int NT = 16 * D * ESZ / 16;
+  if (tid >= NT) return;
+  if (FP8) {
+    const int half = tid / (D / 2), rem = tid % (D / 2), s = rem / 32, j = rem / 8 % 4, tt = rem % 8;
+    const int t = (tt >> 2) * 8 + 4 * half + (tt & 3);
+    if (t >= ps.lo && t < ps.fill) {
+      const u32x2 lo = *reinterpret_cast<const u32x2 *>(ldsk + t * ROW + 64 * s + 8 * j);
+      const u32x2 hi = *reinterpret_cast<const u32x2 *>(ldsk + t * ROW + 64 * s + 32 + 8 * j);
+      *reinterpret_cast<u32x4 *>(kt + 16 * tid) = u32x4{lo[0], lo[1], hi[0], hi[1]};
+    }
+    const int vd = tid / 32 * 32 + tid % 16, t0 = tid / 16 % 2 * 8;  // dims vd and vd + 16 of tokens t0 .. t0 + 7
+    uint32_t b[4] = {0, 0, 0, 0};
+#pragma unroll
+    for (int i = 0; i < 16; ++i)
+      b[i >> 2] |= static_cast<uint32_t>(static_cast<uint8_t>(ldsv[(t0 + (i & 7)) * ROW + vd + (i >> 3) * 16])) << (8 * (i & 3));
+    if (t0 >= ps.lo && t0 + 8 <= ps.fill) {
+      *reinterpret_cast<u32x4 *>(vt + 16 * tid) = u32x4{b[0], b[1], b[2], b[3]};
+    } else {
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        const int t1 = t0 + (i & 7);
+        if (t1 >= ps.lo && t1 < ps.fill) vt[16 * tid + i] = static_cast<char>(b[i >> 2] >> (8 * (i & 3)));
+      }
+    }
+  } else {
+    const int vd = tid / 32 * 16 + tid % 16, t0 = tid / 16 % 2 * 8;
+    uint32_t b[4] = {0, 0, 0, 0};
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+      b[i >> 1] |= static_cast<uint32_t>(*reinterpret_cast<const uint16_t *>(ldsv + (t0 + i) * ROW + 2 * vd)) << (16 * (i & 1));
+    if (t0 >= ps.lo && t0 + 8 <= ps.fill) {
+      *reinterpret_cast<u32x4 *>(vt + 16 * tid) = u32x4{b[0], b[1], b[2], b[3]};
+    } else {
+#pragma unroll
+      for (int i = 0; i < 8; ++i)
+        if (t0 + i >= ps.lo && t0 + i < ps.fill)
+          *reinterpret_cast<uint16_t *>(vt + 16 * tid + 2 * i) = static_cast<uint16_t>(b[i >> 1] >> (16 * (i & 1)));
+    }
+  }
+}
+
+// Row-major pools: rows are copied (or encoded, 8 dims at a time) as they are.
+template <int KV, bool QUANT>
+__global__ __launch_bounds__(256) void spex_write_rows_kernel(ScatterArgs a, Shape sh) {
+  constexpr int ESZ = RowMajorTraits<KV>::kEsz, SSZ = QUANT ? 2 : ESZ, CH = 16 / SSZ;
+  constexpr int kMaxRounds = 64 * 256 / 8 / 256;      // pieces per thread of the largest quantised page
+  const PageSpan ps = page_span(a, sh);
+  const int page = a.page_ids[ps.pi], H = sh.Hkv, D = sh.D, tid = threadIdx.x;
+  const int per = D / CH, n = sh.P * per;
+  const int64_t tile = (static_cast<int64_t>(page) * sh.page_tiles + ps.g) * (static_cast<int64_t>(sh.P) * D * ESZ);
+  char *kt = static_cast<char *>(a.k_pool) + tile, *vt = static_cast<char *>(a.v_pool) + tile;
+  const int sidx = page * H + ps.g;
+  auto source = [&](int c, const void *base) {
+    const int slot = c / per;
+    u32x4 x = {0, 0, 0, 0};
+    if (slot >= ps.lo && slot < ps.hi)
+      x = *reinterpret_cast<const u32x4 *>(static_cast<const char *>(base) +
+                                           ((static_cast<int64_t>(slot - ps.tok0) * H + ps.g) * D + c % per * CH) * SSZ);
+    return x;
+  };
+  if (QUANT) {
+    u32x4 kx[kMaxRounds], vx[kMaxRounds];
+    float ka = 0.f, va = 0.f;
+#pragma unroll
+    for (int r = 0; r < kMaxRounds; ++r) {
+      kx[r] = vx[r] = u32x4{0, 0, 0, 0};
+      if (r * 256 + tid < n) {
+        kx[r] = source(r * 256 + tid, a.k_src);
+        vx[r] = source(r * 256 + tid, a.v_src);
+      }
+      ka = fmaxf(ka, abs_max8(kx[r]));
+      va = fmaxf(va, abs_max8(vx[r]));
+    }
+    const Scales s = quant_scales(a, ps.is_new, sidx, ka, va);
+#pragma unroll
+    for (int r = 0; r < kMaxRounds; ++r) {
+      const int c = r * 256 + tid, slot = c / per;
+      if (c < n && slot >= ps.lo && slot < ps.fill) {
+        *reinterpret_cast<u32x2 *>(kt + c * 8) = encode8(kx[r], 1.0f / s.k);
+        *reinterpret_cast<u32x2 *>(vt + c * 8) = encode8(vx[r], 1.0f / s.v);
+      }
+    }
+  } else {
+    for (int c = tid; c < n; c += 256) {
+      const int slot = c / per;
+      const u32x4 kx = source(c, a.k_src), vx = source(c, a.v_src);
+      if (slot >= ps.lo && slot < ps.fill) {
+        *reinterpret_cast<u32x4 *>(kt + c * 16) = kx;
+        *reinterpret_cast<u32x4 *>(vt + c * 16) = vx;
+      }
+    }
+    if (KV == kFP8 && ps.is_new && tid == 0) {
+      const int idx_new = ps.pi - (a.first_page_is_new ? 0 : 1);
+      a.k_scale[sidx] = a.k_scale_src[idx_new * H + ps.g];
+      a.v_scale[sidx] = a.v_scale_src[idx_new * H + ps.g];
+    }
+  }
+}
+
+// Tokens of a page back in logical order (the inverse of the two kernels above).
+template <int KV, int LAYOUT>
+__global__ __launch_bounds__(256) void spex_read_pages_kernel(GatherArgs a, Shape sh) {
+  constexpr bool TILED = LAYOUT == kMfmaTiled;
+  constexpr int ESZ = RowMajorTraits<KV>::kEsz, CH = 16 / ESZ;
+  constexpr int kRowMax = 128 * ESZ + 16;             // LDS bytes per token, tiled pools
+  __shared__ __attribute__((aligned(16))) char ldsv[TILED ? 16 * kRowMax : 16];
+  const int H = sh.Hkv, D = sh.D, tid = threadIdx.x;
+  const int g = static_cast<int>(blockIdx.x) % H, pi = static_cast<int>(blockIdx.x) / H;
+  const int page = a.page_ids[pi], tok0 = a.first_slot - pi * sh.P;
+  const int lo = pi == 0 ? a.first_slot : 0, hi = min(sh.P, tok0 + a.n_tokens);
+  const int64_t tile = (static_cast<int64_t>(page) * sh.page_tiles + g) * (static_cast<int64_t>(sh.P) * D * ESZ);
+  const char *kt = static_cast<const char *>(a.k_pool) + tile, *vt = static_cast<const char *>(a.v_pool) + tile;
+  char *ko = static_cast<char *>(a.k_out), *vo = static_cast<char *>(a.v_out);
+  auto dst = [&](int slot, int d) { return ((static_cast<int64_t>(slot - tok0) * H + g) * D + d) * ESZ; };
+  if (KV == kFP8 && tid < sh.P && tid >= lo && tid < hi) {
+    const int64_t at = static_cast<int64_t>(tid - tok0) * H + g;
+    if (a.k_scale_out) a.k_scale_out[at] = a.k_scale[page * H + g];
+    if (a.v_scale_out) a.v_scale_out[at] = a.v_scale[page * H + g];
+  }
+  if (!TILED) {
+    const int per = D / CH, n = sh.P * per;
+    for (int c = tid; c < n; c += 256) {
+      const int slot = c / per;
+      if (slot < lo || slot >= hi) continue;
+      *reinterpret_cast<u32x4 *>(ko + dst(slot, c % per * CH)) = *reinterpret_cast<const u32x4 *>(kt + c * 16);
+      *reinterpret_cast<u32x4 *>(vo + dst(slot, c % per * CH)) = *reinterpret_cast<const u32x4 *>(vt + c * 16);
+    }
+    return;
+  }
+  const int n = 16 * D * ESZ / 16, row = D * ESZ + 16;  // <= 256 pieces of 16 bytes
+  if (tid < n) {
+    const u32x4 kx = *reinterpret_cast<const u32x4 *>(kt + 16 * tid), vx = *reinterpret_cast<const u32x4 *>(vt + 16 * tid);
+    if (KV == kFP8) {
+      const int half = tid / (D / 2), rem = tid % (D / 2), s = rem / 32, j = rem / 8 % 4, tt = rem % 8;
+      const int t = (tt >> 2) * 8 + 4 * half + (tt & 3);
+      if (t >= lo && t < hi) {
+        *reinterpret_cast<u32x2 *>(ko + dst(t, 64 * s + 8 * j)) = u32x2{kx[0], kx[1]};
+        *reinterpret_cast<u32x2 *>(ko + dst(t, 64 * s + 32 + 8 * j)) = u32x2{kx[2], kx[3]};
+      }
+      const int vd = tid / 32 * 32 + tid % 16, t0 = tid / 16 % 2 * 8;
+#pragma unroll
+      for (int i = 0; i < 16; ++i)
+        ldsv[(t0 + (i & 7)) * row + vd + (i >> 3) * 16] = static_cast<char>(vx[i >> 2] >> (8 * (i & 3)));
+    } else {
+      const int half = tid / D, rem = tid % D, s = rem / 32, j = rem / 8 % 4, tt = rem % 8;
+      const int t = (tt >> 2) * 8 + 4 * half + (tt & 3);
+      if (t >= lo && t < hi) *reinterpret_cast<u32x4 *>(ko + dst(t, 32 * s + 8 * j)) = kx;
+      const int vd = tid / 32 * 16 + tid % 16, t0 = tid / 16 % 2 * 8;
+#pragma unroll
+      for (int i = 0; i < 8; ++i) *reinterpret_cast<uint16_t *>(ldsv + (t0 + i) * row + 2 * vd) = f16_bits_to_bf16_bits(half_word(vx, i));
+    }
+  }
+  __syncthreads();
+  const int slot = tid / (D / CH), d = tid % (D / CH) * CH;
+  if (tid < n && slot >= lo && slot < hi)
+    *reinterpret_cast<u32x4 *>(vo + dst(slot, d)) = *reinterpret_cast<const u32x4 *>(ldsv + slot * row + d * ESZ);
+}
+
 // One appended token per node: thread = (node, kv head, dim).  Writes the token's K and V element
 // into its slot; where the token starts a page it also zeroes the page's other slots (so that
 // nothing stale can be read from a partial page) and stores the page's fp8 scales.  The first
@@ -2431,19 +2717,62 @@ static hipError_t scatter_layout(const Shape &sh, const ScatterArgs &a, hipStrea
   return hipGetLastError();
 }
 
+// 16-byte accesses of token rows and tiles: every buffer and row 16-byte aligned.
+static bool aligned16(const void *x) { return (reinterpret_cast<uintptr_t>(x) & 15) == 0; }
+static bool wide_rows(const Shape &sh, int src_esz, const void *kp, const void *vp, const void *ks, const void *vs) {
+  const int esz = sh.kv_dtype == kF32 ? 4 : (sh.kv_dtype == kBF16 ? 2 : 1);
+  // an encoded row needs 8 bytes per 16 of its source; everything else moves 16 as they are
+  const bool row = sh.D * src_esz % 16 == 0 && (src_esz != esz || sh.D * esz % 16 == 0);
+  return row && aligned16(kp) && aligned16(vp) && aligned16(ks) && aligned16(vs);
+}
+
 hipError_t launch_scatter_quantise(const Shape &sh, const ScatterArgs &a, hipStream_t stream) {
   if (a.n_pages <= 0) return hipSuccess;
   if (sh.kv_dtype != kFP8) return hipErrorInvalidValue;
   const dim3 grid(static_cast<unsigned>(a.n_pages * sh.Hkv)), block(256);
-  if (sh.layout == kMfmaTiled)
+  if (wide_rows(sh, 2, a.k_pool, a.v_pool, a.k_src, a.v_src)) {
+    if (sh.layout != kMfmaTiled)
+      hipLaunchKernelGGL((spex_write_rows_kernel<kFP8, true>), grid, block, 0, stream, a, sh);
+    else if (sh.D == 64)
+      hipLaunchKernelGGL((spex_write_tiles_kernel<kFP8, 64, true>), grid, block, 0, stream, a, sh);
+    else
+      hipLaunchKernelGGL((spex_write_tiles_kernel<kFP8, 128, true>), grid, block, 0, stream, a, sh);
+  } else if (sh.layout == kMfmaTiled) {
     hipLaunchKernelGGL((spex_scatter_quant_kernel<kMfmaTiled>), grid, block, 0, stream, a, sh);
-  else
+  } else {
     hipLaunchKernelGGL((spex_scatter_quant_kernel<kRowMajor>), grid, block, 0, stream, a, sh);
+  }
+  return hipGetLastError();
+}
+
+template <int KV>
+static hipError_t write_tiles(const Shape &sh, const ScatterArgs &a, hipStream_t stream) {
+  const dim3 grid(static_cast<unsigned>(a.n_pages * sh.Hkv)), block(256);
+  if (sh.D == 64)
+    hipLaunchKernelGGL((spex_write_tiles_kernel<KV, 64, false>), grid, block, 0, stream, a, sh);
+  else
+    hipLaunchKernelGGL((spex_write_tiles_kernel<KV, 128, false>), grid, block, 0, stream, a, sh);
+  return hipGetLastError();
+}
+
+template <int KV>
+static hipError_t write_rows(const Shape &sh, const ScatterArgs &a, hipStream_t stream) {
+  const dim3 grid(static_cast<unsigned>(a.n_pages * sh.Hkv)), block(256);
+  hipLaunchKernelGGL((spex_write_rows_kernel<KV, false>), grid, block, 0, stream, a, sh);
   return hipGetLastError();
 }
 
 hipError_t launch_scatter(const Shape &sh, const ScatterArgs &a, hipStream_t stream) {
   if (a.n_pages <= 0) return hipSuccess;
+  const int esz = sh.kv_dtype == kF32 ? 4 : (sh.kv_dtype == kBF16 ? 2 : 1);
+  if (wide_rows(sh, esz, a.k_pool, a.v_pool, a.k_src, a.v_src)) {
+    if (sh.layout == kMfmaTiled) return sh.kv_dtype == kBF16 ? write_tiles<kBF16>(sh, a, stream) : write_tiles<kFP8>(sh, a, stream);
+    switch (sh.kv_dtype) {
+      case kF32: return write_rows<kF32>(sh, a, stream);
+      case kBF16: return write_rows<kBF16>(sh, a, stream);
+      case kFP8: return write_rows<kFP8>(sh, a, stream);
+    }
+  }
   switch (sh.kv_dtype) {
     case kF32: return scatter_layout<kF32>(sh, a, stream);
     case kBF16: return scatter_layout<kBF16>(sh, a, stream);
@@ -2454,6 +2783,14 @@ hipError_t launch_scatter(const Shape &sh, const ScatterArgs &a, hipStream_t str
 
 template <int KV>
 static hipError_t gather_layout(const Shape &sh, const GatherArgs &a, hipStream_t stream) {
+  if (wide_rows(sh, RowMajorTraits<KV>::kEsz, a.k_pool, a.v_pool, a.k_out, a.v_out)) {
+    const dim3 wgrid(static_cast<unsigned>(a.n_pages * sh.Hkv)), wblock(256);
+    if (sh.layout == kMfmaTiled)
+      hipLaunchKernelGGL((spex_read_pages_kernel<KV, kMfmaTiled>), wgrid, wblock, 0, stream, a, sh);
+    else
+      hipLaunchKernelGGL((spex_read_pages_kernel<KV, kRowMajor>), wgrid, wblock, 0, stream, a, sh);
+    return hipGetLastError();
+  }
   const int64_t total = static_cast<int64_t>(a.n_tokens) * sh.Hkv * sh.D;
   const dim3 grid(static_cast<unsigned>((total + 255) / 256)), block(256);
   if (sh.layout == kMfmaTiled)
