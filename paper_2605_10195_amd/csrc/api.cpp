@@ -40,8 +40,7 @@ bool is_pow2(int32_t x) { return x > 0 && (x & (x - 1)) == 0; }
 struct DevicePlan {
   const int32_t *prefix_items = nullptr, *suffix_items = nullptr, *pg_rec = nullptr, *qt_rec = nullptr;
   const int32_t *part_indptr = nullptr, *part_base = nullptr, *part_hstride = nullptr;
-  const int32_t *merge_qt = nullptr;
-  const int32_t *coop_items[3] = {nullptr, nullptr, nullptr};
+  const int32_t *coop_items[2] = {nullptr, nullptr};
   const int32_t *walk_items = nullptr, *walk_blocks = nullptr, *walk_qt = nullptr, *qt_mask = nullptr;
 };
 
@@ -56,7 +55,7 @@ struct spex_tree {
   bool plan_on_device = false, device_has_split = false, device_has_walk = false;
   bool plan_patched_by_append = false;  // the cached plan was brought up to date by an append call
   DevicePlan dplan;
-  size_t blob_off[15] = {}, blob_ints[15] = {};  // byte offset and length of each list in the blob
+  size_t blob_off[13] = {}, blob_ints[13] = {};  // byte offset and length of each list in the blob
   std::vector<int32_t> pending_patches;          // {array, index, value} not yet on the device
   void *d_patch = nullptr;
   size_t d_patch_cap = 0;
@@ -230,9 +229,9 @@ bool obviously_split(const spex::Plan &pl) {
   return items < 128 && (longest + 31) / 32 > short_walk_blocks(items);
 }
 
-constexpr int kPlanArrays = 15;
+constexpr int kPlanArrays = 13;
 // Index, in the device blob's array list, of the arrays a length patch can touch.
-constexpr int kPatchTarget[5] = {2 /*pg_rec*/, 3 /*qt_rec*/, 12 /*walk_blocks*/, 13 /*walk_qt*/, 11 /*walk_items*/};
+constexpr int kPatchTarget[5] = {2 /*pg_rec*/, 3 /*qt_rec*/, 10 /*walk_blocks*/, 11 /*walk_qt*/, 9 /*walk_items*/};
 
 spex_status_t stage_reserve(spex_tree *t, size_t bytes) {
   t->stage_cur ^= 1;
@@ -268,8 +267,7 @@ spex_status_t upload_plan(spex_tree *t, hipStream_t stream) {
   const spex::Plan &pl = t->plan;
   const std::vector<int32_t> *arrays[kPlanArrays] = {
       &pl.prefix_items, &pl.suffix_items, &pl.pg_rec, &pl.qt_rec,
-      &pl.part_indptr, &pl.part_base,    &pl.part_hstride, &pl.merge_qt,
-      &pl.coop_items[0], &pl.coop_items[1], &pl.coop_items[2],
+      &pl.part_indptr, &pl.part_base,    &pl.part_hstride, &pl.coop_items[0], &pl.coop_items[1],
       &pl.walk_items, &pl.walk_blocks, &pl.walk_qt, &pl.qt_mask};
   size_t total = 0;
   for (int i = 0; i < kPlanArrays; ++i) {
@@ -305,12 +303,11 @@ spex_status_t upload_plan(spex_tree *t, hipStream_t stream) {
   dp.part_indptr = at(4);
   dp.part_base = at(5);
   dp.part_hstride = at(6);
-  dp.merge_qt = at(7);
-  for (int c = 0; c < 3; ++c) dp.coop_items[c] = at(8 + c);
-  dp.walk_items = at(11);
-  dp.walk_blocks = at(12);
-  dp.walk_qt = at(13);
-  dp.qt_mask = pl.qt_mask.empty() ? nullptr : at(14);
+  for (int c = 0; c < 2; ++c) dp.coop_items[c] = at(7 + c);
+  dp.walk_items = at(9);
+  dp.walk_blocks = at(10);
+  dp.walk_qt = at(11);
+  dp.qt_mask = pl.qt_mask.empty() ? nullptr : at(12);
   t->plan_on_device = true;
   t->device_has_split = pl.has_split;
   t->device_has_walk = pl.has_walk;
@@ -409,8 +406,7 @@ spex_status_t upload_plan_static(spex_tree *t, unsigned char *base, DevicePlan *
   const spex::Plan &pl = t->plan;
   const std::vector<int32_t> *arrays[kPlanArrays] = {
       &pl.prefix_items, &pl.suffix_items, &pl.pg_rec, &pl.qt_rec,
-      &pl.part_indptr, &pl.part_base,    &pl.part_hstride, &pl.merge_qt,
-      &pl.coop_items[0], &pl.coop_items[1], &pl.coop_items[2],
+      &pl.part_indptr, &pl.part_base,    &pl.part_hstride, &pl.coop_items[0], &pl.coop_items[1],
       &pl.walk_items, &pl.walk_blocks, &pl.walk_qt, &pl.qt_mask};
   size_t off[kPlanArrays], total = 0;
   for (int i = 0; i < kPlanArrays; ++i) {
@@ -431,12 +427,11 @@ spex_status_t upload_plan_static(spex_tree *t, unsigned char *base, DevicePlan *
   dp->part_indptr = at(4);
   dp->part_base = at(5);
   dp->part_hstride = at(6);
-  dp->merge_qt = at(7);
-  for (int c = 0; c < 3; ++c) dp->coop_items[c] = at(8 + c);
-  dp->walk_items = at(11);
-  dp->walk_blocks = at(12);
-  dp->walk_qt = at(13);
-  dp->qt_mask = pl.qt_mask.empty() ? nullptr : at(14);
+  for (int c = 0; c < 2; ++c) dp->coop_items[c] = at(7 + c);
+  dp->walk_items = at(9);
+  dp->walk_blocks = at(10);
+  dp->walk_qt = at(11);
+  dp->qt_mask = pl.qt_mask.empty() ? nullptr : at(12);
   return SPEX_OK;
 }
 
@@ -895,56 +890,35 @@ static spex_status_t decode_attention_impl(spex_tree_t *t, const spex_node_t *le
   a.qt_rec = dp.qt_rec;
   a.part_o = part_o;
   a.part_ml = part_ml;
-  a.part_indptr = dp.part_indptr;
-  a.part_base = dp.part_base;
-  a.part_hstride = dp.part_hstride;
   a.out = out;
   a.lse = lse;
   a.scale_log2 = sm_scale * 1.4426950408889634f;
   a.qt_mask = dp.qt_mask;
-  const bool generic = t->kernel_mode == 1;
+  const bool generic =
+      t->kernel_mode == 1 || !(spex::has_mfma_kernel(t->shape) || spex::has_rowmajor_kernel(t->shape, a));
+  // Every query token has at least one piece; if none has more, the rows need no merge.
+  a.finish = !generic && pl.part_base.size() == pl.qt_limit.size();
 
-  const int32_t n_prefix_items = static_cast<int32_t>(pl.prefix_items.size() / spex::Plan::kItemInts);
-  const int32_t n_suffix_items = static_cast<int32_t>(pl.suffix_items.size() / spex::Plan::kItemInts);
-  int32_t n_coop_items = 0;
-  for (int c = 0; c < 3; ++c)
-    n_coop_items += static_cast<int32_t>(pl.coop_items[c].size() / spex::Plan::kItemInts);
-  const bool rowmajor = !generic && spex::has_rowmajor_kernel(t->shape, a);
-  if (rowmajor) {
-    // shared and private items in one launch; every row is finished by the merge kernel
-    spex::ItemList lists[4] = {{dp.prefix_items, n_prefix_items, 16 * pl.prefix_row_tiles},
-                               {dp.suffix_items, n_suffix_items, 16 * pl.suffix_row_tiles}};
-    for (int c = 0; c < 2; ++c)
-      lists[2 + c] = {dp.coop_items[c], static_cast<int32_t>(pl.coop_items[c].size() / spex::Plan::kItemInts), 64 << c};
-    HIP_TRY(bracket(0, true));
-    HIP_TRY(spex::launch_rowmajor(t->shape, a, lists, 4, stream));
-    HIP_TRY(bracket(0, false));
+  spex::ItemLists il{};
+  const std::vector<int32_t> *host_items[4] = {&pl.coop_items[1], &pl.coop_items[0], &pl.prefix_items, &pl.suffix_items};
+  const int32_t *dev_items[4] = {dp.coop_items[1], dp.coop_items[0], dp.prefix_items, dp.suffix_items};
+  const int32_t spans[4] = {128, 64, 16 * pl.prefix_row_tiles, 16 * pl.suffix_row_tiles};
+  for (int k = 0; k < 4; ++k) {
+    il.items[k] = dev_items[k];
+    il.n_items[k] = static_cast<int32_t>(host_items[k]->size() / spex::Plan::kItemInts);
+    il.span[k] = spans[k];
   }
-  if (!rowmajor && n_prefix_items + n_coop_items > 0) {
-    HIP_TRY(bracket(0, true));
-    if (n_prefix_items > 0) {
-      a.items = dp.prefix_items;
-      a.n_items = n_prefix_items;
-      HIP_TRY(spex::launch_attention(t->shape, a, true, pl.prefix_row_tiles, generic, stream));
+  HIP_TRY(bracket(0, true));
+  if (generic) {
+    for (int k = 0; k < 4; ++k) {
+      a.items = il.items[k];
+      a.n_items = il.n_items[k];
+      HIP_TRY(spex::launch_generic_attention(t->shape, a, il.span[k], stream));
     }
-    for (int c = 0; c < 3; ++c) {
-      a.items = dp.coop_items[c];
-      a.n_items = static_cast<int32_t>(pl.coop_items[c].size() / spex::Plan::kItemInts);
-      if (a.n_items == 0) continue;
-      if (generic || !spex::has_mfma_kernel(t->shape))  // generic kernels take any row count
-        HIP_TRY(spex::launch_attention(t->shape, a, true, 4 << c, true, stream));
-      else
-        HIP_TRY(spex::launch_prefix_coop(t->shape, a, 1 << c, stream));
-    }
-    HIP_TRY(bracket(0, false));
+  } else {
+    HIP_TRY(spex::launch_split(t->shape, a, il, stream));
   }
-  if (!rowmajor && n_suffix_items > 0) {
-    a.items = dp.suffix_items;
-    a.n_items = n_suffix_items;
-    HIP_TRY(bracket(1, true));
-    HIP_TRY(spex::launch_attention(t->shape, a, false, pl.suffix_row_tiles, generic, stream));
-    HIP_TRY(bracket(1, false));
-  }
+  HIP_TRY(bracket(0, false));
   spex::MergeArgs m{};
   m.part_indptr = dp.part_indptr;
   m.part_base = dp.part_base;
@@ -953,22 +927,19 @@ static spex_status_t decode_attention_impl(spex_tree_t *t, const spex_node_t *le
   m.part_ml = part_ml;
   m.out = out;
   m.lse = lse;
-  // The MFMA suffix kernel finishes the rows of single-chunk suffixes itself; the generic kernels
-  // leave every row to the merge kernel.
-  const bool fused = !generic && spex::has_mfma_kernel(t->shape);
-  m.qt_ids = fused ? dp.merge_qt : nullptr;
-  m.n_qtok = fused ? static_cast<int32_t>(pl.merge_qt.size())
-                   : static_cast<int32_t>(pl.qt_limit.size());
+  m.n_qtok = a.finish ? 0 : static_cast<int32_t>(pl.qt_limit.size());
   m.avg_pieces = static_cast<int32_t>((pl.part_base.size() + pl.qt_limit.size() - 1) / pl.qt_limit.size());
-  HIP_TRY(bracket(2, true));
-  HIP_TRY(spex::launch_merge(t->shape, m, stream));
-  HIP_TRY(bracket(2, false));
+  if (!a.finish) {
+    HIP_TRY(bracket(2, true));
+    HIP_TRY(spex::launch_merge(t->shape, m, stream));
+    HIP_TRY(bracket(2, false));
+  }
 
   t->info[0] = pl.unique_tokens;
   t->info[1] = pl.prefix_tokens;
   t->info[2] = pl.suffix_tokens;
-  t->info[3] = n_prefix_items + n_coop_items;
-  t->info[4] = n_suffix_items;
+  t->info[3] = il.n_items[0] + il.n_items[1] + il.n_items[2];
+  t->info[4] = il.n_items[3];
   t->info[5] = pl.n_partial_rows;
   t->info[6] = plan_state;
   t->info[7] = 0;

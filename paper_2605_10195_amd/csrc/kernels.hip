@@ -6,20 +6,17 @@
 //       fetched once per workgroup and staged in LDS as MFMA operand images, blocks of one
 //       wavefront stream straight into its operand registers, and the online-softmax state stays
 //       in registers until the finished rows are written -- no partial results, no merge.
-//   spex_prefix_coop_kernel
-//       The shared-prefix step of the split path for nodes with many stacked rows: one workgroup
-//       per (task, kv head, span of rows), operand images in LDS as in the tree-walk kernel.
-//   spex_prefix_attn_kernel / spex_suffix_attn_kernel
-//       One wavefront per work item = (task, kv head, row tile).  A task is a run of KV pages
-//       (a chunk of a shared-prefix group or of a private suffix) and a set of query rows; the
-//       wavefront streams the pages once, contracts them against its rows on the matrix cores
-//       (S^T = K Q^T and O^T = V^T P^T with MFMA 16x16x32 bf16, fp32 accumulation), keeps an
-//       online softmax per row and emits the partial state (m, l, o).  The shared-prefix kernel
-//       stacks the rows of all branches below a node, so the node's pages are read once for all
-//       of them; the suffix kernel has the few rows of one branch and is bound by HBM bandwidth.
+//   spex_split_attn_kernel
+//       The split path: one workgroup per work item = (task, kv head, row tiles), all items of a
+//       request in one launch.  A task is a run of KV pages (a chunk of a shared-prefix group or of a
+//       private suffix) and a set of query rows.  Items of many rows stage operand images in LDS as
+//       the tree-walk kernel does; items of few rows split their pages between four wavefronts that
+//       stream them from memory to registers (S^T = K Q^T and O^T = V^T P^T with MFMA 16x16x32,
+//       fp32 accumulation).  Every item keeps an online softmax per row and emits the partial state
+//       (m, l, o); a shared page is read once for all rows below it.
 //   spex_rowmajor_attn_kernel
-//       Same contract for row-major pools (fp32 KV, other page sizes and head dims): all items of a
-//       launch -- shared and private -- in one grid, scores and weighted sums as fp32 MFMAs.
+//       Same contract for row-major pools (fp32 KV, other page sizes and head dims), scores and
+//       weighted sums as fp32 MFMAs.
 //   spex_generic_attn_kernel
 //       Same contract without matrix cores, for rows that are not 16-byte aligned and as a cross-check.
 //   spex_lse_merge_kernel
@@ -383,12 +380,12 @@ __device__ __forceinline__ void block_math(RowState<D, NT> &st, const bf16x8 (&k
 template <int D>
 constexpr int stage_floats() { return 16 * (D + 4); }
 
-// Emit the rows of a wavefront: partial state (m, l, o) for the merge step, or -- for a task
-// flagged final -- the finished output rows after folding in the rows' other pieces.  The
-// accumulators hold 4 consecutive dims of one row per lane (64 B runs at a 512 B stride); they are
-// transposed through the wave-private LDS tile `my` so that every store instruction writes whole
-// rows (1 KiB contiguous) instead of half-filled cache lines.
-template <int D, int NT, bool ALLOW_FINAL>
+// Emit the rows of a wavefront: partial state (m, l, o) for the merge step, or -- when every row of
+// the launch has a single piece -- the finished output rows.  The accumulators hold 4 consecutive
+// dims of one row per lane (64 B runs at a 512 B stride); they are transposed through the
+// wave-private LDS tile `my` so that every store instruction writes whole rows (1 KiB contiguous)
+// instead of half-filled cache lines.
+template <int D, int NT>
 __device__ __forceinline__ void finish_rows(const AttnArgs &p, const Shape &sh, const Item &cur,
                                             int row_base, f32x4 (&o)[NT][D / 16],
                                             const float (&m_in)[NT], const float (&l_in)[NT],
@@ -396,89 +393,26 @@ __device__ __forceinline__ void finish_rows(const AttnArgs &p, const Shape &sh, 
   constexpr int kRowPad = D + 4;  // the pad spreads rows over LDS banks
   const int lane = threadIdx.x & 63, m16 = lane & 15, jj = lane >> 4;
   const int G = sh.G, rows = cur.qt_count * G, g = cur.g;
-  const bool final_task = ALLOW_FINAL && (cur.flags & 2) != 0;
   constexpr int kLanesPerRow = D / 4;  // 16-byte pieces per row
   constexpr int kRowsPerInst = 64 / kLanesPerRow;
   const int sub = lane / kLanesPerRow, piece = lane % kLanesPerRow;
 #pragma unroll
   for (int nt = 0; nt < NT; ++nt) {
-    float l = l_in[nt];
-    float m = m_in[nt];
     const int r0w = row_base + nt * 16;  // first row of this tile
     if (r0w >= rows) break;              // wave-uniform
     const bool row_ok = r0w + m16 < rows;
-    const int hh = (r0w + m16) % G;
-    int64_t dst_row;  // row index in part_o, or in out for a final task
-    if (ALLOW_FINAL && final_task) {
-      // Fold in the other pieces of this row (written by the shared-prefix kernels, which ran
-      // before on the same stream) and normalise.  All rows of a suffix belong to one requested
-      // node, so they have the same number of pieces.
-      int e0 = 0, n_other = 0;
-      if (row_ok) {
-        e0 = p.part_indptr[qtok[nt]];
-        n_other = p.part_indptr[qtok[nt] + 1] - 1 - e0;
-      }
-      const int n_max = uniform(n_other);
-      auto fold = [&](const f32x2 ml, const f32x4 (&oj)[D / 16], bool use) {
-        const float mj = use ? ml[0] : kNegInf;
-        const float m_new = fmaxf(m, mj);
-        const float m_safe = m_new == kNegInf ? 0.f : m_new;
-        const float fa = fast_exp2(m - m_safe), fb = fast_exp2(mj - m_safe);
-        l = l * fa + ml[1] * fb;
-        m = m_new;
-#pragma unroll
-        for (int dt = 0; dt < D / 16; ++dt) o[nt][dt] = o[nt][dt] * fa + oj[dt] * fb;
-      };
-      if (n_max > 0) {
-        // The first 8 pieces are fetched four at a time with all loads of a batch in flight
-        // together.  Indices past a row's last piece are clamped to it (a repeated, finite read
-        // that is weighted with zero), which keeps the batches free of per-piece branches.
-        constexpr int kBatch = 4;
-        int64_t slot[2 * kBatch];
-#pragma unroll
-        for (int j = 0; j < 2 * kBatch; ++j) {
-          const int last = n_other - 1;
-          const int e = e0 + max(0, j < last ? j : last);
-          slot[j] = static_cast<int64_t>(p.part_base[e]) + static_cast<int64_t>(g) * p.part_hstride[e] + hh;
-        }
-#pragma unroll
-        for (int q = 0; q < 2; ++q) {
-          if (q * kBatch < n_max) {
-            f32x2 ml[kBatch];
-            f32x4 oj[kBatch][D / 16];
-#pragma unroll
-            for (int k = 0; k < kBatch; ++k) {
-              ml[k] = *reinterpret_cast<const f32x2 *>(p.part_ml + slot[q * kBatch + k] * 2);
-              const float *src = p.part_o + slot[q * kBatch + k] * D + jj * 4;
-#pragma unroll
-              for (int dt = 0; dt < D / 16; ++dt) oj[k][dt] = *reinterpret_cast<const f32x4 *>(src + dt * 16);
-            }
-#pragma unroll
-            for (int k = 0; k < kBatch; ++k) fold(ml[k], oj[k], q * kBatch + k < n_other);
-          }
-        }
-        for (int j = 2 * kBatch; j < n_max; ++j) {  // deeper paths: one piece at a time
-          const int last = n_other - 1;
-          const int e = e0 + max(0, j < last ? j : last);
-          const int64_t sl = static_cast<int64_t>(p.part_base[e]) + static_cast<int64_t>(g) * p.part_hstride[e] + hh;
-          const f32x2 ml = *reinterpret_cast<const f32x2 *>(p.part_ml + sl * 2);
-          f32x4 oj[D / 16];
-          const float *src = p.part_o + sl * D + jj * 4;
-#pragma unroll
-          for (int dt = 0; dt < D / 16; ++dt) oj[dt] = *reinterpret_cast<const f32x4 *>(src + dt * 16);
-          fold(ml, oj, j < n_other);
-        }
-      }
-      const float inv = 1.0f / l;
+    int64_t dst_row;  // row index in part_o or in out
+    if (p.finish) {
+      const float inv = 1.0f / l_in[nt];
 #pragma unroll
       for (int dt = 0; dt < D / 16; ++dt) o[nt][dt] *= inv;
-      dst_row = static_cast<int64_t>(qtok[nt]) * sh.Hq + g * G + hh;
-      if (row_ok && jj == 0 && p.lse) p.lse[dst_row] = (m + __builtin_log2f(l)) * 0.6931471805599453f;
+      dst_row = static_cast<int64_t>(qtok[nt]) * sh.Hq + g * G + (r0w + m16) % G;
+      if (row_ok && jj == 0 && p.lse) p.lse[dst_row] = (m_in[nt] + __builtin_log2f(l_in[nt])) * 0.6931471805599453f;
     } else {
       dst_row = static_cast<int64_t>(cur.pbase) + static_cast<int64_t>(g) * rows + r0w + m16;
-      if (row_ok && jj == 0) *reinterpret_cast<f32x2 *>(p.part_ml + dst_row * 2) = f32x2{m, l};
+      if (row_ok && jj == 0) *reinterpret_cast<f32x2 *>(p.part_ml + dst_row * 2) = f32x2{m_in[nt], l_in[nt]};
     }
-    float *dst = final_task ? p.out : p.part_o;
+    float *dst = p.finish ? p.out : p.part_o;
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
 #pragma unroll
@@ -510,30 +444,57 @@ struct RawBlock {
   float ks, vs;  // this lane's page scales (fp8), else 1
 };
 
-// ---- wavefront kernel: one wavefront per work item ---------------------------------------------
+// ---- split path: items of few rows -------------------------------------------------------------
+// The work items of a launch, in up to four lists: workgroup wg_end[k - 1] .. wg_end[k] - 1 belong to
+// list k.
+struct SplitLists {
+  static constexpr int kLists = 4;
+  const int32_t *items[kLists];
+  int32_t wg_end[kLists];
+  int32_t n_items[kLists];
+  int32_t span[kLists];     // rows an item of the list covers from its first row on
+};
+// The list the workgroup belongs to and its index there.
+struct ListPos {
+  int k, local, n_items, span;
+  const int32_t *items;
+};
+__device__ __forceinline__ ListPos list_of(const SplitLists &ls, int wg) {
+  ListPos r = {0, wg, ls.n_items[0], ls.span[0], ls.items[0]};
+#pragma unroll
+  for (int i = 1; i < SplitLists::kLists; ++i)
+    if (wg >= ls.wg_end[i - 1]) r = {i, wg - ls.wg_end[i - 1], ls.n_items[i], ls.span[i], ls.items[i]};
+  return r;
+}
+
+template <int D>
+constexpr int wave_fold_floats() { return 4 * (D / 16) * 256 + 4 * 16 * 2; }
+
+// One workgroup per work item of up to 16 * NT rows.  A launch of this path is short of work items and
+// long on latency (a block costs a memory round trip, then its arithmetic), so the item's blocks
+// are split between the four wavefronts, which fold their softmax states through LDS; a chunk of
+// 16 pages is then two blocks deep instead of eight.
 // The K/V loads of block b+1 are in flight while block b is computed.  The steady-state loop is
 // free of conditional loads on purpose: the vector-memory completion counter is in-order, and a
 // load that is issued on one path only would force the compiler to wait for everything
 // outstanding at the join.
-template <int KV, int D, int NT, bool SUFFIX, bool TREE>
-__device__ __forceinline__ void attn_wave(const AttnArgs &p, const Shape &sh) {
+template <int KV, int D, int NT, bool TREE>
+__device__ __forceinline__ void wave_item(const AttnArgs &p, const Shape &sh, const Item &cur, float *lds) {
   constexpr int ESZ = (KV == kFP8) ? 1 : 2;
   constexpr int TILE_BYTES = 16 * D * ESZ;
   const int lane = threadIdx.x & 63;
   const int m16 = lane & 15;
   const int jj = lane >> 4;
-  const int item_idx = uniform(blockIdx.x * 4 + (threadIdx.x >> 6));
-  if (item_idx >= p.n_items) return;
+  const int w = uniform(threadIdx.x >> 6);
   const char *kpool = static_cast<const char *>(p.k_pool);
   const char *vpool = static_cast<const char *>(p.v_pool);
   // Byte offset of this lane inside a K half-tile / a V tile.
   const int k_lane_off = jj * 128 + (m16 & 7) * 16;
   const int v_lane_off = (jj & 1) * 256 + m16 * 16;
 
-  const Item cur = load_item(p.items, item_idx);
-  if (cur.pg_count == 0) return;  // padding item
   const int g = cur.g;
-  const int nblk = (cur.pg_count + 1) >> 1;
+  const int n_all = (cur.pg_count + 1) >> 1;
+  const int b_first = (n_all * w) >> 2, nblk = (n_all * (w + 1)) >> 2;  // blocks b_first .. nblk - 1
 
   auto issue_loads = [&](RawBlock<KV, D> &rb, const BlockMeta &bm) {
     rb.valid_a = bm.vp_a & 127;
@@ -569,7 +530,6 @@ __device__ __forceinline__ void attn_wave(const AttnArgs &p, const Shape &sh) {
   load_rows<D, NT>(p, sh, cur, cur.row0, st);
 
   RawBlock<KV, D> r0, r1;
-  issue_loads(r0, meta(0));
 
   auto compute_block = [&](const RawBlock<KV, D> &rb) {
     bf16x8 kf[2][D / 32];
@@ -600,44 +560,77 @@ __device__ __forceinline__ void attn_wave(const AttnArgs &p, const Shape &sh) {
                       jj < 2 ? rb.pos_a : rb.pos_b, p.scale_log2 * rb.ks, rb.vs);
   };
 
-  BlockMeta bm1 = meta(1);
-  int b = 0;
-  for (; b + 2 < nblk; b += 2) {  // blocks b, b+1, b+2 all exist
-    const BlockMeta bm2 = meta(b + 2);
-    issue_loads(r1, bm1);
-    compute_block(r0);
-    bm1 = meta(b + 3);
-    issue_loads(r0, bm2);
-    compute_block(r1);
-  }
-  if (b + 1 < nblk) {
-    issue_loads(r1, bm1);
-    compute_block(r0);
-    compute_block(r1);
-  } else {
-    compute_block(r0);
+  if (b_first < nblk) {
+    issue_loads(r0, meta(b_first));
+    BlockMeta bm1 = meta(b_first + 1);
+    int b = b_first;
+    for (; b + 2 < nblk; b += 2) {  // blocks b, b+1, b+2 all exist
+      const BlockMeta bm2 = meta(b + 2);
+      issue_loads(r1, bm1);
+      compute_block(r0);
+      bm1 = meta(b + 3);
+      issue_loads(r0, bm2);
+      compute_block(r1);
+    }
+    if (b + 1 < nblk) {
+      issue_loads(r1, bm1);
+      compute_block(r0);
+      compute_block(r1);
+    } else {
+      compute_block(r0);
+    }
   }
 
-  __shared__ float stage[4][stage_floats<D>()];
-  float l_tot[NT];
+  // ---- fold: every wavefront leaves its state in LDS, wavefront w then makes output tiles w, w + 4, ..
+  const int rows = cur.qt_count * sh.G;
+  f32x4 *fo = reinterpret_cast<f32x4 *>(lds);      // [wavefront][16-dim tile][lane]
+  float *fml = lds + 4 * (D / 16) * 256;           // [wavefront][row][m, l]
 #pragma unroll
-  for (int nt = 0; nt < NT; ++nt) {  // the row sum is spread over the four lane groups
-    float l = st.l[nt];
+  for (int nt = 0; nt < NT; ++nt) {
+    if (cur.row0 + nt * 16 >= rows) break;         // uniform over the workgroup
+    float l = st.l[nt];                            // the row sum is spread over the four lane groups
     l += __shfl_xor(l, 16);
     l += __shfl_xor(l, 32);
-    l_tot[nt] = l;
+    if (nt > 0) __syncthreads();
+#pragma unroll
+    for (int dt = 0; dt < D / 16; ++dt) fo[(w * (D / 16) + dt) * 64 + lane] = st.o[nt][dt];
+    if (jj == 0) *reinterpret_cast<f32x2 *>(fml + (w * 16 + m16) * 2) = f32x2{st.m[nt], l};
+    __syncthreads();
+    f32x2 ml[4];
+    float m_all = kNegInf;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      ml[v] = *reinterpret_cast<const f32x2 *>(fml + (v * 16 + m16) * 2);
+      m_all = fmaxf(m_all, ml[v][0]);
+    }
+    const float m_safe = m_all == kNegInf ? 0.f : m_all;  // a row that sees nothing of the item: l = 0
+    float f[4], l_all = 0.f;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      f[v] = fast_exp2(ml[v][0] - m_safe);
+      l_all += ml[v][1] * f[v];
+    }
+    const int row = cur.row0 + nt * 16 + m16;
+    const bool row_ok = row < rows;
+    const int64_t dst_row = p.finish ? static_cast<int64_t>(st.qtok[nt]) * sh.Hq + g * sh.G + row % sh.G
+                                     : static_cast<int64_t>(cur.pbase) + static_cast<int64_t>(g) * rows + row;
+    if (w == 0 && jj == 0 && row_ok) {
+      if (!p.finish)
+        *reinterpret_cast<f32x2 *>(p.part_ml + dst_row * 2) = f32x2{m_all, l_all};
+      else if (p.lse)
+        p.lse[dst_row] = (m_all + __builtin_log2f(l_all)) * 0.6931471805599453f;
+    }
+    const float norm = p.finish ? 1.0f / l_all : 1.0f;
+    float *dst = (p.finish ? p.out : p.part_o) + dst_row * D + jj * 4;
+#pragma unroll
+    for (int i = 0; i < D / 64; ++i) {
+      const int dt = i * 4 + w;
+      f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int v = 0; v < 4; ++v) acc += fo[(v * (D / 16) + dt) * 64 + lane] * f[v];
+      if (row_ok) *reinterpret_cast<f32x4 *>(dst + dt * 16) = acc * norm;
+    }
   }
-  finish_rows<D, NT, SUFFIX>(p, sh, cur, cur.row0, st.o, st.m, l_tot, st.qtok, stage[threadIdx.x >> 6]);
-}
-
-template <int KV, int D, int NT, bool TREE>
-__global__ __launch_bounds__(256, NT == 1 ? 2 : 1) void spex_prefix_attn_kernel(AttnArgs p, Shape sh) {
-  attn_wave<KV, D, NT, false, TREE>(p, sh);
-}
-
-template <int KV, int D, int NT, bool TREE>
-__global__ __launch_bounds__(256, NT == 1 ? 2 : 1) void spex_suffix_attn_kernel(AttnArgs p, Shape sh) {
-  attn_wave<KV, D, NT, true, TREE>(p, sh);
 }
 
 // Block step of the cooperative kernel.  Same contraction as block_math, tuned for many row
@@ -737,15 +730,21 @@ __device__ __forceinline__ u32x4 fp8x8_to_f16x8(uint32_t w0, uint32_t w1, float 
   return r;
 }
 
-// ---- cooperative shared-prefix kernel: one workgroup (4 wavefronts) per work item --------------
+// ---- split path: items of many rows ------------------------------------------------------------
 // For groups with many stacked rows.  The workgroup covers up to 64 * NTW rows of one (task, kv
 // head); wavefront w owns rows row0 + w*16*NTW .. .  Each 32-token block is fetched from global
 // memory once per workgroup -- every wavefront loads a quarter of it -- and is placed in LDS as
 // ready-made MFMA operand images (K as bf16, V^T as fp16, fp8 widened on the way and V multiplied
 // by its page scale) that all four wavefronts read (lane * 16 B, conflict free).  Two LDS buffers
 // and one barrier per block.
+template <int D>
+constexpr int coop_lds_floats() {
+  constexpr int img = 2 * (2 * (D / 32) + D / 16) * 256;
+  return img > 4 * stage_floats<D>() ? img : 4 * stage_floats<D>();
+}
+
 template <int KV, int D, int NTW, bool TREE>
-__global__ __launch_bounds__(256, NTW <= 2 ? 2 : 1) void spex_prefix_coop_kernel(AttnArgs p, Shape sh) {
+__device__ __forceinline__ void coop_item(const AttnArgs &p, const Shape &sh, const Item &cur, float *lds) {
   constexpr bool FP8 = KV == kFP8;
   constexpr int ESZ = FP8 ? 1 : 2;
   constexpr int TILE_BYTES = 16 * D * ESZ;
@@ -755,16 +754,10 @@ __global__ __launch_bounds__(256, NTW <= 2 ? 2 : 1) void spex_prefix_coop_kernel
   constexpr int RK = FP8 ? NKI / 2 : NKI;  // of which K
   constexpr int PER = RAW / 4;             // global loads per wavefront and block
   static_assert(RAW % 4 == 0, "block must split evenly over four wavefronts");
-  constexpr int kImgFloats = NI * 64 * 4;  // one buffer, in 4-byte units
-  constexpr int kLdsFloats =
-      2 * kImgFloats > 4 * stage_floats<D>() ? 2 * kImgFloats : 4 * stage_floats<D>();
-  __shared__ __attribute__((aligned(16))) float lds[kLdsFloats];
   u32x4 *img = reinterpret_cast<u32x4 *>(lds);  // [buf][image][lane]
 
   const int lane = threadIdx.x & 63, m16 = lane & 15, jj = lane >> 4;
   const int w = uniform(threadIdx.x >> 6);
-  const Item cur = load_item(p.items, blockIdx.x);
-  if (cur.pg_count == 0) return;  // padding item (whole workgroup)
   const int g = cur.g;
   const int nblk = (cur.pg_count + 1) >> 1;
   const int rows = cur.qt_count * sh.G;
@@ -864,9 +857,25 @@ __global__ __launch_bounds__(256, NTW <= 2 ? 2 : 1) void spex_prefix_coop_kernel
       m_out[nt] = FP8 ? st.m[nt] : st.m[nt] * p.scale_log2;
       l_out[nt] = lacc[nt][0];
     }
-    finish_rows<D, NTW, false>(p, sh, cur, row_base, st.o, m_out, l_out, st.qtok,
-                               lds + w * stage_floats<D>());
+    finish_rows<D, NTW>(p, sh, cur, row_base, st.o, m_out, l_out, st.qtok, lds + w * stage_floats<D>());
   }
+}
+
+// All items of the split path in one launch: lists 0 and 1 hold groups of up to 128 and up to 64 rows
+// a span, lists 2 and 3 groups of up to 16 rows and private suffixes.
+template <int KV, int D, int NT, bool TREE>
+__global__ __launch_bounds__(256, NT == 1 ? 2 : 1) void spex_split_attn_kernel(AttnArgs p, Shape sh, SplitLists ls) {
+  constexpr int kLds = coop_lds_floats<D>() > wave_fold_floats<D>() ? coop_lds_floats<D>() : wave_fold_floats<D>();
+  __shared__ __attribute__((aligned(16))) float lds[kLds];
+  const ListPos at = list_of(ls, static_cast<int>(blockIdx.x));
+  const Item cur = load_item(at.items, at.local);
+  if (cur.pg_count == 0) return;  // padding item (whole workgroup)
+  if (at.k == 0)
+    coop_item<KV, D, 2, TREE>(p, sh, cur, lds);
+  else if (at.k == 1)
+    coop_item<KV, D, 1, TREE>(p, sh, cur, lds);
+  else
+    wave_item<KV, D, NT, TREE>(p, sh, cur, lds);
 }
 
 // ---- tree-walk kernel: one workgroup carries a block of query rows from the root to the leaves --
@@ -1641,14 +1650,6 @@ __global__ __launch_bounds__(64) void spex_generic_attn_kernel(AttnArgs p, Shape
 // branches, 32 heads of 128: 1010 -> 55 us.  Error against 64 bits 3.5e-7 (generic 4.7e-7).
 // A wavefront's K loads for the next 16 tokens are issued right after the score MFMAs, its V loads
 // right after the PV MFMAs, page records two steps ahead.
-struct SplitLists {
-  static constexpr int kLists = 4;
-  const int32_t *items[kLists];
-  int32_t wg_end[kLists];   // workgroups of lists 0 .. k
-  int32_t n_items[kLists];
-  int32_t span[kLists];     // rows an item of the list covers from its first row on
-};
-
 template <int KV>
 struct RowMajorTraits {};
 template <>
@@ -1672,21 +1673,10 @@ __global__ __launch_bounds__(256, DP <= 128 ? 2 : 1) void spex_rowmajor_attn_ker
 
   const int lane = threadIdx.x & 63, m16 = lane & 15, jj = lane >> 4;
   const int w = uniform(threadIdx.x >> 6);
-  int k = 0;
-#pragma unroll
-  for (int i = 0; i + 1 < SplitLists::kLists; ++i) k += static_cast<int>(blockIdx.x) >= ls.wg_end[i] ? 1 : 0;
-  const int32_t *list = ls.items[0];
-  int first_wg = 0, n_items = ls.n_items[0], span = ls.span[0];
-#pragma unroll
-  for (int i = 1; i < SplitLists::kLists; ++i) {
-    list = k == i ? ls.items[i] : list;
-    first_wg = k == i ? ls.wg_end[i - 1] : first_wg;
-    n_items = k == i ? ls.n_items[i] : n_items;
-    span = k == i ? ls.span[i] : span;
-  }
-  const int local = static_cast<int>(blockIdx.x) - first_wg;
-  const int group = local / n_items;       // 64 rows each
-  const Item it = load_item(list, local - group * n_items);
+  const ListPos at = list_of(ls, static_cast<int>(blockIdx.x));
+  const int span = at.span;
+  const int group = at.local / at.n_items; // 64 rows each
+  const Item it = load_item(at.items, at.local - group * at.n_items);
   if (it.pg_count == 0) return;            // padding item
   const int D = sh.D, G = sh.G, rows = it.qt_count * G;
   const int row_end = min(rows, it.row0 + span);
@@ -1898,8 +1888,16 @@ __global__ __launch_bounds__(256, DP <= 128 ? 2 : 1) void spex_rowmajor_attn_ker
     }
   }
   if (!row_ok) return;
-  const int64_t slot = static_cast<int64_t>(it.pbase) + static_cast<int64_t>(it.g) * rows + row;
-  if (jj == 0) *reinterpret_cast<f32x2 *>(p.part_ml + slot * 2) = f32x2{m, l};
+  const int64_t slot = p.finish ? static_cast<int64_t>(qt) * sh.Hq + it.g * G + row % G
+                                : static_cast<int64_t>(it.pbase) + static_cast<int64_t>(it.g) * rows + row;
+  if (jj == 0) {
+    if (!p.finish)
+      *reinterpret_cast<f32x2 *>(p.part_ml + slot * 2) = f32x2{m, l};
+    else if (p.lse)
+      p.lse[slot] = (m + __builtin_log2f(l)) * 0.6931471805599453f;
+  }
+  const float norm = p.finish ? 1.0f / l : 1.0f;
+  float *dst = (p.finish ? p.out : p.part_o) + slot * D;
   // the lane holds dims 16 VE c + 4 VE jj .. + 4 VE - 1 of its row
 #pragma unroll
   for (int c = 0; c < NC; ++c)
@@ -1909,8 +1907,8 @@ __global__ __launch_bounds__(256, DP <= 128 ? 2 : 1) void spex_rowmajor_attn_ker
       for (int h = 0; h < VE / 4; ++h) {
         const int d = 16 * VE * c + 4 * VE * jj + VE * r + 4 * h;
         if (d < D)
-          *reinterpret_cast<f32x4 *>(p.part_o + slot * D + d) =
-              f32x4{o[c * VE + 4 * h][r], o[c * VE + 4 * h + 1][r], o[c * VE + 4 * h + 2][r], o[c * VE + 4 * h + 3][r]};
+          *reinterpret_cast<f32x4 *>(dst + d) =
+              f32x4{o[c * VE + 4 * h][r], o[c * VE + 4 * h + 1][r], o[c * VE + 4 * h + 2][r], o[c * VE + 4 * h + 3][r]} * norm;
       }
 }
 
@@ -1936,7 +1934,7 @@ __global__ __launch_bounds__(256) void spex_lse_merge_kernel(MergeArgs a, Shape 
   for (int i = 0; i < VEC; ++i) acc[i] = 0.f;
   int64_t orow = 0;
   if (live) {
-    const int qt = a.qt_ids ? a.qt_ids[row / sh.Hq] : static_cast<int>(row / sh.Hq);
+    const int qt = static_cast<int>(row / sh.Hq);
     const int h = static_cast<int>(row % sh.Hq);
     const int g = h / sh.G, hh = h % sh.G;
     orow = static_cast<int64_t>(qt) * sh.Hq + h;
@@ -2504,27 +2502,6 @@ __global__ __launch_bounds__(256) void spex_gather_kv_kernel(GatherArgs a, Shape
   }
 }
 
-template <int KV, int D, int NT>
-hipError_t launch_mfma(const Shape &sh, const AttnArgs &a, bool prefix, hipStream_t stream) {
-  const dim3 grid((a.n_items + 3) / 4), block(256);
-  if (a.qt_mask) {  // draft token trees: visibility masks per query
-    if (prefix)
-      hipLaunchKernelGGL((spex_prefix_attn_kernel<KV, D, NT, true>), grid, block, 0, stream, a, sh);
-    else
-      hipLaunchKernelGGL((spex_suffix_attn_kernel<KV, D, NT, true>), grid, block, 0, stream, a, sh);
-  } else if (prefix) {
-    hipLaunchKernelGGL((spex_prefix_attn_kernel<KV, D, NT, false>), grid, block, 0, stream, a, sh);
-  } else {
-    hipLaunchKernelGGL((spex_suffix_attn_kernel<KV, D, NT, false>), grid, block, 0, stream, a, sh);
-  }
-  return hipGetLastError();
-}
-
-template <int KV, int D>
-hipError_t launch_mfma_nt(const Shape &sh, const AttnArgs &a, bool prefix, int nt, hipStream_t s) {
-  return nt == 1 ? launch_mfma<KV, D, 1>(sh, a, prefix, s) : launch_mfma<KV, D, 2>(sh, a, prefix, s);
-}
-
 template <int KV, int QT>
 hipError_t launch_generic(const Shape &sh, const AttnArgs &a, int rows_per_item, hipStream_t stream) {
   const dim3 grid(a.n_items, rows_per_item), block(64);
@@ -2544,17 +2521,8 @@ bool has_mfma_kernel(const Shape &sh) {
          (sh.kv_dtype == kBF16 || sh.kv_dtype == kFP8) && sh.P == 16 && (sh.D == 64 || sh.D == 128);
 }
 
-hipError_t launch_attention(const Shape &sh, const AttnArgs &a, bool prefix, int row_tiles,
-                            bool force_generic, hipStream_t stream) {
+hipError_t launch_generic_attention(const Shape &sh, const AttnArgs &a, int rows_per_item, hipStream_t stream) {
   if (a.n_items <= 0) return hipSuccess;
-  if (!force_generic && has_mfma_kernel(sh)) {
-    if (sh.kv_dtype == kBF16)
-      return sh.D == 64 ? launch_mfma_nt<kBF16, 64>(sh, a, prefix, row_tiles, stream)
-                        : launch_mfma_nt<kBF16, 128>(sh, a, prefix, row_tiles, stream);
-    return sh.D == 64 ? launch_mfma_nt<kFP8, 64>(sh, a, prefix, row_tiles, stream)
-                      : launch_mfma_nt<kFP8, 128>(sh, a, prefix, row_tiles, stream);
-  }
-  const int rows_per_item = 16 * row_tiles;
   if (sh.kv_dtype == kF32 && sh.q_dtype == kF32) return launch_generic<kF32, kF32>(sh, a, rows_per_item, stream);
   if (sh.kv_dtype == kBF16 && sh.q_dtype == kBF16) return launch_generic<kBF16, kBF16>(sh, a, rows_per_item, stream);
   if (sh.kv_dtype == kFP8 && sh.q_dtype == kBF16) return launch_generic<kFP8, kBF16>(sh, a, rows_per_item, stream);
@@ -2583,52 +2551,56 @@ static hipError_t launch_rowmajor_kv(const Shape &sh, const AttnArgs &a, const S
   return hipGetLastError();
 }
 
-hipError_t launch_rowmajor(const Shape &sh, const AttnArgs &a, const ItemList *lists, int n_lists, hipStream_t stream) {
-  if (!has_rowmajor_kernel(sh, a) || n_lists > SplitLists::kLists) return hipErrorInvalidValue;
+// rows_per_wg: rows of an item one workgroup takes.  n_wg < 0: too many.
+static SplitLists make_lists(const ItemLists &l, int rows_per_wg, int64_t *n_wg) {
   SplitLists ls{};
-  int64_t n_wg = 0;
+  *n_wg = 0;
   for (int k = 0; k < SplitLists::kLists; ++k) {
-    ls.items[k] = k < n_lists ? lists[k].items : nullptr;
-    ls.n_items[k] = k < n_lists && lists[k].n_items > 0 ? lists[k].n_items : 1;  // a divisor
-    ls.span[k] = k < n_lists ? lists[k].rows_per_item : 0;
-    if (k < n_lists) n_wg += static_cast<int64_t>(lists[k].n_items) * ((lists[k].rows_per_item + 63) / 64);
-    if (n_wg > INT32_MAX) return hipErrorInvalidValue;
-    ls.wg_end[k] = static_cast<int32_t>(n_wg);
+    ls.items[k] = l.items[k];
+    ls.n_items[k] = l.n_items[k] > 0 ? l.n_items[k] : 1;  // a divisor
+    ls.span[k] = l.span[k];
+    *n_wg += static_cast<int64_t>(l.n_items[k]) * ((l.span[k] + rows_per_wg - 1) / rows_per_wg);
+    ls.wg_end[k] = static_cast<int32_t>(*n_wg);
+    if (*n_wg > INT32_MAX) {
+      *n_wg = -1;
+      break;
+    }
   }
-  if (n_wg == 0) return hipSuccess;
-  if (sh.kv_dtype == kF32) return launch_rowmajor_kv<kF32>(sh, a, ls, static_cast<int>(n_wg), stream);
-  if (sh.kv_dtype == kBF16) return launch_rowmajor_kv<kBF16>(sh, a, ls, static_cast<int>(n_wg), stream);
-  return launch_rowmajor_kv<kFP8>(sh, a, ls, static_cast<int>(n_wg), stream);
+  return ls;
 }
 
-template <int KV, int D>
-static hipError_t launch_coop_ntw(const Shape &sh, const AttnArgs &a, int ntw, hipStream_t stream) {
-  const dim3 grid(a.n_items), block(256);
-  if (a.qt_mask) {
-    if (ntw == 1)
-      hipLaunchKernelGGL((spex_prefix_coop_kernel<KV, D, 1, true>), grid, block, 0, stream, a, sh);
-    else if (ntw == 2)
-      hipLaunchKernelGGL((spex_prefix_coop_kernel<KV, D, 2, true>), grid, block, 0, stream, a, sh);
-    else
-      hipLaunchKernelGGL((spex_prefix_coop_kernel<KV, D, 4, true>), grid, block, 0, stream, a, sh);
-  } else if (ntw == 1) {
-    hipLaunchKernelGGL((spex_prefix_coop_kernel<KV, D, 1, false>), grid, block, 0, stream, a, sh);
-  } else if (ntw == 2) {
-    hipLaunchKernelGGL((spex_prefix_coop_kernel<KV, D, 2, false>), grid, block, 0, stream, a, sh);
-  } else {
-    hipLaunchKernelGGL((spex_prefix_coop_kernel<KV, D, 4, false>), grid, block, 0, stream, a, sh);
-  }
+template <int KV, int D, int NT>
+static hipError_t launch_split_nt(const Shape &sh, const AttnArgs &a, const SplitLists &ls, int n_wg, hipStream_t stream) {
+  const dim3 grid(n_wg), block(256);
+  if (a.qt_mask)  // draft token trees: visibility masks per query
+    hipLaunchKernelGGL((spex_split_attn_kernel<KV, D, NT, true>), grid, block, 0, stream, a, sh, ls);
+  else
+    hipLaunchKernelGGL((spex_split_attn_kernel<KV, D, NT, false>), grid, block, 0, stream, a, sh, ls);
   return hipGetLastError();
 }
 
-hipError_t launch_prefix_coop(const Shape &sh, const AttnArgs &a, int ntw, hipStream_t stream) {
-  if (a.n_items <= 0) return hipSuccess;
-  if (!has_mfma_kernel(sh) || (ntw != 1 && ntw != 2 && ntw != 4)) return hipErrorInvalidValue;
-  if (sh.kv_dtype == kBF16)
-    return sh.D == 64 ? launch_coop_ntw<kBF16, 64>(sh, a, ntw, stream)
-                      : launch_coop_ntw<kBF16, 128>(sh, a, ntw, stream);
-  return sh.D == 64 ? launch_coop_ntw<kFP8, 64>(sh, a, ntw, stream)
-                    : launch_coop_ntw<kFP8, 128>(sh, a, ntw, stream);
+template <int KV, int D>
+static hipError_t launch_split_d(const Shape &sh, const AttnArgs &a, const SplitLists &ls, int n_wg, hipStream_t stream) {
+  return ls.span[2] <= 16 && ls.span[3] <= 16 ? launch_split_nt<KV, D, 1>(sh, a, ls, n_wg, stream)
+                                              : launch_split_nt<KV, D, 2>(sh, a, ls, n_wg, stream);
+}
+
+hipError_t launch_split(const Shape &sh, const AttnArgs &a, const ItemLists &l, hipStream_t stream) {
+  const bool tiled = has_mfma_kernel(sh);
+  if (!tiled && !has_rowmajor_kernel(sh, a)) return hipErrorInvalidValue;
+  if (l.span[0] > 128 || l.span[1] > 64 || l.span[2] > 32 || l.span[3] > 32) return hipErrorInvalidValue;
+  int64_t n_wg = 0;
+  const SplitLists ls = make_lists(l, tiled ? 128 : 64, &n_wg);
+  if (n_wg < 0) return hipErrorInvalidValue;
+  if (n_wg == 0) return hipSuccess;
+  const int n = static_cast<int>(n_wg);
+  if (tiled && sh.kv_dtype == kBF16)
+    return sh.D == 64 ? launch_split_d<kBF16, 64>(sh, a, ls, n, stream) : launch_split_d<kBF16, 128>(sh, a, ls, n, stream);
+  if (tiled)
+    return sh.D == 64 ? launch_split_d<kFP8, 64>(sh, a, ls, n, stream) : launch_split_d<kFP8, 128>(sh, a, ls, n, stream);
+  if (sh.kv_dtype == kF32) return launch_rowmajor_kv<kF32>(sh, a, ls, n, stream);
+  if (sh.kv_dtype == kBF16) return launch_rowmajor_kv<kBF16>(sh, a, ls, n, stream);
+  return launch_rowmajor_kv<kFP8>(sh, a, ls, n, stream);
 }
 
 template <int KV, int D, int NW, bool TREE>

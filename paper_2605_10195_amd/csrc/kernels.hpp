@@ -30,9 +30,9 @@ struct AttnArgs {
   const int32_t *qt_rec;  // 2 ints per row-set entry: {query token, visible path length}
   float *part_o;   // [partial rows][D] unnormalised sum of exp2(x - m) * V
   float *part_ml;  // [partial rows][2] = {m, l}: running maximum of x = score * log2(e), sum of exp2
-  // Rows of tasks flagged final are finished in place: the other pieces of a row are read through
-  // its merge list (all entries but the last, which is the task itself) and out / lse are written.
-  const int32_t *part_indptr, *part_base, *part_hstride;
+  // every row of the launch has one piece only: write finished rows to out / lse instead (not the
+  // generic kernel)
+  bool finish;
   float *out, *lse;  // lse may be null
   float scale_log2;
   // Draft-tree visibility, or null for the causal chain: 2 ints per query token {index i of the
@@ -64,8 +64,7 @@ struct MergeArgs {
   const int32_t *part_indptr, *part_base, *part_hstride;
   const float *part_o, *part_ml;
   float *out, *lse;
-  const int32_t *qt_ids;  // query tokens to merge, or null for 0 .. n_qtok-1
-  int32_t n_qtok;         // number of query tokens handled by the launch
+  int32_t n_qtok;
   int32_t avg_pieces;     // pieces of an average query token (a hint for the launch shape)
 };
 
@@ -111,30 +110,26 @@ struct GatherArgs {
   int32_t page_ids[kMaxPagesPerScatter];
 };
 
-// prefix == true launches the shared-prefix kernel, else the suffix kernel; row_tiles is the
-// number of 16-row MFMA tiles per wavefront the item list was built for.
-hipError_t launch_attention(const Shape &sh, const AttnArgs &a, bool prefix, int row_tiles,
-                            bool force_generic, hipStream_t stream);
-// Row-major pools: every item of all lists in one launch (n_lists <= 4).  rows_per_item: rows an item
-// of the list covers from its first row on.
-struct ItemList {
-  const int32_t *items;
-  int32_t n_items, rows_per_item;
+// Work items of the split path, by list: groups of more than 64 rows (spans of up to 128), of 17 to
+// 64, of up to 16 rows, and private suffixes.  span: rows an item covers from its first row on.
+struct ItemLists {
+  const int32_t *items[4];
+  int32_t n_items[4], span[4];
 };
+bool has_mfma_kernel(const Shape &sh);
 bool has_rowmajor_kernel(const Shape &sh, const AttnArgs &a);
-hipError_t launch_rowmajor(const Shape &sh, const AttnArgs &a, const ItemList *lists, int n_lists, hipStream_t stream);
+// All lists in one launch; needs has_mfma_kernel or has_rowmajor_kernel.
+hipError_t launch_split(const Shape &sh, const AttnArgs &a, const ItemLists &lists, hipStream_t stream);
+// a.items / a.n_items on the vector ALU; any shape.
+hipError_t launch_generic_attention(const Shape &sh, const AttnArgs &a, int rows_per_item, hipStream_t stream);
 hipError_t launch_merge(const Shape &sh, const MergeArgs &a, hipStream_t stream);
 hipError_t launch_scatter(const Shape &sh, const ScatterArgs &a, hipStream_t stream);
 // fp8 pools: k_src / v_src hold bf16 values; page scales are computed (started pages) or reused.
 hipError_t launch_scatter_quantise(const Shape &sh, const ScatterArgs &a, hipStream_t stream);
 hipError_t launch_gather(const Shape &sh, const GatherArgs &a, hipStream_t stream);
 hipError_t launch_append_tokens(const Shape &sh, const AppendTokensArgs &a, hipStream_t stream);
-bool has_mfma_kernel(const Shape &sh);
 // blob[pairs[2i]] = pairs[2i+1] for i < n (all DEVICE): patches the device copy of a plan.
 hipError_t launch_patch(int32_t *blob, const int32_t *pairs, int32_t n, hipStream_t stream);
-// Cooperative shared-prefix kernel; ntw in {1, 2, 4} = 16-row tiles per wavefront (64 * ntw rows
-// per workgroup).  One work item per workgroup.  Only for shapes with has_mfma_kernel().
-hipError_t launch_prefix_coop(const Shape &sh, const AttnArgs &a, int ntw, hipStream_t stream);
 // Tree-walk kernel; ntw in {1, 2, 4} = 16-row tiles per wavefront and waves in {2, 4, 8} = wavefronts
 // of rows per row block the lists were built for (2: run by four wavefronts, two on each set of
 // rows, which split the path between them; ntw 1 or 2, no draft masks).
