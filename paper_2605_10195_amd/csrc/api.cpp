@@ -136,7 +136,6 @@ spex::Shape make_shape(const spex_config_t &c) {
 
 bool request_matches(const spex::Plan &pl, const spex_tree *t, const int32_t *leaves,
                      const int32_t *q_lens, const uint32_t *masks, int32_t n) {
-  if (!pl.valid) return false;
   if (pl.req_prefix_chunk != t->prefix_chunk || pl.req_suffix_chunk != t->suffix_chunk ||
       pl.req_walk_row_tiles != t->walk_row_tiles || pl.req_walk_waves != t->walk_waves)
     return false;
@@ -173,7 +172,8 @@ spex_status_t make_plan(spex_tree *t, const int32_t *leaves, const int32_t *q_le
   *state = 0;
   const bool by_append = t->plan_patched_by_append;
   t->plan_patched_by_append = false;
-  if (request_matches(t->plan, t, leaves, q_lens, masks, n)) {
+  const bool repeated = request_matches(t->plan, t, leaves, q_lens, masks, n);
+  if (repeated && t->plan.valid) {
     if (t->plan.table_version == t->pt->version()) {
       if (by_append) *state = 2;  // patched already, by the append launch
       return SPEX_OK;
@@ -187,9 +187,12 @@ spex_status_t make_plan(spex_tree *t, const int32_t *leaves, const int32_t *q_le
   *state = 1;
   t->plan_on_device = false;
   t->pending_patches.clear();
-  return plan_status(t, t->planner.begin(*t->pt, leaves, q_lens, masks, n, t->cfg.num_q_heads,
-                                         t->cfg.num_kv_heads, t->prefix_chunk, t->suffix_chunk,
-                                         t->walk_row_tiles, t->walk_waves, &t->plan));
+  const bool growing = repeated && t->plan.topology_version == t->pt->topology_version() && t->plan.calls < 8;
+  const spex_status_t st = plan_status(t, t->planner.begin(*t->pt, leaves, q_lens, masks, n, t->cfg.num_q_heads,
+                                                           t->cfg.num_kv_heads, t->prefix_chunk, t->suffix_chunk,
+                                                           t->walk_row_tiles, t->walk_waves, &t->plan));
+  t->plan.growing = growing;
+  return st;
 }
 
 // Longest tree-walk workgroup (in two-page blocks) up to which a launch of `items` workgroups
@@ -778,12 +781,13 @@ static spex_status_t decode_attention_impl(spex_tree_t *t, const spex_node_t *le
   const spex_status_t st = make_plan(t, leaves, q_lens, draft_masks, n_leaves, &plan_state);
   if (st != SPEX_OK) return st;
   spex::Plan &pl = t->plan;
-  // Which kernels: the tree-walk kernel when its lists exist and fill the chip, or when its
-  // longest workgroup is short; else shared-prefix + suffix + merge, which can split long paths.
-  // A tree-walk workgroup takes about 12 us + 0.8 us per two-page block on its path whatever else
-  // runs, the three split-path launches take 26-45 us for up to 32 work items of this size and
-  // grow with the item count: measured crossing points were 20 blocks at 8-32 items, 40 at 64
-  // and 65 at 96 (bf16, 32 / 8 heads of 128).  Only the lists of the chosen kernels are built.
+  // Which kernels.  The tree-walk kernel needs lists that fill the chip (128 workgroups) or are short:
+  // otherwise the split path, which can cut long paths.  Where both apply, the one whose estimated
+  // time is lower: long paths of few branches keep the tree-walk kernel waiting for its longest
+  // workgroup (32 branches on prompts of 12500 tokens, 292 workgroups: 449 us against 211 through
+  // the split path), many short nodes cost the split path an item and partial rows each (1024
+  // branches on nodes of 16 tokens: 124 against 28).  Only the lists of the chosen kernels are kept
+  // on the device.
   bool want_walk = (t->kernel_mode == 0 || t->kernel_mode == 3) && spex::has_mfma_kernel(t->shape);
   const bool tree_masks = draft_masks != nullptr;
   if (want_walk && t->kernel_mode == 0 && !pl.has_walk && obviously_split(pl))
@@ -793,9 +797,22 @@ static spex_status_t decode_attention_impl(spex_tree_t *t, const spex_node_t *le
   // (walk_waves 2).
   const bool walk_possible = want_walk && pl.walk_ok && (!tree_masks || pl.walk_waves != 2);
   if (t->kernel_mode == 3 && !walk_possible) return SPEX_ERR_UNSUPPORTED;
-  const int32_t short_walk = short_walk_blocks(pl.walk_real_items);
-  const bool use_walk = walk_possible && (t->kernel_mode == 3 || pl.walk_real_items >= 128 ||
-                                          pl.walk_max_item_blocks <= short_walk);
+  const bool fills = walk_possible && (pl.walk_real_items >= 128 ||
+                                       pl.walk_max_item_blocks <= short_walk_blocks(pl.walk_real_items));
+  // Where branches of unequal length grow a token a call, some branch starts a page in most calls:
+  // tree-walk lists are patched then, split lists made again (300 branches: 160 us of host time a
+  // call), so a request that outgrew its last plan within 8 calls keeps the tree-walk kernel.
+  // The estimates are good to some 14 % and a tree-walk plan is the one that lasts, so the split path
+  // must promise 5 % less, or 30 % less for a launch of few workgroups, where the two differ by a
+  // few us either way.  With more workgroups than run at a time (two per compute unit) the longest
+  // one matters little and the estimate is not made.
+  bool use_walk = walk_possible && (t->kernel_mode == 3 || fills);
+  if (use_walk && t->kernel_mode == 0 && !pl.growing && pl.walk_real_items <= 512) {
+    const float least = (pl.walk_real_items >= 128 ? 0.95f : 0.7f) * spex::Planner::estimate_walk(pl);
+    use_walk = t->planner.estimate_split(*t->pt, &pl, t->cfg.head_dim,
+                                         static_cast<int32_t>(elem_size(t->cfg.kv_dtype)), least) >= least;
+  }
+  ++pl.calls;
   if (!use_walk) {
     const spex_status_t ss = plan_status(t, t->planner.ensure_split(*t->pt, &pl));
     if (ss != SPEX_OK) return ss;

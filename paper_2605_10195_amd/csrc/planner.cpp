@@ -17,6 +17,20 @@ int32_t clamp32(int64_t v, int32_t lo, int32_t hi) {
   return static_cast<int32_t>(std::max<int64_t>(lo, std::min<int64_t>(hi, v)));
 }
 
+// Split granularity.  Every extra chunk costs a partial result per row that is written and
+// read back, and every item some 5 us of latency however short, so segments are cut only until
+// the launch has about 256 shared and 1024 private items of 128 tokens or more (a workgroup splits
+// an item's tokens between its wavefronts).  Measured (us a call, bf16, 32 / 8 heads of 128): 16
+// branches on a 512-token prompt 13.6 with shared items of 256 tokens, 11.7 with 128; one
+// prompt of 16000 tokens 23.7 / 20.6 / 20.1 / 27.8 with 256 / 512 / 1024 / 2048, four of them
+// 73 / 66 / 60 / 57; private items of 128 or 256 tokens are within 3 % of each other.
+int32_t auto_prefix_chunk(int64_t pages, int32_t page_size) {
+  return clamp32((pages + 255) / 256, std::max(1, 128 / page_size), std::max(1, 4096 / page_size));
+}
+int32_t auto_suffix_chunk(int64_t pages, int32_t page_size) {
+  return clamp32((pages + 1023) / 1024, std::max(1, 128 / page_size), std::max(1, 1024 / page_size));
+}
+
 struct Segment {
   std::vector<int32_t> ids, valid, pos;
   std::vector<int32_t> last_of;  // node whose last page the entry is, else -1
@@ -248,15 +262,9 @@ PlanError Planner::ensure_split(const PageTable &pt, Plan *plan) {
     prefix_pages_weighted +=
         static_cast<int64_t>(s.ids.size()) * (s.qt_count * G <= 64 ? 1 : (s.qt_count * G + kWideSpan - 1) / kWideSpan);
 
-  // ---- split granularity.  Every extra chunk costs a partial result per row that is written and
-  // read back, so segments are cut only as far as needed to keep the longest work item near
-  // 1/1024 (shared prefix) or 1/2048 (suffix) of the launch, i.e. a few items per wavefront slot.
-  pl.prefix_chunk_pages = prefix_chunk_pages > 0
-                              ? prefix_chunk_pages
-                              : clamp32((prefix_pages_weighted * num_kv_heads + 1023) / 1024, 16, 256);
-  pl.suffix_chunk_pages = suffix_chunk_pages > 0
-                              ? suffix_chunk_pages
-                              : clamp32((suffix_pages * num_kv_heads + 2047) / 2048, 8, 64);
+  pl.prefix_chunk_pages =
+      prefix_chunk_pages > 0 ? prefix_chunk_pages : auto_prefix_chunk(prefix_pages_weighted * num_kv_heads, P);
+  pl.suffix_chunk_pages = suffix_chunk_pages > 0 ? suffix_chunk_pages : auto_suffix_chunk(suffix_pages * num_kv_heads, P);
 
   // ---- tasks
   std::vector<int32_t> qt_req;  // with draft masks: the request of every query token
@@ -424,6 +432,72 @@ PlanError Planner::ensure_split(const PageTable &pt, Plan *plan) {
   }
   pl.has_split = true;
   return PlanError::kOk;
+}
+
+// A fit over 165 forests of every shape (bf16 and fp8, 2 to 8 kv heads of 64 and 128, W = 2 to 3000
+// tree-walk workgroups), each timed through both paths: the middle half of the predictions is within
+// 14 %.  Shared items of more than 16 rows cost their blocks of 32 tokens through LDS, the others
+// the blocks' bytes, and every row of an item its partial state.
+float Planner::estimate_split(const PageTable &pt, Plan *plan, int32_t head_dim, int32_t kv_bytes, float enough) {
+  Plan &pl = *plan;
+  if (pl.split_estimate >= 0.f) return pl.split_estimate;
+  // every token read once, nothing else
+  const double bytes_only = 9.4 + 0.97e-3 * kv_bytes * static_cast<double>(pl.unique_tokens) / 32.0 * pl.num_kv_heads * head_dim / 128.0;
+  if (bytes_only >= enough) return static_cast<float>(bytes_only);
+  const int32_t N = pt.num_nodes(), P = pt.page_size(), G = pl.num_q_heads / pl.num_kv_heads;
+  if (static_cast<int32_t>(est_rows_.size()) < N) {
+    est_rows_.resize(N, 0);
+    est_reqs_.resize(N, 0);
+  }
+  const int32_t n = static_cast<int32_t>(pl.req_leaves.size());
+  auto q_len = [&](int32_t i) { return pl.req_q_lens.empty() ? 1 : pl.req_q_lens[i]; };
+  for (int32_t i = 0; i < n; ++i)
+    for (int32_t k = pl.path_indptr[i]; k < pl.path_indptr[i + 1]; ++k) {
+      const int32_t u = pl.path_nodes[k];
+      if (est_reqs_[u]++ == 0) est_nodes_.push_back(u);
+      est_rows_[u] += q_len(i) * G;
+    }
+  auto pages_of = [&](int32_t u) { return static_cast<int64_t>(pt.node(u).pages.size()); };
+  auto spans = [](int64_t rows) { return rows <= 64 ? 1 : (rows + kWideSpan - 1) / kWideSpan; };
+  std::vector<int64_t> tail(n, 0);  // pages of every request's private nodes
+  int64_t weighted = 0, suffix_pages = 0;
+  for (int32_t u : est_nodes_)
+    if (est_reqs_[u] > 1) weighted += pages_of(u) * spans(est_rows_[u]);
+  int32_t max_rows = 0;
+  for (int32_t i = 0; i < n; ++i) {
+    for (int32_t k = pl.path_indptr[i + 1] - 1; k >= pl.path_indptr[i] && est_reqs_[pl.path_nodes[k]] == 1; --k)
+      tail[i] += pages_of(pl.path_nodes[k]);
+    suffix_pages += tail[i];
+    if (tail[i] > 0) max_rows = std::max(max_rows, q_len(i) * G);
+  }
+  const int32_t H = pl.num_kv_heads;
+  const int64_t pc = pl.req_prefix_chunk > 0 ? pl.req_prefix_chunk : auto_prefix_chunk(weighted * H, P);
+  const int64_t sc = pl.req_suffix_chunk > 0 ? pl.req_suffix_chunk : auto_suffix_chunk(suffix_pages * H, P);
+  double through_lds = 0, streamed = 0, partial_rows = 0;  // per kv head
+  for (int32_t u : est_nodes_) {
+    if (est_reqs_[u] > 1) {
+      const int64_t pg = pages_of(u), rows = est_rows_[u];
+      (rows > kWaveRowsMax ? through_lds : streamed) += static_cast<double>((pg + 1) / 2 * spans(rows));
+      partial_rows += static_cast<double>((pg + pc - 1) / pc * rows);
+    }
+    est_rows_[u] = est_reqs_[u] = 0;
+  }
+  est_nodes_.clear();
+  const int32_t tile = max_rows <= 16 ? 16 : 32;
+  for (int32_t i = 0; i < n; ++i) {
+    const int64_t rows = q_len(i) * G;
+    streamed += static_cast<double>((tail[i] + 1) / 2 * ((rows + tile - 1) / tile));
+    partial_rows += static_cast<double>((tail[i] + sc - 1) / sc * rows);
+  }
+  const double per_head = 4.45e-3 * through_lds + 0.97e-3 * kv_bytes * streamed;  // us at head dim 128
+  pl.split_estimate = static_cast<float>(9.4 + H * head_dim * (per_head / 128.0 + 3.0e-6 * partial_rows));
+  return pl.split_estimate;
+}
+
+// The longest workgroup, or all of them two to a compute unit.
+float Planner::estimate_walk(const Plan &pl) {
+  return 4.5f + 0.63f * static_cast<float>(pl.walk_max_item_blocks) +
+         0.84f / 512.f * static_cast<float>(pl.walk_steps) * static_cast<float>(pl.num_kv_heads);
 }
 
 // Tree-walk lists: the whole path of a set of query rows is handled by one workgroup, which keeps
@@ -789,6 +863,7 @@ void Planner::ensure_walk(const PageTable &pt, Plan *plan) {
     rb_blocks.push_back(total);
     pl.walk_block_visits += total;
     pl.walk_max_item_blocks = std::max(pl.walk_max_item_blocks, rb_rec[2] + longest_private);
+    pl.walk_steps += rb_rec[2] + longest_private;
   };
 
   int32_t wave = 0, used = 0, cur_root = -1;

@@ -105,6 +105,10 @@ struct Plan {
   std::vector<int32_t> walk_items;
   int32_t walk_real_items = 0;       // workgroups with work
   int32_t walk_max_item_blocks = 0;  // longest workgroup: shared blocks + most private blocks of a wavefront
+  int64_t walk_steps = 0;            // the same summed over the row blocks (one kv head each)
+  int32_t calls = 0;                 // attention calls the plan has served
+  bool growing = false;              // made because appends outgrew a plan that had served few calls
+  float split_estimate = -1.f;       // Planner::estimate_split, once per plan
   int64_t walk_block_visits = 0;  // blocks over all row blocks (a block shared by two row blocks counts twice)
 };
 
@@ -123,6 +127,11 @@ class Planner {
   void ensure_csr(const PageTable &pt, Plan *plan);
   PlanError ensure_split(const PageTable &pt, Plan *plan);
   void ensure_walk(const PageTable &pt, Plan *plan);
+  // Microseconds a call takes through the split path / the tree-walk kernel, from the shape of the
+  // request (the first without building the split lists, the second from the tree-walk lists).
+  // A result of `enough` or more may be a lower bound.
+  float estimate_split(const PageTable &pt, Plan *plan, int32_t head_dim, int32_t kv_bytes, float enough);
+  static float estimate_walk(const Plan &plan);
   // Brings a plan up to date after appends to requested nodes (no fork or prune since it was
   // made).  Tokens that fill up a last page change valid counts and limits; a newly started page
   // becomes page b of the node's last block or, in tree-walk lists that are the plan's only
@@ -141,6 +150,7 @@ class Planner {
   int32_t stamp_next_ = 1;
   // dense per-node scratch, reset through touched_
   std::vector<int32_t> live_, pos0_, gindex_, touched_;
+  std::vector<int32_t> est_rows_, est_reqs_, est_nodes_;  // scratch of estimate_split, zero between calls
 };
 
 }  // namespace spex
