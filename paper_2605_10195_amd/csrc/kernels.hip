@@ -950,14 +950,13 @@ __device__ __forceinline__ WalkBlock load_walk_block(const WalkArgs &p, int idx,
   return b;
 }
 
-// Scores of one 32-token block for the row tiles that intersect the wave-relative row range
-// [lo, hi): S^T = K Q^T (see block_math for the operand layout).
+// Scores of one 32-token block for all row tiles of the wavefront: S^T = K Q^T (see block_math for
+// the operand layout).
 template <int D, int NT>
 __device__ __forceinline__ void walk_scores(const bf16x8 (&qf)[NT][D / 32], const bf16x8 (&kf)[2][D / 32],
-                                            int lo, int hi, f32x4 (&sa)[NT], f32x4 (&sb)[NT]) {
+                                            f32x4 (&sa)[NT], f32x4 (&sb)[NT]) {
 #pragma unroll
   for (int nt = 0; nt < NT; ++nt) {
-    if (nt * 16 >= hi || nt * 16 + 16 <= lo) continue;  // wave-uniform
     f32x4 a = {0.f, 0.f, 0.f, 0.f}, b = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int s = 0; s < D / 32; ++s) {
@@ -970,68 +969,72 @@ __device__ __forceinline__ void walk_scores(const bf16x8 (&qf)[NT][D / 32], cons
 }
 
 // Online softmax and O^T += V^T P^T for the same tiles; P rounded to fp16, row sums by MFMA
-// against ones (see block_math_f16).  Rows of a tile outside [lo, hi) see nothing of the block.
+// against ones (see block_math_f16).  Rows outside [lo, hi) see nothing of the block.
+// One path with two branches for all tiles of the wavefront -- masks, which change scores only, and a
+// reference that moves -- so that the tiles' weights and MFMAs form one run of instructions: with
+// a branch per tile the weights of one tile were made while the matrix cores idled.
 template <bool FP8, bool TREE, int D, int NT>
 __device__ __forceinline__ void walk_softmax_pv(const int (&limit)[NT], const int (&qidx)[NT],
                                                 const uint32_t (&dmask)[NT], f32x4 (&o)[NT][D / 16],
-                                                float (&m)[NT], f32x4 (&lacc)[NT],
-                                                const f32x4 (&sa)[NT], const f32x4 (&sb)[NT],
-                                                const f16x8 (&vh)[D / 16], bool tok_masked,
+                                                float (&m)[NT], f32x4 (&lacc)[NT], f32x4 (&sa)[NT],
+                                                f32x4 (&sb)[NT], const f16x8 (&vh)[D / 16], bool tok_masked,
                                                 int valid_l, int pos_l, float c, float slack, int lo,
-                                                int hi) {
+                                                int hi, int rows) {
   const int lane = threadIdx.x & 63, m16 = lane & 15, jj = lane >> 4;
   const _Float16 one = static_cast<_Float16>(1.0f);
   const f16x8 ones = {one, one, one, one, one, one, one, one};
+  // Scores stay raw; scale and subtraction of the reference fuse into one FMA per score.  With
+  // one scale for the whole path (bf16 KV) the reference m is kept on raw scores; with a scale
+  // per page (fp8 KV) it is kept in scaled units (log2 e folded in), and the largest scaled score
+  // of the lane is c * the largest raw one (c > 0, and rounding is monotonic).
+  // Tile rows past the wavefront's last one hold zero queries and are not written: they need no mask.
+  if (tok_masked || lo > 0 || hi < rows) {  // wave-uniform
 #pragma unroll
-  for (int nt = 0; nt < NT; ++nt) {
-    if (nt * 16 >= hi || nt * 16 + 16 <= lo) continue;  // wave-uniform
-    const bool partial_tile = lo > nt * 16 || hi < nt * 16 + 16;
-    // Scores stay raw; scale and subtraction of the reference fuse into one FMA per score.  With
-    // one scale for the whole path (bf16 KV) the reference m is kept on raw scores; with a scale
-    // per page (fp8 KV) it is kept in scaled units (log2 e folded in), and the largest scaled score
-    // of the lane is c * the largest raw one (c > 0, and rounding is monotonic).
-    float x[8];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      x[i] = sa[nt][i];
-      x[4 + i] = sb[nt][i];
-    }
-    if (tok_masked || partial_tile) {
+    for (int nt = 0; nt < NT; ++nt) {
       const int row = nt * 16 + m16;
       const bool row_in = row >= lo && row < hi;
+      uint32_t vm = 0xffu;
+      int vis = valid_l - 8 * (jj & 1);  // tokens of the lane's 8 that exist
       if (TREE) {
         // Draft tree: positions below base = T - q_len are visible, position base + k iff bit k of
         // the row's mask is set.  The lane's 8 tokens start at relative position rel; shifting
         // {mask, 32 ones} right by rel + 32 puts their visibility into the low 8 bits.
         const int base = limit[nt] - 1 - qidx[nt];
-        const int first = 8 * (jj & 1);
-        const int sh = pos_l + first - base + 32;
+        const int sh = pos_l + 8 * (jj & 1) - base + 32;
         const uint64_t bits = (static_cast<uint64_t>(dmask[nt]) << 32) | 0xffffffffull;
-        uint32_t vm = sh <= 0 ? 0xffu : (sh >= 64 ? 0u : static_cast<uint32_t>(bits >> sh) & 0xffu);
-        const int have = valid_l - first;  // tokens of the lane's 8 that exist
-        vm = row_in ? vm : 0u;
-#pragma unroll
-        for (int i = 0; i < 8; ++i) x[i] = (i < have && ((vm >> i) & 1u)) ? x[i] : kNegInf;
+        vm = sh <= 0 ? 0xffu : (sh >= 64 ? 0u : static_cast<uint32_t>(bits >> sh) & 0xffu);
       } else {
-        int vis = limit[nt] - pos_l;
-        vis = vis < valid_l ? vis : valid_l;
-        vis -= 8 * (jj & 1);
-        vis = row_in ? vis : 0;
+        vis = min(vis, limit[nt] - pos_l - 8 * (jj & 1));
+      }
+      if (!tok_masked) vis = 8;  // a block that its rows see whole: only the row range counts
+      if (TREE && !tok_masked) vm = 0xffu;
+      vis = row_in ? vis : 0;
 #pragma unroll
-        for (int i = 0; i < 8; ++i) x[i] = i < vis ? x[i] : kNegInf;
+      for (int i = 0; i < 4; ++i) {
+        sa[nt][i] = i < vis && (!TREE || ((vm >> i) & 1u)) ? sa[nt][i] : kNegInf;
+        sb[nt][i] = 4 + i < vis && (!TREE || ((vm >> (4 + i)) & 1u)) ? sb[nt][i] : kNegInf;
       }
     }
-    const float mx8_raw = fmaxf(fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3])),
-                                fmaxf(fmaxf(x[4], x[5]), fmaxf(x[6], x[7])));
-    const float mx8 = FP8 ? mx8_raw * c : mx8_raw;
-    // Lazy reference: m is the value the row's weights are taken relative to, not its exact
-    // running maximum.  It moves (and o and l are rescaled) only when a score of the row exceeds it
-    // by more than `slack` (2^8 in weight); until then weights are at most 2^8, which fp16 and
-    // the fp32 sums hold.  The decision is taken per row from the row's own scores, so a row's
-    // result does not depend on its neighbours in the tile; most blocks skip the cross-lane
-    // maximum and the rescaling altogether.  m starts at kWalkMInit (finite, far below any score).
-    if (__any(mx8 > m[nt] + slack)) {
-      const float rmax = row_group_max(mx8);
+  }
+  // Lazy reference: m is the value the row's weights are taken relative to, not its exact
+  // running maximum.  It moves (and o and l are rescaled) only when a score of the row exceeds it
+  // by more than `slack` (2^8 in weight); until then weights are at most 2^8, which fp16 and
+  // the fp32 sums hold.  The decision is taken per row from the row's own scores, so a row's
+  // result does not depend on its neighbours in the tile; most blocks skip the cross-lane
+  // maximum and the rescaling altogether.  m starts at kWalkMInit (finite, far below any score).
+  float mx[NT];
+  bool over = false;
+#pragma unroll
+  for (int nt = 0; nt < NT; ++nt) {
+    const float raw = fmaxf(fmaxf(fmaxf(sa[nt][0], sa[nt][1]), fmaxf(sa[nt][2], sa[nt][3])),
+                            fmaxf(fmaxf(sb[nt][0], sb[nt][1]), fmaxf(sb[nt][2], sb[nt][3])));
+    mx[nt] = FP8 ? raw * c : raw;
+    over = over || mx[nt] > m[nt] + slack;
+  }
+  if (__any(over)) {
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) {
+      const float rmax = row_group_max(mx[nt]);
       const float m_new = rmax > m[nt] + slack ? rmax : m[nt];
       const float alpha = fast_exp2(FP8 ? m[nt] - m_new : (m[nt] - m_new) * c);
       m[nt] = m_new;
@@ -1039,20 +1042,17 @@ __device__ __forceinline__ void walk_softmax_pv(const int (&limit)[NT], const in
       for (int dt = 0; dt < D / 16; ++dt) o[nt][dt] *= alpha;
       lacc[nt] *= alpha;
     }
-    float pr[8];
-    if (FP8) {
-      const float neg_m = -m[nt];
+  }
 #pragma unroll
-      for (int i = 0; i < 8; ++i) pr[i] = fast_exp2(__builtin_fmaf(x[i], c, neg_m));
-    } else {
-      const float mc = m[nt] * c;
-#pragma unroll
-      for (int i = 0; i < 8; ++i) pr[i] = fast_exp2(__builtin_fmaf(x[i], c, -mc));
-    }
+  for (int nt = 0; nt < NT; ++nt) {
+    const float mc = FP8 ? m[nt] : m[nt] * c;
     u32x4 pw;
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
-      pw[i] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(pr[2 * i], pr[2 * i + 1]));
+    for (int i = 0; i < 4; ++i) {
+      const float x0 = i < 2 ? sa[nt][2 * i] : sb[nt][2 * i - 4], x1 = i < 2 ? sa[nt][2 * i + 1] : sb[nt][2 * i - 3];
+      pw[i] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(fast_exp2(__builtin_fmaf(x0, c, -mc)),
+                                                                      fast_exp2(__builtin_fmaf(x1, c, -mc))));
+    }
     const f16x8 ph = __builtin_bit_cast(f16x8, pw);
     lacc[nt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ones, ph, lacc[nt], 0, 0, 0);
 #pragma unroll
@@ -1292,7 +1292,7 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && NTW <= 2) ? 2 : 1) void spex_t
 #pragma unroll
           for (int s = 0; s < D / 32; ++s)
             kf[t][s] = __builtin_bit_cast(bf16x8, src[(t * (D / 32) + s) * 64]);
-        walk_scores<D, NTW>(qf, kf, lo, hi, sa, sb);
+        walk_scores<D, NTW>(qf, kf, sa, sb);
       }
       // The V images are fetched only now, into the registers the K images have left, and their
       // LDS latency passes under the softmax arithmetic.
@@ -1302,7 +1302,7 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && NTW <= 2) ? 2 : 1) void spex_t
       for (int dt = 0; dt < D / 16; ++dt) vh[dt] = __builtin_bit_cast(f16x8, src[(NKI + dt) * 64]);
       walk_softmax_pv<FP8, TREE, D, NTW>(limit, qidx, dmask, o, m, lacc, sa, sb, vh, (bm.flags & 1) != 0,
                                    (jj < 2 ? bm.vp_a : bm.vp_b) & 127, (jj < 2 ? bm.vp_a : bm.vp_b) >> 7,
-                                   c, slack, lo, hi);
+                                   c, slack, lo, hi, rows);
     };
     auto meta = [&](int b) {
       return load_walk_block<FP8>(p, blk_begin + (b < n_shared ? b : n_shared - 1), g, sh.Hkv, rec_in_lds,
@@ -1409,7 +1409,7 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && NTW <= 2) ? 2 : 1) void spex_t
           for (int s = 0; s < D / 32; ++s) kf[t][s] = __builtin_bit_cast(bf16x8, kr[t][s]);
       }
       f32x4 sa[NTW], sb[NTW];
-      walk_scores<D, NTW>(qf, kf, lo, hi, sa, sb);
+      walk_scores<D, NTW>(qf, kf, sa, sb);
       if (more) issue_k(kr, refill);
       f16x8 vh[D / 16];
       if (FP8) {
@@ -1425,7 +1425,7 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && NTW <= 2) ? 2 : 1) void spex_t
       if (more) issue_v(vr, refill);
       walk_softmax_pv<FP8, TREE, D, NTW>(limit, qidx, dmask, o, m, lacc, sa, sb, vh, (bm.flags & 1) != 0,
                                    (jj < 2 ? bm.vp_a : bm.vp_b) & 127, (jj < 2 ? bm.vp_a : bm.vp_b) >> 7,
-                                   c, slack, lo, hi);
+                                   c, slack, lo, hi, rows);
     };
     // the j-th private block of this wavefront (past the end: the last one)
     auto rec_at = [&](int j) {
