@@ -805,9 +805,10 @@ static spex_status_t decode_attention_impl(spex_tree_t *t, const spex_node_t *le
   // The estimates are good to some 14 % and a tree-walk plan is the one that lasts, so the split path
   // must promise 5 % less, or 30 % less for a launch of few workgroups, where the two differ by a
   // few us either way.  With more workgroups than run at a time (two per compute unit) the longest
-  // one matters little and the estimate is not made.
+  // one matters little and the estimate is not made; nor for more than 1024 query tokens, whose split
+  // lists take the host longer to make than a call (2500: 1.9 against 1.0 ms for a first call).
   bool use_walk = walk_possible && (t->kernel_mode == 3 || fills);
-  if (use_walk && t->kernel_mode == 0 && !pl.growing && pl.walk_real_items <= 512) {
+  if (use_walk && t->kernel_mode == 0 && !pl.growing && pl.walk_real_items <= 512 && pl.qt_limit.size() <= 1024) {
     const float least = (pl.walk_real_items >= 128 ? 0.95f : 0.7f) * spex::Planner::estimate_walk(pl);
     use_walk = t->planner.estimate_split(*t->pt, &pl, t->cfg.head_dim,
                                          static_cast<int32_t>(elem_size(t->cfg.kv_dtype)), least) >= least;
@@ -872,7 +873,7 @@ static spex_status_t decode_attention_impl(spex_tree_t *t, const spex_node_t *le
     wa.scale_log2 = sm_scale * 1.4426950408889634f;
     wa.qt_mask = dp.qt_mask;
     HIP_TRY(bracket(3, true));
-    HIP_TRY(spex::launch_tree_walk(t->shape, wa, pl.walk_row_tiles, pl.walk_waves, stream));
+    HIP_TRY(spex::launch_tree_walk(t->shape, wa, pl.walk_row_tiles, pl.walk_waves, spex::Planner::walk_in_halves(pl), stream));
     HIP_TRY(bracket(3, false));
     t->info[0] = pl.unique_tokens;
     t->info[1] = pl.prefix_tokens;

@@ -636,9 +636,10 @@ __device__ __forceinline__ void wave_item(const AttnArgs &p, const Shape &sh, co
 // Block step of the cooperative kernel.  Same contraction as block_math, tuned for many row
 // tiles per wavefront, where the vector ALU work of the softmax -- not the matrix cores -- sets
 // the pace:
-//  * P is rounded once to fp16 (11 significant bits; toward zero, one instruction per pair: the
-//    row sum is taken from the same rounded weights, so the mean shortfall cancels in o / l and
-//    what remains has the spread of round-to-nearest) and V^T arrives as fp16 operand images, so
+//  * P is rounded once to fp16 (11 significant bits; to nearest, one instruction per pair, because a
+//    row's pieces are folded with pieces of the other items, whose weights are not rounded: the
+//    mean shortfall of rounding toward zero would weigh this piece 3e-4 too low against them) and
+//    V^T arrives as fp16 operand images, so
 //    PV is one MFMA per tile instead of a hi and a lo one;
 //  * the row sums come from one more MFMA against a tile of ones, which also adds up the four
 //    lane groups and uses the same rounded weights as the numerator;
@@ -695,7 +696,7 @@ __device__ __forceinline__ void block_math_f16(const bf16x8 (&qf)[NT][D / 32], c
     u32x4 pw;
 #pragma unroll
     for (int i = 0; i < 4; ++i)
-      pw[i] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(pr[2 * i], pr[2 * i + 1]));
+      pw[i] = __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{pr[2 * i], pr[2 * i + 1]}, f16x2));
     const f16x8 ph = __builtin_bit_cast(f16x8, pw);
     lacc[nt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ones, ph, lacc[nt], 0, 0, 0);
 #pragma unroll
@@ -1118,7 +1119,7 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && NTW <= 2) ? 2 : 1) void spex_t
   constexpr int NI = NKI + D / 16;         // all operand images per block (1 KiB each)
   constexpr int RAW = FP8 ? NI / 2 : NI;   // 1 KiB global loads per block
   constexpr int RK = FP8 ? NKI / 2 : NKI;  // of which K
-  static_assert(KS == 1 || (KS == 2 && NW == 4), "the path is split between the two halves of four wavefronts");
+  static_assert(KS == 1 || KS == 2, "the path is split between the two halves of the workgroup");
   constexpr int LW = NW / KS;               // wavefronts the lists were made for (each holds C rows)
   constexpr int PER = (RAW + LW - 1) / LW;  // global loads per wavefront and block in the shared phase
   constexpr bool kEven = RAW % LW == 0;     // else the last wavefronts have no piece to fetch
@@ -1228,7 +1229,7 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && NTW <= 2) ? 2 : 1) void spex_t
   // a root has several, and stay in step so that one finds the other's shared blocks in L2),
   // alternating again with every round of 256, takes its private blocks first: the loop below
   // then runs twice, one phase per turn.  Not with four row tiles per wavefront (registers).
-  constexpr bool kStagger = NTW <= 2 && KS == 1;
+  constexpr bool kStagger = NTW <= 2 && (KS == 1 || NW == 8);
   const bool private_first = kStagger && (((blockIdx.x >> 4) ^ (blockIdx.x >> 8)) & 1) != 0;
 #pragma nounroll
   for (int ph = 0; ph < (kStagger ? 2 : 1); ++ph) {
@@ -2615,35 +2616,44 @@ static hipError_t launch_walk_ntw(const Shape &sh, const WalkArgs &a, int ntw, h
   return hipGetLastError();
 }
 
+template <int KV, int D, int NW, bool TREE>
+static hipError_t launch_walk_halves(const Shape &sh, const WalkArgs &a, int ntw, hipStream_t stream) {
+  const dim3 grid(a.n_items), block(64 * NW);
+  if (ntw == 1)
+    hipLaunchKernelGGL((spex_tree_walk_kernel<KV, D, 1, NW, TREE, 2>), grid, block, 0, stream, a, sh);
+  else if (ntw == 2)
+    hipLaunchKernelGGL((spex_tree_walk_kernel<KV, D, 2, NW, TREE, 2>), grid, block, 0, stream, a, sh);
+  else
+    return hipErrorInvalidValue;
+  return hipGetLastError();
+}
+
 template <int KV, int D>
-static hipError_t launch_walk_nw(const Shape &sh, const WalkArgs &a, int ntw, int waves, hipStream_t stream) {
+static hipError_t launch_walk_nw(const Shape &sh, const WalkArgs &a, int ntw, int waves, bool halves, hipStream_t stream) {
+  if (halves) {  // lists for four wavefronts of rows, walked by eight
+    if (waves != 4) return hipErrorInvalidValue;
+    return a.qt_mask ? launch_walk_halves<KV, D, 8, true>(sh, a, ntw, stream)
+                     : launch_walk_halves<KV, D, 8, false>(sh, a, ntw, stream);
+  }
   if (a.qt_mask)  // draft-tree masks: not in the kernel that splits the path
     return waves == 4   ? launch_walk_ntw<KV, D, 4, true>(sh, a, ntw, stream)
            : waves == 8 ? launch_walk_ntw<KV, D, 8, true>(sh, a, ntw, stream)
                         : hipErrorInvalidValue;
-  if (waves == 2) {  // lists for two wavefronts of rows, walked by four: the path is split in two
-    const dim3 grid(a.n_items), block(256);
-    if (ntw == 1)
-      hipLaunchKernelGGL((spex_tree_walk_kernel<KV, D, 1, 4, false, 2>), grid, block, 0, stream, a, sh);
-    else if (ntw == 2)
-      hipLaunchKernelGGL((spex_tree_walk_kernel<KV, D, 2, 4, false, 2>), grid, block, 0, stream, a, sh);
-    else
-      return hipErrorInvalidValue;
-    return hipGetLastError();
-  }
+  // lists for two wavefronts of rows, walked by four: the path is split in two
+  if (waves == 2) return launch_walk_halves<KV, D, 4, false>(sh, a, ntw, stream);
   return waves == 4 ? launch_walk_ntw<KV, D, 4, false>(sh, a, ntw, stream)
                     : launch_walk_ntw<KV, D, 8, false>(sh, a, ntw, stream);
 }
 
-hipError_t launch_tree_walk(const Shape &sh, const WalkArgs &a, int ntw, int waves, hipStream_t stream) {
+hipError_t launch_tree_walk(const Shape &sh, const WalkArgs &a, int ntw, int waves, bool halves, hipStream_t stream) {
   if (a.n_items <= 0) return hipSuccess;
   if (!has_mfma_kernel(sh) || (ntw != 1 && ntw != 2 && ntw != 4) || (waves != 2 && waves != 4 && waves != 8))
     return hipErrorInvalidValue;
   if (sh.kv_dtype == kBF16)
-    return sh.D == 64 ? launch_walk_nw<kBF16, 64>(sh, a, ntw, waves, stream)
-                      : launch_walk_nw<kBF16, 128>(sh, a, ntw, waves, stream);
-  return sh.D == 64 ? launch_walk_nw<kFP8, 64>(sh, a, ntw, waves, stream)
-                    : launch_walk_nw<kFP8, 128>(sh, a, ntw, waves, stream);
+    return sh.D == 64 ? launch_walk_nw<kBF16, 64>(sh, a, ntw, waves, halves, stream)
+                      : launch_walk_nw<kBF16, 128>(sh, a, ntw, waves, halves, stream);
+  return sh.D == 64 ? launch_walk_nw<kFP8, 64>(sh, a, ntw, waves, halves, stream)
+                    : launch_walk_nw<kFP8, 128>(sh, a, ntw, waves, halves, stream);
 }
 
 namespace {

@@ -133,6 +133,7 @@ hipError_t launch_patch(int32_t *blob, const int32_t *pairs, int32_t n, hipStrea
 // Tree-walk kernel; ntw in {1, 2, 4} = 16-row tiles per wavefront and waves in {2, 4, 8} = wavefronts
 // of rows per row block the lists were built for (2: run by four wavefronts, two on each set of
 // rows, which split the path between them; ntw 1 or 2, no draft masks).
-hipError_t launch_tree_walk(const Shape &sh, const WalkArgs &a, int ntw, int waves, hipStream_t stream);
+// halves (waves 4, ntw 1 or 2): eight wavefronts walk the lists made for four, two on each set of rows.
+hipError_t launch_tree_walk(const Shape &sh, const WalkArgs &a, int ntw, int waves, bool halves, hipStream_t stream);
 
 }  // namespace spex

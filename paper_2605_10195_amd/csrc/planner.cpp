@@ -494,10 +494,26 @@ float Planner::estimate_split(const PageTable &pt, Plan *plan, int32_t head_dim,
   return pl.split_estimate;
 }
 
-// The longest workgroup, or all of them two to a compute unit.
+// Eight wavefronts, two on each set of rows, halve every workgroup's path in time but leave one
+// workgroup to a compute unit instead of two.  With up to 256 workgroups there is only one anyway
+// (90 forests: between 1.0 and 1.9 times as fast, 1.3 in the middle; 128 workgroups of up to 82
+// blocks 60.6 -> 45.0 us, 256 of up to 49, fp8, 54.1 -> 44.5).  With some more the launch still lasts as long
+// as its longest workgroup if most are much shorter (304 of up to 89 and 50 on average 71.1 -> 55.9 us,
+// 444 of up to 103 and 51 87.6 -> 82.1), but a second round of equal ones costs more than it saves
+// (336 of 61 blocks 68.3 -> 87.1).  Only where the number of wavefronts is not asked for.
+bool Planner::walk_in_halves(const Plan &pl) {
+  if (pl.req_walk_waves != 0 || pl.walk_waves != 4 || pl.walk_row_tiles > 2) return false;
+  if (pl.walk_real_items <= 256) return true;
+  const int64_t all = static_cast<int64_t>(pl.walk_real_items) * pl.walk_max_item_blocks;
+  return pl.walk_real_items <= 448 && 10 * pl.walk_steps * pl.num_kv_heads <= 6 * all;
+}
+
+// The longest workgroup's blocks, and all workgroups' spread over the 512 that run at a time; fitted as
+// above, with the path halved or not.
 float Planner::estimate_walk(const Plan &pl) {
-  return 4.5f + 0.63f * static_cast<float>(pl.walk_max_item_blocks) +
-         0.84f / 512.f * static_cast<float>(pl.walk_steps) * static_cast<float>(pl.num_kv_heads);
+  const float longest = static_cast<float>(pl.walk_max_item_blocks);
+  const float share = static_cast<float>(pl.walk_steps) * static_cast<float>(pl.num_kv_heads) / 512.f;
+  return walk_in_halves(pl) ? 4.7f + 0.36f * longest + 0.69f * share : 4.5f + 0.63f * longest + 0.84f * share;
 }
 
 // Tree-walk lists: the whole path of a set of query rows is handled by one workgroup, which keeps

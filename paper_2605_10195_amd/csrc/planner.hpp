@@ -132,6 +132,8 @@ class Planner {
   // A result of `enough` or more may be a lower bound.
   float estimate_split(const PageTable &pt, Plan *plan, int32_t head_dim, int32_t kv_bytes, float enough);
   static float estimate_walk(const Plan &plan);
+  // Whether eight wavefronts walk the lists made for four, two on each set of rows.
+  static bool walk_in_halves(const Plan &plan);
   // Brings a plan up to date after appends to requested nodes (no fork or prune since it was
   // made).  Tokens that fill up a last page change valid counts and limits; a newly started page
   // becomes page b of the node's last block or, in tree-walk lists that are the plan's only
