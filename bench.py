@@ -385,8 +385,7 @@ def measure(name, args, steps, warmup, decode_iters, cpu_sample, calibrate=False
     b_tok = wl.kv_bytes_per_token()
     kernels = {}
     walked = info["walk_row_tiles"] > 0
-    for kname, ms, toks in (("prefix", k_ms[0], 0 if walked else info["prefix_tokens"]),
-                            ("suffix", k_ms[1], 0 if walked else info["suffix_tokens"]),
+    for kname, ms, toks in (("split", k_ms[0], 0 if walked else info["kv_tokens"]),   # shared and private items, one launch
                             ("walk", k_ms[3], info["kv_tokens"] if walked else 0)):
         gbps = toks * b_tok / (ms * 1e-3) / 1e9 if ms > 0 else 0.0
         kernels[kname] = dict(ms=float(ms), kv_tokens=int(toks), kv_bytes=float(toks * b_tok),
@@ -395,12 +394,11 @@ def measure(name, args, steps, warmup, decode_iters, cpu_sample, calibrate=False
                                    nq * wl.num_q_heads * (wl.head_dim + 1) * 4)
     kernels["merge"] = dict(ms=float(k_ms[2]), bytes=float(part_bytes),
                             gbps=part_bytes / (k_ms[2] * 1e-3) / 1e9 if k_ms[2] > 0 else 0.0)
-    dominant = "walk" if walked else ("suffix" if k_ms[1] >= k_ms[0] else "prefix")
+    dominant = "walk" if walked else "split"
     dom = kernels[dominant]
-    kernel_name = {"suffix": "spex_suffix_attn_kernel", "prefix": "spex_prefix_attn_kernel",
-                   "walk": "spex_tree_walk_kernel"}[dominant]
+    kernel_name = "spex_tree_walk_kernel" if walked else "spex_split_attn_kernel"
     if wl.kv_dtype == "f32":
-        kernel_name = "spex_generic_attn_kernel"
+        kernel_name = "spex_rowmajor_attn_kernel"
     traffic, traffic_source = profiled_traffic(wl.name, kernel_name)
 
     result = {

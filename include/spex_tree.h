@@ -81,7 +81,7 @@ typedef enum { SPEX_F32 = 0, SPEX_BF16 = 1, SPEX_FP8_E4M3 = 2 } spex_dtype_t;
  *   - a bf16 V magnitude below 2^-17 is stored as the multiple of 2^-24 below it (absolute error
  *     below 2^-24);
  * every kernel on such a pool, the generic one included, sees the stored values.  For an fp8 pool
- * the codes are stored as given and widened when read by the tree-walk and cooperative kernels
+ * the codes are stored as given and widened when read by the tree-walk kernel and the split path
  * (kernel_mode 0 / 3, and 2 for nodes shared by more than 16 query rows):
  *   - an fp8 v_scale above 146 (448 * 146 = 65408) is read as 146;
  *   - code * v_scale is formed in half precision in two steps (the power of two of the scale,
@@ -115,8 +115,9 @@ typedef struct {
                                 v_pool = k_pool + num_kv_heads tiles interleaves K and V of a page
                                 in one buffer, so that a page's K and V share a 64 KiB region. */
   int32_t walk_row_tiles; /* tree-walk kernel: 16-row tiles per wavefront, 1 / 2 / 4; 0 = automatic */
-  int32_t walk_waves;     /* tree-walk kernel: wavefronts of query rows per workgroup, 2 / 4 / 8; 0 = 4.
-                             2: four wavefronts run, two on each set of rows, and split the rows' path
+  int32_t walk_waves;     /* tree-walk kernel: wavefronts of query rows per workgroup, 2 / 4 / 8; 0 =
+                             automatic (then lists for 4 may be walked by eight wavefronts, two on
+                             each set of rows).  2: four wavefronts run, two on each set of rows, and split the rows' path
                              between them (walk_row_tiles 1 or 2, no draft masks) */
 } spex_config_t;
 
@@ -243,7 +244,8 @@ spex_status_t spex_tree_prune(spex_tree_t *tree, spex_node_t node);
  *     query token's rows fit a wavefront; a requested node with more rows than a wavefront takes
  *     is cut into pieces of whole query tokens).  Chosen automatically when it yields >= 128
  *     workgroups, or when no wavefront has more two-page blocks to walk than 20 (up to 32
- *     workgroups) rising to 87 (127 workgroups): 20 + (workgroups - 32) * 7 / 10;
+ *     workgroups) rising to 87 (127 workgroups): 20 + (workgroups - 32) * 7 / 10 -- unless, for up
+ *     to 512 workgroups and 1024 query tokens, the other set's estimated time is clearly lower;
  *   shared-prefix + suffix + merge: every shared node is read once for all rows below it, private
  *     suffixes are split for parallelism, partial softmax states go through memory.  Any shape.
  * Consecutive calls on one handle must use one stream or be separated by a synchronisation,
@@ -329,11 +331,11 @@ spex_status_t spex_tree_stats(const spex_tree_t *tree, int64_t *live_nodes, int6
  *   (page id, valid tokens, path position of the page's first token), rows
  *   qt_list[task_qt_begin .. + task_qt_count) (query-token indices), first partial slot
  *   task_pbase, task_flags bit 0 = some page partial or some row's limit inside the chunk,
- *   bit 1 = suffix task that is the only chunk of its suffix (the suffix kernel then folds the
- *   rows' other pieces in and writes the output rows itself).
+ *   bit 1 = suffix task that is the only chunk of its suffix.
  *   Merge lists: query token t combines entries part_indptr[t] .. part_indptr[t+1]; the slot of
  *   (kv head g, head-in-group hh) in entry e is part_base[e] + g * part_hstride[e] + hh.
- *   merge_qt[n_merge_qt]: the query tokens that still need the separate merge kernel.
+ *   merge_qt[n_merge_qt]: the query tokens without a task of flag bit 1.  (A launch in which every query
+ *   token has one piece finishes its rows itself; otherwise the merge kernel takes all rows.)
  */
 typedef struct {
   int32_t n_leaves, n_qtok, n_groups, n_tasks, n_prefix_tasks, n_pg, n_qt_list, n_parts, n_merge_qt;
@@ -410,7 +412,8 @@ spex_status_t spex_tree_walk_dump(spex_tree_t *tree, const spex_node_t *leaves,
  * Per-kernel timing.  While profiling is enabled, every decode_attention call brackets each of
  * its kernels with HIP events on the call's stream (the last 256 calls are kept).
  * spex_tree_read_profile waits for those events and writes, for each recorded call in order,
- * milliseconds for ms[4*c+0] = shared-prefix kernel, ms[4*c+1] = suffix kernel, ms[4*c+2] = merge
+ * milliseconds for ms[4*c+0] = the split path's launch of shared and private items (the generic kernels'
+ * launches likewise), ms[4*c+1] = 0, ms[4*c+2] = merge
  * kernel, ms[4*c+3] = tree-walk kernel (0 for a kernel that was not launched; cap counts calls,
  * ms holds 4 * cap floats); *n = number of calls; the record is then
  * cleared.  SPEX_ERR_CAPACITY (with *n set) if cap calls are too few.  Enabling or disabling

@@ -633,7 +633,7 @@ __device__ __forceinline__ void wave_item(const AttnArgs &p, const Shape &sh, co
   }
 }
 
-// Block step of the cooperative kernel.  Same contraction as block_math, tuned for many row
+// Block step of items of many rows.  Same contraction as block_math, tuned for many row
 // tiles per wavefront, where the vector ALU work of the softmax -- not the matrix cores -- sets
 // the pace:
 //  * P is rounded once to fp16 (11 significant bits; to nearest, one instruction per pair, because a
@@ -884,7 +884,7 @@ __global__ __launch_bounds__(256, NT == 1 ? 2 : 1) void spex_split_attn_kernel(A
 // root, neighbours in the tree next to each other) and a kv head.  Its block list covers every
 // page on the rows' paths exactly once, each block with the range of rows whose path contains it.
 // Phase 1 walks the blocks whose rows span several wavefronts: the workgroup fetches each block
-// once into LDS operand images (as the cooperative kernel does) and every wavefront contracts it
+// once into LDS operand images (as items of many rows do on the split path) and every wavefront contracts it
 // with the row tiles inside the range.  Phase 2: every wavefront streams the blocks that only its
 // own rows need straight into registers.  The softmax state (m, l, o) of a row stays in registers
 // from the first block to the last, so the only global writes are the finished output rows.
@@ -1051,8 +1051,8 @@ __device__ __forceinline__ void walk_softmax_pv(const int (&limit)[NT], const in
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const float x0 = i < 2 ? sa[nt][2 * i] : sb[nt][2 * i - 4], x1 = i < 2 ? sa[nt][2 * i + 1] : sb[nt][2 * i - 3];
-      pw[i] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(fast_exp2(__builtin_fmaf(x0, c, -mc)),
-                                                                      fast_exp2(__builtin_fmaf(x1, c, -mc))));
+      pw[i] = __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{fast_exp2(__builtin_fmaf(x0, c, -mc)),
+                                                                         fast_exp2(__builtin_fmaf(x1, c, -mc))}, f16x2));
     }
     const f16x8 ph = __builtin_bit_cast(f16x8, pw);
     lacc[nt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ones, ph, lacc[nt], 0, 0, 0);

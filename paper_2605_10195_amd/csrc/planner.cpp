@@ -9,8 +9,8 @@
 namespace spex {
 namespace {
 
-constexpr int32_t kWaveRowsMax = 16;    // largest group the wavefront kernel takes
-constexpr int kWideClass = 1;           // cooperative launch class of groups above 64 rows
+constexpr int32_t kWaveRowsMax = 16;    // largest group whose items need no LDS images
+constexpr int kWideClass = 1;           // item list of groups above 64 rows
 constexpr int32_t kWideSpan = 64 << kWideClass;  // rows per workgroup in that class
 
 int32_t clamp32(int64_t v, int32_t lo, int32_t hi) {
@@ -381,8 +381,8 @@ PlanError Planner::ensure_split(const PageTable &pt, Plan *plan) {
                                           pl.task_pbase[t],    pl.task_flags[t], g, row0};
     items.insert(items.end(), rec, rec + Plan::kItemInts);
   };
-  // Shared-prefix items.  Groups of up to 16 rows go to the wavefront kernel (one item per task
-  // and kv head).  Larger groups go to the cooperative kernel, one workgroup per (task, kv head,
+  // Shared-prefix items.  Groups of up to 16 rows are streamed to registers (one item per task
+  // and kv head).  Larger groups go through LDS, one workgroup per (task, kv head,
   // span of 64 * NTW rows): NTW = 1 for up to 64 rows, else NTW = 2 (spans of 128 rows).
   // The spans of one (task, kv head) read the same pages; workgroup b of a launch runs on XCD
   // b % 8 and every XCD has its own L2, so units are laid out in batches of 8 with span s of unit

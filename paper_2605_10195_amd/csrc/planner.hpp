@@ -16,10 +16,10 @@
 //    (kv head g, local query token r, head-in-group hh) = pbase + g*rows + r*G + hh;
 //  * flag bit 0 (masked): a page of the task is partial, or a row's limit is smaller than the
 //    path position following the task's last token;
-//  * flag bit 1 (final): suffix task that is the only chunk of its suffix; the suffix kernel
-//    folds the other pieces of its rows into it and writes the output rows itself;
-//  * merge_qt: ascending query tokens that still go through the merge kernel (requested nodes
-//    whose suffix is empty or has several chunks).
+//  * flag bit 1 (final): suffix task that is the only chunk of its suffix;
+//  * merge_qt: ascending query tokens without such a task (requested nodes whose suffix is empty or has
+//    several chunks).  Both are part of the dump only: the kernels finish rows themselves where every
+//    query token of the request has a single piece, else all rows go through the merge kernel.
 #pragma once
 
 #include <cstdint>
