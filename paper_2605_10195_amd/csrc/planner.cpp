@@ -24,11 +24,15 @@ int32_t clamp32(int64_t v, int32_t lo, int32_t hi) {
 // branches on a 512-token prompt 13.6 with shared items of 256 tokens, 11.7 with 128; one
 // prompt of 16000 tokens 23.7 / 20.6 / 20.1 / 27.8 with 256 / 512 / 1024 / 2048, four of them
 // 73 / 66 / 60 / 57; private items of 128 or 256 tokens are within 3 % of each other.
-int32_t auto_prefix_chunk(int64_t pages, int32_t page_size) {
-  return clamp32((pages + 255) / 256, std::max(1, 128 / page_size), std::max(1, 4096 / page_size));
+// Items shorter than 16 (shared) and 8 (private) pages only while the launch has at most kFineRows
+// partial rows: beyond that a request would need more room for them than it did with those bounds,
+// and the entry point that allocates nothing has 48 MiB of it.
+constexpr int64_t kFineRows = 40960;
+int32_t auto_prefix_chunk(int64_t pages, int32_t page_size, bool fine) {
+  return clamp32((pages + 255) / 256, fine ? std::max(1, 128 / page_size) : 16, 256);
 }
-int32_t auto_suffix_chunk(int64_t pages, int32_t page_size) {
-  return clamp32((pages + 1023) / 1024, std::max(1, 128 / page_size), std::max(1, 1024 / page_size));
+int32_t auto_suffix_chunk(int64_t pages, int32_t page_size, bool fine) {
+  return clamp32((pages + 1023) / 1024, fine ? std::max(1, 128 / page_size) : 8, 64);
 }
 
 struct Segment {
@@ -262,9 +266,18 @@ PlanError Planner::ensure_split(const PageTable &pt, Plan *plan) {
     prefix_pages_weighted +=
         static_cast<int64_t>(s.ids.size()) * (s.qt_count * G <= 64 ? 1 : (s.qt_count * G + kWideSpan - 1) / kWideSpan);
 
-  pl.prefix_chunk_pages =
-      prefix_chunk_pages > 0 ? prefix_chunk_pages : auto_prefix_chunk(prefix_pages_weighted * num_kv_heads, P);
-  pl.suffix_chunk_pages = suffix_chunk_pages > 0 ? suffix_chunk_pages : auto_suffix_chunk(suffix_pages * num_kv_heads, P);
+  auto choose = [&](bool fine) {
+    pl.prefix_chunk_pages =
+        prefix_chunk_pages > 0 ? prefix_chunk_pages : auto_prefix_chunk(prefix_pages_weighted * num_kv_heads, P, fine);
+    pl.suffix_chunk_pages =
+        suffix_chunk_pages > 0 ? suffix_chunk_pages : auto_suffix_chunk(suffix_pages * num_kv_heads, P, fine);
+    auto chunks = [](const Segment &s, int64_t c) { return (static_cast<int64_t>(s.ids.size()) + c - 1) / c; };
+    int64_t partial = 0;
+    for (const Segment &s : groups) partial += chunks(s, pl.prefix_chunk_pages) * s.qt_count * G;
+    for (const Segment &s : suffixes) partial += chunks(s, pl.suffix_chunk_pages) * s.qt_count * G;
+    return partial * num_kv_heads;
+  };
+  if (choose(true) > kFineRows) choose(false);
 
   // ---- tasks
   std::vector<int32_t> qt_req;  // with draft masks: the request of every query token
@@ -471,8 +484,17 @@ float Planner::estimate_split(const PageTable &pt, Plan *plan, int32_t head_dim,
     if (tail[i] > 0) max_rows = std::max(max_rows, q_len(i) * G);
   }
   const int32_t H = pl.num_kv_heads;
-  const int64_t pc = pl.req_prefix_chunk > 0 ? pl.req_prefix_chunk : auto_prefix_chunk(weighted * H, P);
-  const int64_t sc = pl.req_suffix_chunk > 0 ? pl.req_suffix_chunk : auto_suffix_chunk(suffix_pages * H, P);
+  int64_t pc = 1, sc = 1;
+  auto choose = [&](bool fine) {  // as in ensure_split
+    pc = pl.req_prefix_chunk > 0 ? pl.req_prefix_chunk : auto_prefix_chunk(weighted * H, P, fine);
+    sc = pl.req_suffix_chunk > 0 ? pl.req_suffix_chunk : auto_suffix_chunk(suffix_pages * H, P, fine);
+    int64_t partial = 0;
+    for (int32_t u : est_nodes_)
+      if (est_reqs_[u] > 1) partial += (pages_of(u) + pc - 1) / pc * est_rows_[u];
+    for (int32_t i = 0; i < n; ++i) partial += (tail[i] + sc - 1) / sc * q_len(i) * G;
+    return partial * H;
+  };
+  if (choose(true) > kFineRows) choose(false);
   double through_lds = 0, streamed = 0, partial_rows = 0;  // per kv head
   for (int32_t u : est_nodes_) {
     if (est_reqs_[u] > 1) {
@@ -488,6 +510,12 @@ float Planner::estimate_split(const PageTable &pt, Plan *plan, int32_t head_dim,
     const int64_t rows = q_len(i) * G;
     streamed += static_cast<double>((tail[i] + 1) / 2 * ((rows + tile - 1) / tile));
     partial_rows += static_cast<double>((tail[i] + sc - 1) / sc * rows);
+  }
+  // A request that the tree-walk kernel serves without partial rows is not moved to a path that
+  // needs more room for them than the entry point that allocates nothing has.
+  if (partial_rows * H * (head_dim * 4 + 8) > 40.0 * (1 << 20)) {
+    pl.split_estimate = 1.0e9f;
+    return pl.split_estimate;
   }
   const double per_head = 4.45e-3 * through_lds + 0.97e-3 * kv_bytes * streamed;  // us at head dim 128
   pl.split_estimate = static_cast<float>(9.4 + H * head_dim * (per_head / 128.0 + 3.0e-6 * partial_rows));
