@@ -49,6 +49,8 @@ constexpr float kNegInf = -__builtin_huge_valf();
 // Start value of the tree-walk kernel's softmax reference: finite, so that (-inf) - m stays -inf,
 // and so far below any score that the first visible score replaces it.
 constexpr float kWalkMInit = -1.0e30f;
+// The same for row-major pools, which hold fp32: no finite score lies below it.
+constexpr float kRowMajorMInit = -__FLT_MAX__;
 
 __device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
 
@@ -1724,7 +1726,7 @@ __global__ __launch_bounds__(256, DP <= 128 ? 2 : 1) void spex_rowmajor_attn_ker
   f32x4 o[NO];
 #pragma unroll
   for (int i = 0; i < NO; ++i) o[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-  float m = kWalkMInit, l = 0.f;
+  float m = kRowMajorMInit, l = 0.f;
 
   const int64_t tile_bytes = static_cast<int64_t>(D) * ESZ << logp;
   const char *kpool = static_cast<const char *>(p.k_pool), *vpool = static_cast<const char *>(p.v_pool);
@@ -1818,11 +1820,11 @@ __global__ __launch_bounds__(256, DP <= 128 ? 2 : 1) void spex_rowmajor_attn_ker
         x[r] = (sa[r] + sb[r]) * c;
         x[r] = (r < have && ((vm >> r) & 1u)) ? x[r] : kNegInf;
       }
-      // softmax reference as in the tree-walk kernel: moves only when a score exceeds it by 2^8 in weight
+      // The softmax reference is the running maximum, so that no weight exceeds 1 and a sum of large
+      // fp32 values overflows only where the row's own result does.
       const float mx = fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3]));
-      if (__any(mx > m + 8.f)) {
-        const float rmax = row_group_max(mx);
-        const float m_new = rmax > m + 8.f ? rmax : m;
+      if (__any(mx > m)) {
+        const float m_new = fmaxf(m, row_group_max(mx));
         const float alpha = fast_exp2(m - m_new);
         m = m_new;
         l *= alpha;

@@ -3,6 +3,7 @@ against the numpy oracle.  Tolerances are those of gpu_common.TOL: 1e-5 where pr
 in fp32, the stated bf16 / fp8 bounds elsewhere."""
 
 import pytest
+import torch
 
 import spex_workloads as sw
 from gpu_common import assert_close, run_gpu, run_oracle
@@ -49,3 +50,32 @@ def test_row_major_many_rows():
         wl = sw.spec_at_scale(n_queries=1, prompt=130, step=20, branches=32, heads=(16, 2, 96), kv_dtype=kv,
                               q_dtype="f32" if kv == "f32" else "bf16")
         assert_close(run_gpu(wl), run_oracle(wl), kv, kv)
+
+
+# Row 0: every score between -8e37 and -2e37, so that the first token takes all the weight.  Row 1: scores
+# that rise by less than 2^8 in weight from token to token and over all, and values whose sum under weights
+# of at most 1 stays below the end of fp32.  fp32 weights and sums throughout: 1e-5 as elsewhere.
+@pytest.mark.parametrize("kv", ["f32", "bf16"])
+@pytest.mark.parametrize("n_tokens,chunk", [(1, 0), (7, 0), (300, 0), (300, 1)])
+def test_row_major_scores_and_values_at_the_end_of_the_range(kv, n_tokens, chunk):
+    import paper_2605_10195_amd as spex
+    dt = torch.float32 if kv == "f32" else torch.bfloat16
+    heads, dim, page = 2, 40, 16
+    t = spex.SpexTree(heads, 1, dim, page, kv, kv, num_pages=-(-n_tokens // page) + 1, device="cuda", prefix_chunk_pages=chunk,
+                      suffix_chunk_pages=chunk)
+    (u,) = t.fork(-1, 1)
+    k = torch.zeros((n_tokens, 1, dim))
+    k[:, 0, 0] = 2e18 * (1.0 + 3.0 * torch.arange(n_tokens) / n_tokens)
+    v = (1e36 * (0.5 + 0.5 * torch.arange(n_tokens) / n_tokens))[:, None, None].repeat(1, 1, dim)
+    k, v = k.to(dt).cuda(), v.to(dt).cuda()
+    t.append_step(u, k, v)
+    q = torch.zeros((1, heads, dim))
+    q[0, 0, 0], q[0, 1, 0] = -1e19, 5.0 / 8e18
+    q = q.to(dt).cuda()
+    out, lse = t.decode_attention([u], None, q, 1.0)
+    s = q[0, :, :1].double().cpu() * k[:, 0, 0].double().cpu()
+    want, got = torch.softmax(s, dim=1) @ v[:, 0].double().cpu(), out[0].double().cpu()
+    assert bool(torch.isfinite(got).all())
+    assert float((got / want - 1.0).abs().max()) <= 1e-5
+    assert float((lse[0].double().cpu() / torch.logsumexp(s, dim=1) - 1.0).abs().max()) <= 1e-5
+    t.close()
