@@ -1996,13 +1996,14 @@ __global__ __launch_bounds__(256) void spex_lse_merge_kernel(MergeArgs a, Shape 
     if (!live || s != 0) return;
     float m_all = m;
     for (int k = 1; k < slices; ++k) m_all = fmaxf(m_all, lds_ml[threadIdx.x + k * dv][0]);
-    const float f0 = fast_exp2(m - m_all);
+    const float m_safe = m_all == kNegInf ? 0.f : m_all;  // every score of the row is -inf: lse is -inf too
+    const float f0 = fast_exp2(m - m_safe);
     l *= f0;
 #pragma unroll
     for (int i = 0; i < VEC; ++i) acc[i] *= f0;
     for (int k = 1; k < slices; ++k) {
       const int t = threadIdx.x + k * dv;
-      const float f = fast_exp2(lds_ml[t][0] - m_all);
+      const float f = fast_exp2(lds_ml[t][0] - m_safe);
       l += lds_ml[t][1] * f;
 #pragma unroll
       for (int i = 0; i < VEC; ++i) acc[i] += lds_o[t * VEC + i] * f;

@@ -2,6 +2,8 @@
 against the numpy oracle.  Tolerances are those of gpu_common.TOL: 1e-5 where products and sums are
 in fp32, the stated bf16 / fp8 bounds elsewhere."""
 
+import math
+
 import pytest
 import torch
 
@@ -78,4 +80,21 @@ def test_row_major_scores_and_values_at_the_end_of_the_range(kv, n_tokens, chunk
     assert bool(torch.isfinite(got).all())
     assert float((got / want - 1.0).abs().max()) <= 1e-5
     assert float((lse[0].double().cpu() / torch.logsumexp(s, dim=1) - 1.0).abs().max()) <= 1e-5
+    t.close()
+
+
+@pytest.mark.parametrize("chunk", [64, 4, 1])
+def test_lse_of_a_row_whose_scores_overflow(chunk):
+    """All scores of head 0 are -inf in fp32: its lse is -inf however many pieces and slices the merge folds;
+    head 1 is not touched by it."""
+    import paper_2605_10195_amd as spex
+    t = spex.SpexTree(2, 1, 40, 16, "f32", "f32", num_pages=32, device="cuda", prefix_chunk_pages=chunk, suffix_chunk_pages=chunk)
+    (u,) = t.fork(-1, 1)
+    k = torch.full((300, 1, 40), 1e30, device="cuda")
+    t.append_step(u, k, torch.ones_like(k))
+    q = torch.zeros((1, 2, 40), device="cuda")
+    q[0, 0] = -1e30
+    out, lse = t.decode_attention([u], None, q, 1.0)
+    assert float(lse[0, 0]) == float("-inf")
+    assert abs(float(lse[0, 1]) - math.log(300)) <= 1e-5 and float((out[0, 1] - 1.0).abs().max()) <= 1e-5
     t.close()
