@@ -233,6 +233,47 @@ bool obviously_split(const spex::Plan &pl) {
 }
 
 constexpr int kPlanArrays = 13;
+// The lists of a plan in the order in which they lie in its device copy.  Only those of the kernel set
+// that runs: a request that the automatic choice moved has the tree-walk lists of the comparison
+// too, and both together may not fit where one set does.
+struct PlanArrays {
+  const std::vector<int32_t> *a[kPlanArrays];
+  size_t off[kPlanArrays], total = 0;  // byte offsets (256-byte aligned) and size of the copy
+  PlanArrays(const spex::Plan &pl, bool walk) {
+    static const std::vector<int32_t> none;
+    const std::vector<int32_t> *all[kPlanArrays] = {
+        &pl.prefix_items, &pl.suffix_items, &pl.pg_rec, &pl.qt_rec,
+        &pl.part_indptr, &pl.part_base,    &pl.part_hstride, &pl.coop_items[0], &pl.coop_items[1],
+        &pl.walk_items, &pl.walk_blocks, &pl.walk_qt, &pl.qt_mask};
+    for (int i = 0; i < kPlanArrays; ++i) {
+      const bool both = i == kPlanArrays - 1, of_walk = i >= 9;
+      a[i] = both || of_walk == walk ? all[i] : &none;
+      off[i] = total;
+      total += align_up(a[i]->size() * sizeof(int32_t) + 16, 256);
+    }
+  }
+  void copy_to(char *dst) const {
+    for (int i = 0; i < kPlanArrays; ++i)
+      if (!a[i]->empty()) std::memcpy(dst + off[i], a[i]->data(), a[i]->size() * sizeof(int32_t));
+  }
+  DevicePlan at(const void *base) const {
+    auto ptr = [&](int i) { return reinterpret_cast<const int32_t *>(static_cast<const char *>(base) + off[i]); };
+    DevicePlan dp;
+    dp.prefix_items = ptr(0);
+    dp.suffix_items = ptr(1);
+    dp.pg_rec = ptr(2);
+    dp.qt_rec = ptr(3);
+    dp.part_indptr = ptr(4);
+    dp.part_base = ptr(5);
+    dp.part_hstride = ptr(6);
+    for (int c = 0; c < 2; ++c) dp.coop_items[c] = ptr(7 + c);
+    dp.walk_items = ptr(9);
+    dp.walk_blocks = ptr(10);
+    dp.walk_qt = ptr(11);
+    dp.qt_mask = a[12]->empty() ? nullptr : ptr(12);
+    return dp;
+  }
+};
 // Index, in the device blob's array list, of the arrays a length patch can touch.
 constexpr int kPatchTarget[5] = {2 /*pg_rec*/, 3 /*qt_rec*/, 10 /*walk_blocks*/, 11 /*walk_qt*/, 9 /*walk_items*/};
 
@@ -265,55 +306,33 @@ spex_status_t stage_send(spex_tree *t, void *dst, size_t bytes, hipStream_t stre
   return SPEX_OK;
 }
 
-// Copies every list that has been built to the device (one blob, arrays at 256-byte offsets).
-spex_status_t upload_plan(spex_tree *t, hipStream_t stream) {
+// Copies the lists of the tree-walk kernel, or of the split path, to the device.
+spex_status_t upload_plan(spex_tree *t, bool walk, hipStream_t stream) {
   const spex::Plan &pl = t->plan;
-  const std::vector<int32_t> *arrays[kPlanArrays] = {
-      &pl.prefix_items, &pl.suffix_items, &pl.pg_rec, &pl.qt_rec,
-      &pl.part_indptr, &pl.part_base,    &pl.part_hstride, &pl.coop_items[0], &pl.coop_items[1],
-      &pl.walk_items, &pl.walk_blocks, &pl.walk_qt, &pl.qt_mask};
-  size_t total = 0;
+  const PlanArrays pa(pl, walk);
   for (int i = 0; i < kPlanArrays; ++i) {
-    t->blob_off[i] = total;
-    t->blob_ints[i] = arrays[i]->size();
-    total += align_up(arrays[i]->size() * sizeof(int32_t) + 16, 256);
+    t->blob_off[i] = pa.off[i];
+    t->blob_ints[i] = pa.a[i]->size();
   }
-  const spex_status_t rs = stage_reserve(t, total);
+  const spex_status_t rs = stage_reserve(t, pa.total);
   if (rs != SPEX_OK) return rs;
-  if (total > t->d_plan_cap) {
+  if (pa.total > t->d_plan_cap) {
     if (t->d_plan) HIP_TRY(hipFree(t->d_plan));
     t->d_plan = nullptr;
     t->d_plan_cap = 0;
     // Freeing and allocating device memory synchronises the device, so the workspace grows in
     // large steps: at least 1 MiB, and twice what is needed now.
-    const size_t cap = align_up(std::max<size_t>(2 * total, size_t(1) << 20), 1 << 16);
+    const size_t cap = align_up(std::max<size_t>(2 * pa.total, size_t(1) << 20), 1 << 16);
     HIP_TRY(hipMalloc(&t->d_plan, cap));
     t->d_plan_cap = cap;
   }
-  char *h = static_cast<char *>(t->h_stage);
-  for (int i = 0; i < kPlanArrays; ++i)
-    if (!arrays[i]->empty())
-      std::memcpy(h + t->blob_off[i], arrays[i]->data(), arrays[i]->size() * sizeof(int32_t));
-  const spex_status_t ss = stage_send(t, t->d_plan, total, stream);
+  pa.copy_to(static_cast<char *>(t->h_stage));
+  const spex_status_t ss = stage_send(t, t->d_plan, pa.total, stream);
   if (ss != SPEX_OK) return ss;
-  const char *d = static_cast<const char *>(t->d_plan);
-  auto at = [&](int i) { return reinterpret_cast<const int32_t *>(d + t->blob_off[i]); };
-  DevicePlan &dp = t->dplan;
-  dp.prefix_items = at(0);
-  dp.suffix_items = at(1);
-  dp.pg_rec = at(2);
-  dp.qt_rec = at(3);
-  dp.part_indptr = at(4);
-  dp.part_base = at(5);
-  dp.part_hstride = at(6);
-  for (int c = 0; c < 2; ++c) dp.coop_items[c] = at(7 + c);
-  dp.walk_items = at(9);
-  dp.walk_blocks = at(10);
-  dp.walk_qt = at(11);
-  dp.qt_mask = pl.qt_mask.empty() ? nullptr : at(12);
+  t->dplan = pa.at(t->d_plan);
   t->plan_on_device = true;
-  t->device_has_split = pl.has_split;
-  t->device_has_walk = pl.has_walk;
+  t->device_has_split = !walk;
+  t->device_has_walk = walk;
   t->pending_patches.clear();
   return SPEX_OK;
 }
@@ -405,36 +424,14 @@ spex_status_t static_scratch(unsigned char **out) {
 
 // Copies the lists of the current plan into the plan region of the static scratch (through a
 // pageable host buffer of the handle: no pinned allocation) and fills dp with their addresses.
-spex_status_t upload_plan_static(spex_tree *t, unsigned char *base, DevicePlan *dp, hipStream_t stream) {
-  const spex::Plan &pl = t->plan;
-  const std::vector<int32_t> *arrays[kPlanArrays] = {
-      &pl.prefix_items, &pl.suffix_items, &pl.pg_rec, &pl.qt_rec,
-      &pl.part_indptr, &pl.part_base,    &pl.part_hstride, &pl.coop_items[0], &pl.coop_items[1],
-      &pl.walk_items, &pl.walk_blocks, &pl.walk_qt, &pl.qt_mask};
-  size_t off[kPlanArrays], total = 0;
-  for (int i = 0; i < kPlanArrays; ++i) {
-    off[i] = total;
-    total += align_up(arrays[i]->size() * sizeof(int32_t) + 16, 256);
-  }
-  if (total > kStaticPlanBytes) return SPEX_ERR_CAPACITY;
+spex_status_t upload_plan_static(spex_tree *t, bool walk, unsigned char *base, DevicePlan *dp, hipStream_t stream) {
+  const PlanArrays pa(t->plan, walk);
+  if (pa.total > kStaticPlanBytes) return SPEX_ERR_CAPACITY;
   std::vector<char> &h = t->static_stage;
-  if (h.size() < total) h.resize(total);
-  for (int i = 0; i < kPlanArrays; ++i)
-    if (!arrays[i]->empty()) std::memcpy(h.data() + off[i], arrays[i]->data(), arrays[i]->size() * sizeof(int32_t));
-  HIP_TRY(hipMemcpyAsync(base, h.data(), total, hipMemcpyHostToDevice, stream));
-  auto at = [&](int i) { return reinterpret_cast<const int32_t *>(base + off[i]); };
-  dp->prefix_items = at(0);
-  dp->suffix_items = at(1);
-  dp->pg_rec = at(2);
-  dp->qt_rec = at(3);
-  dp->part_indptr = at(4);
-  dp->part_base = at(5);
-  dp->part_hstride = at(6);
-  for (int c = 0; c < 2; ++c) dp->coop_items[c] = at(7 + c);
-  dp->walk_items = at(9);
-  dp->walk_blocks = at(10);
-  dp->walk_qt = at(11);
-  dp->qt_mask = pl.qt_mask.empty() ? nullptr : at(12);
+  if (h.size() < pa.total) h.resize(pa.total);
+  pa.copy_to(h.data());
+  HIP_TRY(hipMemcpyAsync(base, h.data(), pa.total, hipMemcpyHostToDevice, stream));
+  *dp = pa.at(base);
   return SPEX_OK;
 }
 
@@ -786,8 +783,7 @@ static spex_status_t decode_attention_impl(spex_tree_t *t, const spex_node_t *le
   // time is lower: long paths of few branches keep the tree-walk kernel waiting for its longest
   // workgroup (32 branches on prompts of 12500 tokens, 292 workgroups: 449 us against 211 through
   // the split path), many short nodes cost the split path an item and partial rows each (1024
-  // branches on nodes of 16 tokens: 124 against 28).  Only the lists of the chosen kernels are kept
-  // on the device.
+  // branches on nodes of 16 tokens: 124 against 28).
   bool want_walk = (t->kernel_mode == 0 || t->kernel_mode == 3) && spex::has_mfma_kernel(t->shape);
   const bool tree_masks = draft_masks != nullptr;
   if (want_walk && t->kernel_mode == 0 && !pl.has_walk && obviously_split(pl))
@@ -830,11 +826,11 @@ static spex_status_t decode_attention_impl(spex_tree_t *t, const spex_node_t *le
       return SPEX_ERR_CAPACITY;
     const spex_status_t gs = static_scratch(&sbase);
     if (gs != SPEX_OK) return gs;
-    const spex_status_t us = upload_plan_static(t, sbase, &static_dp, stream);
+    const spex_status_t us = upload_plan_static(t, use_walk, sbase, &static_dp, stream);
     if (us != SPEX_OK) return us;
     if (!t->plan_on_device) t->pending_patches.clear();  // no device copy is waiting for them
   } else if (!t->plan_on_device || (use_walk ? !t->device_has_walk : !t->device_has_split)) {
-    const spex_status_t us = upload_plan(t, stream);
+    const spex_status_t us = upload_plan(t, use_walk, stream);
     if (us != SPEX_OK) return us;
   } else if (!t->pending_patches.empty()) {
     const spex_status_t us = send_patches(t, stream);

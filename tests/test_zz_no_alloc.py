@@ -95,3 +95,26 @@ def test_static_entry_point_refuses_what_does_not_fit():
     torch.cuda.synchronize()
     assert torch.all(torch.isfinite(ref_o))
     tree.close()
+
+
+@pytest.mark.parametrize("trees,tokens,heads", [(512, 22000, (8, 1, 64)), (256, 46000, (8, 2, 64)), (500, 24000, (4, 1, 128))])
+def test_static_entry_point_takes_requests_whose_lists_fit_one_set_at_a_time(trees, tokens, heads):
+    """Long paths of one branch each: the tree-walk lists take 11 MiB, the split path's 6, and the array has 16.
+    The automatic choice (the split path here) needs one of them, and gives what the tree-walk kernel gives."""
+    import paper_2605_10195_amd as spex
+    hq, hkv, dim = heads
+    tree = spex.SpexTree(hq, hkv, dim, 16, num_pages=trees * (-(-tokens // 16)), device="cuda")
+    roots = tree.fork(-1, trees)
+    for u in roots:
+        tree.append_step(u, None, None, n_tokens=tokens)
+    tree.k_pool.view(torch.bfloat16).normal_(0.0, 0.5)
+    tree.v_pool.view(torch.float16).normal_(0.0, 0.5)
+    q = torch.randn((trees, hq, dim), device="cuda").to(torch.bfloat16)
+    out = torch.empty((trees, hq, dim), dtype=torch.float32, device="cuda")
+    lse = torch.empty((trees, hq), dtype=torch.float32, device="cuda")
+    tree.decode_attention(roots, None, q, dim ** -0.5, out, lse, static_scratch=True)
+    assert tree.last_launch_info()["walk_row_tiles"] == 0
+    tree.set_tuning(0, 0, 3, 0, 0)
+    ref_o, ref_l = tree.decode_attention(roots, None, q, dim ** -0.5)
+    assert float((out - ref_o).norm() / ref_o.norm()) <= 1e-3 and float((lse - ref_l).abs().max()) <= 2e-3
+    tree.close()
