@@ -195,43 +195,6 @@ spex_status_t make_plan(spex_tree *t, const int32_t *leaves, const int32_t *q_le
   return st;
 }
 
-// Longest tree-walk workgroup (in two-page blocks) up to which a launch of `items` workgroups
-// (< 128) still goes to the tree-walk kernel.
-int32_t short_walk_blocks(int64_t items) {
-  return items <= 32 ? 20 : 20 + static_cast<int32_t>((items - 32) * 7 / 10);
-}
-
-// True if the automatic choice is certain to be the split path, judged from the request alone:
-// an upper bound on the tree-walk workgroups (no request has more rows than a 16-row wavefront,
-// so none is cut; every wavefront holds at least one request, so a root with r requests has at
-// most ceil(r / 4) row blocks) stays below 128, and a lower bound on
-// the longest workgroup (the longest path, two full pages per block) exceeds what that many
-// workgroups may walk.  Saves building the tree-walk lists just to discard them.
-bool obviously_split(const spex::Plan &pl) {
-  const size_t n = pl.req_leaves.size();
-  if (n == 0 || n > 512) return false;
-  const int32_t G = pl.num_q_heads / pl.num_kv_heads;
-  int32_t roots[512], counts[512], n_roots = 0;
-  int32_t longest = 0;
-  for (size_t i = 0; i < n; ++i) {
-    const int32_t r = pl.path_nodes[pl.path_indptr[i]];
-    int32_t k = 0;
-    while (k < n_roots && roots[k] != r) ++k;
-    if (k == n_roots) {
-      roots[n_roots] = r;
-      counts[n_roots++] = 0;
-    }
-    ++counts[k];
-    const int32_t ql = pl.req_q_lens.empty() ? 1 : pl.req_q_lens[i];
-    if (static_cast<int64_t>(ql) * G > 16) return false;  // may be cut into pieces: no simple bound
-    longest = std::max(longest, pl.qt_limit[pl.qoff[i] + ql - 1]);  // the path's tokens
-  }
-  int64_t items = 0;
-  for (int32_t k = 0; k < n_roots; ++k) items += (counts[k] + 3) / 4;
-  items *= pl.num_kv_heads;
-  return items < 128 && (longest + 31) / 32 > short_walk_blocks(items);
-}
-
 constexpr int kPlanArrays = 13;
 // The lists of a plan in the order in which they lie in its device copy.  Only those of the kernel set
 // that runs: a request that the automatic choice moved has the tree-walk lists of the comparison
@@ -778,36 +741,17 @@ static spex_status_t decode_attention_impl(spex_tree_t *t, const spex_node_t *le
   const spex_status_t st = make_plan(t, leaves, q_lens, draft_masks, n_leaves, &plan_state);
   if (st != SPEX_OK) return st;
   spex::Plan &pl = t->plan;
-  // Which kernels.  The tree-walk kernel needs lists that fill the chip (128 workgroups) or are short:
-  // otherwise the split path, which can cut long paths.  Where both apply, the one whose estimated
-  // time is lower: long paths of few branches keep the tree-walk kernel waiting for its longest
-  // workgroup (32 branches on prompts of 12500 tokens, 292 workgroups: 449 us against 211 through
-  // the split path), many short nodes cost the split path an item and partial rows each (1024
-  // branches on nodes of 16 tokens: 124 against 28).
-  bool want_walk = (t->kernel_mode == 0 || t->kernel_mode == 3) && spex::has_mfma_kernel(t->shape);
   const bool tree_masks = draft_masks != nullptr;
-  if (want_walk && t->kernel_mode == 0 && !pl.has_walk && obviously_split(pl))
-    want_walk = false;  // few requests with long paths: the split path without building the other lists
-  if (want_walk) t->planner.ensure_walk(*t->pt, &pl);
-  // Draft-tree masks are understood by every kernel but the tree-walk kernel that splits the path
-  // (walk_waves 2).
-  const bool walk_possible = want_walk && pl.walk_ok && (!tree_masks || pl.walk_waves != 2);
-  if (t->kernel_mode == 3 && !walk_possible) return SPEX_ERR_UNSUPPORTED;
-  const bool fills = walk_possible && (pl.walk_real_items >= 128 ||
-                                       pl.walk_max_item_blocks <= short_walk_blocks(pl.walk_real_items));
-  // Where branches of unequal length grow a token a call, some branch starts a page in most calls:
-  // tree-walk lists are patched then, split lists made again (300 branches: 160 us of host time a
-  // call), so a request that outgrew its last plan within 8 calls keeps the tree-walk kernel.
-  // The estimates are good to some 14 % and a tree-walk plan is the one that lasts, so the split path
-  // must promise 5 % less, or 30 % less for a launch of few workgroups, where the two differ by a
-  // few us either way.  With more workgroups than run at a time (two per compute unit) the longest
-  // one matters little and the estimate is not made; nor for more than 1024 query tokens, whose split
-  // lists take the host longer to make than a call (2500: 1.9 against 1.0 ms for a first call).
-  bool use_walk = walk_possible && (t->kernel_mode == 3 || fills);
-  if (use_walk && t->kernel_mode == 0 && !pl.growing && pl.walk_real_items <= 512 && pl.qt_limit.size() <= 1024) {
-    const float least = (pl.walk_real_items >= 128 ? 0.95f : 0.7f) * spex::Planner::estimate_walk(pl);
-    use_walk = t->planner.estimate_split(*t->pt, &pl, t->cfg.head_dim,
-                                         static_cast<int32_t>(elem_size(t->cfg.kv_dtype)), least) >= least;
+  bool use_walk = false;
+  if (t->kernel_mode == 3) {
+    if (!spex::has_mfma_kernel(t->shape)) return SPEX_ERR_UNSUPPORTED;
+    t->planner.ensure_walk(*t->pt, &pl);
+    // Draft-tree masks are understood by every kernel but the tree-walk kernel that splits the path
+    // (walk_waves 2).
+    if (!pl.walk_ok || (tree_masks && pl.walk_waves == 2)) return SPEX_ERR_UNSUPPORTED;
+    use_walk = true;
+  } else if (t->kernel_mode == 0 && spex::has_mfma_kernel(t->shape)) {
+    use_walk = t->planner.prefers_walk(*t->pt, &pl, t->cfg.head_dim, static_cast<int32_t>(elem_size(t->cfg.kv_dtype)));
   }
   ++pl.calls;
   if (!use_walk) {
@@ -869,7 +813,7 @@ static spex_status_t decode_attention_impl(spex_tree_t *t, const spex_node_t *le
     wa.scale_log2 = sm_scale * 1.4426950408889634f;
     wa.qt_mask = dp.qt_mask;
     HIP_TRY(bracket(3, true));
-    HIP_TRY(spex::launch_tree_walk(t->shape, wa, pl.walk_row_tiles, pl.walk_waves, spex::Planner::walk_in_halves(pl), stream));
+    HIP_TRY(spex::launch_tree_walk(t->shape, wa, pl.walk_row_tiles, pl.walk_waves, pl.walk_halves, stream));
     HIP_TRY(bracket(3, false));
     t->info[0] = pl.unique_tokens;
     t->info[1] = pl.prefix_tokens;

@@ -41,6 +41,43 @@ struct Segment {
   int32_t qt_begin = 0, qt_count = 0;
 };
 
+// Longest tree-walk workgroup (in two-page blocks) up to which a launch of `items` workgroups
+// (< 128) still goes to the tree-walk kernel.
+int32_t short_walk_blocks(int64_t items) {
+  return items <= 32 ? 20 : 20 + static_cast<int32_t>((items - 32) * 7 / 10);
+}
+
+// True if the automatic choice is certain to be the split path, judged from the request alone:
+// an upper bound on the tree-walk workgroups (no request has more rows than a 16-row wavefront,
+// so none is cut; every wavefront holds at least one request, so a root with r requests has at
+// most ceil(r / 4) row blocks) stays below 128, and a lower bound on
+// the longest workgroup (the longest path, two full pages per block) exceeds what that many
+// workgroups may walk.  Saves building the tree-walk lists just to discard them.
+bool obviously_split(const Plan &pl) {
+  const size_t n = pl.req_leaves.size();
+  if (n == 0 || n > 512) return false;
+  const int32_t G = pl.num_q_heads / pl.num_kv_heads;
+  int32_t roots[512], counts[512], n_roots = 0;
+  int32_t longest = 0;
+  for (size_t i = 0; i < n; ++i) {
+    const int32_t r = pl.path_nodes[pl.path_indptr[i]];
+    int32_t k = 0;
+    while (k < n_roots && roots[k] != r) ++k;
+    if (k == n_roots) {
+      roots[n_roots] = r;
+      counts[n_roots++] = 0;
+    }
+    ++counts[k];
+    const int32_t ql = pl.req_q_lens.empty() ? 1 : pl.req_q_lens[i];
+    if (static_cast<int64_t>(ql) * G > 16) return false;  // may be cut into pieces: no simple bound
+    longest = std::max(longest, pl.qt_limit[pl.qoff[i] + ql - 1]);  // the path's tokens
+  }
+  int64_t items = 0;
+  for (int32_t k = 0; k < n_roots; ++k) items += (counts[k] + 3) / 4;
+  items *= pl.num_kv_heads;
+  return items < 128 && (longest + 31) / 32 > short_walk_blocks(items);
+}
+
 }  // namespace
 
 PlanError Planner::begin(const PageTable &pt, const int32_t *leaves, const int32_t *q_lens,
@@ -451,9 +488,7 @@ PlanError Planner::ensure_split(const PageTable &pt, Plan *plan) {
 // tree-walk workgroups), each timed through both paths: the middle half of the predictions is within
 // 14 %.  Shared items of more than 16 rows cost their blocks of 32 tokens through LDS, the others
 // the blocks' bytes, and every row of an item its partial state.
-float Planner::estimate_split(const PageTable &pt, Plan *plan, int32_t head_dim, int32_t kv_bytes, float enough) {
-  Plan &pl = *plan;
-  if (pl.split_estimate >= 0.f) return pl.split_estimate;
+float Planner::estimate_split(const PageTable &pt, const Plan &pl, int32_t head_dim, int32_t kv_bytes, float enough) {
   // every token read once, nothing else
   const double bytes_only = 9.4 + 0.97e-3 * kv_bytes * static_cast<double>(pl.unique_tokens) / 32.0 * pl.num_kv_heads * head_dim / 128.0;
   if (bytes_only >= enough) return static_cast<float>(bytes_only);
@@ -513,13 +548,9 @@ float Planner::estimate_split(const PageTable &pt, Plan *plan, int32_t head_dim,
   }
   // A request that the tree-walk kernel serves without partial rows is not moved to a path that
   // needs more room for them than the entry point that allocates nothing has.
-  if (partial_rows * H * (head_dim * 4 + 8) > 40.0 * (1 << 20)) {
-    pl.split_estimate = 1.0e9f;
-    return pl.split_estimate;
-  }
+  if (partial_rows * H * (head_dim * 4 + 8) > 40.0 * (1 << 20)) return 1.0e9f;
   const double per_head = 4.45e-3 * through_lds + 0.97e-3 * kv_bytes * streamed;  // us at head dim 128
-  pl.split_estimate = static_cast<float>(9.4 + H * head_dim * (per_head / 128.0 + 3.0e-6 * partial_rows));
-  return pl.split_estimate;
+  return static_cast<float>(9.4 + H * head_dim * (per_head / 128.0 + 3.0e-6 * partial_rows));
 }
 
 // Eight wavefronts, two on each set of rows, halve every workgroup's path in time but leave one
@@ -541,7 +572,41 @@ bool Planner::walk_in_halves(const Plan &pl) {
 float Planner::estimate_walk(const Plan &pl) {
   const float longest = static_cast<float>(pl.walk_max_item_blocks);
   const float share = static_cast<float>(pl.walk_steps) * static_cast<float>(pl.num_kv_heads) / 512.f;
-  return walk_in_halves(pl) ? 4.7f + 0.36f * longest + 0.69f * share : 4.5f + 0.63f * longest + 0.84f * share;
+  return pl.walk_halves ? 4.7f + 0.36f * longest + 0.69f * share : 4.5f + 0.63f * longest + 0.84f * share;
+}
+
+// Which kernels.  The tree-walk kernel needs lists that fill the chip (128 workgroups) or are short:
+// otherwise the split path, which can cut long paths.  Where both apply, the one whose estimated
+// time is lower: long paths of few branches keep the tree-walk kernel waiting for its longest
+// workgroup (32 branches on prompts of 12500 tokens, 292 workgroups: 449 us against 211 through
+// the split path), many short nodes cost the split path an item and partial rows each (1024
+// branches on nodes of 16 tokens: 124 against 28).
+// Where branches of unequal length grow a token a call, some branch starts a page in most calls:
+// tree-walk lists are patched then, split lists made again (300 branches: 160 us of host time a
+// call), so a request that outgrew its last plan within 8 calls keeps the tree-walk kernel.
+// The estimates are good to some 14 % and a tree-walk plan is the one that lasts, so the split path
+// must promise 5 % less, or 30 % less for a launch of few workgroups, where the two differ by a
+// few us either way.  With more workgroups than run at a time (two per compute unit) the longest
+// one matters little and the estimate is not made; nor for more than 1024 query tokens, whose split
+// lists take the host longer to make than a call (2500: 1.9 against 1.0 ms for a first call).
+// Asked once per plan: patches raise the longest workgroup but not the sums behind both estimates, and
+// a plan that moved to the split path could no longer be patched when a page starts.
+bool Planner::prefers_walk(const PageTable &pt, Plan *plan, int32_t head_dim, int32_t kv_bytes) {
+  Plan &pl = *plan;
+  if (pl.route >= 0) return pl.route == 1;
+  bool walk = false;
+  if (pl.has_walk || !obviously_split(pl)) {  // few requests with long paths: no need to build the lists
+    ensure_walk(pt, &pl);
+    // masks: see the kernel that splits the path
+    walk = pl.walk_ok && (pl.req_masks.empty() || pl.walk_waves != 2) &&
+           (pl.walk_real_items >= 128 || pl.walk_max_item_blocks <= short_walk_blocks(pl.walk_real_items));
+    if (walk && !pl.growing && pl.walk_real_items <= 512 && pl.qt_limit.size() <= 1024) {
+      const float least = (pl.walk_real_items >= 128 ? 0.95f : 0.7f) * estimate_walk(pl);
+      walk = estimate_split(pt, pl, head_dim, kv_bytes, least) >= least;
+    }
+  }
+  pl.route = walk ? 1 : 0;
+  return walk;
 }
 
 // Tree-walk lists: the whole path of a set of query rows is handled by one workgroup, which keeps
@@ -995,6 +1060,7 @@ void Planner::ensure_walk(const PageTable &pt, Plan *plan) {
       }
     }
   pl.walk_ok = true;
+  pl.walk_halves = walk_in_halves(pl);
 }
 
 // Appends to requested nodes since the plan was made (no fork, no prune): the lists stay as they

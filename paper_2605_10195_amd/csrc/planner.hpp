@@ -108,7 +108,10 @@ struct Plan {
   int64_t walk_steps = 0;            // the same summed over the row blocks (one kv head each)
   int32_t calls = 0;                 // attention calls the plan has served
   bool growing = false;              // made because appends outgrew a plan that had served few calls
-  float split_estimate = -1.f;       // Planner::estimate_split, once per plan
+  // Decided when the lists are made and kept through length patches, which leave the figures behind
+  // the decisions as they were.
+  bool walk_halves = false;          // eight wavefronts walk the lists made for four, two on each set of rows
+  int32_t route = -1;                // Planner::prefers_walk: -1 not asked yet, 0 split path, 1 tree-walk kernel
   int64_t walk_block_visits = 0;  // blocks over all row blocks (a block shared by two row blocks counts twice)
 };
 
@@ -127,13 +130,8 @@ class Planner {
   void ensure_csr(const PageTable &pt, Plan *plan);
   PlanError ensure_split(const PageTable &pt, Plan *plan);
   void ensure_walk(const PageTable &pt, Plan *plan);
-  // Microseconds a call takes through the split path / the tree-walk kernel, from the shape of the
-  // request (the first without building the split lists, the second from the tree-walk lists).
-  // A result of `enough` or more may be a lower bound.
-  float estimate_split(const PageTable &pt, Plan *plan, int32_t head_dim, int32_t kv_bytes, float enough);
-  static float estimate_walk(const Plan &plan);
-  // Whether eight wavefronts walk the lists made for four, two on each set of rows.
-  static bool walk_in_halves(const Plan &plan);
+  // The automatic choice, made once per plan: true for the tree-walk kernel (its lists are built then).
+  bool prefers_walk(const PageTable &pt, Plan *plan, int32_t head_dim, int32_t kv_bytes);
   // Brings a plan up to date after appends to requested nodes (no fork or prune since it was
   // made).  Tokens that fill up a last page change valid counts and limits; a newly started page
   // becomes page b of the node's last block or, in tree-walk lists that are the plan's only
@@ -142,6 +140,12 @@ class Planner {
   bool patch_lengths(const PageTable &pt, Plan *plan, std::vector<int32_t> *dev_patches);
 
  private:
+  // Microseconds a call takes through the split path / the tree-walk kernel, from the shape of the
+  // request (the first without building the split lists, the second from the tree-walk lists).
+  // A result of `enough` or more may be a lower bound.
+  float estimate_split(const PageTable &pt, const Plan &pl, int32_t head_dim, int32_t kv_bytes, float enough);
+  static float estimate_walk(const Plan &plan);
+  static bool walk_in_halves(const Plan &plan);
   std::vector<int32_t> multi_, last_pg_;
   std::vector<int32_t> stamp_, slot_;  // per-node scratch of build_walk, valid where stamp_ == current stamp
   // scratch of the request ordering in ensure_walk: pre-order rank and child ranges per node,

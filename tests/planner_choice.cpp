@@ -1,0 +1,113 @@
+// Host-only checks of the planner's automatic choices, built with sanitizers by test_host_sanitizers.py:
+// a plan that length patches bring up to date keeps the kernels that a fresh plan of the same request
+// would get, and the rules hold at their boundaries.
+#include <algorithm>
+#include <cstdio>
+#include <vector>
+
+#include "../paper_2605_10195_amd/csrc/planner.hpp"
+
+using namespace spex;
+
+static int failures = 0;
+#define CHECK(cond, ...) \
+  do { \
+    if (!(cond)) { std::printf("line %d: " #cond " ", __LINE__); std::printf(__VA_ARGS__); std::printf("\n"); ++failures; } \
+  } while (0)
+
+struct Forest {
+  PageTable pt;
+  std::vector<int32_t> leaves, q_lens;
+  Forest(int64_t pages, int page_size) : pt(pages, page_size, nullptr) {}
+  // `roots` prompts with `branches` nodes each below them (0: the prompts themselves are asked for)
+  void add(int roots, int prompt, int branches, int tokens, int q_len = 1) {
+    const int r = pt.fork(kNoNode, roots);
+    for (int i = 0; i < roots; ++i) {
+      pt.append(r + i, prompt, nullptr);
+      if (branches == 0) ask(r + i, q_len);
+    }
+    for (int i = 0; i < roots && branches > 0; ++i) {
+      const int f = pt.fork(r + i, branches);
+      for (int k = 0; k < branches; ++k) {
+        pt.append(f + k, tokens, nullptr);
+        ask(f + k, q_len);
+      }
+    }
+  }
+  void ask(int u, int q_len) {
+    leaves.push_back(u);
+    q_lens.push_back(q_len);
+  }
+};
+
+struct Made {
+  Planner planner;
+  Plan plan;
+  Made(const Forest &f, int Hq, int Hkv, int prefix_chunk = 0, int suffix_chunk = 0) {
+    const PlanError e = planner.begin(f.pt, f.leaves.data(), f.q_lens.data(), nullptr, static_cast<int32_t>(f.leaves.size()), Hq,
+                                      Hkv, prefix_chunk, suffix_chunk, 0, 0, &plan);
+    CHECK(e == PlanError::kOk, "begin");
+  }
+};
+
+// Branches that grow a token each per round: as long as the patches hold, choice and halves are those
+// of a plan made afresh.
+static void growth(int roots, int prompt, int branches, int tokens, int Hq, int Hkv, int rounds) {
+  Forest f(roots * (prompt / 16 + 2 + branches * ((tokens + rounds) / 16 + 2)), 16);
+  f.add(roots, prompt, branches, tokens);
+  Made m(f, Hq, Hkv);
+  const bool first = m.planner.prefers_walk(f.pt, &m.plan, 128, 2);
+  std::vector<int32_t> patches;
+  int patched = 0;
+  for (int t = 0; t < rounds; ++t) {
+    for (int32_t u : f.leaves) f.pt.append(u, 1, nullptr);
+    patches.clear();
+    if (!m.planner.patch_lengths(f.pt, &m.plan, &patches)) break;
+    ++patched;
+    Made fresh(f, Hq, Hkv);
+    const bool now = m.planner.prefers_walk(f.pt, &m.plan, 128, 2), want = fresh.planner.prefers_walk(f.pt, &fresh.plan, 128, 2);
+    CHECK(now == first, "%d roots of %d, %d branches: the choice changed after %d tokens", roots, prompt, branches, t + 1);
+    CHECK(now == want, "%d roots of %d, %d branches: a fresh plan chooses otherwise after %d tokens", roots, prompt, branches, t + 1);
+    if (first) CHECK(m.plan.walk_halves == fresh.plan.walk_halves, "halves after %d tokens", t + 1);
+  }
+  CHECK(patched >= std::min(rounds, first ? 40 : 1), "only %d rounds patched", patched);
+}
+
+int main() {
+  growth(8, 2500, 24, 17, 32, 8, 64);
+  growth(8, 3000, 32, 17, 32, 8, 64);
+  growth(32, 600, 16, 40, 32, 8, 64);
+  growth(40, 700, 8, 20, 16, 4, 64);
+
+  // one branch a tree and one kv head: a workgroup per tree
+  auto halves = [](int even, int longer) {
+    Forest f(even * 4 + 4000, 16);
+    f.add(even, 64, 0, 0);
+    if (longer) f.add(1, 16 * 60, 0, 0);
+    Made m(f, 4, 1);
+    m.planner.ensure_walk(f.pt, &m.plan);
+    CHECK(m.plan.walk_ok && m.plan.walk_real_items == even + (longer ? 1 : 0), "%d workgroups", m.plan.walk_real_items);
+    return m.plan.walk_halves;
+  };
+  CHECK(halves(256, 0), "256 even workgroups");
+  CHECK(!halves(257, 0), "257 even workgroups");
+  CHECK(halves(447, 1), "448 workgroups, one of them long");
+  CHECK(!halves(448, 1), "449 workgroups");
+
+  // no estimate beyond 512 workgroups or 1024 query tokens: the tree-walk kernel
+  auto choice = [](int trees, int tokens, int q_len) {
+    Forest f(trees * (tokens / 16 + 1), 16);
+    f.add(trees, tokens, 0, 0, q_len);
+    Made m(f, 4, 1);
+    return m.planner.prefers_walk(f.pt, &m.plan, 128, 2);
+  };
+  CHECK(!choice(512, 20000, 1), "512 workgroups on long paths");
+  CHECK(choice(513, 20000, 1), "513 workgroups");
+  CHECK(!choice(341, 16000, 3), "1023 query tokens");
+  CHECK(choice(342, 16000, 3), "1026 query tokens");
+  CHECK(!choice(16, 20000, 1), "few long paths");
+  CHECK(choice(16, 512, 1), "few short paths");
+
+  if (failures == 0) std::printf("ok\n");
+  return failures != 0;
+}

@@ -58,3 +58,13 @@ def test_planner_fuzz_under_sanitizers(tmp_path):
     assert run.stdout.startswith("ok:"), run.stdout
     patched_with_pages = int(run.stdout.split("(")[1].split()[0])
     assert patched_with_pages > 1000
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
+def test_planner_choices_under_sanitizers(tmp_path):
+    exe = str(tmp_path / "planner_choice")
+    build_with_sanitizers(exe, [os.path.join(HERE, "planner_choice.cpp"), os.path.join(CSRC, "planner.cpp"),
+                                os.path.join(CSRC, "page_table.cpp")])
+    run = subprocess.run([exe], capture_output=True, text=True, timeout=600)
+    assert run.returncode == 0, (run.stdout[-2000:], run.stderr[-4000:])
+    assert run.stdout == "ok\n", run.stdout
