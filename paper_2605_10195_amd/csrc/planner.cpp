@@ -26,13 +26,19 @@ int32_t clamp32(int64_t v, int32_t lo, int32_t hi) {
 // 73 / 66 / 60 / 57; private items of 128 or 256 tokens are within 3 % of each other.
 // Items shorter than 16 (shared) and 8 (private) pages only while the launch has at most kFineRows
 // partial rows: beyond that a request would need more room for them than it did with those bounds,
-// and the entry point that allocates nothing has 48 MiB of it.
+// and the entry point that allocates nothing has 48 MiB of it.  Pages of fewer than four tokens go to the
+// generic kernel, a wavefront per item and row, which needs many items and keeps the 16 and 8 pages
+// (128 tokens instead: 16 branches on pages of 2 tokens 123.9 -> 190.1 us).
 constexpr int64_t kFineRows = 40960;
+int32_t auto_chunk(int64_t pages, int32_t items, int32_t page_size, bool fine, int32_t bound, int32_t most) {
+  const int32_t floor = page_size < 4 ? bound : std::max(1, 128 / page_size);
+  return clamp32((pages + items - 1) / items, fine ? floor : std::max(floor, bound), most);
+}
 int32_t auto_prefix_chunk(int64_t pages, int32_t page_size, bool fine) {
-  return clamp32((pages + 255) / 256, fine ? std::max(1, 128 / page_size) : 16, 256);
+  return auto_chunk(pages, 256, page_size, fine, 16, 256);
 }
 int32_t auto_suffix_chunk(int64_t pages, int32_t page_size, bool fine) {
-  return clamp32((pages + 1023) / 1024, fine ? std::max(1, 128 / page_size) : 8, 64);
+  return auto_chunk(pages, 1024, page_size, fine, 8, 64);
 }
 
 struct Segment {

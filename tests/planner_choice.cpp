@@ -108,6 +108,25 @@ int main() {
   CHECK(!choice(16, 20000, 1), "few long paths");
   CHECK(choice(16, 512, 1), "few short paths");
 
+  // automatic items, by page size: never more partial rows than the shortest items give, and items of
+  // at least those lengths where the partial rows would be too many
+  for (int P = 1; P <= 64; P *= 2)
+    for (int q_len : {1, 64}) {
+      Forest f(2048 / P + 32 * (128 / P + 1) + 1, P);
+      f.add(1, 2048, 32, 128, q_len);
+      const int lo_shared = P < 4 ? 16 : 128 / P, lo_private = P < 4 ? 8 : 128 / P;
+      Made a(f, 32, 8), s(f, 32, 8, lo_shared, lo_private);
+      CHECK(a.planner.ensure_split(f.pt, &a.plan) == PlanError::kOk, "split lists");
+      CHECK(s.planner.ensure_split(f.pt, &s.plan) == PlanError::kOk, "split lists");
+      CHECK(a.plan.n_partial_rows <= s.plan.n_partial_rows, "pages of %d, %d queries: %ld partial rows, %ld with the shortest items", P,
+            q_len, static_cast<long>(a.plan.n_partial_rows), static_cast<long>(s.plan.n_partial_rows));
+      CHECK(a.plan.prefix_chunk_pages >= lo_shared && a.plan.suffix_chunk_pages >= lo_private, "pages of %d, %d queries: items of %d and %d pages",
+            P, q_len, a.plan.prefix_chunk_pages, a.plan.suffix_chunk_pages);
+      if (s.plan.n_partial_rows > 40960)
+        CHECK(a.plan.prefix_chunk_pages >= 16 && a.plan.suffix_chunk_pages >= 8, "pages of %d, %d queries: items of %d and %d pages", P, q_len,
+              a.plan.prefix_chunk_pages, a.plan.suffix_chunk_pages);
+    }
+
   if (failures == 0) std::printf("ok\n");
   return failures != 0;
 }
