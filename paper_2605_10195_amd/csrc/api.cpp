@@ -39,7 +39,7 @@ bool is_pow2(int32_t x) { return x > 0 && (x & (x - 1)) == 0; }
 // Device copy of a Plan: one blob, arrays at 256-byte aligned offsets.
 struct DevicePlan {
   const int32_t *prefix_items = nullptr, *suffix_items = nullptr, *pg_rec = nullptr, *qt_rec = nullptr;
-  const int32_t *part_indptr = nullptr, *part_base = nullptr, *part_hstride = nullptr;
+  const int32_t *part_indptr = nullptr, *part_base = nullptr, *part_hstride = nullptr, *merge_qt = nullptr;
   const int32_t *coop_items[2] = {nullptr, nullptr};
   const int32_t *walk_items = nullptr, *walk_blocks = nullptr, *walk_qt = nullptr, *qt_mask = nullptr;
 };
@@ -55,7 +55,7 @@ struct spex_tree {
   bool plan_on_device = false, device_has_split = false, device_has_walk = false;
   bool plan_patched_by_append = false;  // the cached plan was brought up to date by an append call
   DevicePlan dplan;
-  size_t blob_off[13] = {}, blob_ints[13] = {};  // byte offset and length of each list in the blob
+  size_t blob_off[14] = {}, blob_ints[14] = {};  // byte offset and length of each list in the blob
   std::vector<int32_t> pending_patches;          // {array, index, value} not yet on the device
   void *d_patch = nullptr;
   size_t d_patch_cap = 0;
@@ -195,7 +195,7 @@ spex_status_t make_plan(spex_tree *t, const int32_t *leaves, const int32_t *q_le
   return st;
 }
 
-constexpr int kPlanArrays = 13;
+constexpr int kPlanArrays = 14;
 // The lists of a plan in the order in which they lie in its device copy.  Only those of the kernel set
 // that runs: a request that the automatic choice moved has the tree-walk lists of the comparison
 // too, and both together may not fit where one set does.
@@ -206,10 +206,10 @@ struct PlanArrays {
     static const std::vector<int32_t> none;
     const std::vector<int32_t> *all[kPlanArrays] = {
         &pl.prefix_items, &pl.suffix_items, &pl.pg_rec, &pl.qt_rec,
-        &pl.part_indptr, &pl.part_base,    &pl.part_hstride, &pl.coop_items[0], &pl.coop_items[1],
+        &pl.part_indptr, &pl.part_base,    &pl.part_hstride, &pl.merge_qt, &pl.coop_items[0], &pl.coop_items[1],
         &pl.walk_items, &pl.walk_blocks, &pl.walk_qt, &pl.qt_mask};
     for (int i = 0; i < kPlanArrays; ++i) {
-      const bool both = i == kPlanArrays - 1, of_walk = i >= 9;
+      const bool both = i == kPlanArrays - 1, of_walk = i >= 10;
       a[i] = both || of_walk == walk ? all[i] : &none;
       off[i] = total;
       total += align_up(a[i]->size() * sizeof(int32_t) + 16, 256);
@@ -229,16 +229,17 @@ struct PlanArrays {
     dp.part_indptr = ptr(4);
     dp.part_base = ptr(5);
     dp.part_hstride = ptr(6);
-    for (int c = 0; c < 2; ++c) dp.coop_items[c] = ptr(7 + c);
-    dp.walk_items = ptr(9);
-    dp.walk_blocks = ptr(10);
-    dp.walk_qt = ptr(11);
-    dp.qt_mask = a[12]->empty() ? nullptr : ptr(12);
+    dp.merge_qt = ptr(7);
+    for (int c = 0; c < 2; ++c) dp.coop_items[c] = ptr(8 + c);
+    dp.walk_items = ptr(10);
+    dp.walk_blocks = ptr(11);
+    dp.walk_qt = ptr(12);
+    dp.qt_mask = a[13]->empty() ? nullptr : ptr(13);
     return dp;
   }
 };
 // Index, in the device blob's array list, of the arrays a length patch can touch.
-constexpr int kPatchTarget[5] = {2 /*pg_rec*/, 3 /*qt_rec*/, 10 /*walk_blocks*/, 11 /*walk_qt*/, 9 /*walk_items*/};
+constexpr int kPatchTarget[5] = {2 /*pg_rec*/, 3 /*qt_rec*/, 11 /*walk_blocks*/, 12 /*walk_qt*/, 10 /*walk_items*/};
 
 spex_status_t stage_reserve(spex_tree *t, size_t bytes) {
   t->stage_cur ^= 1;
@@ -449,6 +450,7 @@ spex_status_t spex_tree_create(const spex_config_t *cfg, spex_tree_t **out) {
   if (!t) return SPEX_ERR_INVALID_ARG;
   t->cfg = *cfg;
   t->shape = make_shape(*cfg);
+  t->planner.pool = {spex::has_mfma_kernel(t->shape), cfg->head_dim, static_cast<int32_t>(elem_size(cfg->kv_dtype))};
   t->pt = new (std::nothrow) spex::PageTable(cfg->num_pages, cfg->page_size, cfg->free_order);
   if (!t->pt) {
     delete t;
@@ -751,7 +753,7 @@ static spex_status_t decode_attention_impl(spex_tree_t *t, const spex_node_t *le
     if (!pl.walk_ok || (tree_masks && pl.walk_waves == 2)) return SPEX_ERR_UNSUPPORTED;
     use_walk = true;
   } else if (t->kernel_mode == 0 && spex::has_mfma_kernel(t->shape)) {
-    use_walk = t->planner.prefers_walk(*t->pt, &pl, t->cfg.head_dim, static_cast<int32_t>(elem_size(t->cfg.kv_dtype)));
+    use_walk = t->planner.prefers_walk(*t->pt, &pl);
   }
   ++pl.calls;
   if (!use_walk) {
@@ -866,6 +868,10 @@ static spex_status_t decode_attention_impl(spex_tree_t *t, const spex_node_t *le
     il.n_items[k] = static_cast<int32_t>(host_items[k]->size() / spex::Plan::kItemInts);
     il.span[k] = spans[k];
   }
+  a.part_indptr = dp.part_indptr;
+  a.part_base = dp.part_base;
+  a.part_hstride = dp.part_hstride;
+  const bool phases = !generic && pl.split_phases;
   HIP_TRY(bracket(0, true));
   if (generic) {
     for (int k = 0; k < 4; ++k) {
@@ -873,6 +879,8 @@ static spex_status_t decode_attention_impl(spex_tree_t *t, const spex_node_t *le
       a.n_items = il.n_items[k];
       HIP_TRY(spex::launch_generic_attention(t->shape, a, il.span[k], stream));
     }
+  } else if (phases) {
+    HIP_TRY(spex::launch_split_phases(t->shape, a, il, stream));
   } else {
     HIP_TRY(spex::launch_split(t->shape, a, il, stream));
   }
@@ -885,7 +893,9 @@ static spex_status_t decode_attention_impl(spex_tree_t *t, const spex_node_t *le
   m.part_ml = part_ml;
   m.out = out;
   m.lse = lse;
-  m.n_qtok = a.finish ? 0 : static_cast<int32_t>(pl.qt_limit.size());
+  // in phases the rows of suffixes in one piece are finished with the suffix
+  m.qt_ids = phases ? dp.merge_qt : nullptr;
+  m.n_qtok = a.finish ? 0 : static_cast<int32_t>(phases ? pl.merge_qt.size() : pl.qt_limit.size());
   m.avg_pieces = static_cast<int32_t>((pl.part_base.size() + pl.qt_limit.size() - 1) / pl.qt_limit.size());
   if (!a.finish) {
     HIP_TRY(bracket(2, true));

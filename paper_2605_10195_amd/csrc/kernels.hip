@@ -14,6 +14,9 @@
 //       stream them from memory to registers (S^T = K Q^T and O^T = V^T P^T with MFMA 16x16x32,
 //       fp32 accumulation).  Every item keeps an online softmax per row and emits the partial state
 //       (m, l, o); a shared page is read once for all rows below it.
+//   spex_wave_attn_kernel / spex_coop_attn_kernel
+//       The same items in launches of their own, few rows (a wavefront an item) and many, where there
+//       are items enough; private items come last and finish the rows of suffixes in one piece.
 //   spex_rowmajor_attn_kernel
 //       Same contract for row-major pools (fp32 KV, other page sizes and head dims), scores and
 //       weighted sums as fp32 MFMAs.
@@ -382,12 +385,13 @@ __device__ __forceinline__ void block_math(RowState<D, NT> &st, const bf16x8 (&k
 template <int D>
 constexpr int stage_floats() { return 16 * (D + 4); }
 
-// Emit the rows of a wavefront: partial state (m, l, o) for the merge step, or -- when every row of
-// the launch has a single piece -- the finished output rows.  The accumulators hold 4 consecutive
-// dims of one row per lane (64 B runs at a 512 B stride); they are transposed through the
-// wave-private LDS tile `my` so that every store instruction writes whole rows (1 KiB contiguous)
-// instead of half-filled cache lines.
-template <int D, int NT>
+// Emit the rows of a wavefront: partial state (m, l, o) for the merge step, or the finished output rows:
+// when every row of the launch has a single piece, or (ALLOW_FINAL, in a launch behind the one that wrote the
+// rows' other pieces) for a task flagged final, after folding those in.  The
+// accumulators hold 4 consecutive dims of one row per lane (64 B runs at a 512 B stride); they are
+// transposed through the wave-private LDS tile `my` so that every store instruction writes whole
+// rows (1 KiB contiguous) instead of half-filled cache lines.
+template <int D, int NT, bool ALLOW_FINAL>
 __device__ __forceinline__ void finish_rows(const AttnArgs &p, const Shape &sh, const Item &cur,
                                             int row_base, f32x4 (&o)[NT][D / 16],
                                             const float (&m_in)[NT], const float (&l_in)[NT],
@@ -395,26 +399,92 @@ __device__ __forceinline__ void finish_rows(const AttnArgs &p, const Shape &sh, 
   constexpr int kRowPad = D + 4;  // the pad spreads rows over LDS banks
   const int lane = threadIdx.x & 63, m16 = lane & 15, jj = lane >> 4;
   const int G = sh.G, rows = cur.qt_count * G, g = cur.g;
+  const bool fold_task = ALLOW_FINAL && (cur.flags & 2) != 0 && !p.finish;
+  const bool finish = p.finish || fold_task;
   constexpr int kLanesPerRow = D / 4;  // 16-byte pieces per row
   constexpr int kRowsPerInst = 64 / kLanesPerRow;
   const int sub = lane / kLanesPerRow, piece = lane % kLanesPerRow;
 #pragma unroll
   for (int nt = 0; nt < NT; ++nt) {
+    float l = l_in[nt];
+    float m = m_in[nt];
     const int r0w = row_base + nt * 16;  // first row of this tile
     if (r0w >= rows) break;              // wave-uniform
     const bool row_ok = r0w + m16 < rows;
+    const int hh = (r0w + m16) % G;
     int64_t dst_row;  // row index in part_o or in out
-    if (p.finish) {
-      const float inv = 1.0f / l_in[nt];
+    if (fold_task) {
+      // Fold in the other pieces of this row (written by the shared-prefix kernels, which ran
+      // before on the same stream) and normalise.  All rows of a suffix belong to one requested
+      // node, so they have the same number of pieces.
+      int e0 = 0, n_other = 0;
+      if (row_ok) {
+        e0 = p.part_indptr[qtok[nt]];
+        n_other = p.part_indptr[qtok[nt] + 1] - 1 - e0;
+      }
+      const int n_max = uniform(n_other);
+      auto fold = [&](const f32x2 ml, const f32x4 (&oj)[D / 16], bool use) {
+        const float mj = use ? ml[0] : kNegInf;
+        const float m_new = fmaxf(m, mj);
+        const float m_safe = m_new == kNegInf ? 0.f : m_new;
+        const float fa = fast_exp2(m - m_safe), fb = fast_exp2(mj - m_safe);
+        l = l * fa + ml[1] * fb;
+        m = m_new;
+#pragma unroll
+        for (int dt = 0; dt < D / 16; ++dt) o[nt][dt] = o[nt][dt] * fa + oj[dt] * fb;
+      };
+      if (n_max > 0) {
+        // The first 8 pieces are fetched four at a time with all loads of a batch in flight
+        // together.  Indices past a row's last piece are clamped to it (a repeated, finite read
+        // that is weighted with zero), which keeps the batches free of per-piece branches.
+        constexpr int kBatch = 4;
+        int64_t slot[2 * kBatch];
+#pragma unroll
+        for (int j = 0; j < 2 * kBatch; ++j) {
+          const int last = n_other - 1;
+          const int e = e0 + max(0, j < last ? j : last);
+          slot[j] = static_cast<int64_t>(p.part_base[e]) + static_cast<int64_t>(g) * p.part_hstride[e] + hh;
+        }
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+          if (q * kBatch < n_max) {
+            f32x2 ml[kBatch];
+            f32x4 oj[kBatch][D / 16];
+#pragma unroll
+            for (int k = 0; k < kBatch; ++k) {
+              ml[k] = *reinterpret_cast<const f32x2 *>(p.part_ml + slot[q * kBatch + k] * 2);
+              const float *src = p.part_o + slot[q * kBatch + k] * D + jj * 4;
+#pragma unroll
+              for (int dt = 0; dt < D / 16; ++dt) oj[k][dt] = *reinterpret_cast<const f32x4 *>(src + dt * 16);
+            }
+#pragma unroll
+            for (int k = 0; k < kBatch; ++k) fold(ml[k], oj[k], q * kBatch + k < n_other);
+          }
+        }
+        for (int j = 2 * kBatch; j < n_max; ++j) {  // deeper paths: one piece at a time
+          const int last = n_other - 1;
+          const int e = e0 + max(0, j < last ? j : last);
+          const int64_t sl = static_cast<int64_t>(p.part_base[e]) + static_cast<int64_t>(g) * p.part_hstride[e] + hh;
+          const f32x2 ml = *reinterpret_cast<const f32x2 *>(p.part_ml + sl * 2);
+          f32x4 oj[D / 16];
+          const float *src = p.part_o + sl * D + jj * 4;
+#pragma unroll
+          for (int dt = 0; dt < D / 16; ++dt) oj[dt] = *reinterpret_cast<const f32x4 *>(src + dt * 16);
+          fold(ml, oj, j < n_other);
+        }
+      }
+    }
+    if (finish) {
+      const float inv = 1.0f / l;
 #pragma unroll
       for (int dt = 0; dt < D / 16; ++dt) o[nt][dt] *= inv;
-      dst_row = static_cast<int64_t>(qtok[nt]) * sh.Hq + g * G + (r0w + m16) % G;
-      if (row_ok && jj == 0 && p.lse) p.lse[dst_row] = (m_in[nt] + __builtin_log2f(l_in[nt])) * 0.6931471805599453f;
+      dst_row = static_cast<int64_t>(qtok[nt]) * sh.Hq + g * G + hh;
+      if (row_ok && jj == 0 && p.lse) p.lse[dst_row] = (m + __builtin_log2f(l)) * 0.6931471805599453f;
     } else {
       dst_row = static_cast<int64_t>(cur.pbase) + static_cast<int64_t>(g) * rows + r0w + m16;
-      if (row_ok && jj == 0) *reinterpret_cast<f32x2 *>(p.part_ml + dst_row * 2) = f32x2{m_in[nt], l_in[nt]};
+      if (row_ok && jj == 0) *reinterpret_cast<f32x2 *>(p.part_ml + dst_row * 2) = f32x2{m, l};
     }
-    float *dst = p.finish ? p.out : p.part_o;
+    float *dst = finish ? p.out : p.part_o;
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
 #pragma unroll
@@ -472,15 +542,16 @@ __device__ __forceinline__ ListPos list_of(const SplitLists &ls, int wg) {
 template <int D>
 constexpr int wave_fold_floats() { return 4 * (D / 16) * 256 + 4 * 16 * 2; }
 
-// One workgroup per work item of up to 16 * NT rows.  A launch of this path is short of work items and
+// One work item of up to 16 * NT rows.  SPLIT: a workgroup for it.  A launch that is short of work items is
 // long on latency (a block costs a memory round trip, then its arithmetic), so the item's blocks
 // are split between the four wavefronts, which fold their softmax states through LDS; a chunk of
-// 16 pages is then two blocks deep instead of eight.
+// 16 pages is then two blocks deep instead of eight.  Otherwise a wavefront takes the item (SUFFIX: rows of a
+// private suffix, finished here where it is in one piece).
 // The K/V loads of block b+1 are in flight while block b is computed.  The steady-state loop is
 // free of conditional loads on purpose: the vector-memory completion counter is in-order, and a
 // load that is issued on one path only would force the compiler to wait for everything
 // outstanding at the join.
-template <int KV, int D, int NT, bool TREE>
+template <int KV, int D, int NT, bool TREE, bool SPLIT, bool SUFFIX>
 __device__ __forceinline__ void wave_item(const AttnArgs &p, const Shape &sh, const Item &cur, float *lds) {
   constexpr int ESZ = (KV == kFP8) ? 1 : 2;
   constexpr int TILE_BYTES = 16 * D * ESZ;
@@ -496,7 +567,7 @@ __device__ __forceinline__ void wave_item(const AttnArgs &p, const Shape &sh, co
 
   const int g = cur.g;
   const int n_all = (cur.pg_count + 1) >> 1;
-  const int b_first = (n_all * w) >> 2, nblk = (n_all * (w + 1)) >> 2;  // blocks b_first .. nblk - 1
+  const int b_first = SPLIT ? (n_all * w) >> 2 : 0, nblk = SPLIT ? (n_all * (w + 1)) >> 2 : n_all;  // blocks b_first .. nblk - 1
 
   auto issue_loads = [&](RawBlock<KV, D> &rb, const BlockMeta &bm) {
     rb.valid_a = bm.vp_a & 127;
@@ -583,6 +654,18 @@ __device__ __forceinline__ void wave_item(const AttnArgs &p, const Shape &sh, co
     }
   }
 
+  if constexpr (!SPLIT) {
+    float l_tot[NT];
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) {  // the row sum is spread over the four lane groups
+      float l = st.l[nt];
+      l += __shfl_xor(l, 16);
+      l += __shfl_xor(l, 32);
+      l_tot[nt] = l;
+    }
+    finish_rows<D, NT, SUFFIX>(p, sh, cur, cur.row0, st.o, st.m, l_tot, st.qtok, lds + w * stage_floats<D>());
+    return;
+  }
   // ---- fold: every wavefront leaves its state in LDS, wavefront w then makes output tiles w, w + 4, ..
   const int rows = cur.qt_count * sh.G;
   f32x4 *fo = reinterpret_cast<f32x4 *>(lds);      // [wavefront][16-dim tile][lane]
@@ -860,7 +943,7 @@ __device__ __forceinline__ void coop_item(const AttnArgs &p, const Shape &sh, co
       m_out[nt] = FP8 ? st.m[nt] : st.m[nt] * p.scale_log2;
       l_out[nt] = lacc[nt][0];
     }
-    finish_rows<D, NTW>(p, sh, cur, row_base, st.o, m_out, l_out, st.qtok, lds + w * stage_floats<D>());
+    finish_rows<D, NTW, false>(p, sh, cur, row_base, st.o, m_out, l_out, st.qtok, lds + w * stage_floats<D>());
   }
 }
 
@@ -878,7 +961,28 @@ __global__ __launch_bounds__(256, NT == 1 ? 2 : 1) void spex_split_attn_kernel(A
   else if (at.k == 1)
     coop_item<KV, D, 1, TREE>(p, sh, cur, lds);
   else
-    wave_item<KV, D, NT, TREE>(p, sh, cur, lds);
+    wave_item<KV, D, NT, TREE, true, false>(p, sh, cur, lds);
+}
+
+// The same in launches of their own where there are items enough to fill the chip with a wavefront each (the
+// rule and both sides' times stand with the planner's item lengths).  Items through LDS then keep two
+// workgroups to a compute unit whatever the private items' kernel holds: 220 registers against 390.
+template <int KV, int D, int NT, bool SUFFIX, bool TREE>
+__global__ __launch_bounds__(256, NT == 1 ? 2 : 1) void spex_wave_attn_kernel(AttnArgs p, Shape sh) {
+  __shared__ __attribute__((aligned(16))) float lds[4 * stage_floats<D>()];
+  const int item = uniform(static_cast<int>(blockIdx.x) * 4 + static_cast<int>(threadIdx.x >> 6));
+  if (item >= p.n_items) return;
+  const Item cur = load_item(p.items, item);
+  if (cur.pg_count == 0) return;  // padding item
+  wave_item<KV, D, NT, TREE, false, SUFFIX>(p, sh, cur, lds);
+}
+
+template <int KV, int D, int NTW, bool TREE>
+__global__ __launch_bounds__(256, 2) void spex_coop_attn_kernel(AttnArgs p, Shape sh) {
+  __shared__ __attribute__((aligned(16))) float lds[coop_lds_floats<D>()];
+  const Item cur = load_item(p.items, static_cast<int>(blockIdx.x));
+  if (cur.pg_count == 0) return;  // padding item (whole workgroup)
+  coop_item<KV, D, NTW, TREE>(p, sh, cur, lds);
 }
 
 // ---- tree-walk kernel: one workgroup carries a block of query rows from the root to the leaves --
@@ -1937,7 +2041,7 @@ __global__ __launch_bounds__(256) void spex_lse_merge_kernel(MergeArgs a, Shape 
   for (int i = 0; i < VEC; ++i) acc[i] = 0.f;
   int64_t orow = 0;
   if (live) {
-    const int qt = static_cast<int>(row / sh.Hq);
+    const int qt = a.qt_ids ? a.qt_ids[row / sh.Hq] : static_cast<int>(row / sh.Hq);
     const int h = static_cast<int>(row % sh.Hq);
     const int g = h / sh.G, hh = h % sh.G;
     orow = static_cast<int64_t>(qt) * sh.Hq + h;
@@ -2587,6 +2691,44 @@ template <int KV, int D>
 static hipError_t launch_split_d(const Shape &sh, const AttnArgs &a, const SplitLists &ls, int n_wg, hipStream_t stream) {
   return ls.span[2] <= 16 && ls.span[3] <= 16 ? launch_split_nt<KV, D, 1>(sh, a, ls, n_wg, stream)
                                               : launch_split_nt<KV, D, 2>(sh, a, ls, n_wg, stream);
+}
+
+template <int KV, int D, bool TREE>
+static hipError_t launch_phases_tree(const Shape &sh, AttnArgs a, const ItemLists &l, hipStream_t stream) {
+  const dim3 block(256);
+  for (int k : {2, 0, 1, 3}) {
+    if (l.n_items[k] <= 0) continue;
+    a.items = l.items[k];
+    a.n_items = l.n_items[k];
+    const dim3 waves((l.n_items[k] + 3) / 4), groups(l.n_items[k]);
+    if (k == 0)
+      hipLaunchKernelGGL((spex_coop_attn_kernel<KV, D, 2, TREE>), groups, block, 0, stream, a, sh);
+    else if (k == 1)
+      hipLaunchKernelGGL((spex_coop_attn_kernel<KV, D, 1, TREE>), groups, block, 0, stream, a, sh);
+    else if (k == 2 && l.span[k] <= 16)
+      hipLaunchKernelGGL((spex_wave_attn_kernel<KV, D, 1, false, TREE>), waves, block, 0, stream, a, sh);
+    else if (k == 2)
+      return hipErrorInvalidValue;
+    else if (l.span[k] <= 16)
+      hipLaunchKernelGGL((spex_wave_attn_kernel<KV, D, 1, true, TREE>), waves, block, 0, stream, a, sh);
+    else
+      hipLaunchKernelGGL((spex_wave_attn_kernel<KV, D, 2, true, TREE>), waves, block, 0, stream, a, sh);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
+template <int KV, int D>
+static hipError_t launch_phases_d(const Shape &sh, const AttnArgs &a, const ItemLists &l, hipStream_t stream) {
+  return a.qt_mask ? launch_phases_tree<KV, D, true>(sh, a, l, stream) : launch_phases_tree<KV, D, false>(sh, a, l, stream);
+}
+
+hipError_t launch_split_phases(const Shape &sh, const AttnArgs &a, const ItemLists &l, hipStream_t stream) {
+  if (!has_mfma_kernel(sh) || l.span[0] > 128 || l.span[1] > 64 || l.span[2] > 32 || l.span[3] > 32) return hipErrorInvalidValue;
+  if (sh.kv_dtype == kBF16)
+    return sh.D == 64 ? launch_phases_d<kBF16, 64>(sh, a, l, stream) : launch_phases_d<kBF16, 128>(sh, a, l, stream);
+  return sh.D == 64 ? launch_phases_d<kFP8, 64>(sh, a, l, stream) : launch_phases_d<kFP8, 128>(sh, a, l, stream);
 }
 
 hipError_t launch_split(const Shape &sh, const AttnArgs &a, const ItemLists &l, hipStream_t stream) {

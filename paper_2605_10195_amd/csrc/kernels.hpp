@@ -33,6 +33,9 @@ struct AttnArgs {
   // every row of the launch has one piece only: write finished rows to out / lse instead (not the
   // generic kernel)
   bool finish;
+  // rows of tasks flagged final, finished in place behind the launches of their other pieces: a row's
+  // merge list (all entries but the last, which is the task itself)
+  const int32_t *part_indptr, *part_base, *part_hstride;
   float *out, *lse;  // lse may be null
   float scale_log2;
   // Draft-tree visibility, or null for the causal chain: 2 ints per query token {index i of the
@@ -64,7 +67,8 @@ struct MergeArgs {
   const int32_t *part_indptr, *part_base, *part_hstride;
   const float *part_o, *part_ml;
   float *out, *lse;
-  int32_t n_qtok;
+  const int32_t *qt_ids;  // query tokens to merge, or null for 0 .. n_qtok-1
+  int32_t n_qtok;         // number of query tokens handled by the launch
   int32_t avg_pieces;     // pieces of an average query token (a hint for the launch shape)
 };
 
@@ -120,6 +124,8 @@ bool has_mfma_kernel(const Shape &sh);
 bool has_rowmajor_kernel(const Shape &sh, const AttnArgs &a);
 // All lists in one launch; needs has_mfma_kernel or has_rowmajor_kernel.
 hipError_t launch_split(const Shape &sh, const AttnArgs &a, const ItemLists &lists, hipStream_t stream);
+// The same in up to four launches one behind the other, for launches with items enough (tiled pools).
+hipError_t launch_split_phases(const Shape &sh, const AttnArgs &a, const ItemLists &lists, hipStream_t stream);
 // a.items / a.n_items on the vector ALU; any shape.
 hipError_t launch_generic_attention(const Shape &sh, const AttnArgs &a, int rows_per_item, hipStream_t stream);
 hipError_t launch_merge(const Shape &sh, const MergeArgs &a, hipStream_t stream);

@@ -17,7 +17,7 @@ int32_t clamp32(int64_t v, int32_t lo, int32_t hi) {
   return static_cast<int32_t>(std::max<int64_t>(lo, std::min<int64_t>(hi, v)));
 }
 
-// Split granularity.  Every extra chunk costs a partial result per row that is written and
+// Split granularity and launches.  Every extra chunk costs a partial result per row that is written and
 // read back, and every item some 5 us of latency however short, so segments are cut only until
 // the launch has about 256 shared and 1024 private items of 128 tokens or more (a workgroup splits
 // an item's tokens between its wavefronts).  Measured (us a call, bf16, 32 / 8 heads of 128): 16
@@ -29,16 +29,67 @@ int32_t clamp32(int64_t v, int32_t lo, int32_t hi) {
 // and the entry point that allocates nothing has 48 MiB of it.  Pages of fewer than four tokens go to the
 // generic kernel, a wavefront per item and row, which needs many items and keeps the 16 and 8 pages
 // (128 tokens instead: 16 branches on pages of 2 tokens 123.9 -> 190.1 us).
+// Tiled pools: launches of many items go in phases, shared items and then private ones, a wavefront
+// each, which finish the rows of suffixes in one piece.
+//  * Private items of more than 16 rows (the kernel then holds two row tiles and one workgroup a compute
+//    unit, its items through LDS among them): beyond 512 workgroups.  Over 281 drawn requests of that kind
+//    none is then slower than with phases throughout by more than 2 %, and the choice is 3 % from the
+//    better of both: 64 private items of 32 rows 27 us against 55 in phases, 512 of them 74 against 64, 4096
+//    606 against 362.  Phases have 1024 shared and 2048 private items, because those of many rows are
+//    long: 3 prompts of 10000 tokens, 29 branches of 128 rows 161 us, with 256 shared items 189.
+//  * Up to 16 rows: when there are a great many.  8192 private items 293 us against 328 in phases, 32768
+//    1129 against 1108 (bf16) and 875 against 818 (fp8), 65536 2992 against 2862; head dim 64: 2048
+//    35.7 against 55, 8192 122 against 118 (bf16) and 132 against 119 (fp8).
 constexpr int64_t kFineRows = 40960;
-int32_t auto_chunk(int64_t pages, int32_t items, int32_t page_size, bool fine, int32_t bound, int32_t most) {
-  const int32_t floor = page_size < 4 ? bound : std::max(1, 128 / page_size);
-  return clamp32((pages + items - 1) / items, fine ? floor : std::max(floor, bound), most);
-}
-int32_t auto_prefix_chunk(int64_t pages, int32_t page_size, bool fine) {
-  return auto_chunk(pages, 256, page_size, fine, 16, 256);
-}
-int32_t auto_suffix_chunk(int64_t pages, int32_t page_size, bool fine) {
-  return auto_chunk(pages, 1024, page_size, fine, 8, 64);
+struct Run {
+  int64_t pages;
+  int32_t rows;  // query tokens * G
+};
+struct Chunks {
+  int32_t prefix, suffix;  // pages
+  bool phases;
+  int64_t partial_rows;
+};
+Chunks choose_chunks(const std::vector<Run> &groups, const std::vector<Run> &suffixes, int32_t num_kv_heads, int32_t page_size,
+                     const PoolShape &pool, int32_t prefix_chunk, int32_t suffix_chunk) {
+  int64_t weighted = 0, suffix_pages = 0;  // pages times spans of rows: work items if nothing were split
+  int32_t most_private = 0;
+  auto spans = [](int64_t rows) { return rows <= 64 ? 1 : (rows + kWideSpan - 1) / kWideSpan; };
+  for (const Run &g : groups) weighted += g.pages * spans(g.rows);
+  for (const Run &s : suffixes) {
+    suffix_pages += s.pages;
+    most_private = std::max(most_private, s.rows);
+  }
+  const bool tall = pool.tiled && most_private > 16;
+  auto auto_chunk = [&](int64_t pages, int64_t items, int32_t least, int32_t most) {
+    return clamp32((pages * num_kv_heads + items - 1) / items, least, most);
+  };
+  Chunks c{};
+  auto choose = [&](int64_t shared_items, int64_t private_items, bool fine) {
+    const int32_t lp = page_size < 4 ? 16 : std::max(1, 128 / page_size), ls = page_size < 4 ? 8 : lp;
+    c.prefix = prefix_chunk > 0 ? prefix_chunk : auto_chunk(weighted, shared_items, fine ? lp : std::max(lp, 16), 256);
+    c.suffix = suffix_chunk > 0 ? suffix_chunk : auto_chunk(suffix_pages, private_items, fine ? ls : std::max(ls, 8), 64);
+    auto chunks = [](int64_t pages, int64_t n) { return (pages + n - 1) / n; };
+    int64_t partial = 0, shared_wgs = 0, private_wgs = 0;
+    for (const Run &g : groups) {
+      partial += chunks(g.pages, c.prefix) * g.rows;
+      shared_wgs += chunks(g.pages, c.prefix) * spans(g.rows);
+    }
+    for (const Run &s : suffixes) {
+      partial += chunks(s.pages, c.suffix) * s.rows;
+      private_wgs += chunks(s.pages, c.suffix) * (tall ? (s.rows + 31) / 32 : 1);
+    }
+    c.partial_rows = partial * num_kv_heads;
+    c.phases = pool.tiled && (tall ? (shared_wgs + private_wgs) * num_kv_heads > 512
+                                   : private_wgs * num_kv_heads > (pool.head_dim <= 64 ? 4096 : 16384));
+  };
+  choose(256, 1024, true);
+  if (c.partial_rows > kFineRows) choose(256, 1024, false);
+  if (c.phases && tall) {
+    choose(1024, 2048, false);
+    c.phases = true;
+  }
+  return c;
 }
 
 struct Segment {
@@ -278,7 +329,6 @@ PlanError Planner::ensure_split(const PageTable &pt, Plan *plan) {
     }
   };
   std::vector<Segment> groups(NG), suffixes;
-  int64_t prefix_pages_weighted = 0;
   int32_t max_rows_small = 0;
   for (int32_t gi = 0; gi < NG; ++gi) {
     add_node_pages(groups[gi], pl.group_node[gi]);
@@ -288,7 +338,6 @@ PlanError Planner::ensure_split(const PageTable &pt, Plan *plan) {
     if (group_count[gi] * G <= kWaveRowsMax) max_rows_small = std::max(max_rows_small, group_count[gi] * G);
   }
   suffixes.reserve(n_leaves);
-  int64_t suffix_pages = 0;
   for (int32_t i = 0; i < n_leaves; ++i) {
     const int32_t ql = q_lens ? q_lens[i] : 1;
     int32_t k0 = path_indptr[i + 1];
@@ -298,29 +347,21 @@ PlanError Planner::ensure_split(const PageTable &pt, Plan *plan) {
     if (s.ids.empty()) continue;
     s.qt_begin = n_group_qt + qoff[i];
     s.qt_count = ql;
-    suffix_pages += static_cast<int64_t>(s.ids.size());
     pl.max_rows_suffix = std::max(pl.max_rows_suffix, ql * G);
     suffixes.push_back(std::move(s));
   }
   pl.prefix_row_tiles = max_rows_small <= 16 ? 1 : 2;
   pl.suffix_row_tiles = pl.max_rows_suffix <= 16 ? 1 : 2;
   const int32_t rw_suffix = 16 * pl.suffix_row_tiles;
-  for (const Segment &s : groups)  // work items per page if nothing were split
-    prefix_pages_weighted +=
-        static_cast<int64_t>(s.ids.size()) * (s.qt_count * G <= 64 ? 1 : (s.qt_count * G + kWideSpan - 1) / kWideSpan);
-
-  auto choose = [&](bool fine) {
-    pl.prefix_chunk_pages =
-        prefix_chunk_pages > 0 ? prefix_chunk_pages : auto_prefix_chunk(prefix_pages_weighted * num_kv_heads, P, fine);
-    pl.suffix_chunk_pages =
-        suffix_chunk_pages > 0 ? suffix_chunk_pages : auto_suffix_chunk(suffix_pages * num_kv_heads, P, fine);
-    auto chunks = [](const Segment &s, int64_t c) { return (static_cast<int64_t>(s.ids.size()) + c - 1) / c; };
-    int64_t partial = 0;
-    for (const Segment &s : groups) partial += chunks(s, pl.prefix_chunk_pages) * s.qt_count * G;
-    for (const Segment &s : suffixes) partial += chunks(s, pl.suffix_chunk_pages) * s.qt_count * G;
-    return partial * num_kv_heads;
-  };
-  if (choose(true) > kFineRows) choose(false);
+  {
+    std::vector<Run> shared, priv;
+    for (const Segment &s : groups) shared.push_back({static_cast<int64_t>(s.ids.size()), s.qt_count * G});
+    for (const Segment &s : suffixes) priv.push_back({static_cast<int64_t>(s.ids.size()), s.qt_count * G});
+    const Chunks c = choose_chunks(shared, priv, num_kv_heads, P, pool, prefix_chunk_pages, suffix_chunk_pages);
+    pl.prefix_chunk_pages = c.prefix;
+    pl.suffix_chunk_pages = c.suffix;
+    pl.split_phases = c.phases;
+  }
 
   // ---- tasks
   std::vector<int32_t> qt_req;  // with draft masks: the request of every query token
@@ -494,7 +535,8 @@ PlanError Planner::ensure_split(const PageTable &pt, Plan *plan) {
 // tree-walk workgroups), each timed through both paths: the middle half of the predictions is within
 // 14 %.  Shared items of more than 16 rows cost their blocks of 32 tokens through LDS, the others
 // the blocks' bytes, and every row of an item its partial state.
-float Planner::estimate_split(const PageTable &pt, const Plan &pl, int32_t head_dim, int32_t kv_bytes, float enough) {
+float Planner::estimate_split(const PageTable &pt, const Plan &pl, float enough) {
+  const int32_t head_dim = pool.head_dim, kv_bytes = pool.kv_bytes;
   // every token read once, nothing else
   const double bytes_only = 9.4 + 0.97e-3 * kv_bytes * static_cast<double>(pl.unique_tokens) / 32.0 * pl.num_kv_heads * head_dim / 128.0;
   if (bytes_only >= enough) return static_cast<float>(bytes_only);
@@ -514,34 +556,25 @@ float Planner::estimate_split(const PageTable &pt, const Plan &pl, int32_t head_
   auto pages_of = [&](int32_t u) { return static_cast<int64_t>(pt.node(u).pages.size()); };
   auto spans = [](int64_t rows) { return rows <= 64 ? 1 : (rows + kWideSpan - 1) / kWideSpan; };
   std::vector<int64_t> tail(n, 0);  // pages of every request's private nodes
-  int64_t weighted = 0, suffix_pages = 0;
+  std::vector<Run> shared, priv;
   for (int32_t u : est_nodes_)
-    if (est_reqs_[u] > 1) weighted += pages_of(u) * spans(est_rows_[u]);
+    if (est_reqs_[u] > 1 && pages_of(u) > 0) shared.push_back({pages_of(u), est_rows_[u]});
   int32_t max_rows = 0;
   for (int32_t i = 0; i < n; ++i) {
     for (int32_t k = pl.path_indptr[i + 1] - 1; k >= pl.path_indptr[i] && est_reqs_[pl.path_nodes[k]] == 1; --k)
       tail[i] += pages_of(pl.path_nodes[k]);
-    suffix_pages += tail[i];
-    if (tail[i] > 0) max_rows = std::max(max_rows, q_len(i) * G);
+    if (tail[i] == 0) continue;
+    priv.push_back({tail[i], q_len(i) * G});
+    max_rows = std::max(max_rows, q_len(i) * G);
   }
   const int32_t H = pl.num_kv_heads;
-  int64_t pc = 1, sc = 1;
-  auto choose = [&](bool fine) {  // as in ensure_split
-    pc = pl.req_prefix_chunk > 0 ? pl.req_prefix_chunk : auto_prefix_chunk(weighted * H, P, fine);
-    sc = pl.req_suffix_chunk > 0 ? pl.req_suffix_chunk : auto_suffix_chunk(suffix_pages * H, P, fine);
-    int64_t partial = 0;
-    for (int32_t u : est_nodes_)
-      if (est_reqs_[u] > 1) partial += (pages_of(u) + pc - 1) / pc * est_rows_[u];
-    for (int32_t i = 0; i < n; ++i) partial += (tail[i] + sc - 1) / sc * q_len(i) * G;
-    return partial * H;
-  };
-  if (choose(true) > kFineRows) choose(false);
-  double through_lds = 0, streamed = 0, partial_rows = 0;  // per kv head
+  const Chunks c = choose_chunks(shared, priv, H, P, pool, pl.req_prefix_chunk, pl.req_suffix_chunk);
+  double through_lds = 0, streamed = 0;  // per kv head
+  const double partial_rows = static_cast<double>(c.partial_rows) / H;
   for (int32_t u : est_nodes_) {
     if (est_reqs_[u] > 1) {
       const int64_t pg = pages_of(u), rows = est_rows_[u];
       (rows > kWaveRowsMax ? through_lds : streamed) += static_cast<double>((pg + 1) / 2 * spans(rows));
-      partial_rows += static_cast<double>((pg + pc - 1) / pc * rows);
     }
     est_rows_[u] = est_reqs_[u] = 0;
   }
@@ -550,7 +583,6 @@ float Planner::estimate_split(const PageTable &pt, const Plan &pl, int32_t head_
   for (int32_t i = 0; i < n; ++i) {
     const int64_t rows = q_len(i) * G;
     streamed += static_cast<double>((tail[i] + 1) / 2 * ((rows + tile - 1) / tile));
-    partial_rows += static_cast<double>((tail[i] + sc - 1) / sc * rows);
   }
   // A request that the tree-walk kernel serves without partial rows is not moved to a path that
   // needs more room for them than the entry point that allocates nothing has.
@@ -597,7 +629,7 @@ float Planner::estimate_walk(const Plan &pl) {
 // lists take the host longer to make than a call (2500: 1.9 against 1.0 ms for a first call).
 // Asked once per plan: patches raise the longest workgroup but not the sums behind both estimates, and
 // a plan that moved to the split path could no longer be patched when a page starts.
-bool Planner::prefers_walk(const PageTable &pt, Plan *plan, int32_t head_dim, int32_t kv_bytes) {
+bool Planner::prefers_walk(const PageTable &pt, Plan *plan) {
   Plan &pl = *plan;
   if (pl.route >= 0) return pl.route == 1;
   bool walk = false;
@@ -608,7 +640,7 @@ bool Planner::prefers_walk(const PageTable &pt, Plan *plan, int32_t head_dim, in
            (pl.walk_real_items >= 128 || pl.walk_max_item_blocks <= short_walk_blocks(pl.walk_real_items));
     if (walk && !pl.growing && pl.walk_real_items <= 512 && pl.qt_limit.size() <= 1024) {
       const float least = (pl.walk_real_items >= 128 ? 0.95f : 0.7f) * estimate_walk(pl);
-      walk = estimate_split(pt, pl, head_dim, kv_bytes, least) >= least;
+      walk = estimate_split(pt, pl, least) >= least;
     }
   }
   pl.route = walk ? 1 : 0;

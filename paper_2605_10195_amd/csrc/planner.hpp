@@ -68,6 +68,7 @@ struct Plan {
   int32_t n_prefix_tasks = 0;
   int64_t n_partial_rows = 0;
   int32_t prefix_chunk_pages = 0, suffix_chunk_pages = 0;  // values used
+  bool split_phases = false;  // tiled pools: the split path's lists in launches of their own
 
   // ---- launch lists (device side).  A work item is kItemInts ints:
   //   {pg_begin, pg_count, qt_begin, qt_count, pbase, flags, kv_head, first_row}
@@ -115,6 +116,12 @@ struct Plan {
   int64_t walk_block_visits = 0;  // blocks over all row blocks (a block shared by two row blocks counts twice)
 };
 
+// What the planner has to know of the pool to choose kernels and the lengths of their items.
+struct PoolShape {
+  bool tiled = false;  // MFMA-tiled: the tree-walk kernel and the split path's launches in phases exist
+  int32_t head_dim = 128, kv_bytes = 2;
+};
+
 enum class PlanError { kOk, kBadNode, kEmptyPath, kInvalid, kTooLarge };
 
 // Device arrays a length patch can touch; a patch is the triple {array, int index, new value}.
@@ -122,6 +129,7 @@ enum PatchArray : int32_t { kPatchPgRec = 0, kPatchQtRec = 1, kPatchWalkBlocks =
 
 class Planner {
  public:
+  PoolShape pool;
   // Validates the request, walks the paths and computes the limits; the lists follow on demand.
   PlanError begin(const PageTable &pt, const int32_t *leaves, const int32_t *q_lens,
                   const uint32_t *draft_masks, int32_t n_leaves, int32_t num_q_heads, int32_t num_kv_heads,
@@ -131,7 +139,7 @@ class Planner {
   PlanError ensure_split(const PageTable &pt, Plan *plan);
   void ensure_walk(const PageTable &pt, Plan *plan);
   // The automatic choice, made once per plan: true for the tree-walk kernel (its lists are built then).
-  bool prefers_walk(const PageTable &pt, Plan *plan, int32_t head_dim, int32_t kv_bytes);
+  bool prefers_walk(const PageTable &pt, Plan *plan);
   // Brings a plan up to date after appends to requested nodes (no fork or prune since it was
   // made).  Tokens that fill up a last page change valid counts and limits; a newly started page
   // becomes page b of the node's last block or, in tree-walk lists that are the plan's only
@@ -143,7 +151,7 @@ class Planner {
   // Microseconds a call takes through the split path / the tree-walk kernel, from the shape of the
   // request (the first without building the split lists, the second from the tree-walk lists).
   // A result of `enough` or more may be a lower bound.
-  float estimate_split(const PageTable &pt, const Plan &pl, int32_t head_dim, int32_t kv_bytes, float enough);
+  float estimate_split(const PageTable &pt, const Plan &pl, float enough);
   static float estimate_walk(const Plan &plan);
   static bool walk_in_halves(const Plan &plan);
   std::vector<int32_t> multi_, last_pg_;

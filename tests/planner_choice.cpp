@@ -44,6 +44,7 @@ struct Made {
   Planner planner;
   Plan plan;
   Made(const Forest &f, int Hq, int Hkv, int prefix_chunk = 0, int suffix_chunk = 0) {
+    planner.pool = {f.pt.page_size() == 16, 128, 2};
     const PlanError e = planner.begin(f.pt, f.leaves.data(), f.q_lens.data(), nullptr, static_cast<int32_t>(f.leaves.size()), Hq,
                                       Hkv, prefix_chunk, suffix_chunk, 0, 0, &plan);
     CHECK(e == PlanError::kOk, "begin");
@@ -56,7 +57,7 @@ static void growth(int roots, int prompt, int branches, int tokens, int Hq, int 
   Forest f(roots * (prompt / 16 + 2 + branches * ((tokens + rounds) / 16 + 2)), 16);
   f.add(roots, prompt, branches, tokens);
   Made m(f, Hq, Hkv);
-  const bool first = m.planner.prefers_walk(f.pt, &m.plan, 128, 2);
+  const bool first = m.planner.prefers_walk(f.pt, &m.plan);
   std::vector<int32_t> patches;
   int patched = 0;
   for (int t = 0; t < rounds; ++t) {
@@ -65,7 +66,7 @@ static void growth(int roots, int prompt, int branches, int tokens, int Hq, int 
     if (!m.planner.patch_lengths(f.pt, &m.plan, &patches)) break;
     ++patched;
     Made fresh(f, Hq, Hkv);
-    const bool now = m.planner.prefers_walk(f.pt, &m.plan, 128, 2), want = fresh.planner.prefers_walk(f.pt, &fresh.plan, 128, 2);
+    const bool now = m.planner.prefers_walk(f.pt, &m.plan), want = fresh.planner.prefers_walk(f.pt, &fresh.plan);
     CHECK(now == first, "%d roots of %d, %d branches: the choice changed after %d tokens", roots, prompt, branches, t + 1);
     CHECK(now == want, "%d roots of %d, %d branches: a fresh plan chooses otherwise after %d tokens", roots, prompt, branches, t + 1);
     if (first) CHECK(m.plan.walk_halves == fresh.plan.walk_halves, "halves after %d tokens", t + 1);
@@ -99,7 +100,7 @@ int main() {
     Forest f(trees * (tokens / 16 + 1), 16);
     f.add(trees, tokens, 0, 0, q_len);
     Made m(f, 4, 1);
-    return m.planner.prefers_walk(f.pt, &m.plan, 128, 2);
+    return m.planner.prefers_walk(f.pt, &m.plan);
   };
   CHECK(!choice(512, 20000, 1), "512 workgroups on long paths");
   CHECK(choice(513, 20000, 1), "513 workgroups");
@@ -126,6 +127,25 @@ int main() {
         CHECK(a.plan.prefix_chunk_pages >= 16 && a.plan.suffix_chunk_pages >= 8, "pages of %d, %d queries: items of %d and %d pages", P, q_len,
               a.plan.prefix_chunk_pages, a.plan.suffix_chunk_pages);
     }
+
+  // the split path's launches, one or in phases: (roots, branches, queries, heads) -> workgroups at the bound
+  auto phases = [](int roots, int branches, int q_len, int Hq, int Hkv, int dim, bool tiled = true) {
+    Forest f(roots * (3 + 2 * branches), 16);
+    f.add(roots, 40, branches, 20, q_len);
+    Made m(f, Hq, Hkv);
+    m.planner.pool = {tiled, dim, 2};
+    CHECK(m.planner.ensure_split(f.pt, &m.plan) == PlanError::kOk, "split lists");
+    return m.plan.split_phases;
+  };
+  CHECK(!phases(256, 1, 1, 40, 2, 128), "512 private items of 20 rows");
+  CHECK(phases(257, 1, 1, 40, 2, 128), "514 private items of 20 rows");
+  CHECK(!phases(34, 4, 1, 71, 1, 64), "34 * (4 * 3 + 3) = 510 workgroups");
+  CHECK(phases(35, 4, 1, 71, 1, 64), "525 workgroups");
+  CHECK(!phases(512, 16, 1, 8, 2, 128), "16384 private items of 4 rows");
+  CHECK(phases(513, 16, 1, 8, 2, 128), "16416 private items of 4 rows");
+  CHECK(!phases(64, 16, 1, 16, 4, 64), "4096 private items of 4 rows, head dim 64");
+  CHECK(phases(65, 16, 1, 16, 4, 64), "4160 private items of 4 rows, head dim 64");
+  CHECK(!phases(513, 16, 1, 8, 2, 128, false), "row-major");
 
   if (failures == 0) std::printf("ok\n");
   return failures != 0;

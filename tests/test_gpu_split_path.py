@@ -8,7 +8,7 @@ import pytest
 import torch
 
 import spex_workloads as sw
-from gpu_common import assert_close, run_gpu, run_oracle
+from gpu_common import assert_close, run_gpu, run_oracle, run_oracle_c
 
 pytestmark = pytest.mark.gpu
 
@@ -98,3 +98,32 @@ def test_lse_of_a_row_whose_scores_overflow(chunk):
     assert float(lse[0, 0]) == float("-inf")
     assert abs(float(lse[0, 1]) - math.log(300)) <= 1e-5 and float((out[0, 1] - 1.0).abs().max()) <= 1e-5
     t.close()
+
+
+def _single_pieces(n, **kw):
+    return sw.bfs_tot(n_queries=n, prompt=40, step=20, width=1, keep=1, depth=1, **kw)
+
+
+# Launches of many items go in phases: with more than 16 private rows beyond 512 workgroups, else beyond 4096
+# private items (head dim 64).  Either side of both bounds: draft masks on fp8, requests of 71 rows (three row
+# spans), 4 rows, and requests of one piece each, which no merge follows.
+@pytest.mark.parametrize("make", [
+    lambda more: sw.tot_with_drafts(n_queries=8 + more, prompt=75, step=19, depth=2, drafts=6, heads=(40, 8, 128), token_trees=True),
+    lambda more: sw.tot_with_drafts(n_queries=8 + more, prompt=300, step=19, depth=2, drafts=6, heads=(40, 8, 64), kv_dtype="bf16",
+                                    q_dtype="bf16"),
+    lambda more: sw.bfs_tot(n_queries=34 + more, prompt=75, step=30, width=4, keep=4, depth=1, heads=(71, 1, 64)),
+    lambda more: sw.bfs_tot(n_queries=64 + more, prompt=40, step=20, width=16, keep=16, depth=1, heads=(16, 4, 64)),
+    lambda more: _single_pieces(256 + more, heads=(40, 2, 128)),
+    lambda more: _single_pieces(256 + more, heads=(40, 2, 64), kv_dtype="fp8_e4m3")])
+@pytest.mark.parametrize("more", [0, 1])
+def test_split_path_in_one_launch_and_in_phases(make, more):
+    wl = make(more)
+    assert_close(run_gpu(wl, kernel_mode=2), run_oracle_c(wl), wl.kv_dtype, wl.name)
+
+
+@pytest.mark.parametrize("heads,kv_dtype,chunk", [((40, 2, 128), "bf16", 1), ((40, 2, 64), "fp8_e4m3", 2), ((34, 2, 128), "fp8_e4m3", 0)])
+def test_phases_with_interior_nodes_and_cut_suffixes(heads, kv_dtype, chunk):
+    """Requested nodes with and without live children, some twice, suffixes in one piece and in several."""
+    wl = sw.random_trace(77, heads=heads, kv_dtype=kv_dtype, n_ops=900, n_roots=120, max_q_len=3)
+    got = run_gpu(wl, kernel_mode=2, prefix_chunk_pages=chunk, suffix_chunk_pages=chunk)
+    assert_close(got, run_oracle_c(wl), kv_dtype, f"{heads} chunk {chunk}")
