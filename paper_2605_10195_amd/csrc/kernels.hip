@@ -1087,6 +1087,10 @@ __device__ __forceinline__ void walk_softmax_pv(const int (&limit)[NT], const in
                                                 f32x4 (&sb)[NT], const f16x8 (&vh)[D / 16], bool tok_masked,
                                                 int valid_l, int pos_l, float c, float slack, int lo,
                                                 int hi, int rows) {
+  // With one tile the block is known to touch it; the branch keeps the scores' instructions and the weights'
+  // apart, without it the fp8 kernel takes 178 registers instead of 162 and two workgroups run on a
+  // compute unit instead of three (150 trees of 6 branches, 600 workgroups, 52.8 -> 38.5 us).
+  if (NT == 1 && (hi <= 0 || lo >= 16)) return;
   const int lane = threadIdx.x & 63, m16 = lane & 15, jj = lane >> 4;
   const _Float16 one = static_cast<_Float16>(1.0f);
   const f16x8 ones = {one, one, one, one, one, one, one, one};
