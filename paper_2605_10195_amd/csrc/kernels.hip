@@ -1057,13 +1057,13 @@ __device__ __forceinline__ WalkBlock load_walk_block(const WalkArgs &p, int idx,
   return b;
 }
 
-// Scores of one 32-token block for all row tiles of the wavefront: S^T = K Q^T (see block_math for
-// the operand layout).
-template <int D, int NT>
-__device__ __forceinline__ void walk_scores(const bf16x8 (&qf)[NT][D / 32], const bf16x8 (&kf)[2][D / 32],
-                                            f32x4 (&sa)[NT], f32x4 (&sb)[NT]) {
+// Scores of one 32-token block for row tiles T0 .. T1 - 1 of the wavefront: S^T = K Q^T (see
+// block_math for the operand layout).
+template <int T0, int T1, int D, int NT>
+__device__ __forceinline__ void walk_scores_of(const bf16x8 (&qf)[NT][D / 32], const bf16x8 (&kf)[2][D / 32],
+                                               f32x4 (&sa)[NT], f32x4 (&sb)[NT]) {
 #pragma unroll
-  for (int nt = 0; nt < NT; ++nt) {
+  for (int nt = T0; nt < T1; ++nt) {
     f32x4 a = {0.f, 0.f, 0.f, 0.f}, b = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int s = 0; s < D / 32; ++s) {
@@ -1080,8 +1080,8 @@ __device__ __forceinline__ void walk_scores(const bf16x8 (&qf)[NT][D / 32], cons
 // One path with two branches for all tiles of the wavefront -- masks, which change scores only, and a
 // reference that moves -- so that the tiles' weights and MFMAs form one run of instructions: with
 // a branch per tile the weights of one tile were made while the matrix cores idled.
-template <bool FP8, bool TREE, int D, int NT>
-__device__ __forceinline__ void walk_softmax_pv(const int (&limit)[NT], const int (&qidx)[NT],
+template <bool FP8, bool TREE, int T0, int T1, int D, int NT>
+__device__ __forceinline__ void walk_softmax_pv_of(const int (&limit)[NT], const int (&qidx)[NT],
                                                 const uint32_t (&dmask)[NT], f32x4 (&o)[NT][D / 16],
                                                 float (&m)[NT], f32x4 (&lacc)[NT], f32x4 (&sa)[NT],
                                                 f32x4 (&sb)[NT], const f16x8 (&vh)[D / 16], bool tok_masked,
@@ -1099,9 +1099,9 @@ __device__ __forceinline__ void walk_softmax_pv(const int (&limit)[NT], const in
   // per page (fp8 KV) it is kept in scaled units (log2 e folded in), and the largest scaled score
   // of the lane is c * the largest raw one (c > 0, and rounding is monotonic).
   // Tile rows past the wavefront's last one hold zero queries and are not written: they need no mask.
-  if (tok_masked || lo > 0 || hi < rows) {  // wave-uniform
+  if (tok_masked || lo > 16 * T0 || hi < min(rows, 16 * T1)) {  // wave-uniform
 #pragma unroll
-    for (int nt = 0; nt < NT; ++nt) {
+    for (int nt = T0; nt < T1; ++nt) {
       const int row = nt * 16 + m16;
       const bool row_in = row >= lo && row < hi;
       uint32_t vm = 0xffu;
@@ -1136,7 +1136,7 @@ __device__ __forceinline__ void walk_softmax_pv(const int (&limit)[NT], const in
   float mx[NT];
   bool over = false;
 #pragma unroll
-  for (int nt = 0; nt < NT; ++nt) {
+  for (int nt = T0; nt < T1; ++nt) {
     const float raw = fmaxf(fmaxf(fmaxf(sa[nt][0], sa[nt][1]), fmaxf(sa[nt][2], sa[nt][3])),
                             fmaxf(fmaxf(sb[nt][0], sb[nt][1]), fmaxf(sb[nt][2], sb[nt][3])));
     mx[nt] = FP8 ? raw * c : raw;
@@ -1144,7 +1144,7 @@ __device__ __forceinline__ void walk_softmax_pv(const int (&limit)[NT], const in
   }
   if (__any(over)) {
 #pragma unroll
-    for (int nt = 0; nt < NT; ++nt) {
+    for (int nt = T0; nt < T1; ++nt) {
       const float rmax = row_group_max(mx[nt]);
       const float m_new = rmax > m[nt] + slack ? rmax : m[nt];
       const float alpha = fast_exp2(FP8 ? m[nt] - m_new : (m[nt] - m_new) * c);
@@ -1155,7 +1155,7 @@ __device__ __forceinline__ void walk_softmax_pv(const int (&limit)[NT], const in
     }
   }
 #pragma unroll
-  for (int nt = 0; nt < NT; ++nt) {
+  for (int nt = T0; nt < T1; ++nt) {
     const float mc = FP8 ? m[nt] : m[nt] * c;
     u32x4 pw;
 #pragma unroll
@@ -1169,6 +1169,38 @@ __device__ __forceinline__ void walk_softmax_pv(const int (&limit)[NT], const in
 #pragma unroll
     for (int dt = 0; dt < D / 16; ++dt)
       o[nt][dt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(vh[dt], ph, o[nt][dt], 0, 0, 0);
+  }
+}
+
+// All row tiles of the wavefront together, or (BY_TILE) one after the other, without those that no row
+// of the block lies in: the planner chooses by how many of them there are.  One kernel cannot hold both forms
+// (the accumulators of either side of the branch are then other registers: 130 spilled).
+template <bool BY_TILE, int D, int NT, int T = 0>
+__device__ __forceinline__ void walk_scores(const bf16x8 (&qf)[NT][D / 32], const bf16x8 (&kf)[2][D / 32],
+                                            f32x4 (&sa)[NT], f32x4 (&sb)[NT], int lo, int hi) {
+  if constexpr (!BY_TILE) {
+    walk_scores_of<0, NT, D, NT>(qf, kf, sa, sb);
+  } else if constexpr (T < NT) {
+    if (lo < 16 * T + 16 && hi > 16 * T) walk_scores_of<T, T + 1, D, NT>(qf, kf, sa, sb);
+    walk_scores<BY_TILE, D, NT, T + 1>(qf, kf, sa, sb, lo, hi);
+  }
+}
+template <bool BY_TILE, bool FP8, bool TREE, int D, int NT, int T = 0>
+__device__ __forceinline__ void walk_softmax_pv(const int (&limit)[NT], const int (&qidx)[NT],
+                                                const uint32_t (&dmask)[NT], f32x4 (&o)[NT][D / 16],
+                                                float (&m)[NT], f32x4 (&lacc)[NT], f32x4 (&sa)[NT],
+                                                f32x4 (&sb)[NT], const f16x8 (&vh)[D / 16], bool tok_masked,
+                                                int valid_l, int pos_l, float c, float slack, int lo,
+                                                int hi, int rows) {
+  if constexpr (!BY_TILE) {
+    walk_softmax_pv_of<FP8, TREE, 0, NT, D, NT>(limit, qidx, dmask, o, m, lacc, sa, sb, vh, tok_masked, valid_l, pos_l,
+                                                c, slack, lo, hi, rows);
+  } else if constexpr (T < NT) {
+    if (lo < 16 * T + 16 && hi > 16 * T)
+      walk_softmax_pv_of<FP8, TREE, T, T + 1, D, NT>(limit, qidx, dmask, o, m, lacc, sa, sb, vh, tok_masked, valid_l,
+                                                     pos_l, c, slack, lo, hi, rows);
+    walk_softmax_pv<BY_TILE, FP8, TREE, D, NT, T + 1>(limit, qidx, dmask, o, m, lacc, sa, sb, vh, tok_masked, valid_l,
+                                                      pos_l, c, slack, lo, hi, rows);
   }
 }
 
@@ -1219,7 +1251,7 @@ __device__ __forceinline__ void walk_write_rows(float *out, float *lse, const Sh
 // blocks alternate likewise -- and at the end the upper pair hands its softmax state to the lower
 // one through LDS.  Per block a wavefront then works on twice the rows, so half as many operand
 // images cross the LDS per row, and a row block's longest path takes half as many steps.
-template <int KV, int D, int NTW, int NW, bool TREE, int KS = 1>
+template <int KV, int D, int NTW, int NW, bool TREE, int KS = 1, bool BY_TILE = false>
 __global__ __launch_bounds__(64 * NW, (NW == 4 && NTW <= 2) ? 2 : 1) void spex_tree_walk_kernel(WalkArgs p, Shape sh) {
   constexpr bool FP8 = KV == kFP8;
   constexpr int ESZ = FP8 ? 1 : 2;
@@ -1403,7 +1435,7 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && NTW <= 2) ? 2 : 1) void spex_t
 #pragma unroll
           for (int s = 0; s < D / 32; ++s)
             kf[t][s] = __builtin_bit_cast(bf16x8, src[(t * (D / 32) + s) * 64]);
-        walk_scores<D, NTW>(qf, kf, sa, sb);
+        walk_scores<BY_TILE, D, NTW>(qf, kf, sa, sb, lo, hi);
       }
       // The V images are fetched only now, into the registers the K images have left, and their
       // LDS latency passes under the softmax arithmetic.
@@ -1411,7 +1443,7 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && NTW <= 2) ? 2 : 1) void spex_t
       f16x8 vh[D / 16];
 #pragma unroll
       for (int dt = 0; dt < D / 16; ++dt) vh[dt] = __builtin_bit_cast(f16x8, src[(NKI + dt) * 64]);
-      walk_softmax_pv<FP8, TREE, D, NTW>(limit, qidx, dmask, o, m, lacc, sa, sb, vh, (bm.flags & 1) != 0,
+      walk_softmax_pv<BY_TILE, FP8, TREE, D, NTW>(limit, qidx, dmask, o, m, lacc, sa, sb, vh, (bm.flags & 1) != 0,
                                    (jj < 2 ? bm.vp_a : bm.vp_b) & 127, (jj < 2 ? bm.vp_a : bm.vp_b) >> 7,
                                    c, slack, lo, hi, rows);
     };
@@ -1520,7 +1552,7 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && NTW <= 2) ? 2 : 1) void spex_t
           for (int s = 0; s < D / 32; ++s) kf[t][s] = __builtin_bit_cast(bf16x8, kr[t][s]);
       }
       f32x4 sa[NTW], sb[NTW];
-      walk_scores<D, NTW>(qf, kf, sa, sb);
+      walk_scores<BY_TILE, D, NTW>(qf, kf, sa, sb, lo, hi);
       if (more) issue_k(kr, refill);
       f16x8 vh[D / 16];
       if (FP8) {
@@ -1534,7 +1566,7 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && NTW <= 2) ? 2 : 1) void spex_t
         for (int s = 0; s < D / 16; ++s) vh[s] = __builtin_bit_cast(f16x8, vr[s]);
       }
       if (more) issue_v(vr, refill);
-      walk_softmax_pv<FP8, TREE, D, NTW>(limit, qidx, dmask, o, m, lacc, sa, sb, vh, (bm.flags & 1) != 0,
+      walk_softmax_pv<BY_TILE, FP8, TREE, D, NTW>(limit, qidx, dmask, o, m, lacc, sa, sb, vh, (bm.flags & 1) != 0,
                                    (jj < 2 ? bm.vp_a : bm.vp_b) & 127, (jj < 2 ? bm.vp_a : bm.vp_b) >> 7,
                                    c, slack, lo, hi, rows);
     };
@@ -2754,14 +2786,20 @@ hipError_t launch_split(const Shape &sh, const AttnArgs &a, const ItemLists &l, 
 }
 
 template <int KV, int D, int NW, bool TREE>
-static hipError_t launch_walk_ntw(const Shape &sh, const WalkArgs &a, int ntw, hipStream_t stream) {
+static hipError_t launch_walk_ntw(const Shape &sh, const WalkArgs &a, int ntw, bool by_tile, hipStream_t stream) {
   const dim3 grid(a.n_items), block(64 * NW);
+  // fp8 with two tiles and either type with four; eight wavefronts with four tiles always (straight on,
+  // their accumulators spill: 1044 us where one tile in four is touched, by tile 386)
   if (ntw == 1)
     hipLaunchKernelGGL((spex_tree_walk_kernel<KV, D, 1, NW, TREE>), grid, block, 0, stream, a, sh);
+  else if (ntw == 2 && KV == kFP8 && by_tile)
+    hipLaunchKernelGGL((spex_tree_walk_kernel<KV, D, 2, NW, TREE, 1, KV == kFP8>), grid, block, 0, stream, a, sh);
   else if (ntw == 2)
     hipLaunchKernelGGL((spex_tree_walk_kernel<KV, D, 2, NW, TREE>), grid, block, 0, stream, a, sh);
+  else if (NW == 8 || by_tile)
+    hipLaunchKernelGGL((spex_tree_walk_kernel<KV, D, 4, NW, TREE, 1, true>), grid, block, 0, stream, a, sh);
   else
-    hipLaunchKernelGGL((spex_tree_walk_kernel<KV, D, 4, NW, TREE>), grid, block, 0, stream, a, sh);
+    hipLaunchKernelGGL((spex_tree_walk_kernel<KV, D, 4, NW, TREE, 1, NW == 8>), grid, block, 0, stream, a, sh);
   return hipGetLastError();
 }
 
@@ -2778,31 +2816,32 @@ static hipError_t launch_walk_halves(const Shape &sh, const WalkArgs &a, int ntw
 }
 
 template <int KV, int D>
-static hipError_t launch_walk_nw(const Shape &sh, const WalkArgs &a, int ntw, int waves, bool halves, hipStream_t stream) {
+static hipError_t launch_walk_nw(const Shape &sh, const WalkArgs &a, int ntw, int waves, bool halves, bool by_tile, hipStream_t stream) {
   if (halves) {  // lists for four wavefronts of rows, walked by eight
     if (waves != 4) return hipErrorInvalidValue;
     return a.qt_mask ? launch_walk_halves<KV, D, 8, true>(sh, a, ntw, stream)
                      : launch_walk_halves<KV, D, 8, false>(sh, a, ntw, stream);
   }
-  if (a.qt_mask)  // draft-tree masks: not in the kernel that splits the path
-    return waves == 4   ? launch_walk_ntw<KV, D, 4, true>(sh, a, ntw, stream)
-           : waves == 8 ? launch_walk_ntw<KV, D, 8, true>(sh, a, ntw, stream)
-                        : hipErrorInvalidValue;
+  if (a.qt_mask) {  // draft-tree masks: not in the kernel that splits the path
+    if (waves == 2) return hipErrorInvalidValue;
+    return waves == 4 ? launch_walk_ntw<KV, D, 4, true>(sh, a, ntw, by_tile, stream)
+                      : launch_walk_ntw<KV, D, 8, true>(sh, a, ntw, by_tile, stream);
+  }
   // lists for two wavefronts of rows, walked by four: the path is split in two
   if (waves == 2) return launch_walk_halves<KV, D, 4, false>(sh, a, ntw, stream);
-  return waves == 4 ? launch_walk_ntw<KV, D, 4, false>(sh, a, ntw, stream)
-                    : launch_walk_ntw<KV, D, 8, false>(sh, a, ntw, stream);
+  return waves == 4 ? launch_walk_ntw<KV, D, 4, false>(sh, a, ntw, by_tile, stream)
+                    : launch_walk_ntw<KV, D, 8, false>(sh, a, ntw, by_tile, stream);
 }
 
-hipError_t launch_tree_walk(const Shape &sh, const WalkArgs &a, int ntw, int waves, bool halves, hipStream_t stream) {
+hipError_t launch_tree_walk(const Shape &sh, const WalkArgs &a, int ntw, int waves, bool halves, bool by_tile, hipStream_t stream) {
   if (a.n_items <= 0) return hipSuccess;
   if (!has_mfma_kernel(sh) || (ntw != 1 && ntw != 2 && ntw != 4) || (waves != 2 && waves != 4 && waves != 8))
     return hipErrorInvalidValue;
   if (sh.kv_dtype == kBF16)
-    return sh.D == 64 ? launch_walk_nw<kBF16, 64>(sh, a, ntw, waves, halves, stream)
-                      : launch_walk_nw<kBF16, 128>(sh, a, ntw, waves, halves, stream);
-  return sh.D == 64 ? launch_walk_nw<kFP8, 64>(sh, a, ntw, waves, halves, stream)
-                    : launch_walk_nw<kFP8, 128>(sh, a, ntw, waves, halves, stream);
+    return sh.D == 64 ? launch_walk_nw<kBF16, 64>(sh, a, ntw, waves, halves, by_tile, stream)
+                      : launch_walk_nw<kBF16, 128>(sh, a, ntw, waves, halves, by_tile, stream);
+  return sh.D == 64 ? launch_walk_nw<kFP8, 64>(sh, a, ntw, waves, halves, by_tile, stream)
+                    : launch_walk_nw<kFP8, 128>(sh, a, ntw, waves, halves, by_tile, stream);
 }
 
 namespace {

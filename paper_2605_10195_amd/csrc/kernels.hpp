@@ -140,6 +140,8 @@ hipError_t launch_patch(int32_t *blob, const int32_t *pairs, int32_t n, hipStrea
 // of rows per row block the lists were built for (2: run by four wavefronts, two on each set of
 // rows, which split the path between them; ntw 1 or 2, no draft masks).
 // halves (waves 4, ntw 1 or 2): eight wavefronts walk the lists made for four, two on each set of rows.
-hipError_t launch_tree_walk(const Shape &sh, const WalkArgs &a, int ntw, int waves, bool halves, hipStream_t stream);
+// by_tile: row tiles are worked on one by one, without those that a block does not touch.
+hipError_t launch_tree_walk(const Shape &sh, const WalkArgs &a, int ntw, int waves, bool halves, bool by_tile,
+                            hipStream_t stream);
 
 }  // namespace spex

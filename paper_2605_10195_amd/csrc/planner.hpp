@@ -106,12 +106,14 @@ struct Plan {
   std::vector<int32_t> walk_items;
   int32_t walk_real_items = 0;       // workgroups with work
   int32_t walk_max_item_blocks = 0;  // longest workgroup: shared blocks + most private blocks of a wavefront
+  int64_t walk_tiles_touched = 0, walk_tiles_held = 0;  // row tiles a block's rows lie in / its wavefronts hold, over all blocks
   int64_t walk_steps = 0;            // the same summed over the row blocks (one kv head each)
   int32_t calls = 0;                 // attention calls the plan has served
   bool growing = false;              // made because appends outgrew a plan that had served few calls
   // Decided when the lists are made and kept through length patches, which leave the figures behind
   // the decisions as they were.
   bool walk_halves = false;          // eight wavefronts walk the lists made for four, two on each set of rows
+  bool walk_by_tile = false;         // row tiles are worked on one by one, without those a block does not touch
   int32_t route = -1;                // Planner::prefers_walk: -1 not asked yet, 0 split path, 1 tree-walk kernel
   int64_t walk_block_visits = 0;  // blocks over all row blocks (a block shared by two row blocks counts twice)
 };
@@ -154,6 +156,7 @@ class Planner {
   float estimate_split(const PageTable &pt, const Plan &pl, float enough);
   static float estimate_walk(const Plan &plan);
   static bool walk_in_halves(const Plan &plan);
+  bool walk_by_tile(const Plan &plan) const;
   std::vector<int32_t> multi_, last_pg_;
   std::vector<int32_t> stamp_, slot_;  // per-node scratch of build_walk, valid where stamp_ == current stamp
   // scratch of the request ordering in ensure_walk: pre-order rank and child ranges per node,

@@ -128,6 +128,23 @@ int main() {
               a.plan.prefix_chunk_pages, a.plan.suffix_chunk_pages);
     }
 
+  // row tiles one by one: 6 rows a branch, 27 branches, prompts of `prompt` tokens
+  auto by_tile = [](int prompt, int row_tiles, int waves, int kv_bytes) {
+    Forest f(400, 16);
+    f.add(1, prompt, 27, 70);
+    Made m(f, 6, 1);
+    m.planner.pool = {true, 128, kv_bytes};
+    CHECK(m.planner.begin(f.pt, f.leaves.data(), f.q_lens.data(), nullptr, 27, 6, 1, 0, 0, row_tiles, waves, &m.plan) == PlanError::kOk, "begin");
+    m.planner.ensure_walk(f.pt, &m.plan);
+    const bool few = m.plan.walk_tiles_touched * (row_tiles == 4 ? 4 : 5) < m.plan.walk_tiles_held * (row_tiles == 4 ? 3 : 4);
+    CHECK(few == (prompt < 1000 && row_tiles > 1), "prompt %d, %d tiles: %ld of %ld touched", prompt, row_tiles, static_cast<long>(m.plan.walk_tiles_touched),
+          static_cast<long>(m.plan.walk_tiles_held));
+    return m.plan.walk_by_tile;
+  };
+  CHECK(by_tile(40, 2, 4, 1) && by_tile(40, 2, 8, 1) && by_tile(40, 4, 4, 1) && by_tile(40, 4, 4, 2), "short prompt");
+  CHECK(!by_tile(40, 2, 4, 2) && !by_tile(40, 1, 4, 1) && !by_tile(40, 2, 2, 1), "bf16 with two tiles, one tile, path split in two");
+  CHECK(!by_tile(5000, 2, 4, 1) && !by_tile(5000, 4, 4, 2), "long prompt");
+
   // the split path's launches, one or in phases: (roots, branches, queries, heads) -> workgroups at the bound
   auto phases = [](int roots, int branches, int q_len, int Hq, int Hkv, int dim, bool tiled = true) {
     Forest f(roots * (3 + 2 * branches), 16);

@@ -137,7 +137,8 @@ def test_random_trees_tree_walk_kernel(case, row_tiles, waves):
     assert_close(got, run_oracle(wl), case["kv_dtype"], wl.name)
 
 
-@pytest.mark.parametrize("waves", [0, 2])
+# waves 0: eight wavefronts in halves on the lists made for four; 4 and 8: as many on their own lists; 2: four in halves
+@pytest.mark.parametrize("waves", [0, 2, 4, 8])
 @pytest.mark.parametrize("kv_dtype", ["bf16", "fp8_e4m3"])
 def test_tree_walk_kernel_with_more_blocks_than_its_lds_copy_holds(kv_dtype, waves):
     # 9 000-token prompt + 1 100-token steps: > 256 two-page blocks per row block, so the kernel
@@ -150,6 +151,27 @@ def test_tree_walk_kernel_with_more_blocks_than_its_lds_copy_holds(kv_dtype, wav
     tree.close()
     rbs = np.array(dump["row_blocks"]).reshape(-1, 3 + 3 * dump["waves"])
     assert (rbs[:, 2] + rbs[:, 3:3 + dump["waves"]].sum(1)).max() > 256
+    assert_close(got, run_oracle(wl), kv_dtype, wl.name)
+
+
+# Branches of 6 rows below one prompt: most blocks touch one row tile of a wavefront's two or four, some two, so
+# that the tiles are worked on one by one (fp8 with two tiles, either type with four).
+@pytest.mark.parametrize("row_tiles,waves", [(2, 4), (2, 8), (4, 4), (4, 8)])
+@pytest.mark.parametrize("kv_dtype,dim", [("bf16", 128), ("fp8_e4m3", 128), ("bf16", 64), ("fp8_e4m3", 64)])
+@pytest.mark.parametrize("drafts", [False, True])
+def test_tree_walk_kernel_on_blocks_that_touch_some_row_tiles(row_tiles, waves, kv_dtype, dim, drafts):
+    if drafts:
+        wl = sw.tot_with_drafts(n_queries=2, prompt=40, step=70, depth=3, drafts=3, heads=(4, 2, dim), kv_dtype=kv_dtype, token_trees=True)
+    else:
+        wl = sw.spec_at_scale(n_queries=2, prompt=40, step=70, branches=27, heads=(12, 2, dim), kv_dtype=kv_dtype)
+    tree = build_gpu_tree(wl, kernel_mode=3, walk_row_tiles=row_tiles, walk_waves=waves)
+    dump = tree.walk_dump(wl.leaves, wl.q_lens, wl.draft_masks)
+    lo, hi = (np.array(dump["blocks"]).reshape(-1, 8)[:, 4] & 0xffff, np.array(dump["blocks"]).reshape(-1, 8)[:, 4] >> 16)
+    lo, hi, c = lo[hi > 0], hi[hi > 0], 16 * row_tiles
+    touched, held = ((hi + 15) // 16 - lo // 16).sum(), (((hi + c - 1) // c - lo // c) * row_tiles).sum()
+    assert touched < 0.75 * held
+    got = run_gpu(wl, tree=tree)
+    tree.close()
     assert_close(got, run_oracle(wl), kv_dtype, wl.name)
 
 
