@@ -592,17 +592,25 @@ float Planner::estimate_split(const PageTable &pt, const Plan &pl, float enough)
 }
 
 // Eight wavefronts, two on each set of rows, halve every workgroup's path in time but leave one
-// workgroup to a compute unit instead of two.  With up to 256 workgroups there is only one anyway
-// (90 forests: between 1.0 and 1.9 times as fast, 1.3 in the middle; 128 workgroups of up to 82
-// blocks 60.6 -> 45.0 us, 256 of up to 49, fp8, 54.1 -> 44.5).  With some more the launch still lasts as long
-// as its longest workgroup if most are much shorter (304 of up to 89 and 50 on average 71.1 -> 55.9 us,
-// 444 of up to 103 and 51 87.6 -> 82.1), but a second round of equal ones costs more than it saves
-// (336 of 61 blocks 68.3 -> 87.1).  Only where the number of wavefronts is not asked for.
-bool Planner::walk_in_halves(const Plan &pl) {
+// workgroup to a compute unit instead of two.  With up to 256 workgroups there is only one anyway (padding
+// counted: every XCD runs an eighth of the list, and 228 workgroups of which one XCD has 38 take a second
+// round, 353 -> 390 us).  Over 406 drawn requests 1.0 to 2.0 times as fast, 1.35 in the middle; 128 workgroups of
+// up to 82 blocks 60.6 -> 45.0 us, 256 of up to 49, fp8, 54.1 -> 44.5.  With some more the launch still lasts
+// as long as its longest workgroup if most are much shorter (300 of up to 64 and 35 on average 57.9 -> 36.1
+// us, 448 of up to 47 and 27 51.7 -> 47.8), unless all are short (440 of up to 13 15.3 -> 17.9); a second
+// round of equal ones costs more than it saves (336 of 61 blocks 68.3 -> 87.1).
+// Blocks of 16 KiB with one row tile, all workgroups of about equal length: the whole kernel reads them
+// at 4 to 5 TB/s as soon as there are more than some 24000, and the halves, with two blocks a step, fall behind
+// (192 workgroups of 127 blocks 97 -> 100 us, 256 of 321 268 -> 293; 128 of 133, 17000 blocks, 95 -> 84).
+// Only where the number of wavefronts is not asked for.
+constexpr int64_t kStreamedBlocks = 24000;
+bool Planner::walk_in_halves(const Plan &pl) const {
   if (pl.req_walk_waves != 0 || pl.walk_waves != 4 || pl.walk_row_tiles > 2) return false;
-  if (pl.walk_real_items <= 256) return true;
-  const int64_t all = static_cast<int64_t>(pl.walk_real_items) * pl.walk_max_item_blocks;
-  return pl.walk_real_items <= 448 && 10 * pl.walk_steps * pl.num_kv_heads <= 6 * all;
+  const int64_t blocks = pl.walk_steps * pl.num_kv_heads, slots = static_cast<int64_t>(pl.walk_items.size()) / pl.item_ints();
+  const bool ragged = 10 * blocks <= 6 * static_cast<int64_t>(pl.walk_real_items) * pl.walk_max_item_blocks;
+  if (slots <= 256)
+    return ragged || pl.walk_row_tiles > 1 || pool.kv_bytes * pool.head_dim < 256 || blocks <= kStreamedBlocks;
+  return ragged && pl.walk_real_items <= 448 && pl.walk_max_item_blocks >= 16;
 }
 
 // A wavefront that holds several row tiles works on all of them for every block of its list, in one run of
@@ -622,7 +630,9 @@ bool Planner::walk_by_tile(const Plan &pl) const {
 float Planner::estimate_walk(const Plan &pl) {
   const float longest = static_cast<float>(pl.walk_max_item_blocks);
   const float share = static_cast<float>(pl.walk_steps) * static_cast<float>(pl.num_kv_heads) / 512.f;
-  return pl.walk_halves ? 4.7f + 0.36f * longest + 0.69f * share : 4.5f + 0.63f * longest + 0.84f * share;
+  // the fit has equal workgroups of many 16 KiB blocks as halves, 8 % above what they take whole
+  return pl.walk_halves || (pl.req_walk_waves == 0 && pl.walk_waves == 4 && pl.walk_row_tiles == 1 && pl.walk_real_items <= 256)
+             ? 4.7f + 0.36f * longest + 0.69f * share : 4.5f + 0.63f * longest + 0.84f * share;
 }
 
 // Which kernels.  The tree-walk kernel needs lists that fill the chip (128 workgroups) or are short:

@@ -155,7 +155,7 @@ class Planner {
   // A result of `enough` or more may be a lower bound.
   float estimate_split(const PageTable &pt, const Plan &pl, float enough);
   static float estimate_walk(const Plan &plan);
-  static bool walk_in_halves(const Plan &plan);
+  bool walk_in_halves(const Plan &plan) const;
   bool walk_by_tile(const Plan &plan) const;
   std::vector<int32_t> multi_, last_pg_;
   std::vector<int32_t> stamp_, slot_;  // per-node scratch of build_walk, valid where stamp_ == current stamp

@@ -94,6 +94,23 @@ int main() {
   CHECK(!halves(257, 0), "257 even workgroups");
   CHECK(halves(447, 1), "448 workgroups, one of them long");
   CHECK(!halves(448, 1), "449 workgroups");
+  // equal workgroups of many 16 KiB blocks; 32 and 33 row blocks a root; a ragged launch of short paths
+  auto halves_of = [](int roots, int prompt, int branches, int longer, int Hq, int Hkv, int kv_bytes, int row_tiles = 0) {
+    Forest f(static_cast<int64_t>(roots) * (prompt / 16 + 2 + branches) + longer + 16, 16);
+    f.add(roots, prompt, branches, 16);
+    if (longer) f.add(1, 16 * longer, 0, 0);
+    Made m(f, Hq, Hkv);
+    m.planner.pool = {true, 128, kv_bytes};
+    CHECK(m.planner.begin(f.pt, f.leaves.data(), f.q_lens.data(), nullptr, static_cast<int32_t>(f.leaves.size()), Hq, Hkv, 0, 0, row_tiles, 0,
+                          &m.plan) == PlanError::kOk, "begin");
+    m.planner.ensure_walk(f.pt, &m.plan);
+    return m.plan.walk_halves;
+  };
+  CHECK(halves_of(240, 3200, 0, 0, 4, 1, 2), "24000 blocks of 16 KiB");
+  CHECK(!halves_of(240, 3240, 0, 0, 4, 1, 2), "24480 blocks of 16 KiB");
+  CHECK(halves_of(240, 3240, 0, 0, 4, 1, 1) && halves_of(240, 3240, 0, 0, 4, 1, 2, 2), "24480 blocks of 8 KiB, or with two row tiles");
+  CHECK(halves_of(3, 600, 4 * 32, 0, 32, 2, 2, 1) && !halves_of(3, 600, 4 * 33, 0, 32, 2, 2, 1), "three roots on four pairs of XCDs");
+  CHECK(halves_of(300, 20, 0, 32, 4, 1, 2) && !halves_of(300, 20, 0, 30, 4, 1, 2), "longest of 16 and of 15 blocks");
 
   // no estimate beyond 512 workgroups or 1024 query tokens: the tree-walk kernel
   auto choice = [](int trees, int tokens, int q_len) {
