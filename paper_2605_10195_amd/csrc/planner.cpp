@@ -531,9 +531,8 @@ PlanError Planner::ensure_split(const PageTable &pt, Plan *plan) {
   return PlanError::kOk;
 }
 
-// A fit over 165 forests of every shape (bf16 and fp8, 2 to 8 kv heads of 64 and 128, W = 2 to 3000
-// tree-walk workgroups), each timed through both paths: the middle half of the predictions is within
-// 14 %.  Shared items of more than 16 rows cost their blocks of 32 tokens through LDS, the others
+// A fit over 165 forests (bf16 and fp8, 2 to 8 kv heads of 64 and 128, W = 2 to 3000 tree-walk workgroups),
+// each timed through both paths; see prefers_walk for how far it carries.  Shared items of more than 16 rows cost their blocks of 32 tokens through LDS, the others
 // the blocks' bytes, and every row of an item its partial state.
 float Planner::estimate_split(const PageTable &pt, const Plan &pl, float enough) {
   const int32_t head_dim = pool.head_dim, kv_bytes = pool.kv_bytes;
@@ -644,9 +643,14 @@ float Planner::estimate_walk(const Plan &pl) {
 // Where branches of unequal length grow a token a call, some branch starts a page in most calls:
 // tree-walk lists are patched then, split lists made again (300 branches: 160 us of host time a
 // call), so a request that outgrew its last plan within 8 calls keeps the tree-walk kernel.
-// The estimates are good to some 14 % and a tree-walk plan is the one that lasts, so the split path
-// must promise 5 % less, or 30 % less for a launch of few workgroups, where the two differ by a
-// few us either way.  With more workgroups than run at a time (two per compute unit) the longest
+// A tree-walk plan is the one that lasts and takes the host half as long to make, and the estimates are rough
+// (over 473 drawn requests half of them lie between 0.70 and 1.12 of the measured time for the tree-walk
+// kernel, and between 0.87 and 1.23 for the split path), so the split path must promise less than 0.6 of the
+// other's time, 0.48 at a head dim of 64, whose blocks the tree-walk kernel gets through faster than the fit
+// says, and 4 us besides.  Over 482 more 16 then move, 1.7 times as fast in the middle and none slower; with
+// 0.95 74 moved, 15 of them to a slower kernel (up to 2.05 times over both sets).  For a launch of fewer than
+// 128 workgroups, whose tree-walk time is its longest path, 0.7 (6 moved, none slower; with 0.95 46 and four).
+// With more workgroups than run at a time (two per compute unit) the longest
 // one matters little and the estimate is not made; nor for more than 1024 query tokens, whose split
 // lists take the host longer to make than a call (2500: 1.9 against 1.0 ms for a first call).
 // Asked once per plan: patches raise the longest workgroup but not the sums behind both estimates, and
@@ -661,7 +665,7 @@ bool Planner::prefers_walk(const PageTable &pt, Plan *plan) {
     walk = pl.walk_ok && (pl.req_masks.empty() || pl.walk_waves != 2) &&
            (pl.walk_real_items >= 128 || pl.walk_max_item_blocks <= short_walk_blocks(pl.walk_real_items));
     if (walk && !pl.growing && pl.walk_real_items <= 512 && pl.qt_limit.size() <= 1024) {
-      const float least = (pl.walk_real_items >= 128 ? 0.95f : 0.7f) * estimate_walk(pl);
+      const float least = pl.walk_real_items >= 128 ? (pool.head_dim <= 64 ? 0.48f : 0.6f) * estimate_walk(pl) - 4.f : 0.7f * estimate_walk(pl);
       walk = estimate_split(pt, pl, least) >= least;
     }
   }

@@ -117,6 +117,7 @@ int main() {
     Forest f(trees * (tokens / 16 + 1), 16);
     f.add(trees, tokens, 0, 0, q_len);
     Made m(f, 4, 1);
+    m.planner.pool.head_dim = 64;
     return m.planner.prefers_walk(f.pt, &m.plan);
   };
   CHECK(!choice(512, 20000, 1), "512 workgroups on long paths");

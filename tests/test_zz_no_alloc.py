@@ -97,7 +97,7 @@ def test_static_entry_point_refuses_what_does_not_fit():
     tree.close()
 
 
-@pytest.mark.parametrize("trees,tokens,heads", [(512, 22000, (8, 1, 64)), (256, 46000, (8, 2, 64)), (500, 24000, (4, 1, 128))])
+@pytest.mark.parametrize("trees,tokens,heads", [(512, 22000, (8, 1, 64)), (256, 46000, (8, 2, 64)), (500, 24000, (4, 1, 64))])
 def test_static_entry_point_takes_requests_whose_lists_fit_one_set_at_a_time(trees, tokens, heads):
     """Long paths of one branch each: the tree-walk lists take 11 MiB, the split path's 6, and the array has 16.
     The automatic choice (the split path here) needs one of them, and gives what the tree-walk kernel gives."""
