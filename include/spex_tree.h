@@ -245,7 +245,8 @@ spex_status_t spex_tree_prune(spex_tree_t *tree, spex_node_t node);
  *     is cut into pieces of whole query tokens).  Chosen automatically when it yields >= 128
  *     workgroups, or when no wavefront has more two-page blocks to walk than 20 (up to 32
  *     workgroups) rising to 87 (127 workgroups): 20 + (workgroups - 32) * 7 / 10 -- unless, for up
- *     to 512 workgroups and 1024 query tokens, the other set's estimated time is clearly lower;
+ *     to 512 workgroups and 1024 query tokens, the other set's estimated time is clearly lower; decided when
+ *     a plan is made and kept while appends are patched into it;
  *   shared-prefix + suffix + merge: every shared node is read once for all rows below it, private
  *     suffixes are split for parallelism, partial softmax states go through memory.  Any shape.
  * Consecutive calls on one handle must use one stream or be separated by a synchronisation,
@@ -334,8 +335,9 @@ spex_status_t spex_tree_stats(const spex_tree_t *tree, int64_t *live_nodes, int6
  *   bit 1 = suffix task that is the only chunk of its suffix.
  *   Merge lists: query token t combines entries part_indptr[t] .. part_indptr[t+1]; the slot of
  *   (kv head g, head-in-group hh) in entry e is part_base[e] + g * part_hstride[e] + hh.
- *   merge_qt[n_merge_qt]: the query tokens without a task of flag bit 1.  (A launch in which every query
- *   token has one piece finishes its rows itself; otherwise the merge kernel takes all rows.)
+ *   merge_qt[n_merge_qt]: the query tokens without a task of flag bit 1.  (Launches in phases merge these and
+ *   finish the others' rows with the suffix; a single launch in which every query token has one piece finishes
+ *   its rows itself, otherwise the merge kernel takes all rows.)
  */
 typedef struct {
   int32_t n_leaves, n_qtok, n_groups, n_tasks, n_prefix_tasks, n_pg, n_qt_list, n_parts, n_merge_qt;
@@ -412,8 +414,8 @@ spex_status_t spex_tree_walk_dump(spex_tree_t *tree, const spex_node_t *leaves,
  * Per-kernel timing.  While profiling is enabled, every decode_attention call brackets each of
  * its kernels with HIP events on the call's stream (the last 256 calls are kept).
  * spex_tree_read_profile waits for those events and writes, for each recorded call in order,
- * milliseconds for ms[4*c+0] = the split path's launch of shared and private items (the generic kernels'
- * launches likewise), ms[4*c+1] = 0, ms[4*c+2] = merge
+ * milliseconds for ms[4*c+0] = the split path's launch or launches of shared and private items (the
+ * generic kernels' likewise), ms[4*c+1] = 0, ms[4*c+2] = merge
  * kernel, ms[4*c+3] = tree-walk kernel (0 for a kernel that was not launched; cap counts calls,
  * ms holds 4 * cap floats); *n = number of calls; the record is then
  * cleared.  SPEX_ERR_CAPACITY (with *n set) if cap calls are too few.  Enabling or disabling

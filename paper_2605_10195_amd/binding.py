@@ -435,7 +435,7 @@ class SpexTree:
         _check(lib.spex_tree_set_profiling(self._h, int(enabled)))
 
     def read_profile(self) -> np.ndarray:
-        """[n_calls, 4] milliseconds (prefix, suffix, merge, tree-walk) of the calls recorded so far."""
+        """[n_calls, 4] milliseconds (split path, 0, merge, tree-walk) of the calls recorded so far."""
         ms = np.zeros((256, 4), dtype=np.float32)
         n = C.c_int32()
         _check(lib.spex_tree_read_profile(self._h, ms.ctypes.data_as(C.POINTER(C.c_float)), 256,

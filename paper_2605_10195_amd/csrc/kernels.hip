@@ -1244,9 +1244,9 @@ __device__ __forceinline__ void walk_write_rows(float *out, float *lse, const Sh
   }
 }
 
-// KS = 1: wavefront w holds rows w * C .. of the row block.  KS = 2 (NW = 4): the lists are made
-// for LW = 2 wavefronts of rows; wavefronts w and w + 2 hold the same rows and split the row
-// block's path between them -- shared blocks alternate between the two halves of the workgroup
+// KS = 1: wavefront w holds rows w * C .. of the row block.  KS = 2: the lists are made for LW = NW / 2
+// wavefronts of rows (NW = 8: the lists of four wavefronts, where the planner chooses halves; NW = 4: two,
+// only where asked for); wavefronts w and w + LW hold the same rows and split the row block's path between them -- shared blocks alternate between the two halves of the workgroup
 // (two blocks per barrier, each staged by the pair that computes on it), a list wavefront's private
 // blocks alternate likewise -- and at the end the upper pair hands its softmax state to the lower
 // one through LDS.  Per block a wavefront then works on twice the rows, so half as many operand
@@ -2955,8 +2955,8 @@ template <int KV>
 static hipError_t gather_layout(const Shape &sh, const GatherArgs &a, hipStream_t stream) {
   if (wide_rows(sh, RowMajorTraits<KV>::kEsz, a.k_pool, a.v_pool, a.k_out, a.v_out)) {
     const dim3 wgrid(static_cast<unsigned>(a.n_pages * sh.Hkv)), wblock(256);
-    if (sh.layout == kMfmaTiled)
-      hipLaunchKernelGGL((spex_read_pages_kernel<KV, kMfmaTiled>), wgrid, wblock, 0, stream, a, sh);
+    if (KV != kF32 && sh.layout == kMfmaTiled)  // fp32 pools are row-major
+      hipLaunchKernelGGL((spex_read_pages_kernel<KV, KV == kF32 ? kRowMajor : kMfmaTiled>), wgrid, wblock, 0, stream, a, sh);
     else
       hipLaunchKernelGGL((spex_read_pages_kernel<KV, kRowMajor>), wgrid, wblock, 0, stream, a, sh);
     return hipGetLastError();

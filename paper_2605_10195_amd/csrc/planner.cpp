@@ -99,7 +99,9 @@ struct Segment {
 };
 
 // Longest tree-walk workgroup (in two-page blocks) up to which a launch of `items` workgroups
-// (< 128) still goes to the tree-walk kernel.
+// (< 128) still goes to the tree-walk kernel.  Crossing points measured with four wavefronts to a workgroup (bf16,
+// 32 / 8 heads of 128): 20 blocks at 8 to 32 workgroups, 40 at 64, 65 at 96.  Launches this small run in
+// halves meanwhile, some 1.35 times as fast, and the split path in one launch.
 int32_t short_walk_blocks(int64_t items) {
   return items <= 32 ? 20 : 20 + static_cast<int32_t>((items - 32) * 7 / 10);
 }
@@ -329,13 +331,11 @@ PlanError Planner::ensure_split(const PageTable &pt, Plan *plan) {
     }
   };
   std::vector<Segment> groups(NG), suffixes;
-  int32_t max_rows_small = 0;
   for (int32_t gi = 0; gi < NG; ++gi) {
     add_node_pages(groups[gi], pl.group_node[gi]);
     groups[gi].qt_begin = group_qt_begin[gi];
     groups[gi].qt_count = group_count[gi];
     pl.max_rows_prefix = std::max(pl.max_rows_prefix, group_count[gi] * G);
-    if (group_count[gi] * G <= kWaveRowsMax) max_rows_small = std::max(max_rows_small, group_count[gi] * G);
   }
   suffixes.reserve(n_leaves);
   for (int32_t i = 0; i < n_leaves; ++i) {
@@ -350,7 +350,6 @@ PlanError Planner::ensure_split(const PageTable &pt, Plan *plan) {
     pl.max_rows_suffix = std::max(pl.max_rows_suffix, ql * G);
     suffixes.push_back(std::move(s));
   }
-  pl.prefix_row_tiles = max_rows_small <= 16 ? 1 : 2;
   pl.suffix_row_tiles = pl.max_rows_suffix <= 16 ? 1 : 2;
   const int32_t rw_suffix = 16 * pl.suffix_row_tiles;
   {

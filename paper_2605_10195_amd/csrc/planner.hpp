@@ -18,8 +18,9 @@
 //    path position following the task's last token;
 //  * flag bit 1 (final): suffix task that is the only chunk of its suffix;
 //  * merge_qt: ascending query tokens without such a task (requested nodes whose suffix is empty or has
-//    several chunks).  Both are part of the dump only: the kernels finish rows themselves where every
-//    query token of the request has a single piece, else all rows go through the merge kernel.
+//    several chunks).  Launches in phases finish the rows of flag bit 1 with the suffix and merge merge_qt; a
+//    single launch finishes rows itself where every query token of the request has a single piece, else
+//    all rows go through the merge kernel.
 #pragma once
 
 #include <cstdint>
@@ -77,7 +78,7 @@ struct Plan {
   static constexpr int kItemInts = 8;
   std::vector<int32_t> prefix_items, suffix_items, pg_rec, qt_rec;
   std::vector<int32_t> coop_items[2];  // groups of more than 16 rows, up to 64 / 128 rows per workgroup
-  int32_t prefix_row_tiles = 1, suffix_row_tiles = 1;  // 16-row MFMA tiles per wavefront
+  int32_t suffix_row_tiles = 1;  // 16-row MFMA tiles per wavefront of the private items (shared ones of few rows: 1)
   int32_t max_rows_prefix = 0, max_rows_suffix = 0;
   int64_t prefix_tokens = 0, suffix_tokens = 0;        // distinct KV tokens per kind
 
