@@ -127,3 +127,35 @@ def test_phases_with_interior_nodes_and_cut_suffixes(heads, kv_dtype, chunk):
     wl = sw.random_trace(77, heads=heads, kv_dtype=kv_dtype, n_ops=900, n_roots=120, max_q_len=3)
     got = run_gpu(wl, kernel_mode=2, prefix_chunk_pages=chunk, suffix_chunk_pages=chunk)
     assert_close(got, run_oracle_c(wl), kv_dtype, f"{heads} chunk {chunk}")
+
+
+def test_request_that_outgrows_its_plan_keeps_the_tree_walk_kernel():
+    """160 long paths of one branch: the split path's estimate is lower, and its lists cannot follow a page that
+    starts.  A request that outgrows its plan within 8 calls is planned for the tree-walk kernel, whose
+    lists can; after 8 calls the estimate counts again."""
+    import paper_2605_10195_amd as spex
+    t = spex.SpexTree(4, 1, 64, 16, num_pages=160 * 390, device="cuda")
+    roots = t.fork(-1, 160)
+    for u in roots:
+        t.append_step(u, None, None, n_tokens=6000)       # 375 whole pages
+    t.k_pool.view(torch.bfloat16).normal_(0.0, 0.5)
+    t.v_pool.view(torch.float16).normal_(0.0, 0.5)
+    q = torch.randn((160, 4, 64), device="cuda").to(torch.bfloat16)
+
+    def call(kernels):
+        out, _ = t.decode_attention(roots, None, q, 0.125)
+        assert (t.last_launch_info()["walk_row_tiles"] > 0) == (kernels == "walk")
+        return out
+
+    call("split")
+    for u in roots:
+        t.append_step(u, None, None, n_tokens=1)
+    outs = [call("walk") for _ in range(9)]
+    t.set_tuning(0, 0, 2, 0, 0)
+    ref = call("split")
+    assert float((outs[-1] - ref).norm() / ref.norm()) <= 1e-3
+    t.set_tuning(0, 0, 0, 0, 0)
+    for u in roots:
+        t.append_step(u, None, None, n_tokens=200)
+    call("split")
+    t.close()
