@@ -671,12 +671,13 @@ def test_chain_masks_give_the_bits_of_the_call_without_masks(case):
 
 def test_draft_masks_in_every_kernel_set():
     """Masks in the shared-prefix / suffix / merge kernels (kernel_mode 2) and in the tree-walk kernel
-    with 8 wavefronts; only the kernel that splits the path (walk_waves 2) refuses them."""
+    with 4 wavefronts (0: in halves, two on each set of rows) and with 8; only the kernel that splits the path (walk_waves 2) refuses them."""
     import paper_2605_10195_amd as spex
     wl = token_tree_workload(TOKEN_TREE_CASES[0])
     q = sw.gen_queries(wl, device="cuda")
     ref = run_oracle(wl)
     for kw in (dict(kernel_mode=2), dict(kernel_mode=2, prefix_chunk_pages=1, suffix_chunk_pages=1),
+               dict(kernel_mode=3), dict(kernel_mode=3, walk_waves=4), dict(kernel_mode=3, walk_waves=4, walk_row_tiles=1),
                dict(kernel_mode=3, walk_waves=8), dict(kernel_mode=0, walk_waves=8)):
         tree = build_gpu_tree(wl, **kw)
         got = run_gpu(wl, tree=tree)
