@@ -385,7 +385,7 @@ def measure(name, args, steps, warmup, decode_iters, cpu_sample, calibrate=False
     b_tok = wl.kv_bytes_per_token()
     kernels = {}
     walked = info["walk_row_tiles"] > 0
-    for kname, ms, toks in (("split", k_ms[0], 0 if walked else info["kv_tokens"]),   # shared and private items, one launch
+    for kname, ms, toks in (("split", k_ms[0], 0 if walked else info["kv_tokens"]),   # shared and private items, in one launch or in phases
                             ("walk", k_ms[3], info["kv_tokens"] if walked else 0)):
         gbps = toks * b_tok / (ms * 1e-3) / 1e9 if ms > 0 else 0.0
         kernels[kname] = dict(ms=float(ms), kv_tokens=int(toks), kv_bytes=float(toks * b_tok),
