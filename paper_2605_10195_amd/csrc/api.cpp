@@ -450,7 +450,12 @@ spex_status_t spex_tree_create(const spex_config_t *cfg, spex_tree_t **out) {
   if (!t) return SPEX_ERR_INVALID_ARG;
   t->cfg = *cfg;
   t->shape = make_shape(*cfg);
-  t->planner.pool = {spex::has_mfma_kernel(t->shape), cfg->head_dim, static_cast<int32_t>(elem_size(cfg->kv_dtype))};
+  spex::AttnArgs pools{};
+  pools.k_pool = cfg->k_pool;
+  pools.v_pool = cfg->v_pool;
+  const bool tiled = spex::has_mfma_kernel(t->shape);
+  t->planner.pool = {tiled, !tiled && !spex::has_rowmajor_kernel(t->shape, pools), cfg->head_dim,
+                     static_cast<int32_t>(elem_size(cfg->kv_dtype))};
   t->pt = new (std::nothrow) spex::PageTable(cfg->num_pages, cfg->page_size, cfg->free_order);
   if (!t->pt) {
     delete t;

@@ -26,9 +26,11 @@ int32_t clamp32(int64_t v, int32_t lo, int32_t hi) {
 // 73 / 66 / 60 / 57; private items of 128 or 256 tokens are within 3 % of each other.
 // Items shorter than 16 (shared) and 8 (private) pages only while the launch has at most kFineRows
 // partial rows: beyond that a request would need more room for them than it did with those bounds,
-// and the entry point that allocates nothing has 48 MiB of it.  Pages of fewer than four tokens go to the
-// generic kernel, a wavefront per item and row, which needs many items and keeps the 16 and 8 pages
-// (128 tokens instead: 16 branches on pages of 2 tokens 123.9 -> 190.1 us).
+// and the entry point that allocates nothing has 48 MiB of it.
+// Pools that only the generic kernel serves (rows not 16-byte aligned, pages of fewer than four tokens), a
+// wavefront per item and row, have shorter items and more of them: 1024 shared and 2048 private ones, none that
+// must be longer than those 16 and 8 pages (fp8, 6 / 3 heads of 40, 16 prompts of 8000 tokens: 585 us with 256
+// and 1024, 427 with these; 16 branches on pages of 2 tokens 190 with items of 128 tokens, 92 with these).
 // Tiled pools: launches of many items go in phases, shared items and then private ones, a wavefront
 // each, which finish the rows of suffixes in one piece.
 //  * Private items of more than 16 rows (the kernel then holds two row tiles and one workgroup a compute
@@ -66,7 +68,9 @@ Chunks choose_chunks(const std::vector<Run> &groups, const std::vector<Run> &suf
   };
   Chunks c{};
   auto choose = [&](int64_t shared_items, int64_t private_items, bool fine) {
-    const int32_t lp = page_size < 4 ? 16 : std::max(1, 128 / page_size), ls = page_size < 4 ? 8 : lp;
+    const int32_t fine_pages = std::max(1, 128 / page_size);
+    const int32_t lp = pool.generic ? std::min(fine_pages, 16) : fine_pages;
+    const int32_t ls = pool.generic ? std::min(fine_pages, 8) : fine_pages;
     c.prefix = prefix_chunk > 0 ? prefix_chunk : auto_chunk(weighted, shared_items, fine ? lp : std::max(lp, 16), 256);
     c.suffix = suffix_chunk > 0 ? suffix_chunk : auto_chunk(suffix_pages, private_items, fine ? ls : std::max(ls, 8), 64);
     auto chunks = [](int64_t pages, int64_t n) { return (pages + n - 1) / n; };
@@ -83,8 +87,9 @@ Chunks choose_chunks(const std::vector<Run> &groups, const std::vector<Run> &suf
     c.phases = pool.tiled && (tall ? (shared_wgs + private_wgs) * num_kv_heads > 512
                                    : private_wgs * num_kv_heads > (pool.head_dim <= 64 ? 4096 : 16384));
   };
-  choose(256, 1024, true);
-  if (c.partial_rows > kFineRows) choose(256, 1024, false);
+  const int64_t shared_items = pool.generic ? 1024 : 256, private_items = pool.generic ? 2048 : 1024;
+  choose(shared_items, private_items, true);
+  if (c.partial_rows > kFineRows) choose(shared_items, private_items, false);
   if (c.phases && tall) {
     choose(1024, 2048, false);
     c.phases = true;

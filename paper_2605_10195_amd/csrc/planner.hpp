@@ -121,7 +121,8 @@ struct Plan {
 
 // What the planner has to know of the pool to choose kernels and the lengths of their items.
 struct PoolShape {
-  bool tiled = false;  // MFMA-tiled: the tree-walk kernel and the split path's launches in phases exist
+  bool tiled = false;    // MFMA-tiled: the tree-walk kernel and the split path's launches in phases exist
+  bool generic = false;  // neither tiled nor fit for the row-major kernel
   int32_t head_dim = 128, kv_bytes = 2;
 };
 

@@ -44,7 +44,7 @@ struct Made {
   Planner planner;
   Plan plan;
   Made(const Forest &f, int Hq, int Hkv, int prefix_chunk = 0, int suffix_chunk = 0) {
-    planner.pool = {f.pt.page_size() == 16, 128, 2};
+    planner.pool = {f.pt.page_size() == 16, f.pt.page_size() < 4, 128, 2};
     const PlanError e = planner.begin(f.pt, f.leaves.data(), f.q_lens.data(), nullptr, static_cast<int32_t>(f.leaves.size()), Hq,
                                       Hkv, prefix_chunk, suffix_chunk, 0, 0, &plan);
     CHECK(e == PlanError::kOk, "begin");
@@ -100,7 +100,7 @@ int main() {
     f.add(roots, prompt, branches, 16);
     if (longer) f.add(1, 16 * longer, 0, 0);
     Made m(f, Hq, Hkv);
-    m.planner.pool = {true, 128, kv_bytes};
+    m.planner.pool = {true, false, 128, kv_bytes};
     CHECK(m.planner.begin(f.pt, f.leaves.data(), f.q_lens.data(), nullptr, static_cast<int32_t>(f.leaves.size()), Hq, Hkv, 0, 0, row_tiles, 0,
                           &m.plan) == PlanError::kOk, "begin");
     m.planner.ensure_walk(f.pt, &m.plan);
@@ -127,6 +127,16 @@ int main() {
   CHECK(!choice(16, 20000, 1), "few long paths");
   CHECK(choice(16, 512, 1), "few short paths");
 
+  // pools of the generic kernel: four times as many shared items of a long prompt
+  for (bool generic : {false, true}) {
+    Forest f(2000, 16);
+    f.add(1, 16 * 1024, 4, 16);
+    Made m(f, 8, 4);
+    m.planner.pool = {false, generic, 40, 1};
+    CHECK(m.planner.ensure_split(f.pt, &m.plan) == PlanError::kOk, "split lists");
+    CHECK(m.plan.prefix_chunk_pages == (generic ? 8 : 16), "items of %d pages", m.plan.prefix_chunk_pages);
+  }
+
   // automatic items, by page size: never more partial rows than the shortest items give, and items of
   // at least those lengths where the partial rows would be too many
   for (int P = 1; P <= 64; P *= 2)
@@ -151,7 +161,7 @@ int main() {
     Forest f(400, 16);
     f.add(1, prompt, 27, 70);
     Made m(f, 6, 1);
-    m.planner.pool = {true, 128, kv_bytes};
+    m.planner.pool = {true, false, 128, kv_bytes};
     CHECK(m.planner.begin(f.pt, f.leaves.data(), f.q_lens.data(), nullptr, 27, 6, 1, 0, 0, row_tiles, waves, &m.plan) == PlanError::kOk, "begin");
     m.planner.ensure_walk(f.pt, &m.plan);
     const bool few = m.plan.walk_tiles_touched * (row_tiles == 4 ? 4 : 5) < m.plan.walk_tiles_held * (row_tiles == 4 ? 3 : 4);
@@ -168,7 +178,7 @@ int main() {
     Forest f(roots * (3 + 2 * branches), 16);
     f.add(roots, 40, branches, 20, q_len);
     Made m(f, Hq, Hkv);
-    m.planner.pool = {tiled, dim, 2};
+    m.planner.pool = {tiled, false, dim, 2};
     CHECK(m.planner.ensure_split(f.pt, &m.plan) == PlanError::kOk, "split lists");
     return m.plan.split_phases;
   };
