@@ -534,8 +534,14 @@ struct ListPos {
 __device__ __forceinline__ ListPos list_of(const SplitLists &ls, int wg) {
   ListPos r = {0, wg, ls.n_items[0], ls.span[0], ls.items[0]};
 #pragma unroll
-  for (int i = 1; i < SplitLists::kLists; ++i)
-    if (wg >= ls.wg_end[i - 1]) r = {i, wg - ls.wg_end[i - 1], ls.n_items[i], ls.span[i], ls.items[i]};
+  for (int i = 1; i < SplitLists::kLists; ++i) {  // member by member: as a whole the lists go through scratch memory
+    const bool in = wg >= ls.wg_end[i - 1];
+    r.k = in ? i : r.k;
+    r.local = in ? wg - ls.wg_end[i - 1] : r.local;
+    r.n_items = in ? ls.n_items[i] : r.n_items;
+    r.span = in ? ls.span[i] : r.span;
+    r.items = in ? ls.items[i] : r.items;
+  }
   return r;
 }
 
@@ -1776,23 +1782,24 @@ __global__ __launch_bounds__(64) void spex_generic_attn_kernel(AttnArgs p, Shape
 //   S^T = K Q^T: lane (token m16, group jj) loads 16 bytes of its token's row at a time; every
 //     element (fp32) or octet (16-bit, widened fp8) of the load is one MFMA operand whose
 //     contraction index is the dim the lane holds, and Q is loaded with the same dims.
-//   The result leaves tokens 4 jj .. 4 jj + 3 of row m16 in the lane: P^T as the B operand of four
-//   MFMA 16x16x4, one per r, whose contraction runs over tokens {4 jj + r}.
-//   O^T += V^T P^T: lane (m16, jj) loads VE consecutive dims VE m16 .. of token 4 jj + r; element i
-//     is the A operand of the tile of dims {VE m + i}.
-// All products with the softmax weights are fp32 MFMAs on fp32 weights, so fp32 pools lose nothing
-// and 16-bit and fp8 values (exact in fp32) meet unrounded weights; Q K^T of 16-bit values runs on
-// the bf16 MFMA, whose products are exact in fp32.
+//   The result leaves tokens 4 jj .. 4 jj + 3 of row m16 in the lane.
+//   fp32 pools: P^T as the B operand of four fp32 MFMA 16x16x4, one per r, whose contraction runs over tokens
+//     {4 jj + r}.  Lane (m16, jj) loads VE consecutive dims VE m16 .. of token 4 jj + r; element i is the A
+//     operand of O^T += V^T P^T for the tile of dims {VE m + i}.
+//   16-bit and fp8 pools: two groups of 16 tokens at a time, which leave eight weights in the lane, the
+//     contraction index of a bf16 MFMA 16x16x32.  The lane's V rows of the same eight tokens are turned
+//     token-minor by one byte permutation per register.  A weight goes in as three bf16 pieces that add up to
+//     the fp32 weight, and V is exact in bf16, so every product is the one the fp32 MFMA would see.
 //
-// Why this shape: a lane per token on the vector ALU read 4 bytes per lane at a row's stride and
-// every row read K and V again.  Per 16 tokens and row tile at D = 128 a wavefront issues 32 + 4
-// (bf16) or 64 (fp32) MFMAs, about 1100 or 2050 cycles for 8 or 16 KiB of K and V, three times
-// what memory needs to deliver them, so 16 rows stay memory-bound.
-// Measured against the generic kernel (one launch each for shared and private items): fp32, one
-// tree of 4 branches, 8 heads of 64: 107.7 -> 13.5 us a call; bf16 pages of 32 tokens, 128
-// branches, 32 heads of 128: 1010 -> 55 us.  Error against 64 bits 3.5e-7 (generic 4.7e-7).
-// A wavefront's K loads for the next 16 tokens are issued right after the score MFMAs, its V loads
-// right after the PV MFMAs, page records two steps ahead.
+// Why this shape: per 32 tokens and row tile at D = 128 a wavefront issues 8 + 24 MFMAs of 16 cycles; P V on the
+// fp32 MFMA was 64 of 32 cycles, four times as long as the memory needs for the tokens, and bound the kernel.
+// Measured, fp32 P V -> bf16 pieces: 8 ragged queries of 16 branches, bf16 pages of 32 tokens, heads 32/8/128,
+// 42.3 -> 37.3 us a call; 32 queries 117 -> 101 (fp8 94 -> 75); heads 16/4/256, fp8, 140 -> 73 (two workgroups
+// a compute unit instead of one).  Error against 64 bits 2.9e-7 (3.1e-7 with the fp32 MFMA, 4.7e-7 on the vector ALU).
+// FULL: head dim DP itself, whose addresses and bounds are known when compiled (bf16, 128: 160 registers instead
+// of 186, three workgroups a compute unit instead of two: 114 -> 101 us for the 32 queries above).
+// A wavefront's K loads for the next tokens are issued right after the score MFMAs, its V loads right after the PV
+// MFMAs, page records a step ahead.
 template <int KV>
 struct RowMajorTraits {};
 template <>
@@ -1802,8 +1809,14 @@ struct RowMajorTraits<kBF16> { static constexpr int kEsz = 2; };
 template <>
 struct RowMajorTraits<kFP8> { static constexpr int kEsz = 1; };
 
-template <int KV, int DP>
-__global__ __launch_bounds__(256, DP <= 128 ? 2 : 1) void spex_rowmajor_attn_kernel(AttnArgs p, Shape sh, SplitLists ls) {
+// Workgroups per compute unit: as many as the registers allow without spills.
+constexpr int rowmajor_occupancy(int kv, int dp, bool full) {
+  if (dp > 128) return kv == kFP8 ? 2 : 1;
+  return dp == 64 || (kv != kF32 && (full || kv == kFP8)) ? 3 : 2;
+}
+
+template <int KV, int DP, bool FULL>
+__global__ __launch_bounds__(256, rowmajor_occupancy(KV, DP, FULL)) void spex_rowmajor_attn_kernel(AttnArgs p, Shape sh, SplitLists ls) {
   constexpr int ESZ = RowMajorTraits<KV>::kEsz;
   constexpr int CH = 16 / ESZ;             // elements per 16-byte load
   constexpr int NK = DP / (4 * CH);        // K loads per lane and step
@@ -1811,6 +1824,7 @@ __global__ __launch_bounds__(256, DP <= 128 ? 2 : 1) void spex_rowmajor_attn_ker
   constexpr int NC = DP / (16 * VE);       // V loads per token
   constexpr int NO = DP / 16;              // output tiles
   constexpr int NQ = KV == kF32 ? DP / 4 : DP / 8;  // Q registers
+  constexpr int SUB = KV == kF32 ? 1 : 2;  // groups of 16 tokens per step
   constexpr int kFold = NO * 4 + 2;        // floats per lane a wavefront hands over
   __shared__ float fold[3 * 64 * kFold];
 
@@ -1821,7 +1835,7 @@ __global__ __launch_bounds__(256, DP <= 128 ? 2 : 1) void spex_rowmajor_attn_ker
   const int group = at.local / at.n_items; // 64 rows each
   const Item it = load_item(at.items, at.local - group * at.n_items);
   if (it.pg_count == 0) return;            // padding item
-  const int D = sh.D, G = sh.G, rows = it.qt_count * G;
+  const int D = FULL ? DP : sh.D, G = sh.G, rows = it.qt_count * G;
   const int row_end = min(rows, it.row0 + span);
   const int row_lo = it.row0 + group * 64;
   if (row_lo >= row_end) return;           // whole workgroup
@@ -1885,23 +1899,23 @@ __global__ __launch_bounds__(256, DP <= 128 ? 2 : 1) void spex_rowmajor_attn_ker
   };
   // Dims past D (D < DP) are read from the start of the row instead, so that no load is
   // conditional: in K they meet zeros of Q, in V they make output dims that are not written.
-  u32x4 kr[NK];
-  auto load_k = [&](const Rec &r, int step) {
+  u32x4 kr[SUB][NK];
+  auto load_k = [&](int j, const Rec &r, int step) {
     const int slot = ((step << 4) + m16) & (sh.P - 1);
     const char *src = kpool + (static_cast<int64_t>(r.k.x) * sh.page_tiles + it.g) * tile_bytes +
                       static_cast<int64_t>(slot) * D * ESZ;
 #pragma unroll
     for (int i = 0; i < NK; ++i)
-      kr[i] = *reinterpret_cast<const u32x4 *>(src + (4 * CH * i + CH * jj < D ? 64 * i + 16 * jj : 0));
+      kr[j][i] = *reinterpret_cast<const u32x4 *>(src + (4 * CH * i + CH * jj < D ? 64 * i + 16 * jj : 0));
   };
   struct VReg {
     uint32_t w[VE * ESZ / 4];
   };
-  VReg vr[4][NC];
+  VReg vr[SUB][4][NC];
   int v_off[NC];
 #pragma unroll
   for (int c = 0; c < NC; ++c) v_off[c] = 16 * VE * c + VE * m16 < D ? 16 * VE * c : -VE * m16;
-  auto load_v = [&](const Rec &r, int step) {
+  auto load_v = [&](int j, const Rec &r, int step) {
     const int slot = ((step << 4) + 4 * jj) & (sh.P - 1);
     const char *src = vpool + (static_cast<int64_t>(r.v.x) * sh.page_tiles + it.g) * tile_bytes +
                       (static_cast<int64_t>(slot) * D + VE * m16) * ESZ;
@@ -1909,60 +1923,70 @@ __global__ __launch_bounds__(256, DP <= 128 ? 2 : 1) void spex_rowmajor_attn_ker
     for (int t = 0; t < 4; ++t)
 #pragma unroll
       for (int c = 0; c < NC; ++c)
-        __builtin_memcpy(&vr[t][c], __builtin_assume_aligned(src + (t * D + v_off[c]) * ESZ, VE * ESZ), VE * ESZ);
+        __builtin_memcpy(&vr[j][t][c], __builtin_assume_aligned(src + (t * D + v_off[c]) * ESZ, VE * ESZ), VE * ESZ);
   };
 
   if (has_rows && step0 < step1) {
-    Rec cur = rec_of(step0), nxt = rec_of(step0 + 1);
-    load_k(cur, step0);
-    load_v(cur, step0);
-    for (int st = step0; st < step1; ++st) {
-      const Rec nxt2 = rec_of(st + 2);
-      float ks_l = 1.f, vs_l = 1.f;
-      if (KV == kFP8) {
-        ks_l = p.k_scale[static_cast<int64_t>(cur.v.x) * sh.Hkv + it.g];
-        vs_l = p.v_scale[static_cast<int64_t>(cur.v.x) * sh.Hkv + it.g];
-      }
-      f32x4 sa = {0.f, 0.f, 0.f, 0.f}, sb = {0.f, 0.f, 0.f, 0.f};
+    Rec cur[SUB], nxt[SUB];
 #pragma unroll
-      for (int i = 0; i < NK; ++i) {
-        if (KV == kF32) {
-          const f32x4 kv = __builtin_bit_cast(f32x4, kr[i]), qv = __builtin_bit_cast(f32x4, q[i]);
-          sa = __builtin_amdgcn_mfma_f32_16x16x4f32(kv[0], qv[0], sa, 0, 0, 0);
-          sb = __builtin_amdgcn_mfma_f32_16x16x4f32(kv[1], qv[1], sb, 0, 0, 0);
-          sa = __builtin_amdgcn_mfma_f32_16x16x4f32(kv[2], qv[2], sa, 0, 0, 0);
-          sb = __builtin_amdgcn_mfma_f32_16x16x4f32(kv[3], qv[3], sb, 0, 0, 0);
-        } else if (KV == kBF16) {
-          f32x4 &acc = (i & 1) ? sb : sa;
-          acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kr[i]), __builtin_bit_cast(bf16x8, q[i]), acc, 0, 0, 0);
-        } else {
-          sa = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fp8x8_to_bf16x8(kr[i][0], kr[i][1]), __builtin_bit_cast(bf16x8, q[2 * i]), sa, 0, 0, 0);
-          sb = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fp8x8_to_bf16x8(kr[i][2], kr[i][3]), __builtin_bit_cast(bf16x8, q[2 * i + 1]), sb, 0, 0, 0);
+    for (int j = 0; j < SUB; ++j) {
+      cur[j] = rec_of(step0 + j);
+      nxt[j] = rec_of(step0 + SUB + j);
+      load_k(j, cur[j], step0 + j);
+      load_v(j, cur[j], step0 + j);
+    }
+    for (int st = step0; st < step1; st += SUB) {
+      float x[SUB][4], vs_l[SUB], mx = kNegInf;
+#pragma unroll
+      for (int j = 0; j < SUB; ++j) {
+        float ks_l = 1.f;
+        vs_l[j] = 1.f;
+        if (KV == kFP8) {
+          ks_l = p.k_scale[static_cast<int64_t>(cur[j].v.x) * sh.Hkv + it.g];
+          vs_l[j] = p.v_scale[static_cast<int64_t>(cur[j].v.x) * sh.Hkv + it.g];
         }
-      }
-      load_k(nxt, min(st + 1, step1 - 1));
-      // ---- what the row sees of the lane's four tokens
-      const int slot = ((st << 4) + 4 * jj) & (sh.P - 1);
-      const int pos = (cur.v.y >> 7) + slot;
-      int have = (st << 4) + 4 * jj < n_slots ? (cur.v.y & 127) - slot : 0;
-      uint32_t vm = 0xfu;
-      if (p.qt_mask) {
-        const int shift = pos - d_base + 32;
-        const uint64_t bits = (static_cast<uint64_t>(d_mask) << 32) | 0xffffffffull;
-        vm = shift <= 0 ? 0xfu : (shift >= 64 ? 0u : static_cast<uint32_t>(bits >> shift) & 0xfu);
-      } else {
-        have = min(have, limit - pos);
-      }
-      const float c = p.scale_log2 * ks_l;
-      float x[4];
+        f32x4 sa = {0.f, 0.f, 0.f, 0.f}, sb = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        x[r] = (sa[r] + sb[r]) * c;
-        x[r] = (r < have && ((vm >> r) & 1u)) ? x[r] : kNegInf;
+        for (int i = 0; i < NK; ++i) {
+          const u32x4 &k = kr[j][i];
+          if (KV == kF32) {
+            const f32x4 kv = __builtin_bit_cast(f32x4, k), qv = __builtin_bit_cast(f32x4, q[i]);
+            sa = __builtin_amdgcn_mfma_f32_16x16x4f32(kv[0], qv[0], sa, 0, 0, 0);
+            sb = __builtin_amdgcn_mfma_f32_16x16x4f32(kv[1], qv[1], sb, 0, 0, 0);
+            sa = __builtin_amdgcn_mfma_f32_16x16x4f32(kv[2], qv[2], sa, 0, 0, 0);
+            sb = __builtin_amdgcn_mfma_f32_16x16x4f32(kv[3], qv[3], sb, 0, 0, 0);
+          } else if (KV == kBF16) {
+            f32x4 &acc = (i & 1) ? sb : sa;
+            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, k), __builtin_bit_cast(bf16x8, q[i]), acc, 0, 0, 0);
+          } else {
+            sa = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fp8x8_to_bf16x8(k[0], k[1]), __builtin_bit_cast(bf16x8, q[2 * i]), sa, 0, 0, 0);
+            sb = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fp8x8_to_bf16x8(k[2], k[3]), __builtin_bit_cast(bf16x8, q[2 * i + 1]), sb, 0, 0, 0);
+          }
+        }
+        // ---- what the row sees of the lane's four tokens
+        const int s16 = st + j, slot = ((s16 << 4) + 4 * jj) & (sh.P - 1);
+        const int pos = (cur[j].v.y >> 7) + slot;
+        int have = (SUB == 1 || s16 < step1) && (s16 << 4) + 4 * jj < n_slots ? (cur[j].v.y & 127) - slot : 0;
+        uint32_t vm = 0xfu;
+        if (p.qt_mask) {
+          const int shift = pos - d_base + 32;
+          const uint64_t bits = (static_cast<uint64_t>(d_mask) << 32) | 0xffffffffull;
+          vm = shift <= 0 ? 0xfu : (shift >= 64 ? 0u : static_cast<uint32_t>(bits >> shift) & 0xfu);
+        } else {
+          have = min(have, limit - pos);
+        }
+        const float c = p.scale_log2 * ks_l;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          x[j][r] = (sa[r] + sb[r]) * c;
+          x[j][r] = (r < have && ((vm >> r) & 1u)) ? x[j][r] : kNegInf;
+        }
+        mx = fmaxf(mx, fmaxf(fmaxf(x[j][0], x[j][1]), fmaxf(x[j][2], x[j][3])));
       }
+#pragma unroll
+      for (int j = 0; j < SUB; ++j) load_k(j, nxt[j], min(st + SUB + j, step1 - 1));
       // The softmax reference is the running maximum, so that no weight exceeds 1 and a sum of large
       // fp32 values overflows only where the row's own result does.
-      const float mx = fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3]));
       if (__any(mx > m)) {
         const float m_new = fmaxf(m, row_group_max(mx));
         const float alpha = fast_exp2(m - m_new);
@@ -1971,35 +1995,79 @@ __global__ __launch_bounds__(256, DP <= 128 ? 2 : 1) void spex_rowmajor_attn_ker
 #pragma unroll
         for (int i = 0; i < NO; ++i) o[i] *= alpha;
       }
-      float pr[4];
+      float pr[SUB][4];
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        pr[r] = fast_exp2(x[r] - m);
-        l += pr[r];
-        if (KV == kFP8) pr[r] *= vs_l;
-      }
+      for (int j = 0; j < SUB; ++j)
 #pragma unroll
-      for (int t = 0; t < 4; ++t)
+        for (int r = 0; r < 4; ++r) {
+          pr[j][r] = fast_exp2(x[j][r] - m);
+          l += pr[j][r];
+          if (KV == kFP8) pr[j][r] *= vs_l[j];
+        }
+      if constexpr (KV == kF32) {
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+#pragma unroll
+          for (int cc = 0; cc < NC; ++cc)
+#pragma unroll
+            for (int i = 0; i < VE; ++i)
+              o[cc * VE + i] = __builtin_amdgcn_mfma_f32_16x16x4f32(__builtin_bit_cast(float, vr[0][t][cc].w[i]), pr[0][t], o[cc * VE + i], 0, 0, 0);
+      } else {
+        // Three pieces of 8 significant bits, each cut off toward zero: together the whole fp32 weight.  A piece
+        // of nothing would turn an infinite value into NaN; 2^-40 of the weight, far below its last bit, keeps it
+        // positive.
+        u32x4 pc[3];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          float a = pr[i >> 1][(i & 1) * 2], b = pr[i >> 1][(i & 1) * 2 + 1];
+          const float ta = a * 0x1p-40f, tb = b * 0x1p-40f;
+#pragma unroll
+          for (int n = 0; n < 3; ++n) {
+            pc[n][i] = pack_hi16(a, b);
+            a = a - __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, a) & 0xffff0000u) + ta;
+            b = b - __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, b) & 0xffff0000u) + tb;
+          }
+        }
+        if (st + 1 >= step1) {  // no second group: its loads repeated tokens, which may hold infinities
+#pragma unroll
+          for (int t = 0; t < 4; ++t)
+#pragma unroll
+            for (int cc = 0; cc < NC; ++cc) vr[1][t][cc] = VReg{};
+        }
 #pragma unroll
         for (int cc = 0; cc < NC; ++cc)
 #pragma unroll
-          for (int i = 0; i < VE; ++i) {
-            float v;
-            if (KV == kF32) {
-              v = __builtin_bit_cast(float, vr[t][cc].w[i]);
-            } else if (KV == kBF16) {
-              const uint32_t wd = vr[t][cc].w[i / 2];
-              v = __builtin_bit_cast(float, (i & 1) ? wd & 0xffff0000u : wd << 16);
-            } else {
-              const int wd = static_cast<int>(vr[t][cc].w[i / 4]);
-              const f32x2 two = (i & 2) ? __builtin_amdgcn_cvt_pk_f32_fp8(wd, true) : __builtin_amdgcn_cvt_pk_f32_fp8(wd, false);
-              v = two[i & 1];
+          for (int i2 = 0; i2 < VE / 2; ++i2) {
+            // dims 2 i2 and 2 i2 + 1 of the lane's eight tokens, turned token-minor
+            uint32_t d[8];
+#pragma unroll
+            for (int t = 0; t < 8; ++t) {
+              if constexpr (KV == kBF16) {
+                d[t] = vr[t >> 2][t & 3][cc].w[i2];
+              } else {
+                const int wd = static_cast<int>(vr[t >> 2][t & 3][cc].w[i2 / 2]);
+                d[t] = __builtin_bit_cast(uint32_t, (i2 & 1) ? __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(wd, 1.0f, true)
+                                                             : __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(wd, 1.0f, false));
+              }
             }
-            o[cc * VE + i] = __builtin_amdgcn_mfma_f32_16x16x4f32(v, pr[t], o[cc * VE + i], 0, 0, 0);
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+              u32x4 v;
+#pragma unroll
+              for (int i = 0; i < 4; ++i) v[i] = __builtin_amdgcn_perm(d[2 * i + 1], d[2 * i], e ? 0x07060302u : 0x05040100u);
+              f32x4 &acc = o[cc * VE + 2 * i2 + e];
+#pragma unroll
+              for (int n = 0; n < 3; ++n)
+                acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, v), __builtin_bit_cast(bf16x8, pc[n]), acc, 0, 0, 0);
+            }
           }
-      load_v(nxt, min(st + 1, step1 - 1));
-      cur = nxt;
-      nxt = nxt2;
+      }
+#pragma unroll
+      for (int j = 0; j < SUB; ++j) {
+        load_v(j, nxt[j], min(st + SUB + j, step1 - 1));
+        cur[j] = nxt[j];
+        nxt[j] = rec_of(st + 2 * SUB + j);
+      }
     }
   }
   l += __shfl_xor(l, 16);  // the row sum is spread over the four lane groups
@@ -2686,12 +2754,19 @@ bool has_rowmajor_kernel(const Shape &sh, const AttnArgs &a) {
 template <int KV>
 static hipError_t launch_rowmajor_kv(const Shape &sh, const AttnArgs &a, const SplitLists &ls, int n_wg, hipStream_t stream) {
   const dim3 grid(n_wg), block(256);
+  const auto launch = [&](auto dp) {
+    constexpr int DP = decltype(dp)::value;
+    if (sh.D == DP)
+      hipLaunchKernelGGL((spex_rowmajor_attn_kernel<KV, DP, true>), grid, block, 0, stream, a, sh, ls);
+    else
+      hipLaunchKernelGGL((spex_rowmajor_attn_kernel<KV, DP, false>), grid, block, 0, stream, a, sh, ls);
+  };
   if (sh.D <= 64)
-    hipLaunchKernelGGL((spex_rowmajor_attn_kernel<KV, 64>), grid, block, 0, stream, a, sh, ls);
+    launch(std::integral_constant<int, 64>());
   else if (sh.D <= 128)
-    hipLaunchKernelGGL((spex_rowmajor_attn_kernel<KV, 128>), grid, block, 0, stream, a, sh, ls);
+    launch(std::integral_constant<int, 128>());
   else
-    hipLaunchKernelGGL((spex_rowmajor_attn_kernel<KV, 256>), grid, block, 0, stream, a, sh, ls);
+    launch(std::integral_constant<int, 256>());
   return hipGetLastError();
 }
 

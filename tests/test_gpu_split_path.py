@@ -83,6 +83,45 @@ def test_row_major_scores_and_values_at_the_end_of_the_range(kv, n_tokens, chunk
     t.close()
 
 
+# 16-bit and fp8 rows: tokens go through the kernel 32 at a time, two groups of 16, split between one, two or four
+# wavefronts, so counts around multiples of 16; head dims equal to a padded width and below it.  Weights are
+# fp32 and products exact: 2e-6 is four times the error of fp32 sums of this length (5e-7).  An infinite value
+# reaches every row that sees its token with a weight above 2^-86, as +-inf and not as NaN.
+@pytest.mark.parametrize("kv,dim", [("bf16", 64), ("bf16", 96), ("bf16", 128), ("bf16", 256), ("fp8_e4m3", 48), ("fp8_e4m3", 128),
+                                    ("fp8_e4m3", 256)])
+@pytest.mark.parametrize("n_tokens", [1, 15, 17, 32, 33, 48, 161, 300])
+@pytest.mark.parametrize("heads", [2, 20])
+def test_row_major_sums_keep_fp32_weights(kv, dim, n_tokens, heads):
+    import paper_2605_10195_amd as spex
+    gen = torch.Generator().manual_seed(n_tokens + dim)
+    page = 32
+    pages = -(-n_tokens // page)
+    t = spex.SpexTree(heads, 1, dim, page, "bf16", kv, num_pages=pages, device="cuda", pool_fill=255)
+    (u,) = t.fork(-1, 1)
+    k, v = (torch.randn((n_tokens, 1, dim), generator=gen) for _ in range(2))
+    scale = torch.ones((pages, 1))
+    if kv == "bf16":
+        k, v = k.to(torch.bfloat16), v.to(torch.bfloat16)
+        v[n_tokens // 2, 0, 3] = float("inf")
+        t.append_step(u, k.cuda(), v.cuda())
+    else:
+        k, v = k.to(torch.float8_e4m3fn), v.to(torch.float8_e4m3fn)
+        scale = torch.rand((pages, 1), generator=gen) + 0.5
+        t.append_step(u, k.view(torch.uint8).cuda(), v.view(torch.uint8).cuda(), scale.cuda(), scale.cuda())
+    q = torch.randn((1, heads, dim), generator=gen).to(torch.bfloat16)
+    out, lse = t.decode_attention([u], None, q.cuda(), dim ** -0.5)
+    f = scale.double().repeat_interleave(page)[:n_tokens, None]
+    kd, vd = k[:, 0].double() * f, v[:, 0].double() * f
+    s = q[0].double() @ kd.T * dim ** -0.5
+    want, got = torch.softmax(s, dim=1) @ vd, out[0].double().cpu()
+    if kv == "bf16":
+        assert bool((got[:, 3] == float("inf")).all())
+        want[:, 3] = got[:, 3] = 0.0
+    assert float((got - want).norm() / want.norm()) <= 2e-6
+    assert float((lse[0].double().cpu() - torch.logsumexp(s, dim=1)).abs().max()) <= 2e-6 * (1.0 + math.log(n_tokens))
+    t.close()
+
+
 @pytest.mark.parametrize("chunk", [64, 4, 1])
 def test_lse_of_a_row_whose_scores_overflow(chunk):
     """All scores of head 0 are -inf in fp32: its lse is -inf however many pieces and slices the merge folds;
