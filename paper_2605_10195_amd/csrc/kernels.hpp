@@ -93,7 +93,7 @@ struct AppendTokensArgs {
   float *k_scale, *v_scale;                // pool scale arrays (fp8) or null
   const void *k_src, *v_src;               // [n_nodes][Hkv][D]
   const float *k_scale_src, *v_scale_src;  // [n_nodes][Hkv] (fp8; read only for nodes that start a page)
-  const int32_t *dst;                      // 2 ints per node: {page id, slot | (page is new) << 8}
+  const int32_t *dst;                      // 2 ints per node: {page id, slot | (page is new) << 8}; pinned host memory
   int32_t n_nodes;
   // fp8 pools only: k_src / v_src hold bf16 values, which the kernel encodes with the scale of the
   // page the token lands in (k_scale_src / v_scale_src for a page it starts)
@@ -101,7 +101,7 @@ struct AppendTokensArgs {
   // Length patches of the cached plan, applied by the same launch (thread i < n_patches stores
   // patches[2 i + 1] into plan[patches[2 i]]); n_patches <= number of threads, 0 = none.
   int32_t *plan;
-  const int32_t *patches;
+  const int32_t *patches;                  // pinned host memory, behind dst
   int32_t n_patches;
 };
 

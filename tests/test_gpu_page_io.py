@@ -107,3 +107,37 @@ def test_quantised_runs_give_the_oracle_codes(heads, dim, page, runs, shift):
         assert np.array_equal(got.cpu().view(torch.uint8).numpy(), np.stack(want[j]))
         assert np.array_equal(s.cpu().numpy(), np.stack([scale[j][i // page] for i in range(at)]))
     t.close()
+
+
+@pytest.mark.parametrize("kv,dim", [("f32", 8), ("bf16", 64)])
+def test_many_appends_in_flight(kv, dim):
+    """The lists of appended tokens lie in a ring of four segments that the kernels read while the host fills the
+    next: several times round it, two streams in turn (a segment serves one stream), and a call that needs
+    longer segments in between.  A long kernel in front holds everything back until the host has gone round."""
+    import paper_2605_10195_amd as spex
+    few, many, calls, page = 200, 700, 260, 16
+    t = spex.SpexTree(1, 1, dim, page, kv, kv, num_pages=few * -(-(calls + 1) // page) + many, device="cuda", pool_fill=0xFF)
+    nodes = t.fork(-1, many)
+    g = torch.Generator(device="cuda").manual_seed(1)
+    k = torch.randn((calls + 1, many, 1, dim), generator=g, device="cuda").to(KV[kv])
+    v = torch.randn((calls + 1, many, 1, dim), generator=g, device="cuda").to(KV[kv])
+    big = torch.randn((4096, 4096), device="cuda")
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    torch.cuda.synchronize()
+    for _ in range(8):
+        big = big @ big * 1e-3
+    streams[0].wait_stream(torch.cuda.current_stream())
+    for i in range(calls + 1):
+        s = streams[0] if i < 150 else streams[i % 2]
+        for other in streams:
+            s.wait_stream(other)
+        with torch.cuda.stream(s):
+            n = many if i == 100 else few
+            t.append_tokens(nodes[:n], k[i, :n].contiguous(), v[i, :n].contiguous())
+    torch.cuda.synchronize()
+    for u in (0, 1, few - 1, few, many - 1):
+        want = (k[:, u], v[:, u]) if u < few else (k[100:101, u], v[100:101, u])
+        got_k, got_v, _, _ = t.gather_kv(nodes[u], 0, len(want[0]))
+        assert torch.equal(got_k, want[0])
+        assert_v_round_trip(got_v, want[1]) if kv == "bf16" else _same(got_v, want[1])
+    t.close()
