@@ -1796,8 +1796,6 @@ __global__ __launch_bounds__(64) void spex_generic_attn_kernel(AttnArgs p, Shape
 // Measured, fp32 P V -> bf16 pieces: 8 ragged queries of 16 branches, bf16 pages of 32 tokens, heads 32/8/128,
 // 42.3 -> 37.3 us a call; 32 queries 117 -> 101 (fp8 94 -> 75); heads 16/4/256, fp8, 140 -> 73 (two workgroups
 // a compute unit instead of one).  Error against 64 bits 2.9e-7 (3.1e-7 with the fp32 MFMA, 4.7e-7 on the vector ALU).
-// FULL: head dim DP itself, whose addresses and bounds are known when compiled (bf16, 128: 160 registers instead
-// of 186, three workgroups a compute unit instead of two: 114 -> 101 us for the 32 queries above).
 // A wavefront's K loads for the next tokens are issued right after the score MFMAs, its V loads right after the PV
 // MFMAs, page records a step ahead.
 template <int KV>
@@ -1809,14 +1807,20 @@ struct RowMajorTraits<kBF16> { static constexpr int kEsz = 2; };
 template <>
 struct RowMajorTraits<kFP8> { static constexpr int kEsz = 1; };
 
+// kRowAny: head dims below DP.  kRowFull: DP itself, whose addresses and bounds are known when compiled (bf16, 128:
+// 160 registers instead of 186, three workgroups a compute unit instead of two: 114 -> 101 us for the 32 queries
+// above).  kRowHalf: fp8 rows of a multiple of 8 bytes that is none of 16, K loaded 8 bytes at a time (heads 6/3/40,
+// 31 prompts of 14000 tokens 2935 us in the generic kernel, 74 here; 32 queries of 16 branches 342 -> 22).
+enum RowMode : int { kRowAny, kRowFull, kRowHalf };
+
 // Workgroups per compute unit: as many as the registers allow without spills.
-constexpr int rowmajor_occupancy(int kv, int dp, bool full) {
+constexpr int rowmajor_occupancy(int kv, int dp, int mode) {
   if (dp > 128) return kv == kFP8 ? 2 : 1;
-  return dp == 64 || (kv != kF32 && (full || kv == kFP8)) ? 3 : 2;
+  return dp == 64 || (kv != kF32 && (mode == kRowFull || kv == kFP8)) ? 3 : 2;
 }
 
-template <int KV, int DP, bool FULL>
-__global__ __launch_bounds__(256, rowmajor_occupancy(KV, DP, FULL)) void spex_rowmajor_attn_kernel(AttnArgs p, Shape sh, SplitLists ls) {
+template <int KV, int DP, int MODE>
+__global__ __launch_bounds__(256, rowmajor_occupancy(KV, DP, MODE)) void spex_rowmajor_attn_kernel(AttnArgs p, Shape sh, SplitLists ls) {
   constexpr int ESZ = RowMajorTraits<KV>::kEsz;
   constexpr int CH = 16 / ESZ;             // elements per 16-byte load
   constexpr int NK = DP / (4 * CH);        // K loads per lane and step
@@ -1835,7 +1839,8 @@ __global__ __launch_bounds__(256, rowmajor_occupancy(KV, DP, FULL)) void spex_ro
   const int group = at.local / at.n_items; // 64 rows each
   const Item it = load_item(at.items, at.local - group * at.n_items);
   if (it.pg_count == 0) return;            // padding item
-  const int D = FULL ? DP : sh.D, G = sh.G, rows = it.qt_count * G;
+  static_assert(MODE != kRowHalf || (KV == kFP8 && DP <= 128), "loads of V rows are 8 bytes at most");
+  const int D = MODE == kRowFull ? DP : sh.D, G = sh.G, rows = it.qt_count * G;
   const int row_end = min(rows, it.row0 + span);
   const int row_lo = it.row0 + group * 64;
   if (row_lo >= row_end) return;           // whole workgroup
@@ -1905,8 +1910,16 @@ __global__ __launch_bounds__(256, rowmajor_occupancy(KV, DP, FULL)) void spex_ro
     const char *src = kpool + (static_cast<int64_t>(r.k.x) * sh.page_tiles + it.g) * tile_bytes +
                       static_cast<int64_t>(slot) * D * ESZ;
 #pragma unroll
-    for (int i = 0; i < NK; ++i)
-      kr[j][i] = *reinterpret_cast<const u32x4 *>(src + (4 * CH * i + CH * jj < D ? 64 * i + 16 * jj : 0));
+    for (int i = 0; i < NK; ++i) {
+      const int d = 4 * CH * i + CH * jj;
+      if constexpr (MODE == kRowHalf) {
+        const u32x2 lo = *reinterpret_cast<const u32x2 *>(src + (d < D ? d : 0));
+        const u32x2 hi = *reinterpret_cast<const u32x2 *>(src + (d + 8 < D ? d + 8 : 0));
+        kr[j][i] = u32x4{lo[0], lo[1], hi[0], hi[1]};
+      } else {
+        kr[j][i] = *reinterpret_cast<const u32x4 *>(src + (d < D ? 64 * i + 16 * jj : 0));
+      }
+    }
   };
   struct VReg {
     uint32_t w[VE * ESZ / 4];
@@ -2742,9 +2755,9 @@ hipError_t launch_generic_attention(const Shape &sh, const AttnArgs &a, int rows
 }
 
 bool has_rowmajor_kernel(const Shape &sh, const AttnArgs &a) {
-  // 16-byte loads of whole rows: rows and buffers must be 16-byte aligned; four tokens of a lane
-  // must share a page.  Anything else goes to the generic kernel.
-  const int ch = sh.kv_dtype == kF32 ? 4 : (sh.kv_dtype == kBF16 ? 8 : 16);
+  // 16-byte loads of whole rows: rows and buffers must be 16-byte aligned (fp8 up to 128 dims: rows 8-byte
+  // aligned, see kRowHalf); four tokens of a lane must share a page.  Anything else goes to the generic kernel.
+  const int ch = sh.kv_dtype == kF32 ? 4 : (sh.kv_dtype == kBF16 || sh.D <= 128 ? 8 : 16);
   const bool types = sh.kv_dtype == kF32 ? sh.q_dtype == kF32 : sh.q_dtype == kBF16;
   auto aligned = [](const void *x) { return (reinterpret_cast<uintptr_t>(x) & 15) == 0; };
   return sh.layout == kRowMajor && types && sh.P >= 4 && sh.D % ch == 0 && sh.D <= 256 && aligned(a.k_pool) &&
@@ -2756,10 +2769,16 @@ static hipError_t launch_rowmajor_kv(const Shape &sh, const AttnArgs &a, const S
   const dim3 grid(n_wg), block(256);
   const auto launch = [&](auto dp) {
     constexpr int DP = decltype(dp)::value;
-    if (sh.D == DP)
-      hipLaunchKernelGGL((spex_rowmajor_attn_kernel<KV, DP, true>), grid, block, 0, stream, a, sh, ls);
-    else
-      hipLaunchKernelGGL((spex_rowmajor_attn_kernel<KV, DP, false>), grid, block, 0, stream, a, sh, ls);
+    if (sh.D == DP) {
+      hipLaunchKernelGGL((spex_rowmajor_attn_kernel<KV, DP, kRowFull>), grid, block, 0, stream, a, sh, ls);
+      return;
+    }
+    if constexpr (KV == kFP8 && DP <= 128)
+      if (sh.D % 16 != 0) {
+        hipLaunchKernelGGL((spex_rowmajor_attn_kernel<KV, DP, kRowHalf>), grid, block, 0, stream, a, sh, ls);
+        return;
+      }
+    hipLaunchKernelGGL((spex_rowmajor_attn_kernel<KV, DP, kRowAny>), grid, block, 0, stream, a, sh, ls);
   };
   if (sh.D <= 64)
     launch(std::integral_constant<int, 64>());

@@ -84,11 +84,12 @@ def test_row_major_scores_and_values_at_the_end_of_the_range(kv, n_tokens, chunk
 
 
 # 16-bit and fp8 rows: tokens go through the kernel 32 at a time, two groups of 16, split between one, two or four
-# wavefronts, so counts around multiples of 16; head dims equal to a padded width and below it.  Weights are
+# wavefronts, so counts around multiples of 16; head dims equal to a padded width and below it; fp8 rows of 8 and
+# not of 16 bytes up to 128 dims, and beyond them in the generic kernel.  Weights are
 # fp32 and products exact: 2e-6 is four times the error of fp32 sums of this length (5e-7).  An infinite value
 # reaches every row that sees its token with a weight above 2^-86, as +-inf and not as NaN.
 @pytest.mark.parametrize("kv,dim", [("bf16", 64), ("bf16", 96), ("bf16", 128), ("bf16", 256), ("fp8_e4m3", 48), ("fp8_e4m3", 128),
-                                    ("fp8_e4m3", 256)])
+                                    ("fp8_e4m3", 256), ("fp8_e4m3", 8), ("fp8_e4m3", 40), ("fp8_e4m3", 120), ("fp8_e4m3", 136)])
 @pytest.mark.parametrize("n_tokens", [1, 15, 17, 32, 33, 48, 161, 300])
 @pytest.mark.parametrize("heads", [2, 20])
 def test_row_major_sums_keep_fp32_weights(kv, dim, n_tokens, heads):
