@@ -1011,12 +1011,19 @@ __device__ __forceinline__ float sload_f(const float *base, int64_t idx) {
 }
 
 // The record of a block and, for fp8, the page scales it will need.  Workgroups whose whole
-// block list fits (kWalkRecCap blocks) copy it into LDS once, at the start, with ordinary vector
+// block list fits (walk_rec_cap blocks) copy it into LDS once, at the start, with ordinary vector
 // loads, and read records from there: a scalar load inside the loop misses the scalar cache every
 // other record and, because scalar loads return out of order, the next LDS wait of the wavefront
 // becomes a wait for that miss -- measured at ~1.4 us per block.  Longer lists fall back to the
 // scalar path, requested one or two blocks ahead.
-constexpr int kWalkRecCap = 256;
+// Eight wavefronts on a path in halves, one workgroup a compute unit: records of up to 1024 blocks (32 thousand
+// tokens; fp8 with its scales 768) besides the images.  With 256, 9 prompts of 10000 tokens took 1.5 us a step where
+// those of 3000 took 1.06 (bf16 239 -> 210 us, fp8 242 -> 150; head dim 64, 100 prompts of 12000: 228 -> 156, fp8
+// 307 -> 150).  Whole paths keep 256: two workgroups a compute unit are bound by memory, and with more records in LDS
+// 80 prompts of 12000 tokens took 830 us instead of 621.
+constexpr int walk_rec_cap(int kv, int nw, int ks) {
+  return ks == 2 && nw == 8 ? (kv == kFP8 ? 768 : 1024) : 256;
+}
 
 template <bool FP8>
 __device__ __forceinline__ WalkBlock load_walk_block(const WalkArgs &p, int idx, int g, int Hkv,
@@ -1284,8 +1291,9 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && NTW <= 2) ? 2 : 1) void spex_t
   constexpr int kTailFloats = LW * stage_floats<D>() + (KS == 2 ? LW * kFoldWaveFloats : 0);
   constexpr int kLdsFloats = 2 * KS * kImgFloats > kTailFloats ? 2 * KS * kImgFloats : kTailFloats;
   __shared__ __attribute__((aligned(16))) float lds[kLdsFloats];
-  __shared__ __attribute__((aligned(16))) int32_t rec_lds[kWalkRecCap * 8];
-  __shared__ __attribute__((aligned(16))) float scl_lds[FP8 ? kWalkRecCap * 4 : 4];
+  constexpr int kRecCap = walk_rec_cap(KV, NW, KS);
+  __shared__ __attribute__((aligned(16))) int32_t rec_lds[kRecCap * 8];
+  __shared__ __attribute__((aligned(16))) float scl_lds[FP8 ? kRecCap * 4 : 4];
   u32x4 *img = reinterpret_cast<u32x4 *>(lds);  // [buf][image][lane]
 
   const int lane = threadIdx.x & 63, m16 = lane & 15, jj = lane >> 4;
@@ -1309,7 +1317,7 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && NTW <= 2) ? 2 : 1) void spex_t
   }
   if (n_all == 0) return;  // padding item (whole workgroup)
   if (KS == 2) n_priv = (n_priv + 1 - ks) >> 1;  // private blocks ks, ks + 2, .. of the list wavefront
-  const bool rec_in_lds = n_all <= kWalkRecCap;  // uniform over the workgroup
+  const bool rec_in_lds = n_all <= kRecCap;  // uniform over the workgroup
   if (rec_in_lds) {
     const u32x4 *src = reinterpret_cast<const u32x4 *>(p.blocks + static_cast<int64_t>(blk_begin) * 8);
     for (int i = threadIdx.x; i < n_all * 2; i += 64 * NW) reinterpret_cast<u32x4 *>(rec_lds)[i] = src[i];
@@ -1465,24 +1473,34 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && NTW <= 2) ? 2 : 1) void spex_t
     // one path only would make every later wait a wait for all outstanding loads.  (PF = 4 was
     // measured for one row tile per wavefront and for fp8 with two, where the registers allow it:
     // no gain.)
+    constexpr int PFS = NTW == 1 || FP8 ? 2 : 1;
     if (KS == 2) {
       // Two blocks per barrier: step s holds blocks 2 s (lower pair of wavefronts) and 2 s + 1
-      // (upper pair); each pair stages and computes its own.  The loads of step s + 1 are in
-      // flight while step s is computed.  With an odd number of blocks the upper pair's last
-      // step only moves a copy of the last block.
+      // (upper pair); each pair stages and computes its own.  With an odd number of blocks the upper pair's last
+      // step only moves a copy of the last block.  Loads two steps ahead where the registers allow it (one row
+      // tile, or fp8): 2 to 3 % on paths of 1500 tokens and more, nothing on short ones.
       const int n_steps = (n_shared + 1) >> 1;
-      Raw x;
-      WalkBlock cur = meta(ks);
-      stage_load(x, cur);
-      stage_store(x, 0);
+      Raw x[PFS];
+      WalkBlock bmq[PFS];
+#pragma unroll
+      for (int k = 0; k < PFS; ++k) {
+        bmq[k] = meta(2 * k + ks);
+        stage_load(x[k], bmq[k]);
+      }
+      stage_store(x[0], 0);
       __syncthreads();
-      for (int st = 0; st < n_steps; ++st) {
-        const WalkBlock nxt = meta(2 * (st + 1) + ks);
-        stage_load(x, nxt);
-        if (2 * st + ks < n_shared) compute(st, cur);
-        stage_store(x, (st + 1) & 1);
-        cur = nxt;
-        __syncthreads();
+      for (int st = 0; st < n_steps; st += PFS) {
+#pragma unroll
+        for (int k = 0; k < PFS; ++k) {
+          const int c = st + k;
+          if (k > 0 && c >= n_steps) break;  // uniform; leaves the loop
+          const WalkBlock cur = bmq[k];
+          bmq[k] = meta(2 * (c + PFS) + ks);
+          stage_load(x[k], bmq[k]);
+          if (2 * c + ks < n_shared) compute(c, cur);
+          stage_store(x[(k + 1) % PFS], (c + 1) & 1);
+          __syncthreads();
+        }
       }
     }
     constexpr int PF = 2;

@@ -5,7 +5,7 @@ import pytest
 import torch
 
 import spex_workloads as sw
-from gpu_common import assert_close, assert_v_round_trip, build_gpu_tree, run_gpu, run_oracle
+from gpu_common import assert_close, assert_v_round_trip, build_gpu_tree, run_gpu, run_oracle, run_oracle_c
 
 pytestmark = pytest.mark.gpu
 
@@ -1130,3 +1130,14 @@ def roots_of_requests(wl):
             u = parent[u]
         roots.append(u)
     return roots
+
+
+# Block lists on both sides of what a workgroup keeps in LDS (halves: 1024 records, fp8 768; whole paths 256), odd and
+# even numbers of steps, one step, and a list of the last record that fits.
+@pytest.mark.parametrize("heads", [(8, 1, 128), (4, 2, 64), (24, 1, 128)])
+@pytest.mark.parametrize("kv", ["bf16", "fp8_e4m3"])
+@pytest.mark.parametrize("prompt,waves", [(20, 0), (70, 0), (100, 0), (24448, 0), (24512, 0), (32640, 0), (32704, 0), (33000, 0), (9000, 4)])
+def test_long_and_short_block_lists(heads, kv, prompt, waves):
+    wl = sw.bfs_tot(n_queries=1, prompt=prompt, step=20, width=4, keep=2, depth=1, heads=heads, kv_dtype=kv)
+    got = run_gpu(wl, kernel_mode=3, walk_waves=waves)
+    assert_close(got, run_oracle_c(wl, device="cuda"), kv, f"{heads} {kv} prompt {prompt}")
