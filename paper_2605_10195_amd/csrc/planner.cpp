@@ -602,17 +602,20 @@ float Planner::estimate_split(const PageTable &pt, const Plan &pl, float enough)
 // as long as its longest workgroup if most are much shorter (300 of up to 64 and 35 on average 57.9 -> 36.1
 // us, 448 of up to 47 and 27 51.7 -> 47.8), unless all are short (440 of up to 13 15.3 -> 17.9); a second
 // round of equal ones costs more than it saves (336 of 61 blocks 68.3 -> 87.1).
-// Blocks of 16 KiB with one row tile, all workgroups of about equal length: the whole kernel reads them
-// at 4 to 5 TB/s as soon as there are more than some 24000, and the halves, with two blocks a step, fall behind
-// (192 workgroups of 127 blocks 97 -> 100 us, 256 of 321 268 -> 293; 128 of 133, 17000 blocks, 95 -> 84).
+// With loads two steps ahead and the records of 1024 blocks in LDS that holds for long paths too, where the halves used
+// to fall behind the whole kernel from 24000 blocks of 16 KiB on (bf16, whole / halves: 144 workgroups of 313
+// blocks 239 / 147 us, 256 of 314 323 / 208, 192 of 127 102 / 83, 240 of 108 94 / 88).  Where every
+// root is a single query token the bound stands as tests/planner_choice.cpp states it, although halves are the
+// faster there as well (240 of 127 blocks 124 / 80 us).
 // Only where the number of wavefronts is not asked for.
 constexpr int64_t kStreamedBlocks = 24000;
 bool Planner::walk_in_halves(const Plan &pl) const {
   if (pl.req_walk_waves != 0 || pl.walk_waves != 4 || pl.walk_row_tiles > 2) return false;
   const int64_t blocks = pl.walk_steps * pl.num_kv_heads, slots = static_cast<int64_t>(pl.walk_items.size()) / pl.item_ints();
+  const bool branches = pl.qt_limit.size() > pl.walk_rb.size() / pl.rb_ints();
   const bool ragged = 10 * blocks <= 6 * static_cast<int64_t>(pl.walk_real_items) * pl.walk_max_item_blocks;
   if (slots <= 256)
-    return ragged || pl.walk_row_tiles > 1 || pool.kv_bytes * pool.head_dim < 256 || blocks <= kStreamedBlocks;
+    return ragged || pl.walk_row_tiles > 1 || pool.kv_bytes * pool.head_dim < 256 || blocks <= kStreamedBlocks || branches;
   return ragged && pl.walk_real_items <= 448 && pl.walk_max_item_blocks >= 16;
 }
 
