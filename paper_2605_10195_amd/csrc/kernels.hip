@@ -21,7 +21,7 @@
 //       Same contract for row-major pools (fp32 KV, other page sizes and head dims), scores and
 //       weighted sums as fp32 MFMAs.
 //   spex_generic_attn_kernel
-//       Same contract without matrix cores, for rows that are not 16-byte aligned and as a cross-check.
+//       Same contract without matrix cores, for rows that its loads do not fit and as a cross-check.
 //   spex_lse_merge_kernel
 //       Combines the partial states of every query row (log-sum-exp rule) and normalises.
 //   spex_write_tiles_kernel / spex_write_rows_kernel / spex_read_pages_kernel

@@ -27,7 +27,7 @@ int32_t clamp32(int64_t v, int32_t lo, int32_t hi) {
 // Items shorter than 16 (shared) and 8 (private) pages only while the launch has at most kFineRows
 // partial rows: beyond that a request would need more room for them than it did with those bounds,
 // and the entry point that allocates nothing has 48 MiB of it.
-// Pools that only the generic kernel serves (rows not 16-byte aligned, pages of fewer than four tokens), a
+// Pools that only the generic kernel serves (rows that the row-major kernel does not take, pages of fewer than four tokens), a
 // wavefront per item and row, have shorter items and more of them: 1024 shared and 2048 private ones, none that
 // must be longer than those 16 and 8 pages (fp8, 6 / 3 heads of 40, 16 prompts of 8000 tokens: 585 us with 256
 // and 1024, 427 with these; 16 branches on pages of 2 tokens 190 with items of 128 tokens, 92 with these).
