@@ -109,6 +109,7 @@ int main() {
   CHECK(halves_of(240, 3200, 0, 0, 4, 1, 2), "24000 blocks of 16 KiB");
   CHECK(!halves_of(240, 3240, 0, 0, 4, 1, 2), "24480 blocks of 16 KiB");
   CHECK(halves_of(240, 3240, 0, 0, 4, 1, 1) && halves_of(240, 3240, 0, 0, 4, 1, 2, 2), "24480 blocks of 8 KiB, or with two row tiles");
+  CHECK(halves_of(120, 6480, 2, 0, 4, 1, 2), "24840 blocks of 16 KiB, two branches a root");
   CHECK(halves_of(3, 600, 4 * 32, 0, 32, 2, 2, 1) && !halves_of(3, 600, 4 * 33, 0, 32, 2, 2, 1), "three roots on four pairs of XCDs");
   CHECK(halves_of(300, 20, 0, 32, 4, 1, 2) && !halves_of(300, 20, 0, 30, 4, 1, 2), "longest of 16 and of 15 blocks");
 
