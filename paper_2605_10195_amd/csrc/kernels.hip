@@ -1831,6 +1831,20 @@ struct RowMajorTraits<kFP8> { static constexpr int kEsz = 1; };
 // 31 prompts of 14000 tokens 2935 us in the generic kernel, 74 here; 32 queries of 16 branches 342 -> 22).
 enum RowMode : int { kRowAny, kRowFull, kRowHalf };
 
+// Whether a lane of the wavefront holds a weight, other than 0, below 2^-86: its pieces, or the 2^-40 of it that keeps
+// them positive, would be subnormal bf16 numbers, whose last bit is 2^-133 (weights of 2^-118 and 2^-124 then err by
+// 1e-5 and 1e-3 instead of 8e-8; below 2^-93 an infinite value gives NaN).  Few steps have one, with a score 59 below
+// the row's largest or an fp8 page scale that small, so the smallest of all is looked at first (pages of 32 tokens,
+// 16 branches: 37.5 us without the test, 37.7 with it).
+__device__ __forceinline__ bool beyond_pieces(const float (&pr)[2][4]) {
+  const float lo = fminf(fminf(fminf(pr[0][0], pr[0][1]), fminf(pr[0][2], pr[0][3])), fminf(fminf(pr[1][0], pr[1][1]), fminf(pr[1][2], pr[1][3])));
+  if (!__any(lo < 0x1p-86f)) return false;
+  uint32_t least = 0xffffffffu;  // weight 0 wraps to the top
+#pragma unroll
+  for (int i = 0; i < 8; ++i) least = min(least, __builtin_bit_cast(uint32_t, pr[i >> 2][i & 3]) - 1u);
+  return __any(least < __builtin_bit_cast(uint32_t, 0x1p-86f) - 1u);
+}
+
 // Workgroups per compute unit: as many as the registers allow without spills.
 constexpr int rowmajor_occupancy(int kv, int dp, int mode) {
   if (dp > 128) return kv == kFP8 ? 2 : 1;
@@ -2035,6 +2049,37 @@ __global__ __launch_bounds__(256, rowmajor_occupancy(KV, DP, MODE)) void spex_ro
           l += pr[j][r];
           if (KV == kFP8) pr[j][r] *= vs_l[j];
         }
+      if constexpr (SUB == 2)
+        if (st + 1 >= step1) {  // no second group: its loads repeated tokens, which may hold infinities
+#pragma unroll
+          for (int t = 0; t < 4; ++t)
+#pragma unroll
+            for (int cc = 0; cc < NC; ++cc) vr[1][t][cc] = VReg{};
+        }
+      if constexpr (SUB == 2)
+        if (beyond_pieces(pr)) {  // fp32 weights on the fp32 MFMA; nothing is left for the pieces below
+#pragma unroll
+          for (int t = 0; t < 8; ++t) {
+#pragma unroll
+            for (int cc = 0; cc < NC; ++cc) {
+              VReg &vv = vr[t >> 2][t & 3][cc];
+#pragma unroll
+              for (int i = 0; i < VE; ++i) {
+                float v;
+                if constexpr (KV == kBF16) {
+                  v = __builtin_bit_cast(float, (i & 1) ? vv.w[i / 2] & 0xffff0000u : vv.w[i / 2] << 16);
+                } else {
+                  const int wd = static_cast<int>(vv.w[i / 4]);
+                  const f32x2 two = (i & 2) ? __builtin_amdgcn_cvt_pk_f32_fp8(wd, true) : __builtin_amdgcn_cvt_pk_f32_fp8(wd, false);
+                  v = two[i & 1];
+                }
+                o[cc * VE + i] = __builtin_amdgcn_mfma_f32_16x16x4f32(v, pr[t >> 2][t & 3], o[cc * VE + i], 0, 0, 0);
+              }
+              vv = VReg{};
+            }
+            pr[t >> 2][t & 3] = 0.f;
+          }
+        }
       if constexpr (KV == kF32) {
 #pragma unroll
         for (int t = 0; t < 4; ++t)
@@ -2058,12 +2103,6 @@ __global__ __launch_bounds__(256, rowmajor_occupancy(KV, DP, MODE)) void spex_ro
             a = a - __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, a) & 0xffff0000u) + ta;
             b = b - __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, b) & 0xffff0000u) + tb;
           }
-        }
-        if (st + 1 >= step1) {  // no second group: its loads repeated tokens, which may hold infinities
-#pragma unroll
-          for (int t = 0; t < 4; ++t)
-#pragma unroll
-            for (int cc = 0; cc < NC; ++cc) vr[1][t][cc] = VReg{};
         }
 #pragma unroll
         for (int cc = 0; cc < NC; ++cc)

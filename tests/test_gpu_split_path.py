@@ -87,7 +87,7 @@ def test_row_major_scores_and_values_at_the_end_of_the_range(kv, n_tokens, chunk
 # wavefronts, so counts around multiples of 16; head dims equal to a padded width and below it; fp8 rows of 8 and
 # not of 16 bytes up to 128 dims, and beyond them in the generic kernel.  Weights are
 # fp32 and products exact: 2e-6 is four times the error of fp32 sums of this length (5e-7).  An infinite value
-# reaches every row that sees its token with a weight above 2^-86, as +-inf and not as NaN.
+# reaches every row that sees its token, as +-inf and not as NaN.
 @pytest.mark.parametrize("kv,dim", [("bf16", 64), ("bf16", 96), ("bf16", 128), ("bf16", 256), ("fp8_e4m3", 48), ("fp8_e4m3", 128),
                                     ("fp8_e4m3", 256), ("fp8_e4m3", 8), ("fp8_e4m3", 40), ("fp8_e4m3", 120), ("fp8_e4m3", 136)])
 @pytest.mark.parametrize("n_tokens", [1, 15, 17, 32, 33, 48, 161, 300])
@@ -120,6 +120,50 @@ def test_row_major_sums_keep_fp32_weights(kv, dim, n_tokens, heads):
         want[:, 3] = got[:, 3] = 0.0
     assert float((got - want).norm() / want.norm()) <= 2e-6
     assert float((lse[0].double().cpu() - torch.logsumexp(s, dim=1)).abs().max()) <= 2e-6 * (1.0 + math.log(n_tokens))
+    t.close()
+
+
+# Weights 2^-drop of the row's largest, which a token without a value has (one in every 16, so that every wavefront meets
+# it), and fp8 page scales as small: below 2^-110 a bf16 piece no longer holds a weight's last bits.  Scores are multiples
+# of 1/16 and exact in fp32, so the bound is that of the sums above.
+@pytest.mark.parametrize("kv,dim", [("bf16", 40), ("bf16", 64), ("bf16", 128), ("bf16", 256), ("fp8_e4m3", 40), ("fp8_e4m3", 64),
+                                    ("fp8_e4m3", 128), ("fp8_e4m3", 256)])
+@pytest.mark.parametrize("drop", [20, 85, 88, 112, 118, 124])
+@pytest.mark.parametrize("n_tokens", [16, 45])
+def test_row_major_weights_far_below_the_largest(kv, dim, drop, n_tokens):
+    import paper_2605_10195_amd as spex
+    gen = torch.Generator().manual_seed(drop + dim)
+    heads, page = 6, 32
+    pages = -(-n_tokens // page)
+    t = spex.SpexTree(heads, 1, dim, page, "bf16", kv, num_pages=pages, device="cuda", pool_fill=255)
+    (u,) = t.fork(-1, 1)
+    at = torch.arange(n_tokens)
+    k = torch.zeros((n_tokens, 1, dim))
+    k[at % 16 != 0, 0, 0] = -1.0
+    k[:, 0, 1] = -(at % 16) / 16.0
+    v = torch.rand((n_tokens, 1, dim), generator=gen) + 0.5
+    v[at % 16 == 0] = 0.0
+    q = torch.zeros((1, heads, dim))
+    q[0, :, 1] = 1.0
+    scale = 1.0
+    if kv == "bf16":
+        q[0, :, 0] = drop
+        k, v = k.to(torch.bfloat16), (1e36 * v).to(torch.bfloat16)
+        v[n_tokens - 1, 0, 3] = float("inf")
+        t.append_step(u, k.cuda(), v.cuda())
+    else:
+        scale = 1.3712 * 2.0 ** -drop
+        k, v = k.to(torch.float8_e4m3fn), v.to(torch.float8_e4m3fn)
+        s_v = torch.full((pages, 1), scale)
+        scale = s_v[0, 0].double()
+        t.append_step(u, k.view(torch.uint8).cuda(), v.view(torch.uint8).cuda(), torch.ones((pages, 1)).cuda(), s_v.cuda())
+    out, _ = t.decode_attention([u], None, q.to(torch.bfloat16).cuda(), math.log(2.0))
+    s = q[0].double() @ k[:, 0].double().T * math.log(2.0)
+    want, got = torch.softmax(s, dim=1) @ (v[:, 0].double() * scale), out[0].double().cpu()
+    if kv == "bf16":
+        assert bool((got[:, 3] == float("inf")).all())
+        want[:, 3] = got[:, 3] = 0.0
+    assert float((got - want).norm() / want.norm()) <= 2e-6
     t.close()
 
 
