@@ -186,6 +186,8 @@ spex_status_t spex_tree_append_step_quantize(spex_tree_t *tree, spex_node_t node
  * writes the new page lengths, query limits and started pages into them, and a decode_attention
  * call that repeats the previous request then runs without planning, upload or patch launch (it
  * reports plan state 2).  Both calls must be on the same stream, or ordered by the caller.
+ * The launch reads its lists from pinned memory of the handle when it runs, and later appends use that memory again:
+ * an append is not for recording in a HIP graph.
  */
 spex_status_t spex_tree_append_tokens(spex_tree_t *tree, const spex_node_t *nodes, int32_t n_nodes,
                                       const void *k, const void *v, const float *k_scales,

@@ -62,7 +62,7 @@ struct spex_tree {
 
   void *d_plan = nullptr;
   size_t d_plan_cap = 0;
-  // Pinned staging for host -> device copies (plans, patches, append destinations).  Two slots
+  // Pinned staging for host -> device copies (plans and their patches).  Two slots
   // used in turn: the host may fill one while the copy out of the other is still queued behind
   // earlier kernels, so it can prepare the next call while the GPU runs the current one.
   struct Stage {
@@ -74,16 +74,15 @@ struct spex_tree {
   int stage_cur = 0;
   void *h_stage = nullptr;  // the slot reserved last (stage[stage_cur].h)
   // Pinned lists that the append kernel reads where they are: one block cut into segments that are filled
-  // one after the other, many calls to a segment, so that the host may run that many calls ahead of the GPU.
+  // one after the other, several calls to a segment, so that the host may run that many calls ahead of the GPU.
   struct Ring {
-    static constexpr int kSegments = 4;
+    static constexpr int kSegments = 4, kCalls = 16;  // calls to a segment: at most kCalls
     char *base = nullptr;
     size_t seg_bytes = 0, used = 0;  // bytes of the current segment that calls have taken
     int cur = 0;
     struct Segment {
-      hipEvent_t event = nullptr;  // behind the last kernel that reads the segment
-      hipStream_t stream = nullptr;
-      bool pending = false;
+      hipEvent_t event[kCalls] = {};  // one behind each call's kernel, made when first needed
+      int calls = 0;                  // calls whose lists lie in the segment
     } seg[kSegments];
   } ring;
 
@@ -283,17 +282,26 @@ spex_status_t stage_send(spex_tree *t, void *dst, size_t bytes, hipStream_t stre
   return SPEX_OK;
 }
 
-// Room for up to `bytes` in the ring.  A segment serves one stream, whose last event then covers all its calls.
+// Waits until no kernel reads the segment's lists any more.
+spex_status_t ring_wait(spex_tree::Ring::Segment &s) {
+  for (int i = 0; i < s.calls; ++i) HIP_TRY(hipEventSynchronize(s.event[i]));
+  s.calls = 0;
+  return SPEX_OK;
+}
+
+// Room for up to `bytes` in the ring.  Every call has an event of its own: a later call's event covers the
+// earlier ones only on the same stream, and a handle does not tell streams apart (hipStreamPerThread is one value
+// for all threads' streams, the handle of a destroyed stream may be given out again).
 // Read in place the lists cost the kernel 0.8 us (4.4 -> 5.2, 128 nodes); a copy to the device in front of it took
 // a launch of 2 to 4 us and the gaps around it, and with two staging slots the host was at most two calls ahead of
 // the GPU, which then ran dry while the host forked and pruned (128 branches, 16 tokens: 1063 -> 790 us).
-spex_status_t ring_reserve(spex_tree *t, size_t bytes, hipStream_t stream, int32_t **out) {
+spex_status_t ring_reserve(spex_tree *t, size_t bytes, int32_t **out) {
   spex_tree::Ring &r = t->ring;
   bytes = align_up(bytes, 64);
   if (bytes > r.seg_bytes) {
     for (spex_tree::Ring::Segment &s : r.seg) {
-      if (s.pending) HIP_TRY(hipEventSynchronize(s.event));
-      s.pending = false;
+      const spex_status_t ws = ring_wait(s);
+      if (ws != SPEX_OK) return ws;
     }
     if (r.base) HIP_TRY(hipHostFree(r.base));
     r.base = nullptr;
@@ -304,15 +312,15 @@ spex_status_t ring_reserve(spex_tree *t, size_t bytes, hipStream_t stream, int32
     r.base = static_cast<char *>(h);
     r.seg_bytes = seg;
   }
-  spex_tree::Ring::Segment *s = &r.seg[r.cur];
-  if (r.used + bytes > r.seg_bytes || (r.used > 0 && s->stream != stream)) {
-    r.cur = (r.cur + 1) % spex_tree::Ring::kSegments;
+  if (r.used + bytes > r.seg_bytes || r.seg[r.cur].calls == spex_tree::Ring::kCalls) {
+    const int next = (r.cur + 1) % spex_tree::Ring::kSegments;
+    const spex_status_t ws = ring_wait(r.seg[next]);
+    if (ws != SPEX_OK) return ws;
+    r.cur = next;
     r.used = 0;
-    s = &r.seg[r.cur];
-    if (s->pending) HIP_TRY(hipEventSynchronize(s->event));
-    s->pending = false;
   }
-  s->stream = stream;
+  spex_tree::Ring::Segment &s = r.seg[r.cur];
+  if (!s.event[s.calls]) HIP_TRY(hipEventCreateWithFlags(&s.event[s.calls], hipEventDisableTiming));
   *out = reinterpret_cast<int32_t *>(r.base + static_cast<size_t>(r.cur) * r.seg_bytes + r.used);
   return SPEX_OK;
 }
@@ -321,10 +329,12 @@ spex_status_t ring_reserve(spex_tree *t, size_t bytes, hipStream_t stream, int32
 spex_status_t ring_commit(spex_tree *t, size_t bytes, hipStream_t stream) {
   spex_tree::Ring &r = t->ring;
   spex_tree::Ring::Segment &s = r.seg[r.cur];
+  if (hip_failed(hipEventRecord(s.event[s.calls], stream), "hipEventRecord")) {
+    (void)hipStreamSynchronize(stream);  // nothing else will tell when the kernel has read its lists
+    return SPEX_ERR_DEVICE;
+  }
   r.used += align_up(bytes, 64);
-  if (!s.event) HIP_TRY(hipEventCreateWithFlags(&s.event, hipEventDisableTiming));
-  HIP_TRY(hipEventRecord(s.event, stream));
-  s.pending = true;
+  ++s.calls;
   return SPEX_OK;
 }
 
@@ -543,7 +553,8 @@ void spex_tree_destroy(spex_tree_t *t) {
   }
   if (t->ring.base) (void)hipHostFree(t->ring.base);
   for (spex_tree::Ring::Segment &s : t->ring.seg)
-    if (s.event) (void)hipEventDestroy(s.event);
+    for (hipEvent_t e : s.event)
+      if (e) (void)hipEventDestroy(e);
   for (auto &slot : t->prof)
     for (hipEvent_t e : slot.ev)
       if (e) (void)hipEventDestroy(e);
@@ -668,7 +679,7 @@ static spex_status_t append_tokens_impl(spex_tree_t *t, const spex_node_t *nodes
   const size_t bytes_max = (dst_ints + 2 * patch_room) * sizeof(int32_t);
   int32_t *h = nullptr;
   if (k) {
-    const spex_status_t rs = ring_reserve(t, bytes_max, stream, &h);
+    const spex_status_t rs = ring_reserve(t, bytes_max, &h);
     if (rs != SPEX_OK) return rs;
   }
   for (int32_t i = 0; i < n_nodes; ++i) {

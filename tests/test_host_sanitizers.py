@@ -68,3 +68,20 @@ def test_planner_choices_under_sanitizers(tmp_path):
     run = subprocess.run([exe], capture_output=True, text=True, timeout=600)
     assert run.returncode == 0, (run.stdout[-2000:], run.stderr[-4000:])
     assert run.stdout == "ok\n", run.stdout
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
+def test_append_lists_in_flight_under_sanitizers(tmp_path):
+    """append_tokens with the HIP runtime and the launches replaced by the test's own: no list changes, and none is
+    given back, before its launch has run, whatever streams the handles stand for."""
+    include = "/opt/rocm/include"
+    if not os.path.exists(os.path.join(include, "hip", "hip_runtime.h")):
+        pytest.skip("needs the HIP headers")
+    exe = str(tmp_path / "append_ring")
+    # what hipcc defines for device code, as the host compiler may read it
+    flags = ["-D__HIP_PLATFORM_AMD__", "-I" + include, "-D__align__(n)=__attribute__((aligned(n)))", "-DHIP_SYMBOL(x)=(&x)"]
+    build_with_sanitizers(exe, flags + [os.path.join(HERE, "append_ring.cpp")] +
+                          [os.path.join(CSRC, f) for f in ("api.cpp", "planner.cpp", "page_table.cpp", "sched.cpp")])
+    run = subprocess.run([exe], capture_output=True, text=True, timeout=600)
+    assert run.returncode == 0, (run.stdout[-2000:], run.stderr[-4000:])
+    assert run.stdout == "ok\n", run.stdout
