@@ -172,6 +172,17 @@ def test_error_paths_leave_the_tree_unchanged():
         spex.SpexTree(8, 2, 64, 16, "bf16", "bf16", num_pages=4, host_only=True, free_order=[0, 1, 1, 3])
 
 
+@pytest.mark.parametrize("count", [1.0, np.float64(1.0), True, np.ones(1), 2.0, None, "1"])
+def test_fork_takes_whole_numbers_only(count):
+    t = spex.SpexTree(2, 1, 64, 16, "bf16", "bf16", num_pages=4, host_only=True)
+    with pytest.raises((TypeError, ValueError, ctypes.ArgumentError)):
+        t.fork(-1, count)
+    assert t.fork(-1, 1) == [0] and t.fork(0, np.int64(1)) == [1] and t.fork(-1, 0) == []
+    with pytest.raises(spex.SpexError):
+        t.fork(-1, -1)
+    t.close()
+
+
 def test_plan_is_cached_until_the_tree_changes():
     wl = sw.bfs_tot(n_queries=1, prompt=32, step=16)
     t = host_tree(wl, wl.peak_pages() + 2)
