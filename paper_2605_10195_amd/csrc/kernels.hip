@@ -1886,6 +1886,7 @@ __global__ __launch_bounds__(256, rowmajor_occupancy(KV, DP, MODE)) void spex_ro
   const int n_slots = it.pg_count << logp;
   const int n_steps = (n_slots + 15) >> 4;
   const int step0 = (n_steps * ks) >> ks_log, step1 = (n_steps * (ks + 1)) >> ks_log;
+  const int slot_end = min(n_slots, step1 << 4);
 
   // ---- rows
   const int row = row_base + m16;
@@ -2011,7 +2012,7 @@ __global__ __launch_bounds__(256, rowmajor_occupancy(KV, DP, MODE)) void spex_ro
         // ---- what the row sees of the lane's four tokens
         const int s16 = st + j, slot = ((s16 << 4) + 4 * jj) & (sh.P - 1);
         const int pos = (cur[j].v.y >> 7) + slot;
-        int have = (SUB == 1 || s16 < step1) && (s16 << 4) + 4 * jj < n_slots ? (cur[j].v.y & 127) - slot : 0;
+        int have = (s16 << 4) + 4 * jj < slot_end ? (cur[j].v.y & 127) - slot : 0;
         uint32_t vm = 0xfu;
         if (p.qt_mask) {
           const int shift = pos - d_base + 32;
@@ -2049,13 +2050,17 @@ __global__ __launch_bounds__(256, rowmajor_occupancy(KV, DP, MODE)) void spex_ro
           l += pr[j][r];
           if (KV == kFP8) pr[j][r] *= vs_l[j];
         }
-      if constexpr (SUB == 2)
-        if (st + 1 >= step1) {  // no second group: its loads repeated tokens, which may hold infinities
+      // Loads past the item's pages (of 4 and 8 tokens) or the wavefront's last group repeated tokens, which may hold
+      // infinities: their weight is 0, so their values must be 0 as well.
+      if (((st + SUB) << 4) > slot_end) {
 #pragma unroll
-          for (int t = 0; t < 4; ++t)
+        for (int j = 0; j < SUB; ++j)
+          if (((st + j) << 4) + 4 * jj >= slot_end)
 #pragma unroll
-            for (int cc = 0; cc < NC; ++cc) vr[1][t][cc] = VReg{};
-        }
+            for (int t = 0; t < 4; ++t)
+#pragma unroll
+              for (int cc = 0; cc < NC; ++cc) vr[j][t][cc] = VReg{};
+      }
       if constexpr (SUB == 2)
         if (beyond_pieces(pr)) {  // fp32 weights on the fp32 MFMA; nothing is left for the pieces below
 #pragma unroll

@@ -167,6 +167,33 @@ def test_row_major_weights_far_below_the_largest(kv, dim, drop, n_tokens):
     t.close()
 
 
+# Pages of 4 and 8 tokens: a group of 16 tokens may reach past an item's pages, where the kernel reads tokens of the last
+# page again.  An infinite value there, visible to every row, gives +-inf; a repetition of it under weight 0 would give NaN.
+@pytest.mark.parametrize("kv", ["f32", "bf16"])
+@pytest.mark.parametrize("page", [4, 8, 16])
+@pytest.mark.parametrize("n_tokens", [1, 4, 9, 12, 20, 24, 40, 44, 100])
+@pytest.mark.parametrize("chunk", [0, 3])
+def test_row_major_infinite_value_in_the_last_page(kv, page, n_tokens, chunk):
+    import paper_2605_10195_amd as spex
+    dt, dim = (torch.float32 if kv == "f32" else torch.bfloat16), 40
+    gen = torch.Generator().manual_seed(n_tokens)
+    t = spex.SpexTree(3, 1, dim, page, kv, kv, num_pages=-(-n_tokens // page), device="cuda", pool_fill=255, prefix_chunk_pages=chunk,
+                      suffix_chunk_pages=chunk)
+    (u,) = t.fork(-1, 1)
+    k, v = (torch.randn((n_tokens, 1, dim), generator=gen).to(dt) for _ in range(2))
+    v[n_tokens - 1, 0, 3] = float("inf")
+    v[(n_tokens - 1) // page * page, 0, 5] = float("-inf")
+    t.append_step(u, k.cuda(), v.cuda())
+    q = torch.randn((1, 3, dim), generator=gen).to(dt)
+    got = t.decode_attention([u], None, q.cuda(), dim ** -0.5)[0][0].double().cpu()
+    assert bool((got[:, 3] == float("inf")).all()) and bool((got[:, 5] == float("-inf")).all())
+    v[:, 0, 3] = v[:, 0, 5] = 0.0
+    got[:, 3] = got[:, 5] = 0.0
+    want = torch.softmax(q[0].double() @ k[:, 0].double().T * dim ** -0.5, dim=1) @ v[:, 0].double()
+    assert float((got - want).norm() / want.norm()) <= 2e-6   # fp32 weights and sums, as above
+    t.close()
+
+
 @pytest.mark.parametrize("chunk", [64, 4, 1])
 def test_lse_of_a_row_whose_scores_overflow(chunk):
     """All scores of head 0 are -inf in fp32: its lse is -inf however many pieces and slices the merge folds;
