@@ -110,34 +110,50 @@ def test_quantised_runs_give_the_oracle_codes(heads, dim, page, runs, shift):
 
 
 @pytest.mark.parametrize("kv,dim", [("f32", 8), ("bf16", 64)])
-def test_many_appends_in_flight(kv, dim):
-    """The lists of appended tokens lie in a ring of four segments that the kernels read while the host fills the
-    next: several times round it, two streams in turn (a segment serves one stream), and a call that needs
-    longer segments in between.  A long kernel in front holds everything back until the host has gone round."""
+@pytest.mark.parametrize("phase", ["round and round", "longer lists", "two streams"])
+def test_many_appends_in_flight(kv, dim, phase):
+    """The lists of appended tokens lie in a ring of four segments of 16 calls that the kernels read while the host fills
+    the next.  Behind a long kernel nothing runs until the host has gone round once; then it goes round four times more,
+    or asks for longer segments while the lists of 16 calls wait, or takes two streams in turn."""
     import paper_2605_10195_amd as spex
-    few, many, calls, page = 200, 700, 260, 16
-    t = spex.SpexTree(1, 1, dim, page, kv, kv, num_pages=few * -(-(calls + 1) // page) + many, device="cuda", pool_fill=0xFF)
+    few, many, ring, page = 200, 700, 4 * 16, 16
+    calls = 5 * ring
+    t = spex.SpexTree(1, 1, dim, page, kv, kv, num_pages=few * -(-(calls + 2) // page) + many, device="cuda", pool_fill=0xFF)
     nodes = t.fork(-1, many)
     g = torch.Generator(device="cuda").manual_seed(1)
     k = torch.randn((calls + 1, many, 1, dim), generator=g, device="cuda").to(KV[kv])
     v = torch.randn((calls + 1, many, 1, dim), generator=g, device="cuda").to(KV[kv])
-    big = torch.randn((4096, 4096), device="cuda")
     streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    big = torch.randn((4096, 4096), device="cuda")
+    big = big @ big * 1e-3                                    # loads the library before anything waits behind it
+    at = {u: [] for u in range(many)}                         # tokens of every node, by the call that wrote them
+
+    def append(i, n):
+        t.append_tokens(nodes[:n], k[i, :n].contiguous(), v[i, :n].contiguous())
+        for u in range(n):
+            at[u].append(i)
+
+    append(0, few)                                            # makes the ring
     torch.cuda.synchronize()
-    for _ in range(8):
-        big = big @ big * 1e-3
-    streams[0].wait_stream(torch.cuda.current_stream())
-    for i in range(calls + 1):
-        s = streams[0] if i < 150 else streams[i % 2]
+    with torch.cuda.stream(streams[0]):
+        for _ in range(32):
+            big = big @ big * 1e-3
+        done = torch.cuda.Event()
+        done.record()
+    grow_at = 16 if phase == "longer lists" else calls + 1
+    for i in range(1, calls + 1):
+        if i == min(ring, grow_at):
+            assert not done.query(), "the kernel in front ended before the ring was full"
+        s = streams[i % 2 if phase == "two streams" else 0]
         for other in streams:
             s.wait_stream(other)
         with torch.cuda.stream(s):
-            n = many if i == 100 else few
-            t.append_tokens(nodes[:n], k[i, :n].contiguous(), v[i, :n].contiguous())
+            append(i, many if i == grow_at else few)
     torch.cuda.synchronize()
     for u in (0, 1, few - 1, few, many - 1):
-        want = (k[:, u], v[:, u]) if u < few else (k[100:101, u], v[100:101, u])
-        got_k, got_v, _, _ = t.gather_kv(nodes[u], 0, len(want[0]))
-        assert torch.equal(got_k, want[0])
-        assert_v_round_trip(got_v, want[1]) if kv == "bf16" else _same(got_v, want[1])
+        if not at[u]:
+            continue
+        got_k, got_v, _, _ = t.gather_kv(nodes[u], 0, len(at[u]))
+        assert torch.equal(got_k, k[at[u], u])
+        assert_v_round_trip(got_v, v[at[u], u]) if kv == "bf16" else _same(got_v, v[at[u], u])
     t.close()

@@ -1132,12 +1132,21 @@ def roots_of_requests(wl):
     return roots
 
 
-# Block lists on both sides of what a workgroup keeps in LDS (halves: 1024 records, fp8 768; whole paths 256), odd and
-# even numbers of steps, one step, and a list of the last record that fits.
-@pytest.mark.parametrize("heads", [(8, 1, 128), (4, 2, 64), (24, 1, 128)])
+# Record lists on both sides of what a workgroup keeps in LDS (halves: 1024 records, fp8 768; whole paths, four wavefronts
+# asked for: 256) and between; 1, 3, 4, 5 and 6 blocks, hence odd and even numbers of steps.  The prompt is one block
+# list: shared where the branches' rows take several wavefronts, private where one holds them all (heads 4/2/64).  A root of
+# four branches here has 12 records besides: the branches' own blocks and room to grow.
+@pytest.mark.parametrize("heads,shared", [((8, 1, 128), True), ((4, 2, 64), False), ((24, 2, 64), True), ((24, 1, 128), True)])
 @pytest.mark.parametrize("kv", ["bf16", "fp8_e4m3"])
-@pytest.mark.parametrize("prompt,waves", [(20, 0), (70, 0), (100, 0), (24448, 0), (24512, 0), (32640, 0), (32704, 0), (33000, 0), (9000, 4)])
-def test_long_and_short_block_lists(heads, kv, prompt, waves):
-    wl = sw.bfs_tot(n_queries=1, prompt=prompt, step=20, width=4, keep=2, depth=1, heads=heads, kv_dtype=kv)
-    got = run_gpu(wl, kernel_mode=3, walk_waves=waves)
-    assert_close(got, run_oracle_c(wl, device="cuda"), kv, f"{heads} {kv} prompt {prompt}")
+@pytest.mark.parametrize("records,waves", [(13, 0), (15, 0), (16, 0), (17, 0), (18, 0), (256, 0), (257, 0), (401, 0), (768, 0), (769, 0), (1024, 0),
+                                           (1025, 0), (256, 4), (257, 4)])
+def test_long_and_short_block_lists(heads, shared, kv, records, waves):
+    wl = sw.bfs_tot(n_queries=1, prompt=32 * (records - 12), step=20, width=4, keep=2, depth=1, heads=heads, kv_dtype=kv)
+    tree = build_gpu_tree(wl, kernel_mode=3, walk_waves=waves)
+    lists = tree.walk_dump(wl.leaves, wl.q_lens)
+    assert lists["waves"] == 4
+    kv_head, first, n_shared, *own = lists["items"][:7]
+    assert n_shared + sum(x >> 16 for x in own) == records and n_shared == (records - 12 if shared else 0)
+    got = run_gpu(wl, tree)
+    assert_close(got, run_oracle_c(wl, device="cuda"), kv, f"{heads} {kv} {records} records")
+    tree.close()

@@ -29,13 +29,15 @@ def test_merge_of_many_and_few_pieces(heads, kv_dtype, chunk, prompt):
 
 # Row-major pools: every type; head dims at and between the padded widths 64, 128 and 256; pages of 4
 # to 64 tokens (a 16-token step spans pages, or a page several steps); 1 to 140 rows per item (one,
-# two, four wavefronts per row tile, several groups of 64 rows); drafts with masks; and shapes whose
-# rows are not 16-byte aligned or whose pages hold fewer than four tokens (the generic kernel).
+# two, four wavefronts per row tile, several groups of 64 rows); drafts with masks; fp8 rows of 8 and not of
+# 16 bytes (heads of 24 and 40); and shapes whose rows are not 16-byte (fp8 8-byte) aligned or whose pages hold fewer
+# than four tokens (the generic kernel: bf16 heads of 20, fp8 heads of 20 and 136, pages of two).
 @pytest.mark.parametrize("heads,kv_dtype,page", [
     ((4, 2, 64), "f32", 16), ((4, 1, 128), "f32", 32), ((6, 3, 36), "f32", 4), ((2, 1, 256), "f32", 8), ((2, 2, 132), "f32", 16),
     ((6, 3, 40), "bf16", 16), ((8, 2, 128), "bf16", 32), ((8, 2, 128), "bf16", 4), ((28, 4, 96), "bf16", 64), ((4, 2, 256), "bf16", 16),
     ((8, 2, 64), "bf16", 8), ((10, 2, 128), "fp8_e4m3", 32), ((8, 4, 48), "fp8_e4m3", 16), ((4, 1, 256), "fp8_e4m3", 4),
-    ((4, 2, 64), "fp8_e4m3", 64), ((6, 3, 20), "bf16", 16), ((4, 2, 64), "bf16", 2), ((4, 2, 24), "fp8_e4m3", 16)])
+    ((4, 2, 64), "fp8_e4m3", 64), ((6, 3, 20), "bf16", 16), ((4, 2, 64), "bf16", 2), ((4, 2, 24), "fp8_e4m3", 16),
+    ((6, 3, 40), "fp8_e4m3", 4), ((4, 2, 20), "fp8_e4m3", 16), ((4, 2, 136), "fp8_e4m3", 16)])
 @pytest.mark.parametrize("q_len,drafts", [(1, False), (5, False), (7, True)])
 def test_row_major_pools(heads, kv_dtype, page, q_len, drafts):
     wl = sw.tot_with_drafts(n_queries=2, prompt=75, step=19, depth=2, drafts=q_len, heads=heads, kv_dtype=kv_dtype,
@@ -84,18 +86,18 @@ def test_row_major_scores_and_values_at_the_end_of_the_range(kv, n_tokens, chunk
 
 
 # 16-bit and fp8 rows: tokens go through the kernel 32 at a time, two groups of 16, split between one, two or four
-# wavefronts, so counts around multiples of 16; head dims equal to a padded width and below it; fp8 rows of 8 and
-# not of 16 bytes up to 128 dims, and beyond them in the generic kernel.  Weights are
-# fp32 and products exact: 2e-6 is four times the error of fp32 sums of this length (5e-7).  An infinite value
-# reaches every row that sees its token, as +-inf and not as NaN.
+# wavefronts, so counts around multiples of 16; pages that hold a step and pages of four tokens; head dims equal to a
+# padded width and below it; fp8 rows of 8 and not of 16 bytes up to 128 dims, and beyond them in the generic kernel.
+# Weights are fp32 and products exact: 2e-6 is four times the error of fp32 sums of this length (5e-7).  An infinite
+# value reaches every row that sees its token, as +-inf and not as NaN.
 @pytest.mark.parametrize("kv,dim", [("bf16", 64), ("bf16", 96), ("bf16", 128), ("bf16", 256), ("fp8_e4m3", 48), ("fp8_e4m3", 128),
                                     ("fp8_e4m3", 256), ("fp8_e4m3", 8), ("fp8_e4m3", 40), ("fp8_e4m3", 120), ("fp8_e4m3", 136)])
 @pytest.mark.parametrize("n_tokens", [1, 15, 17, 32, 33, 48, 161, 300])
 @pytest.mark.parametrize("heads", [2, 20])
-def test_row_major_sums_keep_fp32_weights(kv, dim, n_tokens, heads):
+@pytest.mark.parametrize("page", [32, 4])
+def test_row_major_sums_keep_fp32_weights(kv, dim, n_tokens, heads, page):
     import paper_2605_10195_amd as spex
     gen = torch.Generator().manual_seed(n_tokens + dim)
-    page = 32
     pages = -(-n_tokens // page)
     t = spex.SpexTree(heads, 1, dim, page, "bf16", kv, num_pages=pages, device="cuda", pool_fill=255)
     (u,) = t.fork(-1, 1)
