@@ -18,8 +18,8 @@
 //       The same items in launches of their own, few rows (a wavefront an item) and many, where there
 //       are items enough; private items come last and finish the rows of suffixes in one piece.
 //   spex_rowmajor_attn_kernel
-//       Same contract for row-major pools (fp32 KV, other page sizes and head dims), scores and
-//       weighted sums as fp32 MFMAs.
+//       Same contract for row-major pools (fp32 KV, other page sizes and head dims): fp32 pools on the fp32
+//       MFMA, 16-bit and fp8 ones on the bf16 MFMA with weights in three pieces.
 //   spex_generic_attn_kernel
 //       Same contract without matrix cores, for rows that its loads do not fit and as a cross-check.
 //   spex_lse_merge_kernel

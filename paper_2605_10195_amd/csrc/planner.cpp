@@ -106,7 +106,8 @@ struct Segment {
 // Longest tree-walk workgroup (in two-page blocks) up to which a launch of `items` workgroups
 // (< 128) still goes to the tree-walk kernel.  Crossing points measured with four wavefronts to a workgroup (bf16,
 // 32 / 8 heads of 128): 20 blocks at 8 to 32 workgroups, 40 at 64, 65 at 96.  Launches this small run in
-// halves meanwhile, some 1.35 times as fast, and the split path in one launch.
+// halves meanwhile, 1.35 to 2 times as fast, and the split path in one launch: both sides are faster than when the
+// points were measured.
 int32_t short_walk_blocks(int64_t items) {
   return items <= 32 ? 20 : 20 + static_cast<int32_t>((items - 32) * 7 / 10);
 }
@@ -604,9 +605,10 @@ float Planner::estimate_split(const PageTable &pt, const Plan &pl, float enough)
 // round of equal ones costs more than it saves (336 of 61 blocks 68.3 -> 87.1).
 // With loads two steps ahead and the records of 1024 blocks in LDS that holds for long paths too, where the halves used
 // to fall behind the whole kernel from 24000 blocks of 16 KiB on (bf16, whole / halves: 144 workgroups of 313
-// blocks 239 / 147 us, 256 of 314 323 / 208, 192 of 127 102 / 83, 240 of 108 94 / 88).  Where every
-// root is a single query token the bound stands as tests/planner_choice.cpp states it, although halves are the
-// faster there as well (240 of 127 blocks 124 / 80 us).
+// blocks 239 / 147 us, 256 of 314 323 / 208, 192 of 127 102 / 83, 240 of 108 94 / 88), and beyond 1024 records, whose
+// loads are scalar (two branches a root: 256 workgroups of 973 blocks 908 / 593, of 1051 968 / 641, of 1254 1175 / 765; 128 of
+// 1051 897 / 488; 64 of 3754 3185 / 1663).  Where every root is a single query token the bound stands as
+// tests/planner_choice.cpp states it, although halves are the faster there as well (240 of 127 blocks 124 / 80 us).
 // Only where the number of wavefronts is not asked for.
 constexpr int64_t kStreamedBlocks = 24000;
 bool Planner::walk_in_halves(const Plan &pl) const {
@@ -636,7 +638,8 @@ bool Planner::walk_by_tile(const Plan &pl) const {
 float Planner::estimate_walk(const Plan &pl) {
   const float longest = static_cast<float>(pl.walk_max_item_blocks);
   const float share = static_cast<float>(pl.walk_steps) * static_cast<float>(pl.num_kv_heads) / 512.f;
-  // the fit has equal workgroups of many 16 KiB blocks as halves, 8 % above what they take whole
+  // the fit has all of these as halves, those that walk_in_halves leaves whole too, and is from before halves held the
+  // records of long paths: 240 workgroups of 127 blocks 91 us, 80 as halves and 124 whole; 144 of 313 178, 147 and 239
   return pl.walk_halves || (pl.req_walk_waves == 0 && pl.walk_waves == 4 && pl.walk_row_tiles == 1 && pl.walk_real_items <= 256)
              ? 4.7f + 0.36f * longest + 0.69f * share : 4.5f + 0.63f * longest + 0.84f * share;
 }
