@@ -1826,7 +1826,7 @@ template <>
 struct RowMajorTraits<kFP8> { static constexpr int kEsz = 1; };
 
 // kRowAny: head dims below DP.  kRowFull: DP itself, whose addresses and bounds are known when compiled (bf16, 128:
-// 160 registers instead of 186, three workgroups a compute unit instead of two: 114 -> 101 us for the 32 queries
+// 161 registers instead of 182, three workgroups a compute unit instead of two: 114 -> 101 us for the 32 queries
 // above).  kRowHalf: fp8 rows of a multiple of 8 bytes that is none of 16, K loaded 8 bytes at a time (heads 6/3/40,
 // 31 prompts of 14000 tokens 2935 us in the generic kernel, 74 here; 32 queries of 16 branches 342 -> 22).
 enum RowMode : int { kRowAny, kRowFull, kRowHalf };

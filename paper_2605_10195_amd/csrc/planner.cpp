@@ -602,7 +602,8 @@ float Planner::estimate_split(const PageTable &pt, const Plan &pl, float enough)
 // up to 82 blocks 60.6 -> 45.0 us, 256 of up to 49, fp8, 54.1 -> 44.5.  With some more the launch still lasts
 // as long as its longest workgroup if most are much shorter (300 of up to 64 and 35 on average 57.9 -> 36.1
 // us, 448 of up to 47 and 27 51.7 -> 47.8), unless all are short (440 of up to 13 15.3 -> 17.9); a second
-// round of equal ones costs more than it saves (336 of 61 blocks 68.3 -> 87.1).
+// round of equal ones costs more than it saves (bf16, 336 of 77 blocks 80 -> 85 us, 336 of 142 144 -> 153, 320 of 395
+// 333 -> 416; fp8, 336 of 77 43 -> 85, 320 of 395 177 either way).
 // With loads two steps ahead and the records of 1024 blocks in LDS that holds for long paths too, where the halves used
 // to fall behind the whole kernel from 24000 blocks of 16 KiB on (bf16, whole / halves: 144 workgroups of 313
 // blocks 239 / 147 us, 256 of 314 323 / 208, 192 of 127 102 / 83, 240 of 108 94 / 88), and beyond 1024 records, whose
