@@ -292,9 +292,9 @@ spex_status_t ring_wait(spex_tree::Ring::Segment &s) {
 // Room for up to `bytes` in the ring.  Every call has an event of its own: a later call's event covers the
 // earlier ones only on the same stream, and a handle does not tell streams apart (hipStreamPerThread is one value
 // for all threads' streams, the handle of a destroyed stream may be given out again).
-// Read in place the lists cost the kernel 0.8 us (4.4 -> 5.2, 128 nodes); a copy to the device in front of it took
-// a launch of 2 to 4 us and the gaps around it, and with two staging slots the host was at most two calls ahead of
-// the GPU, which then ran dry while the host forked and pruned (128 branches, 16 tokens: 1063 -> 790 us).
+// Read in place the lists cost the kernel 1 to 2 us (128 nodes 3.6 -> 4.8, 4096 of 2 kv heads 11.4 -> 13.3); a copy to the
+// device in front of it took a launch of 2 to 4 us and the gaps around it, and with two staging slots the host was at most
+// two calls ahead of the GPU, which then ran dry while the host forked and pruned (128 branches, 16 tokens: 1063 -> 790 us).
 spex_status_t ring_reserve(spex_tree *t, size_t bytes, int32_t **out) {
   spex_tree::Ring &r = t->ring;
   bytes = align_up(bytes, 64);
