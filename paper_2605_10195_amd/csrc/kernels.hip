@@ -1886,8 +1886,9 @@ __global__ __launch_bounds__(256, rowmajor_occupancy(KV, DP, MODE)) void spex_ro
 
   const int logp = 31 - __builtin_clz(sh.P);
   const int n_slots = it.pg_count << logp;
-  const int n_steps = (n_slots + 15) >> 4;
-  const int step0 = (n_steps * ks) >> ks_log, step1 = (n_steps * (ks + 1)) >> ks_log;
+  // 16 tokens a step, SUB steps a turn of the loop; wavefronts share an item by whole turns
+  const int n_steps = (n_slots + 15) >> 4, n_turns = (n_steps + SUB - 1) / SUB;
+  const int step0 = ((n_turns * ks) >> ks_log) * SUB, step1 = min(n_steps, ((n_turns * (ks + 1)) >> ks_log) * SUB);
   const int slot_end = min(n_slots, step1 << 4);
 
   // ---- rows
@@ -1939,21 +1940,40 @@ __global__ __launch_bounds__(256, rowmajor_occupancy(KV, DP, MODE)) void spex_ro
   };
   // Dims past D (D < DP) are read from the start of the row instead, so that no load is
   // conditional: in K they meet zeros of Q, in V they make output dims that are not written.
+  // Steps past the wavefront's last one are read as well, for the same reason, but by all lanes from the first token of
+  // the last step: one cache line, and one just read, instead of 16.  An item of 76 tokens is one turn or none for a
+  // wavefront, which used to request its tokens up to four times (8 ragged queries of 16 branches, bf16 pages of 32
+  // tokens: 35.7 -> 30.3 us a call, 32 queries 131 -> 116; fp32 heads 28/4/128, 64 prompts of 1024 142 -> 137;
+  // the start of the tile instead, a line that may be no wavefront's own: 4 prompts of 12000 tokens 57.4, 52.4 so,
+  // 54.1 with whole rows repeated).
   u32x4 kr[SUB][NK];
   auto load_k = [&](int j, const Rec &r, int step) {
-    const int slot = ((step << 4) + m16) & (sh.P - 1);
-    const char *src = kpool + (static_cast<int64_t>(r.k.x) * sh.page_tiles + it.g) * tile_bytes +
-                      static_cast<int64_t>(slot) * D * ESZ;
+    const int msk = step < step1 ? -1 : 0;  // uniform
+    const int slot = ((min(step, step1 - 1) << 4) + (m16 & msk)) & (sh.P - 1), dj = MODE == kRowFull ? 0 : CH * jj & msk;
+    const char *src = kpool + (static_cast<int64_t>(r.k.x) * sh.page_tiles + it.g) * tile_bytes + (slot * D * ESZ + (MODE == kRowFull ? 16 * jj & msk : 0));
 #pragma unroll
     for (int i = 0; i < NK; ++i) {
-      const int d = 4 * CH * i + CH * jj;
+      const int d = 4 * CH * i + dj;
       if constexpr (MODE == kRowHalf) {
         const u32x2 lo = *reinterpret_cast<const u32x2 *>(src + (d < D ? d : 0));
         const u32x2 hi = *reinterpret_cast<const u32x2 *>(src + (d + 8 < D ? d + 8 : 0));
         kr[j][i] = u32x4{lo[0], lo[1], hi[0], hi[1]};
       } else {
-        kr[j][i] = *reinterpret_cast<const u32x4 *>(src + (d < D ? 64 * i + 16 * jj : 0));
+        kr[j][i] = *reinterpret_cast<const u32x4 *>(src + (MODE == kRowFull || d < D ? d * ESZ : 0));
       }
+    }
+  };
+  // Page scales of the four tokens of the lane, ahead of their keys: behind the values already on their way they
+  // would make the scores wait for those.
+  struct Scales {
+    float k, v;
+  };
+  Scales scl[SUB];
+  auto load_scales = [&](int j, const Rec &r) {
+    scl[j] = {1.f, 1.f};
+    if (KV == kFP8) {
+      const int64_t at_page = static_cast<int64_t>(r.v.x) * sh.Hkv + it.g;
+      scl[j] = {p.k_scale[at_page], p.v_scale[at_page]};
     }
   };
   struct VReg {
@@ -1964,14 +1984,14 @@ __global__ __launch_bounds__(256, rowmajor_occupancy(KV, DP, MODE)) void spex_ro
 #pragma unroll
   for (int c = 0; c < NC; ++c) v_off[c] = 16 * VE * c + VE * m16 < D ? 16 * VE * c : -VE * m16;
   auto load_v = [&](int j, const Rec &r, int step) {
-    const int slot = ((step << 4) + 4 * jj) & (sh.P - 1);
-    const char *src = vpool + (static_cast<int64_t>(r.v.x) * sh.page_tiles + it.g) * tile_bytes +
-                      (static_cast<int64_t>(slot) * D + VE * m16) * ESZ;
+    const int msk = step < step1 ? -1 : 0;
+    const int slot = ((min(step, step1 - 1) << 4) + (4 * jj & msk)) & (sh.P - 1);
+    const char *src = vpool + (static_cast<int64_t>(r.v.x) * sh.page_tiles + it.g) * tile_bytes + (slot * D + (VE * m16 & msk)) * ESZ;
 #pragma unroll
     for (int t = 0; t < 4; ++t)
 #pragma unroll
       for (int c = 0; c < NC; ++c)
-        __builtin_memcpy(&vr[j][t][c], __builtin_assume_aligned(src + (t * D + v_off[c]) * ESZ, VE * ESZ), VE * ESZ);
+        __builtin_memcpy(&vr[j][t][c], __builtin_assume_aligned(src + (t * D + (MODE == kRowFull ? 16 * VE * c : v_off[c] & msk)) * ESZ, VE * ESZ), VE * ESZ);
   };
 
   if (has_rows && step0 < step1) {
@@ -1980,6 +2000,7 @@ __global__ __launch_bounds__(256, rowmajor_occupancy(KV, DP, MODE)) void spex_ro
     for (int j = 0; j < SUB; ++j) {
       cur[j] = rec_of(step0 + j);
       nxt[j] = rec_of(step0 + SUB + j);
+      load_scales(j, cur[j]);
       load_k(j, cur[j], step0 + j);
       load_v(j, cur[j], step0 + j);
     }
@@ -1987,12 +2008,7 @@ __global__ __launch_bounds__(256, rowmajor_occupancy(KV, DP, MODE)) void spex_ro
       float x[SUB][4], vs_l[SUB], mx = kNegInf;
 #pragma unroll
       for (int j = 0; j < SUB; ++j) {
-        float ks_l = 1.f;
-        vs_l[j] = 1.f;
-        if (KV == kFP8) {
-          ks_l = p.k_scale[static_cast<int64_t>(cur[j].v.x) * sh.Hkv + it.g];
-          vs_l[j] = p.v_scale[static_cast<int64_t>(cur[j].v.x) * sh.Hkv + it.g];
-        }
+        vs_l[j] = scl[j].v;
         f32x4 sa = {0.f, 0.f, 0.f, 0.f}, sb = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int i = 0; i < NK; ++i) {
@@ -2023,7 +2039,7 @@ __global__ __launch_bounds__(256, rowmajor_occupancy(KV, DP, MODE)) void spex_ro
         } else {
           have = min(have, limit - pos);
         }
-        const float c = p.scale_log2 * ks_l;
+        const float c = p.scale_log2 * scl[j].k;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
           x[j][r] = (sa[r] + sb[r]) * c;
@@ -2032,7 +2048,10 @@ __global__ __launch_bounds__(256, rowmajor_occupancy(KV, DP, MODE)) void spex_ro
         mx = fmaxf(mx, fmaxf(fmaxf(x[j][0], x[j][1]), fmaxf(x[j][2], x[j][3])));
       }
 #pragma unroll
-      for (int j = 0; j < SUB; ++j) load_k(j, nxt[j], min(st + SUB + j, step1 - 1));
+      for (int j = 0; j < SUB; ++j) {
+        load_scales(j, nxt[j]);
+        load_k(j, nxt[j], st + SUB + j);
+      }
       // The softmax reference is the running maximum, so that no weight exceeds 1 and a sum of large
       // fp32 values overflows only where the row's own result does.
       if (__any(mx > m)) {
@@ -2141,7 +2160,7 @@ __global__ __launch_bounds__(256, rowmajor_occupancy(KV, DP, MODE)) void spex_ro
       }
 #pragma unroll
       for (int j = 0; j < SUB; ++j) {
-        load_v(j, nxt[j], min(st + SUB + j, step1 - 1));
+        load_v(j, nxt[j], st + SUB + j);
         cur[j] = nxt[j];
         nxt[j] = rec_of(st + 2 * SUB + j);
       }
