@@ -879,6 +879,7 @@ static spex_status_t decode_attention_impl(spex_tree_t *t, const spex_node_t *le
     wa.lse = lse;
     wa.scale_log2 = sm_scale * 1.4426950408889634f;
     wa.qt_mask = dp.qt_mask;
+    wa.cut = pl.walk_cut;
     HIP_TRY(bracket(3, true));
     HIP_TRY(spex::launch_tree_walk(t->shape, wa, pl.walk_row_tiles, pl.walk_waves, pl.walk_halves,
                                    pl.walk_by_tile, stream));

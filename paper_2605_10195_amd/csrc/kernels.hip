@@ -1264,7 +1264,13 @@ __device__ __forceinline__ void walk_write_rows(float *out, float *lse, const Sh
 // blocks alternate likewise -- and at the end the upper pair hands its softmax state to the lower
 // one through LDS.  Per block a wavefront then works on twice the rows, so half as many operand
 // images cross the LDS per row, and a row block's longest path takes half as many steps.
-template <int KV, int D, int NTW, int NW, bool TREE, int KS = 1, bool BY_TILE = false>
+//
+// CUT: for requests of more rows than a row block holds, whose first row blocks see nothing of the request's last
+// tokens: blocks at the end of the lists that none of the workgroup's rows sees are left out (128 queries of 4 heads, four
+// row blocks on paths of 36 blocks: 1.5 blocks on average, 1505 -> 1477 us; 256 queries on a prompt of 100: 401 -> 380).
+// A kernel of its own, because the test alone, where nothing can be left out, made short launches slower (512
+// workgroups of 1 to 3 blocks 15.9 -> 16.4 us).
+template <int KV, int D, int NTW, int NW, bool TREE, int KS = 1, bool BY_TILE = false, bool CUT = false>
 __global__ __launch_bounds__(64 * NW, (NW == 4 && NTW <= 2) ? 2 : 1) void spex_tree_walk_kernel(WalkArgs p, Shape sh) {
   constexpr bool FP8 = KV == kFP8;
   constexpr int ESZ = FP8 ? 1 : 2;
@@ -1301,7 +1307,7 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && NTW <= 2) ? 2 : 1) void spex_t
   const int64_t ir = static_cast<int64_t>(blockIdx.x) * kItemInts;
   const int g = sload(p.items, ir + 0);
   const int blk_begin = sload(p.items, ir + 1);
-  const int n_shared = sload(p.items, ir + 2);
+  int n_shared = sload(p.items, ir + 2);
   // per wavefront: private blocks | room << 16; a wavefront's records are followed by the unused
   // part of its room, so n_all spans records that no wavefront walks
   const int rw = KS == 1 ? w : w % LW;  // the list wavefront whose rows this wavefront holds
@@ -1316,7 +1322,6 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && NTW <= 2) ? 2 : 1) void spex_t
     priv_begin += v < rw ? room : 0;
   }
   if (n_all == 0) return;  // padding item (whole workgroup)
-  if (KS == 2) n_priv = (n_priv + 1 - ks) >> 1;  // private blocks ks, ks + 2, .. of the list wavefront
   const bool rec_in_lds = n_all <= kRecCap;  // uniform over the workgroup
   if (rec_in_lds) {
     const u32x4 *src = reinterpret_cast<const u32x4 *>(p.blocks + static_cast<int64_t>(blk_begin) * 8);
@@ -1333,6 +1338,16 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && NTW <= 2) ? 2 : 1) void spex_t
   const int qt_begin = sload(p.items, ir + 3 + LW + rw);
   const int qt_count = sload(p.items, ir + 3 + 2 * LW + rw);
   const int rows = qt_count * sh.G;
+  // CUT: where the paths of the workgroup's rows end for them, as a maximum over the lanes (with masks an upper
+  // bound: 32 drafts).  The workgroup's entries follow each other from its first wavefront's on.
+  int seen_end = 0;
+  if constexpr (CUT) {
+    int entries = 0;
+#pragma unroll
+    for (int v = 0; v < LW; ++v) entries += sload(p.items, ir + 3 + 2 * LW + v);
+    const int32_t *rec = p.qt_rec + 2 * static_cast<int64_t>(sload(p.items, ir + 3 + LW));
+    for (int i = lane; i < entries; i += 64) seen_end = max(seen_end, rec[2 * i + 1] + (TREE ? 31 : 0));
+  }
   const bool has_rows = rows > 0;
   const char *kpool = static_cast<const char *>(p.k_pool);
   const char *vpool = static_cast<const char *>(p.v_pool);
@@ -1377,6 +1392,20 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && NTW <= 2) ? 2 : 1) void spex_t
       for (int s = 0; s < D / 32; ++s) qf[nt][s] = __builtin_bit_cast(bf16x8, u32x4{0, 0, 0, 0});
     }
   }
+
+  if constexpr (CUT) {  // every wavefront cuts the shared list alike
+    auto unseen = [&](int idx) {
+      const int32_t *r = rec_lds + (uniform(idx) - blk_begin) * 8;
+      const int64_t far = static_cast<int64_t>(uniform(idx)) * 8;
+      const int flags = rec_in_lds ? uniform(r[5]) : sload(p.blocks, far + 5);
+      if (!(flags & 1)) return false;
+      const int pos = (rec_in_lds ? uniform(r[1]) : sload(p.blocks, far + 1)) >> 7;
+      return !__any(seen_end > pos);
+    };
+    while (n_shared > 0 && unseen(blk_begin + n_shared - 1)) --n_shared;
+    while (n_priv > 0 && unseen(priv_begin + n_priv - 1)) --n_priv;
+  }
+  if (KS == 2) n_priv = (n_priv + 1 - ks) >> 1;  // private blocks ks, ks + 2, .. of the list wavefront
 
   // The two phases run in either order (the online softmax does not care).  The shared phase is
   // bound by the matrix cores and LDS, the private phase by memory; workgroups that start together
@@ -2971,6 +3000,8 @@ static hipError_t launch_walk_ntw(const Shape &sh, const WalkArgs &a, int ntw, b
     hipLaunchKernelGGL((spex_tree_walk_kernel<KV, D, 1, NW, TREE>), grid, block, 0, stream, a, sh);
   else if (ntw == 2 && KV == kFP8 && by_tile)
     hipLaunchKernelGGL((spex_tree_walk_kernel<KV, D, 2, NW, TREE, 1, KV == kFP8>), grid, block, 0, stream, a, sh);
+  else if (ntw == 2 && NW == 4 && a.cut)
+    hipLaunchKernelGGL((spex_tree_walk_kernel<KV, D, 2, NW, TREE, 1, false, NW == 4>), grid, block, 0, stream, a, sh);
   else if (ntw == 2)
     hipLaunchKernelGGL((spex_tree_walk_kernel<KV, D, 2, NW, TREE>), grid, block, 0, stream, a, sh);
   else if (NW == 8 || by_tile)
@@ -2985,6 +3016,8 @@ static hipError_t launch_walk_halves(const Shape &sh, const WalkArgs &a, int ntw
   const dim3 grid(a.n_items), block(64 * NW);
   if (ntw == 1)
     hipLaunchKernelGGL((spex_tree_walk_kernel<KV, D, 1, NW, TREE, 2>), grid, block, 0, stream, a, sh);
+  else if (ntw == 2 && NW == 8 && a.cut)
+    hipLaunchKernelGGL((spex_tree_walk_kernel<KV, D, 2, NW, TREE, 2, false, NW == 8>), grid, block, 0, stream, a, sh);
   else if (ntw == 2)
     hipLaunchKernelGGL((spex_tree_walk_kernel<KV, D, 2, NW, TREE, 2>), grid, block, 0, stream, a, sh);
   else

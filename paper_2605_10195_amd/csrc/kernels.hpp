@@ -61,6 +61,7 @@ struct WalkArgs {
   float *out, *lse;       // lse may be null
   float scale_log2;
   const int32_t *qt_mask; // as in AttnArgs; null for the causal chain
+  bool cut;               // some request has more rows than a row block holds
 };
 
 struct MergeArgs {

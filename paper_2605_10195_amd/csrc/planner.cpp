@@ -828,6 +828,7 @@ void Planner::ensure_walk(const PageTable &pt, Plan *plan) {
     if (wide && n8 * num_kv_heads >= 1024) NW = 8;
   }
   pl.walk_waves = NW;
+  pl.walk_cut = max_rows > NW * C;
   const int32_t rb_ints = 3 + 3 * NW, item_ints = NW <= 4 ? 16 : 32;
 
   // Order of the requests: by root, then by path (node ids root first, lexicographic, a proper

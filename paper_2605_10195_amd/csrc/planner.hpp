@@ -114,6 +114,7 @@ struct Plan {
   // Decided when the lists are made and kept through length patches, which leave the figures behind
   // the decisions as they were.
   bool walk_halves = false;          // eight wavefronts walk the lists made for four, two on each set of rows
+  bool walk_cut = false;             // some request has more rows than a row block holds
   bool walk_by_tile = false;         // row tiles are worked on one by one, without those a block does not touch
   int32_t route = -1;                // Planner::prefers_walk: -1 not asked yet, 0 split path, 1 tree-walk kernel
   int64_t walk_block_visits = 0;  // blocks over all row blocks (a block shared by two row blocks counts twice)

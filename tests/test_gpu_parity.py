@@ -354,6 +354,27 @@ def test_wide_groups_match_oracle(wl, mode):
         assert_close(got, ref, wl.kv_dtype, f"{wl.name} mode {mode} chunks {chunks}")
 
 
+# Requests of more rows than a row block holds: its blocks behind their last visible token are left out.  Steps that end
+# on a block, in it and one token past it, queries that begin in the parent, lists beyond the LDS copy, masks of 32 drafts.
+def _cut(prompt, step, more=0, **kw):
+    wl = sw.step_prefill(n_queries=2, prompt=prompt, step=step, width=4, keep=2, depth=2, **kw)
+    wl.q_lens = [step + more] * len(wl.leaves)
+    return wl
+
+
+@pytest.mark.parametrize("make", [
+    lambda: _cut(40, 128, heads=(8, 2, 128)), lambda: _cut(75, 77, heads=(28, 4, 128), kv_dtype="fp8_e4m3"),
+    lambda: _cut(16, 65, heads=(16, 2, 64)), lambda: _cut(60, 30, more=40, heads=(8, 1, 64)),
+    lambda: sw.step_prefill(n_queries=1, prompt=8300, step=100, width=2, keep=1, depth=1, heads=(8, 2, 64)),
+    lambda: sw.tot_with_drafts(n_queries=2, prompt=50, step=17, depth=2, drafts=32, heads=(16, 2, 128), token_trees=True)])
+@pytest.mark.parametrize("waves", [0, 2, 4, 8])
+def test_row_blocks_without_the_tokens_none_of_their_rows_sees(make, waves):
+    wl = make()
+    if wl.draft_masks and waves == 2:
+        pytest.skip("draft masks do not combine with two wavefronts of rows")
+    assert_close(run_gpu(wl, kernel_mode=3, walk_waves=waves), run_oracle_c(wl), wl.kv_dtype, f"{wl.name} {waves}")
+
+
 @pytest.mark.parametrize("kv_dtype", ["bf16", "fp8_e4m3", "f32"])
 def test_interleaved_kv_pool(kv_dtype):
     wl = sw.random_trace(61, heads=(8, 2, 128) if kv_dtype != "f32" else (4, 2, 64), kv_dtype=kv_dtype,
