@@ -935,6 +935,7 @@ static spex_status_t decode_attention_impl(spex_tree_t *t, const spex_node_t *le
     il.n_items[k] = static_cast<int32_t>(host_items[k]->size() / spex::Plan::kItemInts);
     il.span[k] = spans[k];
   }
+  il.longest = pl.longest_streamed;
   a.part_indptr = dp.part_indptr;
   a.part_base = dp.part_base;
   a.part_hstride = dp.part_hstride;

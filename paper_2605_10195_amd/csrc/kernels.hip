@@ -303,23 +303,28 @@ __device__ __forceinline__ void load_rows(const AttnArgs &p, const Shape &sh, co
 // page jj/2.  After the two score tiles this lane holds the scores of exactly those 8 tokens, i.e.
 // the operand layout of the PV product, so P never leaves the registers.
 // VF16: vf holds fp16 (V of a bf16 pool as stored), else bf16 (widened fp8 codes).
-template <bool TREE, bool VF16, int D, int NT>
+template <bool TREE, bool VF16, int D, int NT, class Refill>
 __device__ __forceinline__ void block_math(RowState<D, NT> &st, const bf16x8 (&kf)[2][D / 32],
                                            const bf16x8 (&vf)[D / 16], bool masked, int valid_l,
-                                           int pos_l, float c, float vs) {
+                                           int pos_l, float c, float vs, Refill refill_k) {
+  f32x4 sa[NT], sb[NT];
 #pragma unroll
   for (int nt = 0; nt < NT; ++nt) {
-    f32x4 sa = {0.f, 0.f, 0.f, 0.f}, sb = {0.f, 0.f, 0.f, 0.f};
+    sa[nt] = sb[nt] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int s = 0; s < D / 32; ++s) {
-      sa = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[0][s], st.qf[nt][s], sa, 0, 0, 0);
-      sb = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[1][s], st.qf[nt][s], sb, 0, 0, 0);
+      sa[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[0][s], st.qf[nt][s], sa[nt], 0, 0, 0);
+      sb[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[1][s], st.qf[nt][s], sb[nt], 0, 0, 0);
     }
+  }
+  refill_k();
+#pragma unroll
+  for (int nt = 0; nt < NT; ++nt) {
     float x[8];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      x[i] = sa[i] * c;
-      x[4 + i] = sb[i] * c;
+      x[i] = sa[nt][i] * c;
+      x[4 + i] = sb[nt][i] * c;
     }
     if (masked) mask_scores<TREE>(x, st.limit[nt], st.qidx[nt], st.dmask[nt], valid_l, pos_l, true);
     float mx = fmaxf(fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3])),
@@ -505,15 +510,14 @@ __device__ __forceinline__ void finish_rows(const AttnArgs &p, const Shape &sh, 
   }
 }
 
-// Raw 128-bit pieces of one 32-token block (two pages) of one kv head, as loaded.
+// Raw 128-bit pieces of one 32-token block (two pages) of one kv head, as loaded, and the lane's page scales (fp8).
 template <int KV, int D>
 struct RawBlock {
   static constexpr int NK = (KV == kFP8) ? D / 64 : D / 32;  // loads per K half-tile
   static constexpr int NV = (KV == kFP8) ? D / 32 : D / 16;
   u32x4 k[2][NK];
   u32x4 v[NV];
-  int valid_a, valid_b, pos_a, pos_b;
-  float ks, vs;  // this lane's page scales (fp8), else 1
+  float ks = 1.f, vs = 1.f;
 };
 
 // ---- split path: items of few rows -------------------------------------------------------------
@@ -553,11 +557,14 @@ constexpr int wave_fold_floats() { return 4 * (D / 16) * 256 + 4 * 16 * 2; }
 // are split between the four wavefronts, which fold their softmax states through LDS; a chunk of
 // 16 pages is then two blocks deep instead of eight.  Otherwise a wavefront takes the item (SUFFIX: rows of a
 // private suffix, finished here where it is in one piece).
-// The K/V loads of block b+1 are in flight while block b is computed.  The steady-state loop is
-// free of conditional loads on purpose: the vector-memory completion counter is in-order, and a
-// load that is issued on one path only would force the compiler to wait for everything
-// outstanding at the join.
-template <int KV, int D, int NT, bool TREE, bool SPLIT, bool SUFFIX>
+// DEEP: the K/V loads of block b+1 are in flight while block b is computed, in registers of their own.  The
+// steady-state loop is free of conditional loads on purpose: the vector-memory completion counter is in-order, and a
+// load that is issued on one path only would force the compiler to wait for everything outstanding at the join.
+// Otherwise one set of registers, K's requested behind the score MFMAs of the block before, V's at the start of the
+// block (130 and not 216 registers for fp8 heads of 128, 213 and not 392 with two row tiles).  K past the
+// last block is requested as well, by all lanes from one address: a copy of the step without it makes the compiler carry
+// the state over in 64 moves a step, which wait for the loads.
+template <int KV, int D, int NT, bool TREE, bool SPLIT, bool SUFFIX, bool DEEP>
 __device__ __forceinline__ void wave_item(const AttnArgs &p, const Shape &sh, const Item &cur, float *lds) {
   constexpr int ESZ = (KV == kFP8) ? 1 : 2;
   constexpr int TILE_BYTES = 16 * D * ESZ;
@@ -575,31 +582,29 @@ __device__ __forceinline__ void wave_item(const AttnArgs &p, const Shape &sh, co
   const int n_all = (cur.pg_count + 1) >> 1;
   const int b_first = SPLIT ? (n_all * w) >> 2 : 0, nblk = SPLIT ? (n_all * (w + 1)) >> 2 : n_all;  // blocks b_first .. nblk - 1
 
-  auto issue_loads = [&](RawBlock<KV, D> &rb, const BlockMeta &bm) {
-    rb.valid_a = bm.vp_a & 127;
-    rb.valid_b = bm.vp_b & 127;
-    rb.pos_a = bm.vp_a >> 7;
-    rb.pos_b = bm.vp_b >> 7;
-    const int64_t tile_a = (static_cast<int64_t>(bm.pid_a) * sh.page_tiles + g);
-    const int64_t tile_b = (static_cast<int64_t>(bm.pid_b) * sh.page_tiles + g);
-    const char *kp = kpool + (m16 < 8 ? tile_a : tile_b) * TILE_BYTES + k_lane_off;
-    const char *vp = vpool + (jj < 2 ? tile_a : tile_b) * TILE_BYTES + v_lane_off;
+  auto tile_of = [&](int pid) { return static_cast<int64_t>(pid) * sh.page_tiles + g; };
+  auto issue_k = [&](RawBlock<KV, D> &rb, const BlockMeta &bm, int64_t tile_a, int64_t tile_b, int msk) {
+    if (KV == kFP8) {
+      const int sidx = (jj < 2 ? bm.pid_a : bm.pid_b) * sh.Hkv + g;
+      rb.ks = p.k_scale[sidx];
+      rb.vs = p.v_scale[sidx];
+    }
+    const char *kp = kpool + (m16 < 8 ? tile_a : tile_b) * TILE_BYTES + (k_lane_off & msk);
 #pragma unroll
     for (int t = 0; t < 2; ++t)
 #pragma unroll
       for (int s = 0; s < RawBlock<KV, D>::NK; ++s)
         rb.k[t][s] = load_kv(kp + t * (TILE_BYTES / 2) + s * 512);
+  };
+  auto issue_v = [&](RawBlock<KV, D> &rb, int64_t tile_a, int64_t tile_b) {
+    const char *vp = vpool + (jj < 2 ? tile_a : tile_b) * TILE_BYTES + v_lane_off;
 #pragma unroll
-    for (int s = 0; s < RawBlock<KV, D>::NV; ++s)
-      rb.v[s] = load_kv(vp + s * 512);
-    if (KV == kFP8) {
-      const int sidx = (jj < 2 ? bm.pid_a : bm.pid_b) * sh.Hkv + g;
-      rb.ks = p.k_scale[sidx];
-      rb.vs = p.v_scale[sidx];
-    } else {
-      rb.ks = 1.f;
-      rb.vs = 1.f;
-    }
+    for (int s = 0; s < RawBlock<KV, D>::NV; ++s) rb.v[s] = load_kv(vp + s * 512);
+  };
+  auto issue_loads = [&](RawBlock<KV, D> &rb, const BlockMeta &bm) {
+    const int64_t tile_a = tile_of(bm.pid_a), tile_b = tile_of(bm.pid_b);
+    issue_k(rb, bm, tile_a, tile_b, -1);
+    issue_v(rb, tile_a, tile_b);
   };
   // page records of block min(b, nblk - 1)
   auto meta = [&](int b) { return load_block_meta(p.pg_rec, cur, b < nblk ? b : nblk - 1); };
@@ -608,9 +613,8 @@ __device__ __forceinline__ void wave_item(const AttnArgs &p, const Shape &sh, co
   RowState<D, NT> st;
   load_rows<D, NT>(p, sh, cur, cur.row0, st);
 
-  RawBlock<KV, D> r0, r1;
-
-  auto compute_block = [&](const RawBlock<KV, D> &rb) {
+  // One block; refill_k is called where its K registers (and scales) are free.
+  auto compute_block = [&](const RawBlock<KV, D> &rb, const BlockMeta &bm, auto refill_k) {
     bf16x8 kf[2][D / 32];
     bf16x8 vf[D / 16];
     if (KV == kFP8) {
@@ -635,28 +639,50 @@ __device__ __forceinline__ void wave_item(const AttnArgs &p, const Shape &sh, co
       for (int s = 0; s < D / 16; ++s) vf[s] = __builtin_bit_cast(bf16x8, rb.v[s]);
     }
     // This lane's score registers cover tokens 8*(jj&1) .. +7 of page A (jj < 2) or B.
-    block_math<TREE, KV == kBF16, D, NT>(st, kf, vf, task_masked || rb.valid_b == 0, jj < 2 ? rb.valid_a : rb.valid_b,
-                      jj < 2 ? rb.pos_a : rb.pos_b, p.scale_log2 * rb.ks, rb.vs);
+    const int vp = jj < 2 ? bm.vp_a : bm.vp_b;
+    block_math<TREE, KV == kBF16, D, NT>(st, kf, vf, task_masked || (bm.vp_b & 127) == 0, vp & 127, vp >> 7,
+                                         p.scale_log2 * rb.ks, rb.vs, refill_k);
   };
 
   if (b_first < nblk) {
-    issue_loads(r0, meta(b_first));
-    BlockMeta bm1 = meta(b_first + 1);
-    int b = b_first;
-    for (; b + 2 < nblk; b += 2) {  // blocks b, b+1, b+2 all exist
-      const BlockMeta bm2 = meta(b + 2);
-      issue_loads(r1, bm1);
-      compute_block(r0);
-      bm1 = meta(b + 3);
-      issue_loads(r0, bm2);
-      compute_block(r1);
-    }
-    if (b + 1 < nblk) {
-      issue_loads(r1, bm1);
-      compute_block(r0);
-      compute_block(r1);
+    RawBlock<KV, D> r0;
+    BlockMeta m0 = meta(b_first);
+    if constexpr (DEEP) {
+      const auto nothing = [] {};
+      RawBlock<KV, D> r1;
+      issue_loads(r0, m0);
+      BlockMeta m1 = meta(b_first + 1);
+      int b = b_first;
+      for (; b + 2 < nblk; b += 2) {  // blocks b, b+1, b+2 all exist
+        const BlockMeta m2 = meta(b + 2);
+        issue_loads(r1, m1);
+        compute_block(r0, m0, nothing);
+        const BlockMeta m3 = meta(b + 3);
+        issue_loads(r0, m2);
+        compute_block(r1, m1, nothing);
+        m0 = m2;
+        m1 = m3;
+      }
+      if (b + 1 < nblk) {
+        issue_loads(r1, m1);
+        compute_block(r0, m0, nothing);
+        compute_block(r1, m1, nothing);
+      } else {
+        compute_block(r0, m0, nothing);
+      }
     } else {
-      compute_block(r0);
+      BlockMeta m1 = meta(b_first + 1);
+      int64_t tile_a = tile_of(m0.pid_a), tile_b = tile_of(m0.pid_b);
+      issue_k(r0, m0, tile_a, tile_b, -1);
+      for (int b = b_first; b < nblk; ++b) {
+        const BlockMeta m2 = meta(b + 2);
+        issue_v(r0, tile_a, tile_b);
+        tile_a = tile_of(m1.pid_a);
+        tile_b = tile_of(m1.pid_b);
+        compute_block(r0, m0, [&] { issue_k(r0, m1, tile_a, tile_b, b + 1 < nblk ? -1 : 0); });
+        m0 = m1;
+        m1 = m2;
+      }
     }
   }
 
@@ -955,32 +981,36 @@ __device__ __forceinline__ void coop_item(const AttnArgs &p, const Shape &sh, co
 
 // All items of the split path in one launch: lists 0 and 1 hold groups of up to 128 and up to 64 rows
 // a span, lists 2 and 3 groups of up to 16 rows and private suffixes.
-template <int KV, int D, int NT, bool TREE>
-__global__ __launch_bounds__(256, NT == 1 ? 2 : 1) void spex_split_attn_kernel(AttnArgs p, Shape sh, SplitLists ls) {
+// LEAN: for launches of many short items, none in list 0: three workgroups a compute unit where the other form holds two
+// (heads of 64: five and three).
+constexpr int split_occupancy(int d, int nt, bool lean) {
+  return d == 64 ? (lean ? 5 : 3) : (lean ? 3 : 2);
+}
+template <int KV, int D, int NT, bool TREE, bool LEAN>
+__global__ __launch_bounds__(256, split_occupancy(D, NT, LEAN)) void spex_split_attn_kernel(AttnArgs p, Shape sh, SplitLists ls) {
   constexpr int kLds = coop_lds_floats<D>() > wave_fold_floats<D>() ? coop_lds_floats<D>() : wave_fold_floats<D>();
   __shared__ __attribute__((aligned(16))) float lds[kLds];
   const ListPos at = list_of(ls, static_cast<int>(blockIdx.x));
   const Item cur = load_item(at.items, at.local);
   if (cur.pg_count == 0) return;  // padding item (whole workgroup)
-  if (at.k == 0)
+  if (!LEAN && at.k == 0)
     coop_item<KV, D, 2, TREE>(p, sh, cur, lds);
-  else if (at.k == 1)
+  else if (at.k <= 1)
     coop_item<KV, D, 1, TREE>(p, sh, cur, lds);
   else
-    wave_item<KV, D, NT, TREE, true, false>(p, sh, cur, lds);
+    wave_item<KV, D, NT, TREE, true, false, NT == 1 && !LEAN>(p, sh, cur, lds);
 }
 
 // The same in launches of their own where there are items enough to fill the chip with a wavefront each (the
-// rule and both sides' times stand with the planner's item lengths).  Items through LDS then keep two
-// workgroups to a compute unit whatever the private items' kernel holds: 220 registers against 390.
+// rule and both sides' times stand with the planner's item lengths).
 template <int KV, int D, int NT, bool SUFFIX, bool TREE>
-__global__ __launch_bounds__(256, NT == 1 ? 2 : 1) void spex_wave_attn_kernel(AttnArgs p, Shape sh) {
+__global__ __launch_bounds__(256, 2) void spex_wave_attn_kernel(AttnArgs p, Shape sh) {
   __shared__ __attribute__((aligned(16))) float lds[4 * stage_floats<D>()];
   const int item = uniform(static_cast<int>(blockIdx.x) * 4 + static_cast<int>(threadIdx.x >> 6));
   if (item >= p.n_items) return;
   const Item cur = load_item(p.items, item);
   if (cur.pg_count == 0) return;  // padding item
-  wave_item<KV, D, NT, TREE, false, SUFFIX>(p, sh, cur, lds);
+  wave_item<KV, D, NT, TREE, false, SUFFIX, NT == 1>(p, sh, cur, lds);
 }
 
 template <int KV, int D, int NTW, bool TREE>
@@ -2920,19 +2950,32 @@ static SplitLists make_lists(const ItemLists &l, int rows_per_wg, int64_t *n_wg)
 }
 
 template <int KV, int D, int NT>
-static hipError_t launch_split_nt(const Shape &sh, const AttnArgs &a, const SplitLists &ls, int n_wg, hipStream_t stream) {
+static hipError_t launch_split_nt(const Shape &sh, const AttnArgs &a, const SplitLists &ls, int n_wg, int longest, hipStream_t stream) {
   const dim3 grid(n_wg), block(256);
-  if (a.qt_mask)  // draft token trees: visibility masks per query
-    hipLaunchKernelGGL((spex_split_attn_kernel<KV, D, NT, true>), grid, block, 0, stream, a, sh, ls);
+  // More workgroups than run at a time in the other form, and no long items, which want their loads a block ahead.
+  // bf16 heads of 128 read as fast with two workgroups a compute unit.  Times of both forms, us: fp8 heads of 128, items of 8
+  // pages, 6144 workgroups 73.6 / 63.6, 1536 25.0 / 22.7, of 16 pages 768 18.5 / 16.4, of 128 pages 768 36.4 / 37.2;
+  // heads of 64, 8 pages, 1536 23.3 / 21.2 (fp8 24.9 / 20.4); bf16 heads of 128, 16 pages, 3072 82.6 / 85.1.
+  if constexpr (NT == 1 && !(KV == kBF16 && D == 128)) {
+    if (ls.wg_end[0] == 0 && n_wg > 256 * split_occupancy(D, NT, false) && longest <= 16) {
+      if (a.qt_mask)  // draft token trees: visibility masks per query
+        hipLaunchKernelGGL((spex_split_attn_kernel<KV, D, NT, true, true>), grid, block, 0, stream, a, sh, ls);
+      else
+        hipLaunchKernelGGL((spex_split_attn_kernel<KV, D, NT, false, true>), grid, block, 0, stream, a, sh, ls);
+      return hipGetLastError();
+    }
+  }
+  if (a.qt_mask)
+    hipLaunchKernelGGL((spex_split_attn_kernel<KV, D, NT, true, false>), grid, block, 0, stream, a, sh, ls);
   else
-    hipLaunchKernelGGL((spex_split_attn_kernel<KV, D, NT, false>), grid, block, 0, stream, a, sh, ls);
+    hipLaunchKernelGGL((spex_split_attn_kernel<KV, D, NT, false, false>), grid, block, 0, stream, a, sh, ls);
   return hipGetLastError();
 }
 
 template <int KV, int D>
-static hipError_t launch_split_d(const Shape &sh, const AttnArgs &a, const SplitLists &ls, int n_wg, hipStream_t stream) {
-  return ls.span[2] <= 16 && ls.span[3] <= 16 ? launch_split_nt<KV, D, 1>(sh, a, ls, n_wg, stream)
-                                              : launch_split_nt<KV, D, 2>(sh, a, ls, n_wg, stream);
+static hipError_t launch_split_d(const Shape &sh, const AttnArgs &a, const SplitLists &ls, int n_wg, int longest, hipStream_t stream) {
+  return ls.span[2] <= 16 && ls.span[3] <= 16 ? launch_split_nt<KV, D, 1>(sh, a, ls, n_wg, longest, stream)
+                                              : launch_split_nt<KV, D, 2>(sh, a, ls, n_wg, longest, stream);
 }
 
 template <int KV, int D, bool TREE>
@@ -2983,9 +3026,9 @@ hipError_t launch_split(const Shape &sh, const AttnArgs &a, const ItemLists &l, 
   if (n_wg == 0) return hipSuccess;
   const int n = static_cast<int>(n_wg);
   if (tiled && sh.kv_dtype == kBF16)
-    return sh.D == 64 ? launch_split_d<kBF16, 64>(sh, a, ls, n, stream) : launch_split_d<kBF16, 128>(sh, a, ls, n, stream);
+    return sh.D == 64 ? launch_split_d<kBF16, 64>(sh, a, ls, n, l.longest, stream) : launch_split_d<kBF16, 128>(sh, a, ls, n, l.longest, stream);
   if (tiled)
-    return sh.D == 64 ? launch_split_d<kFP8, 64>(sh, a, ls, n, stream) : launch_split_d<kFP8, 128>(sh, a, ls, n, stream);
+    return sh.D == 64 ? launch_split_d<kFP8, 64>(sh, a, ls, n, l.longest, stream) : launch_split_d<kFP8, 128>(sh, a, ls, n, l.longest, stream);
   if (sh.kv_dtype == kF32) return launch_rowmajor_kv<kF32>(sh, a, ls, n, stream);
   if (sh.kv_dtype == kBF16) return launch_rowmajor_kv<kBF16>(sh, a, ls, n, stream);
   return launch_rowmajor_kv<kFP8>(sh, a, ls, n, stream);

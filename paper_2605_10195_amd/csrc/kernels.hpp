@@ -120,6 +120,7 @@ struct GatherArgs {
 struct ItemLists {
   const int32_t *items[4];
   int32_t n_items[4], span[4];
+  int32_t longest;  // pages of the longest item of the last two lists
 };
 bool has_mfma_kernel(const Shape &sh);
 bool has_rowmajor_kernel(const Shape &sh, const AttnArgs &a);

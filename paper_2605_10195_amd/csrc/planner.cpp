@@ -33,8 +33,8 @@ int32_t clamp32(int64_t v, int32_t lo, int32_t hi) {
 // and 1024, 427 with these; 16 branches on pages of 2 tokens 190 with items of 128 tokens, 92 with these).
 // Tiled pools: launches of many items go in phases, shared items and then private ones, a wavefront
 // each, which finish the rows of suffixes in one piece.
-//  * Private items of more than 16 rows (the kernel then holds two row tiles and one workgroup a compute
-//    unit, its items through LDS among them): beyond 512 workgroups.  Over 281 drawn requests of that kind
+//  * Private items of more than 16 rows (the kernel then holds two row tiles; when the rule was made, one workgroup a
+//    compute unit, its items through LDS among them): beyond 512 workgroups.  Over 281 drawn requests of that kind
 //    none is then slower than with phases throughout by more than 2 %, and the choice is 3 % from the
 //    better of both: 64 private items of 32 rows 27 us against 55 in phases, 512 of them 74 against 64, 4096
 //    606 against 362.  Phases have 1024 shared and 2048 private items, because those of many rows are
@@ -522,6 +522,8 @@ PlanError Planner::ensure_split(const PageTable &pt, Plan *plan) {
     for (int32_t rt = 0; rt < n_rt; ++rt)
       for (int32_t g = 0; g < num_kv_heads; ++g) push_item(pl.suffix_items, t, g, rt * rw_suffix);
   }
+  for (const std::vector<int32_t> *items : {&pl.prefix_items, &pl.suffix_items})
+    for (size_t i = 1; i < items->size(); i += Plan::kItemInts) pl.longest_streamed = std::max(pl.longest_streamed, (*items)[i]);
   pl.pg_rec.resize(pl.pg_id.size() * 2);
   for (size_t i = 0; i < pl.pg_id.size(); ++i) {
     pl.pg_rec[2 * i] = pl.pg_id[i];

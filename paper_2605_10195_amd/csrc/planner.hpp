@@ -79,6 +79,7 @@ struct Plan {
   std::vector<int32_t> prefix_items, suffix_items, pg_rec, qt_rec;
   std::vector<int32_t> coop_items[2];  // groups of more than 16 rows, up to 64 / 128 rows per workgroup
   int32_t suffix_row_tiles = 1;  // 16-row MFMA tiles per wavefront of the private items (shared ones of few rows: 1)
+  int32_t longest_streamed = 0;  // pages of the longest of prefix_items and suffix_items
   int32_t max_rows_prefix = 0, max_rows_suffix = 0;
   int64_t prefix_tokens = 0, suffix_tokens = 0;        // distinct KV tokens per kind
 

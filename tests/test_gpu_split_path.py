@@ -234,6 +234,23 @@ def test_split_path_in_one_launch_and_in_phases(make, more):
     assert_close(run_gpu(wl, kernel_mode=2), run_oracle_c(wl), wl.kv_dtype, wl.name)
 
 
+# More short items than run at a time (512 workgroups, 768 with heads of 64), which the form with one set of K and V
+# registers takes, and fewer; items of one page to 16 and beyond (the other form), of whole and of partial blocks; masks.
+@pytest.mark.parametrize("heads,kv_dtype", [((8, 2, 128), "fp8_e4m3"), ((8, 2, 64), "bf16"), ((12, 4, 64), "fp8_e4m3")])
+@pytest.mark.parametrize("trees", [20, 50])
+@pytest.mark.parametrize("step,chunk", [(1, 0), (33, 0), (250, 16), (280, 17), (100, 3)])
+def test_many_short_items(heads, kv_dtype, trees, step, chunk):
+    wl = sw.bfs_tot(n_queries=trees, prompt=21, step=step, width=8, keep=8, depth=1, heads=heads, kv_dtype=kv_dtype)
+    got = run_gpu(wl, kernel_mode=2, prefix_chunk_pages=chunk, suffix_chunk_pages=chunk)
+    assert_close(got, run_oracle_c(wl), kv_dtype, f"{heads} {kv_dtype} {trees} {step}")
+
+
+@pytest.mark.parametrize("heads,kv_dtype", [((8, 2, 128), "fp8_e4m3"), ((8, 2, 64), "bf16")])
+def test_many_short_items_with_draft_masks(heads, kv_dtype):
+    wl = sw.tot_with_drafts(n_queries=100, prompt=40, step=19, depth=2, drafts=3, heads=heads, kv_dtype=kv_dtype, token_trees=True)
+    assert_close(run_gpu(wl, kernel_mode=2), run_oracle_c(wl), kv_dtype, kv_dtype)
+
+
 @pytest.mark.parametrize("heads,kv_dtype,chunk", [((40, 2, 128), "bf16", 1), ((40, 2, 64), "fp8_e4m3", 2), ((34, 2, 128), "fp8_e4m3", 0)])
 def test_phases_with_interior_nodes_and_cut_suffixes(heads, kv_dtype, chunk):
     """Requested nodes with and without live children, some twice, suffixes in one piece and in several."""
