@@ -939,7 +939,7 @@ static spex_status_t decode_attention_impl(spex_tree_t *t, const spex_node_t *le
   a.part_indptr = dp.part_indptr;
   a.part_base = dp.part_base;
   a.part_hstride = dp.part_hstride;
-  const bool phases = !generic && pl.split_phases;
+  const bool phases = !generic && pl.split_phases && !pl.split_together;
   HIP_TRY(bracket(0, true));
   if (generic) {
     for (int k = 0; k < 4; ++k) {

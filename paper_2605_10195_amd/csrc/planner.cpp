@@ -39,6 +39,10 @@ int32_t clamp32(int64_t v, int32_t lo, int32_t hi) {
 //    better of both: 64 private items of 32 rows 27 us against 55 in phases, 512 of them 74 against 64, 4096
 //    606 against 362.  Phases have 1024 shared and 2048 private items, because those of many rows are
 //    long: 3 prompts of 10000 tokens, 29 branches of 128 rows 161 us, with 256 shared items 189.
+//    With two workgroups a compute unit the same items are faster together, in one launch, up to 1536 of them (1024
+//    with heads of 64), in phases / together: 480 50.6 / 30.8 us, 640 36.6 / 23.9, 960 58.0 / 39.4, 1056 98 / 59, 1408
+//    43.8 / 34.7, 2048 short ones 55.3 / 58.5, 8192 302 / 345; heads of 64: 832 44.8 / 26, 1296 25.8 / 24.1,
+//    1152 20.4 / 21.4, 1728 27.5 / 29.5.
 //  * Up to 16 rows: when there are a great many.  8192 private items 293 us against 328 in phases, 32768
 //    1129 against 1108 (bf16) and 875 against 818 (fp8), 65536 2992 against 2862; head dim 64: 2048
 //    35.7 against 55, 8192 122 against 118 (bf16) and 132 against 119 (fp8).
@@ -49,7 +53,7 @@ struct Run {
 };
 struct Chunks {
   int32_t prefix, suffix;  // pages
-  bool phases;
+  bool phases, together;
   int64_t partial_rows;
 };
 Chunks choose_chunks(const std::vector<Run> &groups, const std::vector<Run> &suffixes, int32_t num_kv_heads, int32_t page_size,
@@ -84,6 +88,7 @@ Chunks choose_chunks(const std::vector<Run> &groups, const std::vector<Run> &suf
       private_wgs += chunks(s.pages, c.suffix) * (tall ? (s.rows + 31) / 32 : 1);
     }
     c.partial_rows = partial * num_kv_heads;
+    c.together = (shared_wgs + private_wgs) * num_kv_heads <= (pool.head_dim <= 64 ? 1024 : 1536);
     c.phases = pool.tiled && (tall ? (shared_wgs + private_wgs) * num_kv_heads > 512
                                    : private_wgs * num_kv_heads > (pool.head_dim <= 64 ? 4096 : 16384));
   };
@@ -93,6 +98,8 @@ Chunks choose_chunks(const std::vector<Run> &groups, const std::vector<Run> &suf
   if (c.phases && tall) {
     choose(1024, 2048, false);
     c.phases = true;
+  } else {
+    c.together = false;
   }
   return c;
 }
@@ -366,6 +373,7 @@ PlanError Planner::ensure_split(const PageTable &pt, Plan *plan) {
     pl.prefix_chunk_pages = c.prefix;
     pl.suffix_chunk_pages = c.suffix;
     pl.split_phases = c.phases;
+    pl.split_together = c.together;
   }
 
   // ---- tasks

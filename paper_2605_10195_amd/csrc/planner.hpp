@@ -69,7 +69,8 @@ struct Plan {
   int32_t n_prefix_tasks = 0;
   int64_t n_partial_rows = 0;
   int32_t prefix_chunk_pages = 0, suffix_chunk_pages = 0;  // values used
-  bool split_phases = false;  // tiled pools: the split path's lists in launches of their own
+  bool split_phases = false;  // tiled pools: items are cut for the split path's lists in launches of their own
+  bool split_together = false;  // and few enough to go in one launch all the same
 
   // ---- launch lists (device side).  A work item is kItemInts ints:
   //   {pg_begin, pg_count, qt_begin, qt_count, pbase, flags, kv_head, first_row}

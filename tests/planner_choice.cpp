@@ -193,6 +193,21 @@ int main() {
   CHECK(phases(65, 16, 1, 16, 4, 64), "4160 private items of 4 rows, head dim 64");
   CHECK(!phases(513, 16, 1, 8, 2, 128, false), "row-major");
 
+  // items of more than 16 rows cut for phases that go in one launch all the same
+  auto together = [](int roots, int branches, int q_len, int Hq, int Hkv, int dim, int prompt = 40) {
+    Forest f(roots * (3 + prompt / 16 + 2 * branches), 16);
+    f.add(roots, prompt, branches, 20, q_len);
+    Made m(f, Hq, Hkv);
+    m.planner.pool = {true, false, dim, 2};
+    CHECK(m.planner.ensure_split(f.pt, &m.plan) == PlanError::kOk, "split lists");
+    return m.plan.split_together;
+  };
+  CHECK(!together(256, 1, 1, 40, 2, 128) && together(257, 1, 1, 40, 2, 128), "512 items are not cut for phases, 514 are");
+  CHECK(together(768, 1, 1, 40, 2, 128) && !together(769, 1, 1, 40, 2, 128), "1536 and 1538 items");
+  CHECK(together(68, 4, 1, 71, 1, 64) && !together(69, 4, 1, 71, 1, 64), "1020 and 1035 workgroups, head dim 64");
+  CHECK(together(13, 8, 8, 32, 8, 128, 600) && !together(14, 8, 8, 32, 8, 128, 600), "1456 and 1568 workgroups, prompts of 38 pages");
+  CHECK(!together(513, 16, 1, 8, 2, 128), "4 rows");
+
   if (failures == 0) std::printf("ok\n");
   return failures != 0;
 }

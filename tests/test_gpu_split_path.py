@@ -234,6 +234,21 @@ def test_split_path_in_one_launch_and_in_phases(make, more):
     assert_close(run_gpu(wl, kernel_mode=2), run_oracle_c(wl), wl.kv_dtype, wl.name)
 
 
+# Items of more than 16 rows that are cut for phases but go in one launch, and beyond the bounds of 1536 workgroups (1024
+# with heads of 64) in phases.
+@pytest.mark.parametrize("make", [
+    lambda more: sw.tot_with_drafts(n_queries=24 + more, prompt=75, step=19, depth=2, drafts=6, heads=(40, 8, 128), token_trees=True),
+    lambda more: sw.tot_with_drafts(n_queries=12 + 8 * more, prompt=300, step=19, depth=2, drafts=6, heads=(40, 8, 64), kv_dtype="bf16",
+                                    q_dtype="bf16"),
+    lambda more: sw.bfs_tot(n_queries=68 + more, prompt=75, step=30, width=4, keep=4, depth=1, heads=(71, 1, 64)),
+    lambda more: _single_pieces(768 + more, heads=(40, 2, 128)),
+    lambda more: _single_pieces(512 + more, heads=(40, 2, 64), kv_dtype="fp8_e4m3")])
+@pytest.mark.parametrize("more", [0, 1])
+def test_items_of_two_row_tiles_together_and_in_phases(make, more):
+    wl = make(more)
+    assert_close(run_gpu(wl, kernel_mode=2), run_oracle_c(wl), wl.kv_dtype, wl.name)
+
+
 # More short items than run at a time (512 workgroups, 768 with heads of 64), which the form with one set of K and V
 # registers takes, and fewer; items of one page to 16 and beyond (the other form), of whole and of partial blocks; masks.
 @pytest.mark.parametrize("heads,kv_dtype", [((8, 2, 128), "fp8_e4m3"), ((8, 2, 64), "bf16"), ((12, 4, 64), "fp8_e4m3")])
