@@ -1909,7 +1909,7 @@ __device__ __forceinline__ bool beyond_pieces(const float (&pr)[2][4]) {
 constexpr int rowmajor_occupancy(int kv, int dp, int mode) {
   if (dp > 128) return kv == kFP8 ? 2 : 1;
   if (dp == 64 && kv == kF32 && mode == kRowFull) return 5;
-  return dp == 64 || (kv != kF32 && (mode == kRowFull || kv == kFP8)) ? 3 : 2;
+  return dp == 64 || kv != kF32 || mode == kRowFull ? 3 : 2;
 }
 
 template <int KV, int DP, int MODE>
@@ -1923,7 +1923,7 @@ __global__ __launch_bounds__(256, rowmajor_occupancy(KV, DP, MODE)) void spex_ro
   constexpr int NQ = KV == kF32 ? DP / 4 : DP / 8;  // Q registers
   constexpr int SUB = KV == kF32 ? 1 : 2;  // groups of 16 tokens per step
   constexpr int kFold = NO * 4 + 2;        // floats per lane a wavefront hands over
-  __shared__ float fold[3 * 64 * kFold];
+  __shared__ float fold[4 * 64 * kFold];
 
   const int lane = threadIdx.x & 63, m16 = lane & 15, jj = lane >> 4;
   const int w = uniform(threadIdx.x >> 6);
@@ -2061,9 +2061,14 @@ __global__ __launch_bounds__(256, rowmajor_occupancy(KV, DP, MODE)) void spex_ro
       nxt[j] = rec_of(step0 + SUB + j);
       load_scales(j, cur[j]);
       load_k(j, cur[j], step0 + j);
-      load_v(j, cur[j], step0 + j);
     }
     for (int st = step0; st < step1; st += SUB) {
+      // 16-bit and fp8 values go out before the keys are waited for: left to itself the compiler puts them behind the first
+      // MFMA (fp8 pages of 32 tokens 27.4 -> 26.6 us, heads 6/3/40 22.8 -> 21.9, bf16 heads of 96 33.6 -> 32.9; fp32
+      // 45.1 -> 45.8).
+#pragma unroll
+      for (int j = 0; j < SUB; ++j) load_v(j, cur[j], st + j);
+      if constexpr (KV != kF32) __builtin_amdgcn_sched_barrier(0);
       float x[SUB][4], vs_l[SUB], mx = kNegInf;
 #pragma unroll
       for (int j = 0; j < SUB; ++j) {
@@ -2219,7 +2224,6 @@ __global__ __launch_bounds__(256, rowmajor_occupancy(KV, DP, MODE)) void spex_ro
       }
 #pragma unroll
       for (int j = 0; j < SUB; ++j) {
-        load_v(j, nxt[j], st + SUB + j);
         cur[j] = nxt[j];
         nxt[j] = rec_of(st + 2 * SUB + j);
       }
@@ -2228,35 +2232,40 @@ __global__ __launch_bounds__(256, rowmajor_occupancy(KV, DP, MODE)) void spex_ro
   l += __shfl_xor(l, 16);  // the row sum is spread over the four lane groups
   l += __shfl_xor(l, 32);
 
-  // ---- the wavefronts of one row tile fold their states
+  // ---- output.  The wavefronts of one row tile fold their states through LDS: each leaves its own, and folds and stores
+  // a share of every row, its quarter or half of the registers r (against the first wavefront alone: heads 16/4/256
+  // 40.8 -> 38.4 us, fp8 29.1 -> 28.2; others within 1 %).
+  const int n_states = 1 << ks_log;
+  const float *states = fold + (rt << ks_log) * (64 * kFold) + lane;
+  float f[4] = {1.f, 0.f, 0.f, 0.f};
   if (ks_log > 0) {
-    if (ks > 0) {
-      float *f = fold + static_cast<int>(w - rt - 1) * (64 * kFold) + lane;
+    float *own = fold + w * (64 * kFold) + lane;
 #pragma unroll
-      for (int i = 0; i < NO; ++i)
+    for (int i = 0; i < NO; ++i)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) f[(i * 4 + r) * 64] = o[i][r];
-      f[NO * 4 * 64] = m;
-      f[(NO * 4 + 1) * 64] = l;
-    }
+      for (int r = 0; r < 4; ++r) own[(i * 4 + r) * 64] = o[i][r];
+    own[NO * 4 * 64] = m;
+    own[(NO * 4 + 1) * 64] = l;
     __syncthreads();
-    if (ks > 0) return;
-    for (int j = 1; j < (1 << ks_log); ++j) {
-      const float *f = fold + static_cast<int>(w + j - rt - 1) * (64 * kFold) + lane;
-      const float mj = f[NO * 4 * 64], m_new = fmaxf(m, mj);
-      const float fa = fast_exp2(m - m_new), fb = fast_exp2(mj - m_new);
-      m = m_new;
-      l = l * fa + f[(NO * 4 + 1) * 64] * fb;
+    float mv[4], lv[4];
 #pragma unroll
-      for (int i = 0; i < NO; ++i)
+    for (int v = 0; v < 4; ++v) {
+      const int at_v = v < n_states ? v : 0;
+      mv[v] = states[at_v * (64 * kFold) + NO * 4 * 64];
+      lv[v] = v < n_states ? states[at_v * (64 * kFold) + (NO * 4 + 1) * 64] : 0.f;
+    }
+    m = fmaxf(fmaxf(mv[0], mv[1]), fmaxf(mv[2], mv[3]));
+    l = 0.f;
 #pragma unroll
-        for (int r = 0; r < 4; ++r) o[i][r] = o[i][r] * fa + f[(i * 4 + r) * 64] * fb;
+    for (int v = 0; v < 4; ++v) {
+      f[v] = fast_exp2(mv[v] - m);
+      l += lv[v] * f[v];
     }
   }
   if (!row_ok) return;
   const int64_t slot = p.finish ? static_cast<int64_t>(qt) * sh.Hq + it.g * G + row % G
                                 : static_cast<int64_t>(it.pbase) + static_cast<int64_t>(it.g) * rows + row;
-  if (jj == 0) {
+  if (jj == 0 && ks == 0) {
     if (!p.finish)
       *reinterpret_cast<f32x2 *>(p.part_ml + slot * 2) = f32x2{m, l};
     else if (p.lse)
@@ -2265,13 +2274,32 @@ __global__ __launch_bounds__(256, rowmajor_occupancy(KV, DP, MODE)) void spex_ro
   const float norm = p.finish ? 1.0f / l : 1.0f;
   float *dst = (p.finish ? p.out : p.part_o) + slot * D;
   // the lane holds dims 16 VE c + 4 VE jj .. + 4 VE - 1 of its row
+  auto dim_of = [&](int c, int r, int h) { return 16 * VE * c + 4 * VE * jj + VE * r + 4 * h; };
+  if (ks_log > 0) {
+    const int r_end = (4 * (ks + 1)) >> ks_log;
+    for (int r = (4 * ks) >> ks_log; r < r_end; ++r)
+#pragma unroll
+      for (int c = 0; c < NC; ++c)
+#pragma unroll
+        for (int h = 0; h < VE / 4; ++h) {
+          f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+          for (int v = 0; v < 4; ++v)
+            if (v < n_states)  // uniform
+#pragma unroll
+              for (int e = 0; e < 4; ++e) acc[e] += states[v * (64 * kFold) + ((c * VE + 4 * h + e) * 4 + r) * 64] * f[v];
+          const int d = dim_of(c, r, h);
+          if (d < D) *reinterpret_cast<f32x4 *>(dst + d) = acc * norm;
+        }
+    return;
+  }
 #pragma unroll
   for (int c = 0; c < NC; ++c)
 #pragma unroll
     for (int r = 0; r < 4; ++r)
 #pragma unroll
       for (int h = 0; h < VE / 4; ++h) {
-        const int d = 16 * VE * c + 4 * VE * jj + VE * r + 4 * h;
+        const int d = dim_of(c, r, h);
         if (d < D)
           *reinterpret_cast<f32x4 *>(dst + d) =
               f32x4{o[c * VE + 4 * h][r], o[c * VE + 4 * h + 1][r], o[c * VE + 4 * h + 2][r], o[c * VE + 4 * h + 3][r]} * norm;
