@@ -220,6 +220,10 @@ struct PlanArrays {
         &pl.prefix_items, &pl.suffix_items, &pl.pg_rec, &pl.qt_rec,
         &pl.part_indptr, &pl.part_base,    &pl.part_hstride, &pl.merge_qt, &pl.coop_items[0], &pl.coop_items[1],
         &pl.walk_items, &pl.walk_blocks, &pl.walk_qt, &pl.qt_mask};
+    if (pl.merge_stride > 0) {  // the pieces' records in place of the arrays they are made of
+      all[4] = &pl.merge_rec;
+      all[5] = all[6] = &none;
+    }
     for (int i = 0; i < kPlanArrays; ++i) {
       const bool both = i == kPlanArrays - 1, of_walk = i >= 10;
       a[i] = both || of_walk == walk ? all[i] : &none;
@@ -954,7 +958,8 @@ static spex_status_t decode_attention_impl(spex_tree_t *t, const spex_node_t *le
   }
   HIP_TRY(bracket(0, false));
   spex::MergeArgs m{};
-  m.part_indptr = dp.part_indptr;
+  m.part_indptr = m.rec = dp.part_indptr;
+  m.stride = pl.merge_stride;
   m.part_base = dp.part_base;
   m.part_hstride = dp.part_hstride;
   m.part_o = part_o;

@@ -65,12 +65,15 @@ struct WalkArgs {
 };
 
 struct MergeArgs {
-  const int32_t *part_indptr, *part_base, *part_hstride;
+  const int32_t *part_indptr, *part_base, *part_hstride;  // or, where stride > 0:
+  const int32_t *rec;     // {base, hstride} of the query tokens' pieces, `stride` pairs each, base -1 behind the last one
+  int32_t stride;
   const float *part_o, *part_ml;
   float *out, *lse;
   const int32_t *qt_ids;  // query tokens to merge, or null for 0 .. n_qtok-1
   int32_t n_qtok;         // number of query tokens handled by the launch
   int32_t avg_pieces;     // pieces of an average query token (a hint for the launch shape)
+  bool heads_first;       // order of the workgroups; set by launch_merge
 };
 
 // Page ids travel in the kernel arguments.  128 pages (2048 tokens of 16-token pages) per launch: with
@@ -130,7 +133,7 @@ hipError_t launch_split(const Shape &sh, const AttnArgs &a, const ItemLists &lis
 hipError_t launch_split_phases(const Shape &sh, const AttnArgs &a, const ItemLists &lists, hipStream_t stream);
 // a.items / a.n_items on the vector ALU; any shape.
 hipError_t launch_generic_attention(const Shape &sh, const AttnArgs &a, int rows_per_item, hipStream_t stream);
-hipError_t launch_merge(const Shape &sh, const MergeArgs &a, hipStream_t stream);
+hipError_t launch_merge(const Shape &sh, const MergeArgs &args, hipStream_t stream);
 hipError_t launch_scatter(const Shape &sh, const ScatterArgs &a, hipStream_t stream);
 // fp8 pools: k_src / v_src hold bf16 values; page scales are computed (started pages) or reused.
 hipError_t launch_scatter_quantise(const Shape &sh, const ScatterArgs &a, hipStream_t stream);

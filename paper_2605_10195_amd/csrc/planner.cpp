@@ -474,6 +474,20 @@ PlanError Planner::ensure_split(const PageTable &pt, Plan *plan) {
     pl.part_indptr.push_back(static_cast<int32_t>(pl.part_base.size()));
   }
 
+  if (!pl.split_phases || pl.split_together) {
+    size_t most = 0;
+    for (const auto &lst : parts) most = std::max(most, lst.size());
+    if (2 * most * parts.size() <= pl.part_indptr.size() + 2 * pl.part_base.size()) {
+      pl.merge_stride = static_cast<int32_t>(most);
+      pl.merge_rec.reserve(2 * most * parts.size());
+      for (const auto &lst : parts)
+        for (size_t k = 0; k < most; ++k) {
+          pl.merge_rec.push_back(k < lst.size() ? lst[k].first : -1);
+          pl.merge_rec.push_back(k < lst.size() ? lst[k].second : 0);
+        }
+    }
+  }
+
   // ---- launch lists, heaviest tasks first
   const int32_t n_tasks = static_cast<int32_t>(pl.task_pbase.size());
   auto order_of = [&](int32_t lo, int32_t hi) {

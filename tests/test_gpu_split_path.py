@@ -27,6 +27,38 @@ def test_merge_of_many_and_few_pieces(heads, kv_dtype, chunk, prompt):
     assert_close(got, run_oracle(wl), kv_dtype, f"{heads} {kv_dtype} chunk {chunk} prompt {prompt}")
 
 
+# Pieces' records at a fixed stride (all query tokens with the same number, or one short of it, the rest filled up) and
+# through part_indptr (uneven prompts); 1, 3, 4, 8 and 16 kv heads; 2 to 24 heads each, more and fewer than the rows of a workgroup.
+@pytest.mark.parametrize("heads", [(2, 1, 64), (24, 1, 128), (12, 3, 40), (20, 4, 128), (8, 8, 64), (32, 16, 64)])
+@pytest.mark.parametrize("prompts", [(64, 64), (64, 64, 64, 48), (16, 300)])
+def test_merge_records_at_a_stride(heads, prompts):
+    import paper_2605_10195_amd as spex
+    gen = torch.Generator().manual_seed(len(prompts))
+    Hq, Hkv, D = heads
+    kv = "bf16" if D >= 64 else "f32"
+    dt = torch.bfloat16 if kv == "bf16" else torch.float32
+    t = spex.SpexTree(Hq, Hkv, D, 16, kv, kv, num_pages=200, device="cuda", kernel_mode=2, prefix_chunk_pages=1, suffix_chunk_pages=1)
+    leaves, paths = [], []
+    for n in prompts:
+        (root,) = t.fork(-1, 1)
+        k, v = (torch.randn((n, Hkv, D), generator=gen).to(dt) for _ in range(2))
+        t.append_step(root, k.cuda(), v.cuda())
+        for u in t.fork(root, 2):
+            ku, vu = (torch.randn((20, Hkv, D), generator=gen).to(dt) for _ in range(2))
+            t.append_step(u, ku.cuda(), vu.cuda())
+            leaves.append(u)
+            paths.append((torch.cat([k, ku]).double(), torch.cat([v, vu]).double()))
+    q = torch.randn((len(leaves), Hq, D), generator=gen).to(dt)
+    out, lse = t.decode_attention(leaves, None, q.cuda(), D ** -0.5)
+    for i, (k, v) in enumerate(paths):
+        s = torch.einsum("hd,thd->ht", q[i].double(), k.repeat_interleave(Hq // Hkv, dim=1)) * D ** -0.5
+        want = torch.einsum("ht,thd->hd", torch.softmax(s, dim=1), v.repeat_interleave(Hq // Hkv, dim=1))
+        tol = 1e-5 if kv == "f32" else 1e-3     # gpu_common.TOL
+        assert float((out[i].double().cpu() - want).norm() / want.norm()) <= tol
+        assert float((lse[i].double().cpu() - torch.logsumexp(s, dim=1)).abs().max()) <= tol
+    t.close()
+
+
 # Row-major pools: every type; head dims at and between the padded widths 64, 128 and 256; pages of 4
 # to 64 tokens (a 16-token step spans pages, or a page several steps); 1 to 140 rows per item (one,
 # two, four wavefronts per row tile, several groups of 64 rows); drafts with masks; fp8 rows of 8 and not of
