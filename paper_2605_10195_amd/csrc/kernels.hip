@@ -982,24 +982,30 @@ __device__ __forceinline__ void coop_item(const AttnArgs &p, const Shape &sh, co
 
 // All items of the split path in one launch: lists 0 and 1 hold groups of up to 128 and up to 64 rows
 // a span, lists 2 and 3 groups of up to 16 rows and private suffixes.
-// LEAN: for launches of many short items, none in list 0: three workgroups a compute unit where the other form holds two
+// kSplitLean: for launches of many short items, none in list 0: three workgroups a compute unit where the others hold two
 // (heads of 64: five and three).
-constexpr int split_occupancy(int d, int nt, bool lean) {
-  return d == 64 ? (lean ? 5 : 3) : (lean ? 3 : 2);
+// kSplitTiles: for launches that leave the chip room: items of many rows go as row tiles of 16 NT, a workgroup each that
+// splits the pages between its wavefronts, instead of one through LDS, whose blocks follow each other.  The tiles read the
+// pages again, from L2.
+enum SplitForm : int { kSplitFull, kSplitLean, kSplitTiles };
+constexpr int split_occupancy(int d, int nt, int form) {
+  return d == 64 ? (form == kSplitLean ? 5 : 3) : (form == kSplitLean ? 3 : 2);
 }
-template <int KV, int D, int NT, bool TREE, bool LEAN>
-__global__ __launch_bounds__(256, split_occupancy(D, NT, LEAN)) void spex_split_attn_kernel(AttnArgs p, Shape sh, SplitLists ls) {
-  constexpr int kLds = coop_lds_floats<D>() > wave_fold_floats<D>() ? coop_lds_floats<D>() : wave_fold_floats<D>();
+template <int KV, int D, int NT, bool TREE, int FORM>
+__global__ __launch_bounds__(256, split_occupancy(D, NT, FORM)) void spex_split_attn_kernel(AttnArgs p, Shape sh, SplitLists ls) {
+  constexpr int kLds = FORM != kSplitTiles && coop_lds_floats<D>() > wave_fold_floats<D>() ? coop_lds_floats<D>() : wave_fold_floats<D>();
   __shared__ __attribute__((aligned(16))) float lds[kLds];
   const ListPos at = list_of(ls, static_cast<int>(blockIdx.x));
-  const Item cur = load_item(at.items, at.local);
-  if (cur.pg_count == 0) return;  // padding item (whole workgroup)
-  if (!LEAN && at.k == 0)
+  const int tile = FORM == kSplitTiles ? at.local / at.n_items : 0;
+  Item cur = load_item(at.items, at.local - tile * at.n_items);
+  cur.row0 += tile * 16 * NT;
+  if (cur.pg_count == 0 || (FORM == kSplitTiles && cur.row0 >= cur.qt_count * sh.G)) return;  // whole workgroup: padding item, or no such tile
+  if (FORM == kSplitFull && at.k == 0)
     coop_item<KV, D, 2, TREE>(p, sh, cur, lds);
-  else if (at.k <= 1)
+  else if (FORM != kSplitTiles && at.k <= 1)
     coop_item<KV, D, 1, TREE>(p, sh, cur, lds);
   else
-    wave_item<KV, D, NT, TREE, true, false, NT == 1 && !LEAN>(p, sh, cur, lds);
+    wave_item<KV, D, NT, TREE, true, false, NT == 1 && FORM != kSplitLean>(p, sh, cur, lds);
 }
 
 // The same in launches of their own where there are items enough to fill the chip with a wavefront each (the
@@ -2988,33 +2994,40 @@ static SplitLists make_lists(const ItemLists &l, int rows_per_wg, int64_t *n_wg)
   return ls;
 }
 
-template <int KV, int D, int NT>
-static hipError_t launch_split_nt(const Shape &sh, const AttnArgs &a, const SplitLists &ls, int n_wg, int longest, hipStream_t stream) {
+template <int KV, int D, int NT, int FORM>
+static hipError_t launch_split_form(const Shape &sh, const AttnArgs &a, const SplitLists &ls, int n_wg, hipStream_t stream) {
   const dim3 grid(n_wg), block(256);
+  if (a.qt_mask)  // draft token trees: visibility masks per query
+    hipLaunchKernelGGL((spex_split_attn_kernel<KV, D, NT, true, FORM>), grid, block, 0, stream, a, sh, ls);
+  else
+    hipLaunchKernelGGL((spex_split_attn_kernel<KV, D, NT, false, FORM>), grid, block, 0, stream, a, sh, ls);
+  return hipGetLastError();
+}
+
+template <int KV, int D, int NT>
+static hipError_t launch_split_nt(const Shape &sh, const AttnArgs &a, const ItemLists &l, const SplitLists &ls, int n_wg, hipStream_t stream) {
+  // Tiles where all of them run at once, two workgroups a compute unit.  Through LDS / as tiles, us: a prompt of 4096 under 16
+  // rows bf16 12.2 / 9.5, fp8 13.9 / 10.5, prompts under 48 to 128 rows 14.6 / 10.3, 24.3 / 18.7; of 513 to 1024 tiles
+  // 14.5 / 12.7, 13.1 / 13.3, 14.2 / 17.7; of more 15.7 / 18.9, 22.7 / 28.2.
+  int64_t n_tiles = 0;
+  const SplitLists tiles = make_lists(l, 16 * NT, &n_tiles);
+  if (ls.wg_end[1] > 0 && n_tiles >= 0 && n_tiles <= 512)
+    return launch_split_form<KV, D, NT, kSplitTiles>(sh, a, tiles, static_cast<int>(n_tiles), stream);
   // More workgroups than run at a time in the other form, and no long items, which want their loads a block ahead.
   // bf16 heads of 128 read as fast with two workgroups a compute unit.  Times of both forms, us: fp8 heads of 128, items of 8
   // pages, 6144 workgroups 73.6 / 63.6, 1536 25.0 / 22.7, of 16 pages 768 18.5 / 16.4, of 128 pages 768 36.4 / 37.2;
   // heads of 64, 8 pages, 1536 23.3 / 21.2 (fp8 24.9 / 20.4); bf16 heads of 128, 16 pages, 3072 82.6 / 85.1.
   if constexpr (NT == 1 && !(KV == kBF16 && D == 128)) {
-    if (ls.wg_end[0] == 0 && n_wg > 256 * split_occupancy(D, NT, false) && longest <= 16) {
-      if (a.qt_mask)  // draft token trees: visibility masks per query
-        hipLaunchKernelGGL((spex_split_attn_kernel<KV, D, NT, true, true>), grid, block, 0, stream, a, sh, ls);
-      else
-        hipLaunchKernelGGL((spex_split_attn_kernel<KV, D, NT, false, true>), grid, block, 0, stream, a, sh, ls);
-      return hipGetLastError();
-    }
+    if (ls.wg_end[0] == 0 && n_wg > 256 * split_occupancy(D, NT, kSplitFull) && l.longest <= 16)
+      return launch_split_form<KV, D, NT, kSplitLean>(sh, a, ls, n_wg, stream);
   }
-  if (a.qt_mask)
-    hipLaunchKernelGGL((spex_split_attn_kernel<KV, D, NT, true, false>), grid, block, 0, stream, a, sh, ls);
-  else
-    hipLaunchKernelGGL((spex_split_attn_kernel<KV, D, NT, false, false>), grid, block, 0, stream, a, sh, ls);
-  return hipGetLastError();
+  return launch_split_form<KV, D, NT, kSplitFull>(sh, a, ls, n_wg, stream);
 }
 
 template <int KV, int D>
-static hipError_t launch_split_d(const Shape &sh, const AttnArgs &a, const SplitLists &ls, int n_wg, int longest, hipStream_t stream) {
-  return ls.span[2] <= 16 && ls.span[3] <= 16 ? launch_split_nt<KV, D, 1>(sh, a, ls, n_wg, longest, stream)
-                                              : launch_split_nt<KV, D, 2>(sh, a, ls, n_wg, longest, stream);
+static hipError_t launch_split_d(const Shape &sh, const AttnArgs &a, const ItemLists &l, const SplitLists &ls, int n_wg, hipStream_t stream) {
+  return ls.span[2] <= 16 && ls.span[3] <= 16 ? launch_split_nt<KV, D, 1>(sh, a, l, ls, n_wg, stream)
+                                              : launch_split_nt<KV, D, 2>(sh, a, l, ls, n_wg, stream);
 }
 
 template <int KV, int D, bool TREE>
@@ -3065,9 +3078,9 @@ hipError_t launch_split(const Shape &sh, const AttnArgs &a, const ItemLists &l, 
   if (n_wg == 0) return hipSuccess;
   const int n = static_cast<int>(n_wg);
   if (tiled && sh.kv_dtype == kBF16)
-    return sh.D == 64 ? launch_split_d<kBF16, 64>(sh, a, ls, n, l.longest, stream) : launch_split_d<kBF16, 128>(sh, a, ls, n, l.longest, stream);
+    return sh.D == 64 ? launch_split_d<kBF16, 64>(sh, a, l, ls, n, stream) : launch_split_d<kBF16, 128>(sh, a, l, ls, n, stream);
   if (tiled)
-    return sh.D == 64 ? launch_split_d<kFP8, 64>(sh, a, ls, n, l.longest, stream) : launch_split_d<kFP8, 128>(sh, a, ls, n, l.longest, stream);
+    return sh.D == 64 ? launch_split_d<kFP8, 64>(sh, a, l, ls, n, stream) : launch_split_d<kFP8, 128>(sh, a, l, ls, n, stream);
   if (sh.kv_dtype == kF32) return launch_rowmajor_kv<kF32>(sh, a, ls, n, stream);
   if (sh.kv_dtype == kBF16) return launch_rowmajor_kv<kBF16>(sh, a, ls, n, stream);
   return launch_rowmajor_kv<kFP8>(sh, a, ls, n, stream);

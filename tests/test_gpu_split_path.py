@@ -298,6 +298,32 @@ def test_many_short_items_with_draft_masks(heads, kv_dtype):
     assert_close(run_gpu(wl, kernel_mode=2), run_oracle_c(wl), kv_dtype, kv_dtype)
 
 
+# Prompts shared by 17 to 128 rows and more, as row tiles of 16 and of 32 (20 heads a kv head) in a workgroup each: the last
+# tile full, of one row and none at all (items of fewer rows than the list's span), chunks of one page, of a few and the planner's.
+@pytest.mark.parametrize("heads,kv_dtype", [((8, 2, 128), "bf16"), ((8, 2, 64), "fp8_e4m3"), ((20, 1, 64), "bf16"), ((20, 1, 128), "fp8_e4m3"),
+                                            ((17, 1, 128), "bf16")])
+@pytest.mark.parametrize("width", [2, 5, 8, 9, 16, 17, 33])
+@pytest.mark.parametrize("prompt,chunk", [(21, 0), (160, 3), (70, 1)])
+def test_items_of_many_rows_as_row_tiles(heads, kv_dtype, width, prompt, chunk):
+    wl = sw.bfs_tot(n_queries=1, prompt=prompt, step=20, width=width, keep=width, depth=1, heads=heads, kv_dtype=kv_dtype)
+    got = run_gpu(wl, kernel_mode=2, prefix_chunk_pages=chunk, suffix_chunk_pages=chunk)
+    assert_close(got, run_oracle_c(wl), kv_dtype, f"{heads} {kv_dtype} {width} {prompt}")
+
+
+# Either side of 512 row tiles: a prompt of 16 leaves takes 4 tiles of 16 rows (two of 32 with drafts' masks) a kv head
+# and each leaf one or two, beyond which the items of many rows go through LDS.
+@pytest.mark.parametrize("kv_dtype,dim", [("bf16", 128), ("fp8_e4m3", 64)])
+@pytest.mark.parametrize("drafts", [0, 5])
+@pytest.mark.parametrize("n_queries", [12, 13, 24, 26, 27])
+def test_items_of_many_rows_as_row_tiles_and_through_lds(kv_dtype, dim, drafts, n_queries):
+    if drafts:
+        wl = sw.tot_with_drafts(n_queries=n_queries, prompt=75, step=19, depth=2, drafts=drafts, heads=(10, 2, dim), kv_dtype=kv_dtype,
+                                token_trees=True)
+    else:
+        wl = sw.bfs_tot(n_queries=n_queries, prompt=40, step=20, width=16, keep=16, depth=1, heads=(8, 2, dim), kv_dtype=kv_dtype)
+    assert_close(run_gpu(wl, kernel_mode=2), run_oracle_c(wl), kv_dtype, f"{kv_dtype} {drafts} {n_queries}")
+
+
 @pytest.mark.parametrize("heads,kv_dtype,chunk", [((40, 2, 128), "bf16", 1), ((40, 2, 64), "fp8_e4m3", 2), ((34, 2, 128), "fp8_e4m3", 0)])
 def test_phases_with_interior_nodes_and_cut_suffixes(heads, kv_dtype, chunk):
     """Requested nodes with and without live children, some twice, suffixes in one piece and in several."""
