@@ -310,11 +310,11 @@ def test_items_of_many_rows_as_row_tiles(heads, kv_dtype, width, prompt, chunk):
     assert_close(got, run_oracle_c(wl), kv_dtype, f"{heads} {kv_dtype} {width} {prompt}")
 
 
-# Either side of 512 row tiles: a prompt of 16 leaves takes 4 tiles of 16 rows (two of 32 with drafts' masks) a kv head
-# and each leaf one or two, beyond which the items of many rows go through LDS.
+# Either side of 512 row tiles (of 16 rows and fp8 2048, heads of 64 1536): a prompt of 16 leaves takes 4 tiles of 16 rows (two
+# of 32 with drafts' masks) a kv head and each leaf one or two, beyond which the items of many rows go through LDS.
 @pytest.mark.parametrize("kv_dtype,dim", [("bf16", 128), ("fp8_e4m3", 64)])
 @pytest.mark.parametrize("drafts", [0, 5])
-@pytest.mark.parametrize("n_queries", [12, 13, 24, 26, 27])
+@pytest.mark.parametrize("n_queries", [12, 13, 24, 26, 27, 38, 39])
 def test_items_of_many_rows_as_row_tiles_and_through_lds(kv_dtype, dim, drafts, n_queries):
     if drafts:
         wl = sw.tot_with_drafts(n_queries=n_queries, prompt=75, step=19, depth=2, drafts=drafts, heads=(10, 2, dim), kv_dtype=kv_dtype,
