@@ -941,6 +941,7 @@ static spex_status_t decode_attention_impl(spex_tree_t *t, const spex_node_t *le
     il.span[k] = spans[k];
   }
   il.longest = pl.longest_streamed;
+  il.tiles = pl.split_tiles;
   a.part_indptr = dp.part_indptr;
   a.part_base = dp.part_base;
   a.part_hstride = dp.part_hstride;

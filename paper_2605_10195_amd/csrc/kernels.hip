@@ -3009,14 +3009,15 @@ static hipError_t launch_split_nt(const Shape &sh, const AttnArgs &a, const Item
   // Tiles where all of them run at once, two workgroups a compute unit.  Through LDS / as tiles, us: a prompt of 4096 under 16
   // rows bf16 12.2 / 9.5, fp8 13.9 / 10.5, prompts under 48 to 128 rows 14.6 / 10.3, 24.3 / 18.7; of 513 to 1024 tiles
   // 14.5 / 12.7, 13.1 / 13.3, 14.2 / 17.7; of more 15.7 / 18.9, 22.7 / 28.2.
-  // Up to four rounds of one set of 16 rows where a tile's page is small: the items through LDS take as long a block
-  // whatever its bytes.  fp8 heads of 128: 1344 tiles 41 / 25, 1728 34 / 26, 2016 43 / 35, 1280 27 / 23, 1920 33 / 31, 2560
-  // 35 / 42, 4480 50 / 57; fp8 heads of 64: 544 15.3 / 11.7, 1536 40 / 16, 2048 12.8 / 13.9; bf16 heads of 64: 544
-  // 13.3 / 11.7, 1536 33 / 24, 2176 20.3 / 20.5, 3072 35 / 44.
-  constexpr int64_t kMaxTiles = NT > 1 ? 512 : D == 64 ? 1536 : KV == kFP8 ? 2048 : 512;
+  // fp8, one set of 16 rows: up to four rounds (three with heads of 64), because the items through LDS take as long a block
+  // whatever its bytes.  Heads of 128: 1344 tiles 41 / 25, 1728 34 / 26, 2016 43 / 35, 1280 27 / 23, 1920 33 / 31, 2560
+  // 35 / 42, 4480 50 / 57; of 64: 544 15.3 / 11.7, 1408 35 / 22, 1536 40 / 16, 2048 12.8 / 13.9.  bf16 heads of 64 gain too
+  // little: 544 13.3 / 11.7, 1536 33 / 24, 1408 28 / 31, 2176 20.3 / 20.5, 3072 35 / 44.
+  // Items that were cut for tiles go so whatever their number.
+  constexpr int64_t kMaxTiles = NT > 1 || KV != kFP8 ? 512 : D == 64 ? 1536 : 2048;
   int64_t n_tiles = 0;
   const SplitLists tiles = make_lists(l, 16 * NT, &n_tiles);
-  if (ls.wg_end[1] > 0 && n_tiles >= 0 && n_tiles <= kMaxTiles)
+  if (ls.wg_end[1] > 0 && n_tiles >= 0 && (n_tiles <= kMaxTiles || (l.tiles && NT == 1)))
     return launch_split_form<KV, D, NT, kSplitTiles>(sh, a, tiles, static_cast<int>(n_tiles), stream);
   // More workgroups than run at a time in the other form, and no long items, which want their loads a block ahead.
   // bf16 heads of 128 read as fast with two workgroups a compute unit.  Times of both forms, us: fp8 heads of 128, items of 8

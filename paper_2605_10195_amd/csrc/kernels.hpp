@@ -124,6 +124,7 @@ struct ItemLists {
   const int32_t *items[4];
   int32_t n_items[4], span[4];
   int32_t longest;  // pages of the longest item of the last two lists
+  bool tiles;       // cut to go as row tiles of 16, a workgroup each
 };
 bool has_mfma_kernel(const Shape &sh);
 bool has_rowmajor_kernel(const Shape &sh, const AttnArgs &a);

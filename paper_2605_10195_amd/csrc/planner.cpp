@@ -46,22 +46,38 @@ int32_t clamp32(int64_t v, int32_t lo, int32_t hi) {
 //  * Up to 16 rows: when there are a great many.  8192 private items 293 us against 328 in phases, 32768
 //    1129 against 1108 (bf16) and 875 against 818 (fp8), 65536 2992 against 2862; head dim 64: 2048
 //    35.7 against 55, 8192 122 against 118 (bf16) and 132 against 119 (fp8).
+// Items that go as row tiles of 16, a workgroup each (fp8; private items of up to 16 rows): as many shared items as leave one
+// round of 512 workgroups (768 with heads of 64) with the private ones, at least 64, and longer ones than through LDS: a
+// workgroup splits its pages between wavefronts that have loads in flight, and every item's rows cost a partial state each.
+// Only while all tiles stay below kMostTiles; beyond, the items go through LDS, cut as above.  Items through LDS / tiles of the
+// same cut / of this one, us, heads of 128: two prompts of 6000 tokens under 32 rows 25 / 15.4 / 14.5, 64 rows 27 / 23 /
+// 17.4, 128 rows 36 / 42 / 27.7; of 12000 under 112 rows 39 / 39 / 26; 12 of 2000 under 64 rows 45 / 46 / 37; 20 of 6000
+// under 32 rows, two kv heads, 51 / 28 / 22; 24 of 2000 under 64 rows (3840 tiles) 66 / 90 / 76, through LDS.  Heads of 64:
+// 8 prompts of 3000 tokens under 128 rows 22 / 20.5 / 14.7.  bf16 gains little or loses: heads of 128, 128 rows 30 / 72 / 35;
+// of 64, 11 prompts of 8400 under 64 rows 28 / 31 / 35.
 constexpr int64_t kFineRows = 40960;
+constexpr int64_t kMostTiles = 2048;
 struct Run {
   int64_t pages;
   int32_t rows;  // query tokens * G
 };
 struct Chunks {
   int32_t prefix, suffix;  // pages
-  bool phases, together;
+  bool phases, together, tiles;
   int64_t partial_rows;
 };
 Chunks choose_chunks(const std::vector<Run> &groups, const std::vector<Run> &suffixes, int32_t num_kv_heads, int32_t page_size,
                      const PoolShape &pool, int32_t prefix_chunk, int32_t suffix_chunk) {
   int64_t weighted = 0, suffix_pages = 0;  // pages times spans of rows: work items if nothing were split
-  int32_t most_private = 0;
+  int64_t shared_pages = 0, tile_pages = 0;  // pages, pages times row tiles of 16
+  int32_t most_private = 0, most_shared = 0;
   auto spans = [](int64_t rows) { return rows <= 64 ? 1 : (rows + kWideSpan - 1) / kWideSpan; };
-  for (const Run &g : groups) weighted += g.pages * spans(g.rows);
+  for (const Run &g : groups) {
+    weighted += g.pages * spans(g.rows);
+    shared_pages += g.pages;
+    tile_pages += g.pages * ((g.rows + 15) / 16);
+    most_shared = std::max(most_shared, g.rows);
+  }
   for (const Run &s : suffixes) {
     suffix_pages += s.pages;
     most_private = std::max(most_private, s.rows);
@@ -100,6 +116,26 @@ Chunks choose_chunks(const std::vector<Run> &groups, const std::vector<Run> &suf
     c.phases = true;
   } else {
     c.together = false;
+  }
+  c.tiles = false;
+  if (pool.tiled && !tall && !c.phases && most_shared > 16 && tile_pages > 0 && prefix_chunk <= 0 && pool.kv_bytes == 1) {
+    int64_t private_wgs = 0, tiles = 0, partial = 0;
+    for (const Run &s : suffixes) {
+      private_wgs += (s.pages + c.suffix - 1) / c.suffix;
+      partial += (s.pages + c.suffix - 1) / c.suffix * s.rows;
+    }
+    private_wgs *= num_kv_heads;
+    const int64_t items = std::clamp<int64_t>(((pool.head_dim <= 64 ? 768 : 512) - private_wgs) * shared_pages / tile_pages, 64, 256);
+    const int32_t chunk = std::max(c.prefix, auto_chunk(shared_pages, items, 1, 256));
+    for (const Run &g : groups) {
+      tiles += (g.pages + chunk - 1) / chunk * ((g.rows + 15) / 16);
+      partial += (g.pages + chunk - 1) / chunk * g.rows;
+    }
+    if (tiles * num_kv_heads + private_wgs <= kMostTiles) {
+      c.tiles = true;
+      c.prefix = chunk;
+      c.partial_rows = partial * num_kv_heads;
+    }
   }
   return c;
 }
@@ -374,6 +410,7 @@ PlanError Planner::ensure_split(const PageTable &pt, Plan *plan) {
     pl.suffix_chunk_pages = c.suffix;
     pl.split_phases = c.phases;
     pl.split_together = c.together;
+    pl.split_tiles = c.tiles;
   }
 
   // ---- tasks

@@ -75,6 +75,7 @@ struct Plan {
   int32_t prefix_chunk_pages = 0, suffix_chunk_pages = 0;  // values used
   bool split_phases = false;  // tiled pools: items are cut for the split path's lists in launches of their own
   bool split_together = false;  // and few enough to go in one launch all the same
+  bool split_tiles = false;     // shared items cut to go as row tiles of 16, a workgroup each
 
   // ---- launch lists (device side).  A work item is kItemInts ints:
   //   {pg_begin, pg_count, qt_begin, qt_count, pbase, flags, kv_head, first_row}

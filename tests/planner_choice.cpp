@@ -208,6 +208,26 @@ int main() {
   CHECK(together(13, 8, 8, 32, 8, 128, 600) && !together(14, 8, 8, 32, 8, 128, 600), "1456 and 1568 workgroups, prompts of 38 pages");
   CHECK(!together(513, 16, 1, 8, 2, 128), "4 rows");
 
+  // shared items cut to go as row tiles of 16: pages of an item, 0 if they are not
+  auto tiles = [](int roots, int prompt, int branches, int dim, int kv_bytes, int chunk = 0) {
+    Forest f(roots * (1 + (prompt + 15) / 16 + 2 * branches), 16);
+    f.add(roots, prompt, branches, 20);
+    Made m(f, 32, 8, chunk), bf16(f, 32, 8, chunk);
+    m.planner.pool = {true, false, dim, kv_bytes};
+    CHECK(m.planner.ensure_split(f.pt, &m.plan) == PlanError::kOk, "split lists");
+    CHECK(bf16.planner.ensure_split(f.pt, &bf16.plan) == PlanError::kOk, "split lists");
+    CHECK(!bf16.plan.split_tiles, "bf16 heads of 128");
+    CHECK(m.plan.n_partial_rows <= bf16.plan.n_partial_rows, "%d prompts of %d: more partial rows", roots, prompt);
+    return m.plan.split_tiles ? m.plan.prefix_chunk_pages : 0;
+  };
+  CHECK(tiles(2, 6000, 8, 128, 1) == 32, "128 private items leave 192 of two tiles for 6000 pages and heads");
+  CHECK(tiles(2, 6000, 16, 64, 1) == 47, "256 private items leave 128 of four tiles, heads of 64");
+  CHECK(tiles(2, 6000, 32, 128, 1) == 94 && tiles(2, 6000, 32, 128, 2) == 0 && tiles(2, 6000, 8, 64, 2) == 0, "no room: 64 items; bf16");
+  CHECK(tiles(2, 300, 5, 64, 1) == 8, "short prompts: items of 8 pages");
+  CHECK(tiles(2, 6000, 4, 128, 1) == 0 && tiles(2, 6000, 5, 128, 1) > 0, "16 and 20 rows");
+  CHECK(tiles(2, 6000, 8, 128, 1, 24) == 0, "length given");
+  CHECK(tiles(12, 2000, 16, 128, 1) == 188 && tiles(13, 2000, 16, 128, 1) == 0, "1920 and 2080 tiles");
+
   if (failures == 0) std::printf("ok\n");
   return failures != 0;
 }

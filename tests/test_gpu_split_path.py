@@ -303,14 +303,14 @@ def test_many_short_items_with_draft_masks(heads, kv_dtype):
 @pytest.mark.parametrize("heads,kv_dtype", [((8, 2, 128), "bf16"), ((8, 2, 64), "fp8_e4m3"), ((20, 1, 64), "bf16"), ((20, 1, 128), "fp8_e4m3"),
                                             ((17, 1, 128), "bf16")])
 @pytest.mark.parametrize("width", [2, 5, 8, 9, 16, 17, 33])
-@pytest.mark.parametrize("prompt,chunk", [(21, 0), (160, 3), (70, 1)])
+@pytest.mark.parametrize("prompt,chunk", [(21, 0), (160, 3), (70, 1), (3001, 0)])
 def test_items_of_many_rows_as_row_tiles(heads, kv_dtype, width, prompt, chunk):
     wl = sw.bfs_tot(n_queries=1, prompt=prompt, step=20, width=width, keep=width, depth=1, heads=heads, kv_dtype=kv_dtype)
     got = run_gpu(wl, kernel_mode=2, prefix_chunk_pages=chunk, suffix_chunk_pages=chunk)
     assert_close(got, run_oracle_c(wl), kv_dtype, f"{heads} {kv_dtype} {width} {prompt}")
 
 
-# Either side of 512 row tiles (of 16 rows and fp8 2048, heads of 64 1536): a prompt of 16 leaves takes 4 tiles of 16 rows (two
+# Either side of 512 row tiles (fp8 of 16 rows 2048, heads of 64 1536): a prompt of 16 leaves takes 4 tiles of 16 rows (two
 # of 32 with drafts' masks) a kv head and each leaf one or two, beyond which the items of many rows go through LDS.
 @pytest.mark.parametrize("kv_dtype,dim", [("bf16", 128), ("fp8_e4m3", 64)])
 @pytest.mark.parametrize("drafts", [0, 5])
