@@ -12,8 +12,9 @@
 //       private suffix) and a set of query rows.  Items of many rows stage operand images in LDS as
 //       the tree-walk kernel does; items of few rows split their pages between four wavefronts that
 //       stream them from memory to registers (S^T = K Q^T and O^T = V^T P^T with MFMA 16x16x32,
-//       fp32 accumulation).  Every item keeps an online softmax per row and emits the partial state
-//       (m, l, o); a shared page is read once for all rows below it.
+//       fp32 accumulation).  Small launches, and fp8 ones of middle size, take the row tiles of the first kind the
+//       second way, a workgroup each.  Every item keeps an online softmax per row and emits the partial state
+//       (m, l, o); a shared page is read from memory once for all rows below it.
 //   spex_wave_attn_kernel / spex_coop_attn_kernel
 //       The same items in launches of their own, few rows (a wavefront an item) and many, where there
 //       are items enough; private items come last and finish the rows of suffixes in one piece.

@@ -21,7 +21,7 @@ int32_t clamp32(int64_t v, int32_t lo, int32_t hi) {
 // read back, and every item some 5 us of latency however short, so segments are cut only until
 // the launch has about 256 shared and 1024 private items of 128 tokens or more (a workgroup splits
 // an item's tokens between its wavefronts).  Measured (us a call, bf16, 32 / 8 heads of 128): 16
-// branches on a 512-token prompt 13.6 with shared items of 256 tokens, 11.7 with 128; one
+// branches on a 512-token prompt 13.6 with shared items of 256 tokens, 11.7 with 128, both through LDS; one
 // prompt of 16000 tokens 23.7 / 20.6 / 20.1 / 27.8 with 256 / 512 / 1024 / 2048, four of them
 // 73 / 66 / 60 / 57; private items of 128 or 256 tokens are within 3 % of each other.
 // Items shorter than 16 (shared) and 8 (private) pages only while the launch has at most kFineRows
@@ -598,7 +598,8 @@ PlanError Planner::ensure_split(const PageTable &pt, Plan *plan) {
 }
 
 // A fit over 165 forests (bf16 and fp8, 2 to 8 kv heads of 64 and 128, W = 2 to 3000 tree-walk workgroups),
-// each timed through both paths; see prefers_walk for how far it carries.  Shared items of more than 16 rows cost their blocks of 32 tokens through LDS, the others
+// each timed through both paths; see prefers_walk for how far it carries.  Shared items of more than 16 rows cost their blocks of 32 tokens through LDS (also where
+// they go as row tiles, which is faster: the estimate then errs to the tree-walk kernel), the others
 // the blocks' bytes, and every row of an item its partial state.
 float Planner::estimate_split(const PageTable &pt, const Plan &pl, float enough) {
   const int32_t head_dim = pool.head_dim, kv_bytes = pool.kv_bytes;
