@@ -51,6 +51,9 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
 constexpr float kNegInf = -__builtin_huge_valf();
+// Largest V page scale the fp16 operand images can hold: 448 * 146 = 65408 <= 65504.  A larger
+// scale is read as this one (the page's values shrink together instead of turning into infinities).
+constexpr float kMaxVScaleF16 = 146.0f;
 // Start value of the tree-walk kernel's softmax reference: finite, so that (-inf) - m stays -inf,
 // and so far below any score that the first visible score replaces it.
 constexpr float kWalkMInit = -1.0e30f;
@@ -566,8 +569,10 @@ constexpr int wave_fold_floats() { return 4 * (D / 16) * 256 + 4 * 16 * 2; }
 // block (130 and not 216 registers for fp8 heads of 128, 213 and not 392 with two row tiles).  K past the
 // last block is requested as well, by all lanes from one address: a copy of the step without it makes the compiler carry
 // the state over in 64 moves a step, which wait for the loads.
-template <int KV, int D, int NT, bool TREE, bool SPLIT, bool SUFFIX, bool DEEP>
-__device__ __forceinline__ void wave_item(const AttnArgs &p, const Shape &sh, const Item &cur, float *lds) {
+// CAP: V page scales above v_most are read as v_most, so that a node shared by many rows gives the same values as a row
+// tile and through LDS.
+template <int KV, int D, int NT, bool TREE, bool SPLIT, bool SUFFIX, bool DEEP, bool CAP = false>
+__device__ __forceinline__ void wave_item(const AttnArgs &p, const Shape &sh, const Item &cur, float *lds, float v_most = 0.f) {
   constexpr int ESZ = (KV == kFP8) ? 1 : 2;
   constexpr int TILE_BYTES = 16 * D * ESZ;
   const int lane = threadIdx.x & 63;
@@ -643,7 +648,7 @@ __device__ __forceinline__ void wave_item(const AttnArgs &p, const Shape &sh, co
     // This lane's score registers cover tokens 8*(jj&1) .. +7 of page A (jj < 2) or B.
     const int vp = jj < 2 ? bm.vp_a : bm.vp_b;
     block_math<TREE, KV == kBF16, D, NT>(st, kf, vf, task_masked || (bm.vp_b & 127) == 0, vp & 127, vp >> 7,
-                                         p.scale_log2 * rb.ks, rb.vs, refill_k);
+                                         p.scale_log2 * rb.ks, CAP ? fminf(rb.vs, v_most) : rb.vs, refill_k);
   };
 
   if (b_first < nblk) {
@@ -824,9 +829,6 @@ __device__ __forceinline__ void block_math_f16(const bf16x8 (&qf)[NT][D / 32], c
   }
 }
 
-// Largest V page scale the fp16 operand images can hold: 448 * 146 = 65408 <= 65504.  A larger
-// scale is read as this one (the page's values shrink together instead of turning into infinities).
-constexpr float kMaxVScaleF16 = 146.0f;
 // Smallest K page scale used in a product with a masked (-inf) score: a scale of 0 (an all-zero
 // page) would turn -inf into NaN; with this value the page's scores are 0 to within 1e-27.
 constexpr float kMinKScale = 1.0e-30f;
@@ -1006,7 +1008,8 @@ __global__ __launch_bounds__(256, split_occupancy(D, NT, FORM)) void spex_split_
   else if (FORM != kSplitTiles && at.k <= 1)
     coop_item<KV, D, 1, TREE>(p, sh, cur, lds);
   else
-    wave_item<KV, D, NT, TREE, true, false, NT == 1 && FORM != kSplitLean>(p, sh, cur, lds);
+    wave_item<KV, D, NT, TREE, true, false, NT == 1 && FORM != kSplitLean, KV == kFP8 && FORM == kSplitTiles>(
+        p, sh, cur, lds, at.k <= 1 ? kMaxVScaleF16 : __builtin_huge_valf());
 }
 
 // The same in launches of their own where there are items enough to fill the chip with a wavefront each (the

@@ -4,6 +4,7 @@ in fp32, the stated bf16 / fp8 bounds elsewhere."""
 
 import math
 
+import numpy as np
 import pytest
 import torch
 
@@ -322,6 +323,43 @@ def test_items_of_many_rows_as_row_tiles_and_through_lds(kv_dtype, dim, drafts, 
     else:
         wl = sw.bfs_tot(n_queries=n_queries, prompt=40, step=20, width=16, keep=16, depth=1, heads=(8, 2, dim), kv_dtype=kv_dtype)
     assert_close(run_gpu(wl, kernel_mode=2), run_oracle_c(wl), kv_dtype, f"{kv_dtype} {drafts} {n_queries}")
+
+
+# A V page scale above 146 is read as 146 in nodes shared by more than 16 rows, whether few of them go as row tiles or many
+# through LDS, bit for bit; in a branch of up to 16 rows it is read as given.
+@pytest.mark.parametrize("heads,queries,width", [((8, 2, 128), 1, 8), ((8, 2, 64), 1, 8), ((20, 1, 128), 1, 3), ((8, 2, 128), 40, 32), ((8, 2, 64), 40, 32)])
+def test_large_v_scales_of_nodes_shared_by_many_rows(heads, queries, width):
+    import paper_2605_10195_amd as spex
+    Hq, Hkv, D = heads
+    rng = np.random.default_rng(3)
+
+    def codes(n):
+        return torch.from_numpy(rng.integers(0, 0x7F, size=(n, Hkv, D), dtype=np.uint8)).cuda()
+
+    kr, vr, kb, vb = codes(40), codes(40), codes(20), codes(20)
+    q = torch.from_numpy(rng.standard_normal((queries * width, Hq, D)).astype(np.float32)).to(torch.bfloat16).cuda()
+
+    def run(root_scale, branch_scale):
+        t = spex.SpexTree(Hq, Hkv, D, 16, "bf16", "fp8_e4m3", num_pages=queries * (3 + 2 * width), device="cuda", kernel_mode=2)
+        ks = torch.full((3, Hkv), 1e-3, dtype=torch.float32, device="cuda")
+        leaves = []
+        for root in t.fork(-1, queries):
+            t.append_step(root, kr, vr, ks, torch.full_like(ks, root_scale))
+            for u in t.fork(root, width):
+                t.append_step(u, kb, vb, ks[:2], torch.full_like(ks[:2], branch_scale))
+                leaves.append(u)
+        out, _ = t.decode_attention(leaves, None, q, D ** -0.5)
+        torch.cuda.synchronize()
+        t.close()
+        return out
+
+    want = run(146.0, 1.0)
+    for scale in (147.0, 200.0, 1e4):
+        assert torch.equal(run(scale, 1.0), want), scale
+    if Hq // Hkv <= 16:
+        # root values 0: the output is the branch's share, linear in its scale
+        a, b = run(0.0, 100.0).double(), run(0.0, 400.0).double()
+        assert float((b - 4 * a).norm() / b.norm()) <= 1e-6
 
 
 @pytest.mark.parametrize("heads,kv_dtype,chunk", [((40, 2, 128), "bf16", 1), ((40, 2, 64), "fp8_e4m3", 2), ((34, 2, 128), "fp8_e4m3", 0)])
