@@ -35,8 +35,8 @@
 //   spex_patch_plan_kernel
 //       Applies {index, value} patches to the device copy of the cached launch lists.
 #include "kernels.hpp"
+#include "launch_shape.hpp"
 
-#include <algorithm>
 #include <climits>
 
 namespace spex {
@@ -2318,27 +2318,31 @@ __global__ __launch_bounds__(256, rowmajor_occupancy(KV, DP, MODE)) void spex_ro
 }
 
 // ---- merge -----------------------------------------------------------------------------------
-// One row (query token, query head) per slices * D / VEC threads, threadIdx = (vector of the row, slice, row): slice s
-// folds pieces s, s + slices, .. of the row, a thread VEC consecutive dims, and the slices are folded
+// One row (query token, query head) per slices * D / VEC threads, threadIdx = (vector of the row, slice and query token,
+// query head): slice s folds pieces s, s + slices, .. of the row, a thread VEC consecutive dims, and the slices are folded
 // through LDS.  Bound by latency, not bytes: a piece is a chain of dependent reads (its slot, then m, l and o), so
 // four pieces of a slice are requested together and the row's pieces are spread over the slices; where the pieces'
 // records lie at a fixed stride the chain is one read shorter than through part_indptr.  One query of 16 branches, 12.2 us
 // a call: 11.3 so and without divisions, 10.9 with the kv heads on their XCDs.
-constexpr int kMergeBatch = 4;
-
+// Where a kv head has few query heads a workgroup takes several query tokens, as many as fill its 256 threads: with one the
+// LDS arrays let a compute unit hold 26 workgroups of 16 to 64 threads.  4096 query tokens, this kernel alone, us, with one
+// token a workgroup / several: heads 32/32/128 71.8 / 41.1, 16/16/64 37.0 / 15.9, 6/3/40 9.7 / 7.3, 8/4/64 11.7 / 8.9,
+// 12/4/96 16.6 / 14.5, 24/8/128 37.9 / 32.2; 4 and more heads a kv head of 128 as before (32/8 41.2 / 41.6, 28/4 40.7 / 40.9).
+// Up to 128 threads only: 12/4/96 16.9, 24/8/128 38.0, the others the same; 64: 32/32/128 43.9, 16/16/64 16.5.
 template <int VEC>
-__global__ __launch_bounds__(256) void spex_lse_merge_kernel(MergeArgs a, Shape sh) {
-  __shared__ __attribute__((aligned(16))) float lds_o[256 * VEC];
-  __shared__ float lds_ml[256][2];
-  const int dv = static_cast<int>(blockDim.x), slices = static_cast<int>(blockDim.y);
-  const int c = static_cast<int>(threadIdx.x), s = static_cast<int>(threadIdx.y);
-  const int tid = (static_cast<int>(threadIdx.z) * slices + s) * dv + c;
+__global__ __launch_bounds__(kMergeThreads) void spex_lse_merge_kernel(MergeArgs a, Shape sh) {
+  __shared__ __attribute__((aligned(16))) float lds_o[kMergeThreads * VEC];
+  __shared__ float lds_ml[kMergeThreads][2];
+  const int dv = static_cast<int>(blockDim.x), slices = 1 << a.slice_log2, tokens = static_cast<int>(blockDim.y) >> a.slice_log2;
+  const int c = static_cast<int>(threadIdx.x), s = static_cast<int>(threadIdx.y) & (slices - 1);
+  const int tid = (static_cast<int>(threadIdx.z) * static_cast<int>(blockDim.y) + static_cast<int>(threadIdx.y)) * dv + c;
   // With 8 kv heads (or a multiple) they come fastest, as in the items: a row's pieces were then written on the XCD that
   // reads them.  Otherwise the query tokens do.
-  const int qi = static_cast<int>(a.heads_first ? blockIdx.z : blockIdx.x), g = static_cast<int>(a.heads_first ? blockIdx.x : blockIdx.y);
+  const int qi = static_cast<int>(a.heads_first ? blockIdx.z : blockIdx.x) * tokens + (static_cast<int>(threadIdx.y) >> a.slice_log2);
+  const int g = static_cast<int>(a.heads_first ? blockIdx.x : blockIdx.y);
   const int hh = static_cast<int>((a.heads_first ? blockIdx.y : blockIdx.z) * blockDim.z + threadIdx.z);
-  const bool live = hh < sh.G;
-  const int qt = a.qt_ids ? a.qt_ids[qi] : qi;
+  const bool live = hh < sh.G && qi < a.n_qtok;
+  const int qt = a.qt_ids && live ? a.qt_ids[qi] : qi;
   const int64_t orow = static_cast<int64_t>(qt) * sh.Hq + g * sh.G + hh;
   float m = kNegInf, l = 0.f, acc[VEC];
 #pragma unroll
@@ -3176,17 +3180,12 @@ hipError_t launch_patch(int32_t *blob, const int32_t *pairs, int32_t n, hipStrea
 hipError_t launch_merge(const Shape &sh, const MergeArgs &args, hipStream_t stream) {
   MergeArgs a = args;
   if (a.n_qtok <= 0) return hipSuccess;
-  const int vec = (sh.D % 4 == 0) ? 4 : 1;
-  // Slices per row: one per kMergeBatch pieces of the average row, so that a slice runs one or two
-  // rounds, as many as 256 threads hold.
-  const int dv = sh.D / vec;
-  int slices = 1;
-  while (slices < 8 && slices * 2 * dv <= 256 && slices * kMergeBatch < a.avg_pieces) slices *= 2;
-  const int rpw = std::min(256 / (dv * slices), sh.G);
-  const unsigned n = static_cast<unsigned>(a.n_qtok), heads = static_cast<unsigned>(sh.Hkv), parts = static_cast<unsigned>((sh.G + rpw - 1) / rpw);
-  a.heads_first = sh.Hkv % 8 == 0 && n <= 65535;
-  const dim3 grid = a.heads_first ? dim3(heads, parts, n) : dim3(n, heads, parts), block(dv, slices, rpw);
-  if (vec == 4)
+  const MergeShape m = merge_shape(sh.Hkv, sh.G, sh.D, a.n_qtok, a.avg_pieces);
+  a.heads_first = m.heads_first;
+  a.slice_log2 = m.slice_log2;
+  const unsigned n = static_cast<unsigned>((static_cast<int64_t>(a.n_qtok) + m.tokens - 1) / m.tokens), heads = static_cast<unsigned>(sh.Hkv), parts = static_cast<unsigned>(m.parts);
+  const dim3 grid = m.heads_first ? dim3(heads, parts, n) : dim3(n, heads, parts), block(m.dv, m.tokens << m.slice_log2, m.rows);
+  if (m.vec == 4)
     hipLaunchKernelGGL(spex_lse_merge_kernel<4>, grid, block, 0, stream, a, sh);
   else
     hipLaunchKernelGGL(spex_lse_merge_kernel<1>, grid, block, 0, stream, a, sh);

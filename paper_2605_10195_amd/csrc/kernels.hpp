@@ -73,7 +73,8 @@ struct MergeArgs {
   const int32_t *qt_ids;  // query tokens to merge, or null for 0 .. n_qtok-1
   int32_t n_qtok;         // number of query tokens handled by the launch
   int32_t avg_pieces;     // pieces of an average query token (a hint for the launch shape)
-  bool heads_first;       // order of the workgroups; set by launch_merge
+  bool heads_first;       // order of the workgroups and log2 of the slices of a row; set by launch_merge
+  int32_t slice_log2;
 };
 
 // Page ids travel in the kernel arguments.  128 pages (2048 tokens of 16-token pages) per launch: with

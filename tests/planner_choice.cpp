@@ -5,6 +5,7 @@
 #include <cstdio>
 #include <vector>
 
+#include "../paper_2605_10195_amd/csrc/launch_shape.hpp"
 #include "../paper_2605_10195_amd/csrc/planner.hpp"
 
 using namespace spex;
@@ -227,6 +228,21 @@ int main() {
   CHECK(tiles(2, 6000, 4, 128, 1) == 0 && tiles(2, 6000, 5, 128, 1) > 0, "16 and 20 rows");
   CHECK(tiles(2, 6000, 8, 128, 1, 24) == 0, "length given");
   CHECK(tiles(12, 2000, 16, 128, 1) == 188 && tiles(13, 2000, 16, 128, 1) == 0, "1920 and 2080 tiles");
+
+  // merge workgroups: within 256 threads, every row in one of them, and more than half full wherever there are rows enough
+  for (int Hkv : {1, 3, 8, 32})
+    for (int G : {1, 2, 3, 4, 7, 8, 20, 71})
+      for (int D : {1, 30, 40, 64, 96, 128, 255, 256})
+        for (int64_t n : {1, 7, 512, 70000})
+          for (int pieces : {2, 6, 40}) {
+            const MergeShape m = merge_shape(Hkv, G, D, n, pieces);
+            CHECK(m.threads() <= kMergeThreads && m.dv * m.vec == D && m.rows >= 1 && m.tokens >= 1 && m.tokens <= n, "%d %d %d", G, D, pieces);
+            CHECK(m.rows * m.parts >= G && m.rows * (m.parts - 1) < G, "%d %d %d", G, D, pieces);
+            CHECK(2 * m.threads() > kMergeThreads || m.tokens == n, "%d heads a kv head of %d, %d pieces: %d threads", G, D, pieces,
+                  m.threads());
+            const bool eighths = Hkv % 8 == 0;
+            CHECK(!m.heads_first || (eighths && n <= 65535), "the grid's third dimension");
+          }
 
   if (failures == 0) std::printf("ok\n");
   return failures != 0;

@@ -60,6 +60,25 @@ def test_merge_records_at_a_stride(heads, prompts):
     t.close()
 
 
+# Merge workgroups of several query tokens (1 to 3 heads a kv head): fewer query tokens than one holds, as many, one more and many, in 1
+# to 8 slices; the last case in phases, which merge a list of query tokens.
+@pytest.mark.parametrize("heads,kv_dtype", [((8, 8, 64), "bf16"), ((16, 8, 128), "bf16"), ((6, 3, 40), "f32"), ((2, 2, 1), "f32"), ((3, 3, 255), "f32"),
+                                            ((12, 4, 96), "fp8_e4m3")])
+@pytest.mark.parametrize("queries,width,prompt,chunk", [(1, 1, 40, 1), (1, 5, 200, 1), (3, 5, 20, 0), (4, 4, 20, 0), (11, 3, 20, 0), (24, 11, 70, 2)])
+def test_merge_of_several_query_tokens(heads, kv_dtype, queries, width, prompt, chunk):
+    wl = sw.bfs_tot(n_queries=queries, prompt=prompt, step=21, width=width, keep=width, depth=1, heads=heads, kv_dtype=kv_dtype,
+                    q_dtype="f32" if kv_dtype == "f32" else "bf16")
+    got = run_gpu(wl, prefix_chunk_pages=chunk, suffix_chunk_pages=chunk, kernel_mode=2)
+    assert_close(got, run_oracle_c(wl), kv_dtype, f"{heads} {kv_dtype} {queries} x {width}")
+
+
+@pytest.mark.parametrize("heads", [(8, 8, 64), (16, 8, 64)])
+def test_merge_list_of_several_query_tokens_a_workgroup(heads):
+    wl = sw.random_trace(78, heads=heads, n_ops=1200, n_roots=250)
+    got = run_gpu(wl, kernel_mode=2, prefix_chunk_pages=1, suffix_chunk_pages=3)
+    assert_close(got, run_oracle_c(wl), "bf16", f"{heads}")
+
+
 # Row-major pools: every type; head dims at and between the padded widths 64, 128 and 256; pages of 4
 # to 64 tokens (a 16-token step spans pages, or a page several steps); 1 to 140 rows per item (one,
 # two, four wavefronts per row tile, several groups of 64 rows); drafts with masks; fp8 rows of 8 and not of
