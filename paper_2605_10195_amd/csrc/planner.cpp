@@ -514,14 +514,21 @@ PlanError Planner::ensure_split(const PageTable &pt, Plan *plan) {
   if (!pl.split_phases || pl.split_together) {
     size_t most = 0;
     for (const auto &lst : parts) most = std::max(most, lst.size());
-    if (2 * most * parts.size() <= pl.part_indptr.size() + 2 * pl.part_base.size()) {
+    // most == 1: every row is finished by its item
+    if (most > 1 && 2 * most * parts.size() <= pl.part_indptr.size() + 2 * pl.part_base.size()) {
       pl.merge_stride = static_cast<int32_t>(most);
-      pl.merge_rec.reserve(2 * most * parts.size());
-      for (const auto &lst : parts)
-        for (size_t k = 0; k < most; ++k) {
-          pl.merge_rec.push_back(k < lst.size() ? lst[k].first : -1);
-          pl.merge_rec.push_back(k < lst.size() ? lst[k].second : 0);
+      pl.merge_rec.resize(2 * most * parts.size());
+      int32_t *rec = pl.merge_rec.data();
+      for (const auto &lst : parts) {
+        for (const auto &e : lst) {
+          *rec++ = e.first;
+          *rec++ = e.second;
         }
+        for (size_t k = lst.size(); k < most; ++k) {
+          *rec++ = -1;
+          *rec++ = 0;
+        }
+      }
     }
   }
 

@@ -67,7 +67,8 @@ struct Plan {
   std::vector<int32_t> pg_id, pg_valid, pg_pos, qt_list;
   std::vector<int32_t> part_indptr, part_base, part_hstride, merge_qt;
   // One launch and merge: {part_base, part_hstride} of every query token's pieces at a stride of merge_stride pairs, base -1
-  // behind the last one.  Only where that takes no more room than the three arrays (else empty, stride 0).
+  // behind the last one.  Only where some row has several pieces and that takes no more room than the three arrays (else empty,
+  // stride 0).
   std::vector<int32_t> merge_rec;
   int32_t merge_stride = 0;
   int32_t n_prefix_tasks = 0;

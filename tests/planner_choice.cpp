@@ -209,6 +209,28 @@ int main() {
   CHECK(together(13, 8, 8, 32, 8, 128, 600) && !together(14, 8, 8, 32, 8, 128, 600), "1456 and 1568 workgroups, prompts of 38 pages");
   CHECK(!together(513, 16, 1, 8, 2, 128), "4 rows");
 
+  // pieces' records at a stride: pairs a query token, 0 where nothing is merged (every row in one piece) or where they
+  // would take more room
+  auto stride = [](int roots, int prompt, int branches, int more) {
+    Forest f(2 * roots * (2 + prompt / 16 + branches * 2) + more / 16 + 1, 16);
+    f.add(roots, prompt, branches, 20);
+    if (more > 0) f.add(1, more, 0, 0);
+    Made m(f, 8, 2, 1, 1);
+    CHECK(m.planner.ensure_split(f.pt, &m.plan) == PlanError::kOk, "split lists");
+    CHECK(static_cast<int>(m.plan.merge_rec.size()) == 2 * m.plan.merge_stride * static_cast<int>(f.leaves.size()), "%d roots", roots);
+    for (size_t t = 0; t < f.leaves.size() && m.plan.merge_stride > 0; ++t)
+      for (int k = 0; k < m.plan.merge_stride; ++k) {
+        const int e = m.plan.part_indptr[t] + k;
+        const bool there = e < m.plan.part_indptr[t + 1];
+        const int32_t *rec = &m.plan.merge_rec[2 * (t * m.plan.merge_stride + k)];
+        CHECK(rec[0] == (there ? m.plan.part_base[e] : -1) && (!there || rec[1] == m.plan.part_hstride[e]), "%d roots", roots);
+      }
+    return m.plan.merge_stride;
+  };
+  CHECK(stride(3, 40, 4, 0) == 5 && stride(20, 40, 4, 33) == 5, "prompts of 3 pages, branches of 2, a prompt alone of 3");
+  CHECK(stride(3, 40, 4, 400) == 0, "a prompt alone of 25 pages");
+  CHECK(stride(5, 16, 0, 0) == 0, "one piece each");
+
   // shared items cut to go as row tiles of 16: pages of an item, 0 if they are not
   auto tiles = [](int roots, int prompt, int branches, int dim, int kv_bytes, int chunk = 0) {
     Forest f(roots * (1 + (prompt + 15) / 16 + 2 * branches), 16);
