@@ -2336,8 +2336,6 @@ __global__ __launch_bounds__(kMergeThreads) void spex_lse_merge_kernel(MergeArgs
   const int dv = static_cast<int>(blockDim.x), slices = 1 << a.slice_log2, tokens = static_cast<int>(blockDim.y) >> a.slice_log2;
   const int c = static_cast<int>(threadIdx.x), s = static_cast<int>(threadIdx.y) & (slices - 1);
   const int tid = (static_cast<int>(threadIdx.z) * static_cast<int>(blockDim.y) + static_cast<int>(threadIdx.y)) * dv + c;
-  // With 8 kv heads (or a multiple) they come fastest, as in the items: a row's pieces were then written on the XCD that
-  // reads them.  Otherwise the query tokens do.
   const int qi = static_cast<int>(a.heads_first ? blockIdx.z : blockIdx.x) * tokens + (static_cast<int>(threadIdx.y) >> a.slice_log2);
   const int g = static_cast<int>(a.heads_first ? blockIdx.x : blockIdx.y);
   const int hh = static_cast<int>((a.heads_first ? blockIdx.y : blockIdx.z) * blockDim.z + threadIdx.z);

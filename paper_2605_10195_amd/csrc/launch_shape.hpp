@@ -30,7 +30,11 @@ inline MergeShape merge_shape(int32_t num_kv_heads, int32_t heads_per_kv, int32_
   s.rows = std::min(room, heads_per_kv);
   s.parts = (heads_per_kv + s.rows - 1) / s.rows;
   s.tokens = static_cast<int32_t>(std::min<int64_t>(room / s.rows, n_qtok));
-  s.heads_first = num_kv_heads % 8 == 0 && n_qtok <= 65535;
+  // kv heads before query tokens in the grid where they are a multiple of 4: a kv head's workgroups then run on the one or two
+  // XCDs that had its items.  Query tokens first / kv heads first, us a call, medians of 7 runs: heads 16/4/128 26.8 / 24.8,
+  // 15.0 / 14.0, 22.4 / 19.6, 28/4/128 20.5 / 19.2, 33.5 / 32.0; with 2, 3 and 6 kv heads either may win: 8/2/128
+  // 12.4 / 13.0, 18.8 / 18.7, 16/2/64 11.5 / 12.1, 16.9 / 16.4, 12/3/128 13.6 / 14.0, 18.6 / 18.2, 24/6/128 20.2 / 21.0, 34.7 / 33.8.
+  s.heads_first = num_kv_heads % 4 == 0 && n_qtok <= 65535;
   return s;
 }
 

@@ -252,7 +252,7 @@ int main() {
   CHECK(tiles(12, 2000, 16, 128, 1) == 188 && tiles(13, 2000, 16, 128, 1) == 0, "1920 and 2080 tiles");
 
   // merge workgroups: within 256 threads, every row in one of them, and more than half full wherever there are rows enough
-  for (int Hkv : {1, 3, 8, 32})
+  for (int Hkv : {1, 3, 4, 32})
     for (int G : {1, 2, 3, 4, 7, 8, 20, 71})
       for (int D : {1, 30, 40, 64, 96, 128, 255, 256})
         for (int64_t n : {1, 7, 512, 70000})
@@ -262,8 +262,8 @@ int main() {
             CHECK(m.rows * m.parts >= G && m.rows * (m.parts - 1) < G, "%d %d %d", G, D, pieces);
             CHECK(2 * m.threads() > kMergeThreads || m.tokens == n, "%d heads a kv head of %d, %d pieces: %d threads", G, D, pieces,
                   m.threads());
-            const bool eighths = Hkv % 8 == 0;
-            CHECK(!m.heads_first || (eighths && n <= 65535), "the grid's third dimension");
+            const bool fours = Hkv % 4 == 0;
+            CHECK(m.heads_first == (fours && n <= 65535), "%d kv heads, %d query tokens", Hkv, static_cast<int>(n));
           }
 
   if (failures == 0) std::printf("ok\n");
