@@ -2326,21 +2326,22 @@ __global__ __launch_bounds__(256, rowmajor_occupancy(KV, DP, MODE)) void spex_ro
 // a call: 11.3 so and without divisions, 10.9 with the kv heads on their XCDs.
 // Where a kv head has few query heads a workgroup takes several query tokens, as many as fill its 256 threads: with one the
 // LDS arrays let a compute unit hold 26 workgroups of 16 to 64 threads.  4096 query tokens, this kernel alone, us, with one
-// token a workgroup / several: heads 32/32/128 71.8 / 41.1, 16/16/64 37.0 / 15.9, 6/3/40 9.7 / 7.3, 8/4/64 11.7 / 8.9,
-// 12/4/96 16.6 / 14.5, 24/8/128 37.9 / 32.2; 4 and more heads a kv head of 128 as before (32/8 41.2 / 41.6, 28/4 40.7 / 40.9).
-// Up to 128 threads only: 12/4/96 16.9, 24/8/128 38.0, the others the same; 64: 32/32/128 43.9, 16/16/64 16.5.
-template <int VEC>
+// token a workgroup / several: heads 32/32/128 71.8 / 41.1, 16/16/64 37.0 / 15.9, 6/3/40 9.7 / 7.2, 8/4/64 11.7 / 9.0,
+// 12/4/96 16.6 / 14.3, 24/8/128 37.8 / 32.2.  Up to 128 threads only: 12/4/96 16.9, 24/8/128 38.0, the others the same.
+// MANY: several query tokens a workgroup.
+template <int VEC, bool MANY>
 __global__ __launch_bounds__(kMergeThreads) void spex_lse_merge_kernel(MergeArgs a, Shape sh) {
   __shared__ __attribute__((aligned(16))) float lds_o[kMergeThreads * VEC];
   __shared__ float lds_ml[kMergeThreads][2];
-  const int dv = static_cast<int>(blockDim.x), slices = 1 << a.slice_log2, tokens = static_cast<int>(blockDim.y) >> a.slice_log2;
-  const int c = static_cast<int>(threadIdx.x), s = static_cast<int>(threadIdx.y) & (slices - 1);
+  const int dv = static_cast<int>(blockDim.x), slices = MANY ? 1 << a.slice_log2 : static_cast<int>(blockDim.y);
+  const int c = static_cast<int>(threadIdx.x), s = MANY ? static_cast<int>(threadIdx.y) & (slices - 1) : static_cast<int>(threadIdx.y);
   const int tid = (static_cast<int>(threadIdx.z) * static_cast<int>(blockDim.y) + static_cast<int>(threadIdx.y)) * dv + c;
-  const int qi = static_cast<int>(a.heads_first ? blockIdx.z : blockIdx.x) * tokens + (static_cast<int>(threadIdx.y) >> a.slice_log2);
+  int qi = static_cast<int>(a.heads_first ? blockIdx.z : blockIdx.x);  // uniform unless MANY: what hangs on it alone are scalar loads
+  if (MANY) qi = qi * (static_cast<int>(blockDim.y) >> a.slice_log2) + (static_cast<int>(threadIdx.y) >> a.slice_log2);
   const int g = static_cast<int>(a.heads_first ? blockIdx.x : blockIdx.y);
   const int hh = static_cast<int>((a.heads_first ? blockIdx.y : blockIdx.z) * blockDim.z + threadIdx.z);
-  const bool live = hh < sh.G && qi < a.n_qtok;
-  const int qt = a.qt_ids && live ? a.qt_ids[qi] : qi;
+  const bool live = hh < sh.G && (!MANY || qi < a.n_qtok);
+  const int qt = a.qt_ids && (!MANY || live) ? a.qt_ids[qi] : qi;
   const int64_t orow = static_cast<int64_t>(qt) * sh.Hq + g * sh.G + hh;
   float m = kNegInf, l = 0.f, acc[VEC];
 #pragma unroll
@@ -3183,10 +3184,9 @@ hipError_t launch_merge(const Shape &sh, const MergeArgs &args, hipStream_t stre
   a.slice_log2 = m.slice_log2;
   const unsigned n = static_cast<unsigned>((static_cast<int64_t>(a.n_qtok) + m.tokens - 1) / m.tokens), heads = static_cast<unsigned>(sh.Hkv), parts = static_cast<unsigned>(m.parts);
   const dim3 grid = m.heads_first ? dim3(heads, parts, n) : dim3(n, heads, parts), block(m.dv, m.tokens << m.slice_log2, m.rows);
-  if (m.vec == 4)
-    hipLaunchKernelGGL(spex_lse_merge_kernel<4>, grid, block, 0, stream, a, sh);
-  else
-    hipLaunchKernelGGL(spex_lse_merge_kernel<1>, grid, block, 0, stream, a, sh);
+  const auto kernel = m.vec == 4 ? (m.tokens > 1 ? spex_lse_merge_kernel<4, true> : spex_lse_merge_kernel<4, false>)
+                                 : (m.tokens > 1 ? spex_lse_merge_kernel<1, true> : spex_lse_merge_kernel<1, false>);
+  hipLaunchKernelGGL(kernel, grid, block, 0, stream, a, sh);
   return hipGetLastError();
 }
 

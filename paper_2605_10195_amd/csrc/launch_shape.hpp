@@ -26,12 +26,14 @@ inline MergeShape merge_shape(int32_t num_kv_heads, int32_t heads_per_kv, int32_
   s.dv = head_dim / s.vec;
   // One slice per kMergeBatch pieces of the average row, so that a slice runs one or two batches.
   while (s.slice_log2 < 3 && (s.dv << (s.slice_log2 + 1)) <= kMergeThreads && (kMergeBatch << s.slice_log2) < avg_pieces) ++s.slice_log2;
-  const int32_t room = kMergeThreads / (s.dv << s.slice_log2);
+  const int32_t row = s.dv << s.slice_log2, room = kMergeThreads / row;
   // Query heads in equal shares: with 5 of them, 4 and 1 (heads 40/8/128, 650 query tokens of 24 pieces 15.7 us, 14.1 so; 72/8/128,
   // 1600 of 2 pieces 40.0 and 32.6).
   s.parts = (heads_per_kv + room - 1) / room;
   s.rows = (heads_per_kv + s.parts - 1) / s.parts;
-  s.tokens = static_cast<int32_t>(std::min<int64_t>(room / s.rows, n_qtok));
+  // Several query tokens where one leaves a workgroup fewer than half of its threads (figures at the kernel); with 128 threads
+  // a second token costs more than it gives (32/8/128, 1 slice: 9.2 us, 9.6 with two).
+  s.tokens = 2 * s.rows * row >= kMergeThreads ? 1 : static_cast<int32_t>(std::min<int64_t>(room / s.rows, n_qtok));
   // kv heads before query tokens in the grid where they are a multiple of 4: a kv head's workgroups then run on the one or two
   // XCDs that had its items.  Query tokens first / kv heads first, us a call, medians of 7 runs: heads 16/4/128 26.8 / 24.8,
   // 15.0 / 14.0, 22.4 / 19.6, 28/4/128 20.5 / 19.2, 33.5 / 32.0; with 2, 3 and 6 kv heads either may win: 8/2/128

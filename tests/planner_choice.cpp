@@ -251,8 +251,8 @@ int main() {
   CHECK(tiles(2, 6000, 8, 128, 1, 24) == 0, "length given");
   CHECK(tiles(12, 2000, 16, 128, 1) == 188 && tiles(13, 2000, 16, 128, 1) == 0, "1920 and 2080 tiles");
 
-  // merge workgroups: within 256 threads, every row in one of them, more than half full wherever there are rows enough, and
-  // the query heads of a kv head in equal shares
+  // merge workgroups: within 256 threads, every row in one of them, at least half full wherever there are rows enough, the heads of
+  // a kv head in equal shares, and no grid dimension but the first beyond 65535
   for (int Hkv : {1, 3, 4, 32})
     for (int G : {1, 2, 3, 4, 7, 8, 20, 71})
       for (int D : {1, 30, 40, 64, 96, 128, 255, 256})
@@ -261,7 +261,7 @@ int main() {
             const MergeShape m = merge_shape(Hkv, G, D, n, pieces);
             CHECK(m.threads() <= kMergeThreads && m.dv * m.vec == D && m.rows >= 1 && m.tokens >= 1 && m.tokens <= n, "%d %d %d", G, D, pieces);
             CHECK(m.rows * m.parts >= G && m.rows * (m.parts - 1) < G && m.rows * m.parts - G < m.parts, "%d %d %d", G, D, pieces);
-            CHECK(2 * m.threads() > kMergeThreads || m.tokens == n, "%d heads a kv head of %d, %d pieces: %d threads", G, D, pieces,
+            CHECK(2 * m.threads() >= kMergeThreads || m.tokens == n, "%d heads a kv head of %d, %d pieces: %d threads", G, D, pieces,
                   m.threads());
             const bool fours = Hkv % 4 == 0;
             CHECK(m.heads_first == (fours && n <= 65535), "%d kv heads, %d query tokens", Hkv, static_cast<int>(n));
