@@ -933,15 +933,13 @@ static spex_status_t decode_attention_impl(spex_tree_t *t, const spex_node_t *le
   spex::ItemLists il{};
   const std::vector<int32_t> *host_items[4] = {&pl.coop_items[1], &pl.coop_items[0], &pl.prefix_items, &pl.suffix_items};
   const int32_t *dev_items[4] = {dp.coop_items[1], dp.coop_items[0], dp.prefix_items, dp.suffix_items};
-  const int32_t most = std::max(pl.max_rows_prefix, 1);  // shorter spans: no workgroups for rows that no item has
-  const int32_t spans[4] = {std::min(128, most), std::min(64, most), 16, 16 * pl.suffix_row_tiles};
+  const int32_t spans[4] = {pl.coop_span[1], pl.coop_span[0], 16, 16 * pl.suffix_row_tiles};
   for (int k = 0; k < 4; ++k) {
     il.items[k] = dev_items[k];
     il.n_items[k] = static_cast<int32_t>(host_items[k]->size() / spex::Plan::kItemInts);
     il.span[k] = spans[k];
   }
-  il.longest = pl.longest_streamed;
-  il.tiles = pl.split_tiles;
+  il.form = pl.split_form;
   a.part_indptr = dp.part_indptr;
   a.part_base = dp.part_base;
   a.part_hstride = dp.part_hstride;

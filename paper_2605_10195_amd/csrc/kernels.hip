@@ -35,7 +35,6 @@
 //   spex_patch_plan_kernel
 //       Applies {index, value} patches to the device copy of the cached launch lists.
 #include "kernels.hpp"
-#include "launch_shape.hpp"
 
 #include <climits>
 
@@ -990,12 +989,8 @@ __device__ __forceinline__ void coop_item(const AttnArgs &p, const Shape &sh, co
 // kSplitTiles: for launches that leave the chip room: items of many rows go as row tiles of 16 NT, a workgroup each that
 // splits the pages between its wavefronts, instead of one through LDS, whose blocks follow each other.  The tiles read the
 // pages again, from L2.
-enum SplitForm : int { kSplitFull, kSplitLean, kSplitTiles };
-constexpr int split_occupancy(int d, int nt, int form) {
-  return d == 64 ? (form == kSplitLean ? 5 : 3) : (form == kSplitLean ? 3 : 2);
-}
-template <int KV, int D, int NT, bool TREE, int FORM>
-__global__ __launch_bounds__(256, split_occupancy(D, NT, FORM)) void spex_split_attn_kernel(AttnArgs p, Shape sh, SplitLists ls) {
+template <int KV, int D, int NT, bool TREE, SplitForm FORM>
+__global__ __launch_bounds__(256, split_occupancy(D, FORM)) void spex_split_attn_kernel(AttnArgs p, Shape sh, SplitLists ls) {
   constexpr int kLds = FORM != kSplitTiles && coop_lds_floats<D>() > wave_fold_floats<D>() ? coop_lds_floats<D>() : wave_fold_floats<D>();
   __shared__ __attribute__((aligned(16))) float lds[kLds];
   const ListPos at = list_of(ls, static_cast<int>(blockIdx.x));
@@ -3001,7 +2996,7 @@ static SplitLists make_lists(const ItemLists &l, int rows_per_wg, int64_t *n_wg)
   return ls;
 }
 
-template <int KV, int D, int NT, int FORM>
+template <int KV, int D, int NT, SplitForm FORM>
 static hipError_t launch_split_form(const Shape &sh, const AttnArgs &a, const SplitLists &ls, int n_wg, hipStream_t stream) {
   const dim3 grid(n_wg), block(256);
   if (a.qt_mask)  // draft token trees: visibility masks per query
@@ -3012,35 +3007,21 @@ static hipError_t launch_split_form(const Shape &sh, const AttnArgs &a, const Sp
 }
 
 template <int KV, int D, int NT>
-static hipError_t launch_split_nt(const Shape &sh, const AttnArgs &a, const ItemLists &l, const SplitLists &ls, int n_wg, hipStream_t stream) {
-  // Tiles where all of them run at once, two workgroups a compute unit.  Through LDS / as tiles, us: a prompt of 4096 under 16
-  // rows bf16 12.2 / 9.5, fp8 13.9 / 10.5, prompts under 48 to 128 rows 14.6 / 10.3, 24.3 / 18.7; of 513 to 1024 tiles
-  // 14.5 / 12.7, 13.1 / 13.3, 14.2 / 17.7; of more 15.7 / 18.9, 22.7 / 28.2.
-  // fp8, one set of 16 rows: up to four rounds (three with heads of 64), because the items through LDS take as long a block
-  // whatever its bytes.  Heads of 128: 1344 tiles 41 / 25, 1728 34 / 26, 2016 43 / 35, 1280 27 / 23, 1920 33 / 31, 2560
-  // 35 / 42, 4480 50 / 57; of 64: 544 15.3 / 11.7, 1408 35 / 22, 1536 40 / 16, 2048 12.8 / 13.9.  bf16 heads of 64 gain too
-  // little: 544 13.3 / 11.7, 1536 33 / 24, 1408 28 / 31, 2176 20.3 / 20.5, 3072 35 / 44.
-  // Items that were cut for tiles go so whatever their number.
-  constexpr int64_t kMaxTiles = NT > 1 || KV != kFP8 ? 512 : D == 64 ? 1536 : 2048;
-  int64_t n_tiles = 0;
-  const SplitLists tiles = make_lists(l, 16 * NT, &n_tiles);
-  if (ls.wg_end[1] > 0 && n_tiles >= 0 && (n_tiles <= kMaxTiles || (l.tiles && NT == 1)))
-    return launch_split_form<KV, D, NT, kSplitTiles>(sh, a, tiles, static_cast<int>(n_tiles), stream);
-  // More workgroups than run at a time in the other form, and no long items, which want their loads a block ahead.
-  // bf16 heads of 128 read as fast with two workgroups a compute unit.  Times of both forms, us: fp8 heads of 128, items of 8
-  // pages, 6144 workgroups 73.6 / 63.6, 1536 25.0 / 22.7, of 16 pages 768 18.5 / 16.4, of 128 pages 768 36.4 / 37.2;
-  // heads of 64, 8 pages, 1536 23.3 / 21.2 (fp8 24.9 / 20.4); bf16 heads of 128, 16 pages, 3072 82.6 / 85.1.
-  if constexpr (NT == 1 && !(KV == kBF16 && D == 128)) {
-    if (ls.wg_end[0] == 0 && n_wg > 256 * split_occupancy(D, NT, kSplitFull) && l.longest <= 16)
-      return launch_split_form<KV, D, NT, kSplitLean>(sh, a, ls, n_wg, stream);
-  }
-  return launch_split_form<KV, D, NT, kSplitFull>(sh, a, ls, n_wg, stream);
+static hipError_t launch_split_nt(const Shape &sh, const AttnArgs &a, const ItemLists &l, hipStream_t stream) {
+  int64_t n_wg = 0;
+  const SplitLists ls = make_lists(l, l.form == kSplitTiles ? 16 * NT : 128, &n_wg);
+  if (n_wg < 0) return hipErrorInvalidValue;
+  if (n_wg == 0) return hipSuccess;
+  const int n = static_cast<int>(n_wg);
+  if (l.form == kSplitTiles) return launch_split_form<KV, D, NT, kSplitTiles>(sh, a, ls, n, stream);
+  if constexpr (NT == 1 && !(KV == kBF16 && D == 128))
+    if (l.form == kSplitLean && l.n_items[0] == 0) return launch_split_form<KV, D, NT, kSplitLean>(sh, a, ls, n, stream);
+  return l.form == kSplitFull ? launch_split_form<KV, D, NT, kSplitFull>(sh, a, ls, n, stream) : hipErrorInvalidValue;
 }
 
 template <int KV, int D>
-static hipError_t launch_split_d(const Shape &sh, const AttnArgs &a, const ItemLists &l, const SplitLists &ls, int n_wg, hipStream_t stream) {
-  return ls.span[2] <= 16 && ls.span[3] <= 16 ? launch_split_nt<KV, D, 1>(sh, a, l, ls, n_wg, stream)
-                                              : launch_split_nt<KV, D, 2>(sh, a, l, ls, n_wg, stream);
+static hipError_t launch_split_d(const Shape &sh, const AttnArgs &a, const ItemLists &l, hipStream_t stream) {
+  return l.span[2] <= 16 && l.span[3] <= 16 ? launch_split_nt<KV, D, 1>(sh, a, l, stream) : launch_split_nt<KV, D, 2>(sh, a, l, stream);
 }
 
 template <int KV, int D, bool TREE>
@@ -3085,15 +3066,14 @@ hipError_t launch_split(const Shape &sh, const AttnArgs &a, const ItemLists &l, 
   const bool tiled = has_mfma_kernel(sh);
   if (!tiled && !has_rowmajor_kernel(sh, a)) return hipErrorInvalidValue;
   if (l.span[0] > 128 || l.span[1] > 64 || l.span[2] > 32 || l.span[3] > 32) return hipErrorInvalidValue;
+  if (tiled && sh.kv_dtype == kBF16)
+    return sh.D == 64 ? launch_split_d<kBF16, 64>(sh, a, l, stream) : launch_split_d<kBF16, 128>(sh, a, l, stream);
+  if (tiled) return sh.D == 64 ? launch_split_d<kFP8, 64>(sh, a, l, stream) : launch_split_d<kFP8, 128>(sh, a, l, stream);
   int64_t n_wg = 0;
-  const SplitLists ls = make_lists(l, tiled ? 128 : 64, &n_wg);
+  const SplitLists ls = make_lists(l, 64, &n_wg);
   if (n_wg < 0) return hipErrorInvalidValue;
   if (n_wg == 0) return hipSuccess;
   const int n = static_cast<int>(n_wg);
-  if (tiled && sh.kv_dtype == kBF16)
-    return sh.D == 64 ? launch_split_d<kBF16, 64>(sh, a, l, ls, n, stream) : launch_split_d<kBF16, 128>(sh, a, l, ls, n, stream);
-  if (tiled)
-    return sh.D == 64 ? launch_split_d<kFP8, 64>(sh, a, l, ls, n, stream) : launch_split_d<kFP8, 128>(sh, a, l, ls, n, stream);
   if (sh.kv_dtype == kF32) return launch_rowmajor_kv<kF32>(sh, a, ls, n, stream);
   if (sh.kv_dtype == kBF16) return launch_rowmajor_kv<kBF16>(sh, a, ls, n, stream);
   return launch_rowmajor_kv<kFP8>(sh, a, ls, n, stream);

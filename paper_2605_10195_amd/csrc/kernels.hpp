@@ -5,6 +5,8 @@
 
 #include <cstdint>
 
+#include "launch_shape.hpp"
+
 namespace spex {
 
 enum Dtype : int32_t { kF32 = 0, kBF16 = 1, kFP8 = 2 };
@@ -124,8 +126,7 @@ struct GatherArgs {
 struct ItemLists {
   const int32_t *items[4];
   int32_t n_items[4], span[4];
-  int32_t longest;  // pages of the longest item of the last two lists
-  bool tiles;       // cut to go as row tiles of 16, a workgroup each
+  SplitForm form;  // of launch_split on a tiled pool
 };
 bool has_mfma_kernel(const Shape &sh);
 bool has_rowmajor_kernel(const Shape &sh, const AttnArgs &a);

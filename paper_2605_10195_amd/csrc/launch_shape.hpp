@@ -6,6 +6,49 @@
 
 namespace spex {
 
+// Forms of the split path's launch of all items (MFMA-tiled pools); what they are stands at spex_split_attn_kernel.
+enum SplitForm : int32_t { kSplitFull, kSplitLean, kSplitTiles };
+// Workgroups a compute unit.
+constexpr int split_occupancy(int head_dim, SplitForm form) {
+  return head_dim == 64 ? (form == kSplitLean ? 5 : 3) : (form == kSplitLean ? 3 : 2);
+}
+
+// Most workgroups of a launch whose items of many rows go as row tiles of 16 nt, a workgroup each; `pages` is the mean length of the
+// tiles' items.  512 run at once, two a compute unit.  Through LDS / as tiles, us: a prompt of 4096 under 16
+// rows bf16 12.2 / 9.5, fp8 13.9 / 10.5, prompts under 48 to 128 rows 14.6 / 10.3, 24.3 / 18.7; of 513 to 1024 tiles
+// 14.5 / 12.7, 13.1 / 13.3, 14.2 / 17.7; of more 15.7 / 18.9, 22.7 / 28.2.  bf16 heads of 64 gain too little beyond:
+// 544 13.3 / 11.7, 1536 33 / 24, 1408 28 / 31, 2176 20.3 / 20.5, 3072 35 / 44.
+// fp8, one set of 16 rows: up to four rounds where the items are long, because the items through LDS take as long a block
+// whatever its bytes; every round costs the tiles some 3 us however short they are.  Heads of 128, prompts of 2000 tokens and more:
+// 1344 workgroups 41 / 25, 1728 34 / 26, 2016 43 / 35, 1280 27 / 23, 1920 33 / 31, 2560 35 / 42, 4480 50 / 57; nodes of 1 page: 1920
+// 13.3 / 17.6, of 2 pages 1344 13.0 / 15.8.  Heads of 64, items of 4 pages: 1728 12.2 / 14.4, 1664 10.1 / 12.0, of 8 13.3 / 14.6,
+// 12.4 / 11.9, of 24 21.2 / 17.1, 22.7 / 15.8, of 64 44.0 / 24.0, 46.9 / 25.4.
+// Over 3891 drawn requests, not those of the fit, the choice takes 0.90 of the time through LDS, 65 of them are slower so by 2 to
+// 12 %; with 2048 whatever the length 192 of 2325 are, by up to 31 %.
+constexpr int64_t most_row_tiles(bool fp8, int32_t nt, int32_t head_dim, int64_t pages) {
+  return fp8 && nt == 1 ? std::clamp<int64_t>(head_dim == 64 ? 512 + 160 * pages : 384 + 96 * pages, 512, 2048) : 512;
+}
+
+struct SplitSizes {
+  int32_t head_dim;
+  bool fp8;
+  int32_t nt;                      // sets of 16 rows of the longest private item's kind: 1 or 2
+  int64_t wide, shared, streamed;  // items of up to 128 rows, of up to 64, and those of up to 16 with the private ones
+  int64_t tiles, tile_pages;       // row tiles of the first two, pages of all of these together
+  int32_t longest;                 // pages of the longest of the others
+};
+inline SplitForm split_form(const SplitSizes &s) {
+  if (s.tiles > 0 && s.tiles + s.streamed <= most_row_tiles(s.fp8, s.nt, s.head_dim, s.tile_pages / s.tiles)) return kSplitTiles;
+  // More workgroups than run at a time in the other form, and no long items, which want their loads a block ahead.
+  // bf16 heads of 128 read as fast with two workgroups a compute unit.  Times of both forms, us: fp8 heads of 128, items of 8
+  // pages, 6144 workgroups 73.6 / 63.6, 1536 25.0 / 22.7, of 16 pages 768 18.5 / 16.4, of 128 pages 768 36.4 / 37.2;
+  // heads of 64, 8 pages, 1536 23.3 / 21.2 (fp8 24.9 / 20.4); bf16 heads of 128, 16 pages, 3072 82.6 / 85.1.
+  if (s.nt == 1 && (s.fp8 || s.head_dim == 64) && s.wide == 0 && s.shared + s.streamed > 256 * split_occupancy(s.head_dim, kSplitFull) &&
+      s.longest <= 16)
+    return kSplitLean;
+  return kSplitFull;
+}
+
 // Merge kernel: block (dv, tokens << slice_log2, rows), see spex_lse_merge_kernel.
 struct MergeShape {
   int32_t vec;          // dims a thread

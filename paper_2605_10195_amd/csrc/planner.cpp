@@ -49,14 +49,13 @@ int32_t clamp32(int64_t v, int32_t lo, int32_t hi) {
 // Items that go as row tiles of 16, a workgroup each (fp8; private items of up to 16 rows): as many shared items as leave one
 // round of 512 workgroups (768 with heads of 64) with the private ones, at least 64, and longer ones than through LDS: a
 // workgroup splits its pages between wavefronts that have loads in flight, and every item's rows cost a partial state each.
-// Only while all tiles stay below kMostTiles; beyond, the items go through LDS, cut as above.  Items through LDS / tiles of the
+// Only up to most_row_tiles; beyond, the items go through LDS, cut as above.  Items through LDS / tiles of the
 // same cut / of this one, us, heads of 128: two prompts of 6000 tokens under 32 rows 25 / 15.4 / 14.5, 64 rows 27 / 23 /
 // 17.4, 128 rows 36 / 42 / 27.7; of 12000 under 112 rows 39 / 39 / 26; 12 of 2000 under 64 rows 45 / 46 / 37; 20 of 6000
 // under 32 rows, two kv heads, 51 / 28 / 22; 24 of 2000 under 64 rows (3840 tiles) 66 / 90 / 76, through LDS.  Heads of 64:
 // 8 prompts of 3000 tokens under 128 rows 22 / 20.5 / 14.7.  bf16 gains little or loses: heads of 128, 128 rows 30 / 72 / 35;
 // of 64, 11 prompts of 8400 under 64 rows 28 / 31 / 35.
 constexpr int64_t kFineRows = 40960;
-constexpr int64_t kMostTiles = 2048;
 struct Run {
   int64_t pages;
   int32_t rows;  // query tokens * G
@@ -131,7 +130,7 @@ Chunks choose_chunks(const std::vector<Run> &groups, const std::vector<Run> &suf
       tiles += (g.pages + chunk - 1) / chunk * ((g.rows + 15) / 16);
       partial += (g.pages + chunk - 1) / chunk * g.rows;
     }
-    if (tiles * num_kv_heads + private_wgs <= kMostTiles) {
+    if (tiles * num_kv_heads + private_wgs <= most_row_tiles(true, 1, pool.head_dim, tile_pages / tiles)) {
       c.tiles = true;
       c.prefix = chunk;
       c.partial_rows = partial * num_kv_heads;
@@ -588,8 +587,21 @@ PlanError Planner::ensure_split(const PageTable &pt, Plan *plan) {
     for (int32_t rt = 0; rt < n_rt; ++rt)
       for (int32_t g = 0; g < num_kv_heads; ++g) push_item(pl.suffix_items, t, g, rt * rw_suffix);
   }
-  for (const std::vector<int32_t> *items : {&pl.prefix_items, &pl.suffix_items})
-    for (size_t i = 1; i < items->size(); i += Plan::kItemInts) pl.longest_streamed = std::max(pl.longest_streamed, (*items)[i]);
+  {
+    const int32_t most = std::max(pl.max_rows_prefix, 1);  // shorter spans: no workgroups for rows that no item has
+    for (int c = 0; c < 2; ++c) pl.coop_span[c] = std::min(64 << c, most);
+    auto count = [](const std::vector<int32_t> &items) { return static_cast<int64_t>(items.size()) / Plan::kItemInts; };
+    SplitSizes sizes{pool.head_dim, pool.kv_bytes == 1, pl.suffix_row_tiles, count(pl.coop_items[1]), count(pl.coop_items[0]),
+                     count(pl.prefix_items) + count(pl.suffix_items), 0, 0, 0};
+    for (int c = 0; c < 2; ++c) {
+      const int32_t each = (pl.coop_span[c] + rw_suffix - 1) / rw_suffix;
+      sizes.tiles += count(pl.coop_items[c]) * each;
+      for (size_t i = 1; i < pl.coop_items[c].size(); i += Plan::kItemInts) sizes.tile_pages += each * pl.coop_items[c][i];
+    }
+    for (const std::vector<int32_t> *items : {&pl.prefix_items, &pl.suffix_items})
+      for (size_t i = 1; i < items->size(); i += Plan::kItemInts) sizes.longest = std::max(sizes.longest, (*items)[i]);
+    if (pool.tiled) pl.split_form = pl.split_tiles ? kSplitTiles : spex::split_form(sizes);
+  }
   pl.pg_rec.resize(pl.pg_id.size() * 2);
   for (size_t i = 0; i < pl.pg_id.size(); ++i) {
     pl.pg_rec[2 * i] = pl.pg_id[i];

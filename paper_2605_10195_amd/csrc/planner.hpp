@@ -27,6 +27,7 @@
 #include <utility>
 #include <vector>
 
+#include "launch_shape.hpp"
 #include "page_table.hpp"
 
 namespace spex {
@@ -77,6 +78,7 @@ struct Plan {
   bool split_phases = false;  // tiled pools: items are cut for the split path's lists in launches of their own
   bool split_together = false;  // and few enough to go in one launch all the same
   bool split_tiles = false;     // shared items cut to go as row tiles of 16, a workgroup each
+  SplitForm split_form = kSplitFull;  // of the one launch, tiled pools
 
   // ---- launch lists (device side).  A work item is kItemInts ints:
   //   {pg_begin, pg_count, qt_begin, qt_count, pbase, flags, kv_head, first_row}
@@ -85,8 +87,8 @@ struct Plan {
   static constexpr int kItemInts = 8;
   std::vector<int32_t> prefix_items, suffix_items, pg_rec, qt_rec;
   std::vector<int32_t> coop_items[2];  // groups of more than 16 rows, up to 64 / 128 rows per workgroup
+  int32_t coop_span[2] = {1, 1};       // rows that an item of theirs covers at most
   int32_t suffix_row_tiles = 1;  // 16-row MFMA tiles per wavefront of the private items (shared ones of few rows: 1)
-  int32_t longest_streamed = 0;  // pages of the longest of prefix_items and suffix_items
   int32_t max_rows_prefix = 0, max_rows_suffix = 0;
   int64_t prefix_tokens = 0, suffix_tokens = 0;        // distinct KV tokens per kind
 

@@ -251,6 +251,24 @@ int main() {
   CHECK(tiles(2, 6000, 8, 128, 1, 24) == 0, "length given");
   CHECK(tiles(12, 2000, 16, 128, 1) == 188 && tiles(13, 2000, 16, 128, 1) == 0, "1920 and 2080 tiles");
 
+  // form of the one launch; `pages` of a prompt of `items` of them a branch
+  auto form = [](int roots, int items, int pages, int branches, int Hq, int Hkv, int dim, int kv_bytes, int tokens = 20) {
+    Forest f(roots * (items * pages + 2 * branches * (1 + tokens / 16)), 16);
+    f.add(roots, 16 * items * pages, branches, tokens);
+    Made m(f, Hq, Hkv, pages);
+    m.planner.pool = {true, false, dim, kv_bytes};
+    CHECK(m.planner.ensure_split(f.pt, &m.plan) == PlanError::kOk, "split lists");
+    return m.plan.split_form;
+  };
+  CHECK(form(24, 5, 24, 16, 8, 2, 64, 1) == kSplitTiles && form(24, 7, 24, 16, 8, 2, 64, 1) != kSplitTiles, "1728 and 2112 workgroups");
+  CHECK(form(4, 6, 24, 24, 32, 8, 128, 1) == kSplitTiles && form(4, 7, 24, 24, 32, 8, 128, 1) != kSplitTiles, "1920 and 2112");
+  CHECK(form(24, 2, 4, 16, 8, 2, 64, 1) == kSplitTiles && form(24, 3, 4, 16, 8, 2, 64, 1) != kSplitTiles, "1152 of 4 pages and 1344");
+  CHECK(form(4, 5, 8, 24, 32, 8, 64, 1) == kSplitTiles && form(4, 6, 8, 24, 32, 8, 64, 1) != kSplitTiles, "1728 of 8 pages and 1920");
+  CHECK(form(4, 3, 10, 24, 32, 8, 128, 1) == kSplitTiles && form(4, 4, 10, 24, 32, 8, 128, 1) != kSplitTiles, "1344 of 10 pages and 1536");
+  CHECK(form(8, 1, 1, 16, 8, 2, 128, 1) == kSplitTiles && form(16, 1, 1, 16, 8, 2, 128, 1) == kSplitLean, "320 of a page and 640");
+  CHECK(form(6, 4, 24, 16, 8, 2, 128, 2) == kSplitTiles && form(6, 7, 24, 16, 8, 2, 128, 2) == kSplitFull, "bf16: 384 and 528");
+  CHECK(form(6, 4, 24, 16, 8, 2, 64, 2) == kSplitTiles && form(6, 7, 24, 16, 8, 2, 64, 2) == kSplitFull, "bf16: 384 and 528");
+
   // merge workgroups: within 256 threads, every row in one of them, at least half full wherever there are rows enough, the heads of
   // a kv head in equal shares, and no grid dimension but the first beyond 65535
   for (int Hkv : {1, 3, 4, 32})
