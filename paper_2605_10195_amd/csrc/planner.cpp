@@ -588,16 +588,18 @@ PlanError Planner::ensure_split(const PageTable &pt, Plan *plan) {
       for (int32_t g = 0; g < num_kv_heads; ++g) push_item(pl.suffix_items, t, g, rt * rw_suffix);
   }
   {
-    const int32_t most = std::max(pl.max_rows_prefix, 1);  // shorter spans: no workgroups for rows that no item has
-    for (int c = 0; c < 2; ++c) pl.coop_span[c] = std::min(64 << c, most);
     auto count = [](const std::vector<int32_t> &items) { return static_cast<int64_t>(items.size()) / Plan::kItemInts; };
     SplitSizes sizes{pool.head_dim, pool.kv_bytes == 1, pl.suffix_row_tiles, count(pl.coop_items[1]), count(pl.coop_items[0]),
                      count(pl.prefix_items) + count(pl.suffix_items), 0, 0, 0};
-    for (int c = 0; c < 2; ++c) {
-      const int32_t each = (pl.coop_span[c] + rw_suffix - 1) / rw_suffix;
-      sizes.tiles += count(pl.coop_items[c]) * each;
-      for (size_t i = 1; i < pl.coop_items[c].size(); i += Plan::kItemInts) sizes.tile_pages += each * pl.coop_items[c][i];
-    }
+    for (int c = 0; c < 2; ++c)
+      for (size_t i = 0; i < pl.coop_items[c].size(); i += Plan::kItemInts) {
+        const int32_t *item = &pl.coop_items[c][i];
+        if (item[1] == 0) continue;  // padding
+        const int32_t rows = std::min(item[3] * G - item[7], 64 << c), n_tiles = (rows + rw_suffix - 1) / rw_suffix;
+        pl.coop_span[c] = std::max(pl.coop_span[c], rows);
+        sizes.tiles += n_tiles;
+        sizes.tile_pages += static_cast<int64_t>(n_tiles) * item[1];
+      }
     for (const std::vector<int32_t> *items : {&pl.prefix_items, &pl.suffix_items})
       for (size_t i = 1; i < items->size(); i += Plan::kItemInts) sizes.longest = std::max(sizes.longest, (*items)[i]);
     if (pool.tiled) pl.split_form = pl.split_tiles ? kSplitTiles : spex::split_form(sizes);

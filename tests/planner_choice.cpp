@@ -269,6 +269,24 @@ int main() {
   CHECK(form(6, 4, 24, 16, 8, 2, 128, 2) == kSplitTiles && form(6, 7, 24, 16, 8, 2, 128, 2) == kSplitFull, "bf16: 384 and 528");
   CHECK(form(6, 4, 24, 16, 8, 2, 64, 2) == kSplitTiles && form(6, 7, 24, 16, 8, 2, 64, 2) == kSplitFull, "bf16: 384 and 528");
 
+  // row tiles are those that items have, whatever the largest group of the request, and a list's span is its own largest item's
+  auto mixed = [](int small, int wide_branches, int *span) {
+    Forest f(small * 20 + 200, 16);
+    f.add(small, 60, 5, 20);
+    if (wide_branches > 0) f.add(1, 60, wide_branches, 20);
+    Made m(f, 8, 2);
+    m.planner.pool = {true, false, 128, 2};
+    CHECK(m.planner.ensure_split(f.pt, &m.plan) == PlanError::kOk, "split lists");
+    span[0] = m.plan.coop_span[0];
+    span[1] = m.plan.coop_span[1];
+    return m.plan.split_form;
+  };
+  int span[2];
+  CHECK(mixed(36, 0, span) == kSplitTiles && span[0] == 20 && span[1] == 1, "504 workgroups");
+  CHECK(mixed(33, 16, span) == kSplitTiles && span[0] == 64, "132 tiles of 20 rows, 8 of 64 and 362 private items");
+  CHECK(mixed(30, 33, span) == kSplitTiles && span[0] == 20 && span[1] == 128, "one group of 132 rows");
+  CHECK(mixed(37, 0, span) == kSplitFull, "518 workgroups");
+
   // merge workgroups: within 256 threads, every row in one of them, at least half full wherever there are rows enough, the heads of
   // a kv head in equal shares, and no grid dimension but the first beyond 65535
   for (int Hkv : {1, 3, 4, 32})
