@@ -77,11 +77,13 @@ inline MergeShape merge_shape(int32_t num_kv_heads, int32_t heads_per_kv, int32_
   // Several query tokens where one leaves a workgroup fewer than half of its threads (figures at the kernel); with 128 threads
   // a second token costs more than it gives (32/8/128, 1 slice: 9.2 us, 9.6 with two).
   s.tokens = 2 * s.rows * row >= kMergeThreads ? 1 : static_cast<int32_t>(std::min<int64_t>(room / s.rows, n_qtok));
-  // kv heads before query tokens in the grid where they are a multiple of 4: a kv head's workgroups then run on the one or two
-  // XCDs that had its items.  Query tokens first / kv heads first, us a call, medians of 7 runs: heads 16/4/128 26.8 / 24.8,
-  // 15.0 / 14.0, 22.4 / 19.6, 28/4/128 20.5 / 19.2, 33.5 / 32.0; with 2, 3 and 6 kv heads either may win: 8/2/128
-  // 12.4 / 13.0, 18.8 / 18.7, 16/2/64 11.5 / 12.1, 16.9 / 16.4, 12/3/128 13.6 / 14.0, 18.6 / 18.2, 24/6/128 20.2 / 21.0, 34.7 / 33.8.
-  s.heads_first = num_kv_heads % 4 == 0 && n_qtok <= 65535;
+  // kv heads before query tokens in the grid, so that the workgroups of a query token, which read neighbouring rows, run at the same
+  // time (and a kv head's on the XCDs that had its items where they are a multiple of 4).  The attention launch gains as well
+  // as the merge.  Query tokens first / kv heads first, us a call, medians of 5 to 7 runs: heads 16/4/128 26.8 / 24.8, 15.0 / 14.0,
+  // 22.4 / 19.6, 28/4/128 20.5 / 19.2, 33.5 / 32.0, 16/2/64 15.9 / 14.7, 17.4 / 16.6, 14/2/128 23.1 / 21.9, 24/6/128 34.9 / 33.8,
+  // 27.0 / 25.7, 12/3/128 18.8 / 18.0; the other way round 24 trees of 8 branches, 8/2/128 12.3 / 13.1, 16/2/64 11.5 / 12.3, and
+  // 24/6/128 20.2 / 21.0.  One kv head: 26.9 / 27.3, 22.9 / 24.5 with its parts first.
+  s.heads_first = num_kv_heads > 1 && n_qtok <= 65535;
   return s;
 }
 
