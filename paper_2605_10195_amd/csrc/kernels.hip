@@ -2006,15 +2006,17 @@ __global__ __launch_bounds__(256, rowmajor_occupancy(KV, DP, MODE)) void spex_ro
   // Dims past D (D < DP) are read from the start of the row instead, so that no load is
   // conditional: in K they meet zeros of Q, in V they make output dims that are not written.
   // Steps past the wavefront's last one are read as well, for the same reason, but by all lanes from the first token of
-  // the last step: one cache line, and one just read, instead of 16.  An item of 76 tokens is one turn or none for a
+  // the last step: one cache line (in the modes whose offsets are the lane's own, one row), and one just read, instead of 16 rows.
+  // An item of 76 tokens is one turn or none for a
   // wavefront, which used to request its tokens up to four times (8 ragged queries of 16 branches, bf16 pages of 32
   // tokens: 35.7 -> 30.3 us a call, 32 queries 131 -> 116; fp32 heads 28/4/128, 64 prompts of 1024 142 -> 137;
   // the start of the tile instead, a line that may be no wavefront's own: 4 prompts of 12000 tokens 57.4, 52.4 so,
-  // 54.1 with whole rows repeated).
+  // 54.1 with whole rows repeated).  Offsets that took part in this were made anew every step: fp32 heads 12/4/80, 8 branches of 67
+  // queries on 6 prompts of 4400 610 -> 587 us, 6/3/40 179 -> 174, 6/2/200, 64 prompts of 1024, 96 -> 92.
   u32x4 kr[SUB][NK];
   auto load_k = [&](int j, const Rec &r, int step) {
     const int msk = step < step1 ? -1 : 0;  // uniform
-    const int slot = ((min(step, step1 - 1) << 4) + (m16 & msk)) & (sh.P - 1), dj = MODE == kRowFull ? 0 : CH * jj & msk;
+    const int slot = ((min(step, step1 - 1) << 4) + (m16 & msk)) & (sh.P - 1), dj = MODE == kRowFull ? 0 : CH * jj;
     const char *src = kpool + (static_cast<int64_t>(r.k.x) * sh.page_tiles + it.g) * tile_bytes + (slot * D * ESZ + (MODE == kRowFull ? 16 * jj & msk : 0));
 #pragma unroll
     for (int i = 0; i < NK; ++i) {
@@ -2051,12 +2053,12 @@ __global__ __launch_bounds__(256, rowmajor_occupancy(KV, DP, MODE)) void spex_ro
   auto load_v = [&](int j, const Rec &r, int step) {
     const int msk = step < step1 ? -1 : 0;
     const int slot = ((min(step, step1 - 1) << 4) + (4 * jj & msk)) & (sh.P - 1);
-    const char *src = vpool + (static_cast<int64_t>(r.v.x) * sh.page_tiles + it.g) * tile_bytes + (slot * D + (VE * m16 & msk)) * ESZ;
+    const char *src = vpool + (static_cast<int64_t>(r.v.x) * sh.page_tiles + it.g) * tile_bytes + (slot * D + (MODE == kRowFull ? VE * m16 & msk : VE * m16)) * ESZ;
 #pragma unroll
     for (int t = 0; t < 4; ++t)
 #pragma unroll
       for (int c = 0; c < NC; ++c)
-        __builtin_memcpy(&vr[j][t][c], __builtin_assume_aligned(src + (t * D + (MODE == kRowFull ? 16 * VE * c : v_off[c] & msk)) * ESZ, VE * ESZ), VE * ESZ);
+        __builtin_memcpy(&vr[j][t][c], __builtin_assume_aligned(src + (t * D + (MODE == kRowFull ? 16 * VE * c : v_off[c])) * ESZ, VE * ESZ), VE * ESZ);
   };
 
   if (has_rows && step0 < step1) {
