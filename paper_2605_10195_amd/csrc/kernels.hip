@@ -1929,6 +1929,10 @@ __global__ __launch_bounds__(256, rowmajor_occupancy(KV, DP, MODE)) void spex_ro
   constexpr int NQ = KV == kF32 ? DP / 4 : DP / 8;  // Q registers
   constexpr int SUB = KV == kF32 ? 1 : 2;  // groups of 16 tokens per step
   constexpr int kFold = NO * 4 + 2;        // floats per lane a wavefront hands over
+  // A step's values are requested at its start, or for most fp32 rows at the end of the step before: us a call with values at the
+  // start / at the end, heads 8/2/64 290 / 279, 16/2/64 566 / 538, 12/4/96 609 / 574, 12/4/80 587 / 535 (8 branches of 67 queries on
+  // 6 prompts of 4400), 6/2/200 77.0 / 73.9 (of 16 on 8 of 512); 32/8/128 1373 / 1407 and 141 / 145, 6/3/40 174 / 178.
+  constexpr bool kEarlyV = KV != kF32 || (DP == 128 && MODE == kRowFull) || (DP == 64 && MODE == kRowAny);
   __shared__ float fold[4 * 64 * kFold];
 
   const int lane = threadIdx.x & 63, m16 = lane & 15, jj = lane >> 4;
@@ -2069,13 +2073,15 @@ __global__ __launch_bounds__(256, rowmajor_occupancy(KV, DP, MODE)) void spex_ro
       nxt[j] = rec_of(step0 + SUB + j);
       load_scales(j, cur[j]);
       load_k(j, cur[j], step0 + j);
+      if constexpr (!kEarlyV) load_v(j, cur[j], step0 + j);
     }
     for (int st = step0; st < step1; st += SUB) {
       // 16-bit and fp8 values go out before the keys are waited for: left to itself the compiler puts them behind the first
       // MFMA (fp8 pages of 32 tokens 27.4 -> 26.6 us, heads 6/3/40 22.8 -> 21.9, bf16 heads of 96 33.6 -> 32.9; fp32
       // 45.1 -> 45.8).
+      if constexpr (kEarlyV)
 #pragma unroll
-      for (int j = 0; j < SUB; ++j) load_v(j, cur[j], st + j);
+        for (int j = 0; j < SUB; ++j) load_v(j, cur[j], st + j);
       if constexpr (KV != kF32) __builtin_amdgcn_sched_barrier(0);
       float x[SUB][4], vs_l[SUB], mx = kNegInf;
 #pragma unroll
@@ -2232,6 +2238,7 @@ __global__ __launch_bounds__(256, rowmajor_occupancy(KV, DP, MODE)) void spex_ro
       }
 #pragma unroll
       for (int j = 0; j < SUB; ++j) {
+        if constexpr (!kEarlyV) load_v(j, nxt[j], st + SUB + j);
         cur[j] = nxt[j];
         nxt[j] = rec_of(st + 2 * SUB + j);
       }
