@@ -435,6 +435,12 @@ spex_status_t spex_tree_read_profile(spex_tree_t *tree, float *ms, int32_t cap, 
  * with work, [4] two-page blocks summed over workgroups of one kv head, [5] 0). */
 spex_status_t spex_tree_last_launch_info(const spex_tree_t *tree, int64_t info[8]);
 
+/* How the split path runs the cached plan (made by plan_dump or a decode_attention call), for tests: -1 = the plan
+ * has no lists of the split path; 0 = one launch, on MFMA-tiled pools with nodes of more than 16 query rows through LDS;
+ * 1 = the same with one set of K and V registers; 2 = such nodes as row tiles, a workgroup each; 3 = launches
+ * one after another. */
+spex_status_t spex_tree_split_form(const spex_tree_t *tree, int32_t *form);
+
 #ifdef __cplusplus
 }
 #endif

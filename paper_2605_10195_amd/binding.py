@@ -82,7 +82,7 @@ EXPORTS = [
     "spex_tree_decode_attention_static", "spex_tree_node_info", "spex_tree_path_pages",
     "spex_tree_free_pages", "spex_tree_stats", "spex_tree_plan_dump", "spex_tree_gather_kv",
     "spex_tree_set_tuning", "spex_tree_set_profiling", "spex_tree_read_profile",
-    "spex_tree_last_launch_info", "spex_tree_walk_dump", "spex_tree_append_tokens", "spex_tree_append_tokens_quantize", "spex_tree_append_step_quantize",
+    "spex_tree_last_launch_info", "spex_tree_split_form", "spex_tree_walk_dump", "spex_tree_append_tokens", "spex_tree_append_tokens_quantize", "spex_tree_append_step_quantize",
 ]
 # spex_sched.h: host-side scheduling primitives
 SCHED_EXPORTS = [
@@ -133,6 +133,7 @@ def _load():
     lib.spex_tree_set_profiling.argtypes = [vp, i32]
     lib.spex_tree_read_profile.argtypes = [vp, C.POINTER(f32), i32, _I32P]
     lib.spex_tree_last_launch_info.argtypes = [vp, C.POINTER(i64)]
+    lib.spex_tree_split_form.argtypes = [vp, _I32P]
     _F64P = C.POINTER(C.c_double)
     lib.spex_sched_rebase_widths.argtypes = [_F64P, i32, i32, C.c_double, _I32P]
     lib.spex_sched_ucb_select.argtypes = [C.POINTER(SearchTreeView), _I32P]
@@ -469,6 +470,13 @@ class SpexTree:
         d["walk_waves"] = d["walk_row_tiles"] // 256
         d["walk_row_tiles"] %= 256
         return d
+
+    def split_form(self) -> int:
+        """How the split path runs the cached plan (for tests): -1 no lists of it, 0 one launch, 1 with one set of
+        registers, 2 row tiles, 3 launches one after another."""
+        form = C.c_int32()
+        _check(lib.spex_tree_split_form(self._h, C.byref(form)))
+        return form.value
 
 
 # ---- functions named like the C entry points ------------------------------------------------

@@ -1213,4 +1213,11 @@ spex_status_t spex_tree_last_launch_info(const spex_tree_t *t, int64_t info[8]) 
   return SPEX_OK;
 }
 
+spex_status_t spex_tree_split_form(const spex_tree_t *t, int32_t *form) {
+  if (!t || !form) return SPEX_ERR_INVALID_ARG;
+  const spex::Plan &pl = t->plan;
+  *form = !pl.valid || !pl.has_split ? -1 : (pl.split_phases && !pl.split_together ? 3 : static_cast<int32_t>(pl.split_form));
+  return SPEX_OK;
+}
+
 }  // extern "C"

@@ -287,6 +287,17 @@ int main() {
   CHECK(mixed(30, 33, span) == kSplitTiles && span[0] == 20 && span[1] == 128, "one group of 132 rows");
   CHECK(mixed(37, 0, span) == kSplitFull, "518 workgroups");
 
+  // requests of more rows than a row block holds (two tiles of 16 a wavefront, four wavefronts) have their block lists cut
+  auto cut = [](int q_len, int Hq, int Hkv) {
+    Forest f(200, 16);
+    f.add(2, 300, 2, 150, q_len);
+    Made m(f, Hq, Hkv);
+    m.planner.ensure_walk(f.pt, &m.plan);
+    CHECK(m.plan.walk_ok && m.plan.walk_row_tiles == 2 && m.plan.walk_waves == 4, "two tiles, four wavefronts");
+    return m.plan.walk_cut;
+  };
+  CHECK(!cut(32, 8, 2) && cut(33, 8, 2), "128 and 132 rows");
+
   // merge workgroups: within 256 threads, every row in one of them, at least half full wherever there are rows enough, the heads of
   // a kv head in equal shares, and no grid dimension but the first beyond 65535
   for (int Hkv : {1, 3, 4, 32})

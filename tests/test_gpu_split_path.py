@@ -9,9 +9,32 @@ import pytest
 import torch
 
 import spex_workloads as sw
-from gpu_common import assert_close, run_gpu, run_oracle, run_oracle_c
+from gpu_common import assert_close, build_gpu_tree, run_gpu, run_oracle, run_oracle_c
 
 pytestmark = pytest.mark.gpu
+THROUGH_LDS, ONE_REGISTER_SET, ROW_TILES, IN_PHASES = range(4)  # SpexTree.split_form
+
+
+def planned_form(wl, **kw):
+    """The form that the split path takes for a workload, from a plan made without a GPU (draft masks do not change it)."""
+    import paper_2605_10195_amd as spex
+    t = spex.SpexTree(wl.num_q_heads, wl.num_kv_heads, wl.head_dim, wl.page_size, wl.q_dtype, wl.kv_dtype, num_pages=wl.peak_pages(),
+                      device="cpu", **kw)
+    sw.replay(wl, t, only_nodes=set())
+    t.plan_dump(wl.leaves, wl.q_lens)
+    form = t.split_form()
+    t.close()
+    return form
+
+
+def run_form(wl, form, **kw):
+    """As run_gpu on the split path, which has to take the form named."""
+    tree = build_gpu_tree(wl, kernel_mode=2, **kw)
+    got = run_gpu(wl, tree=tree)
+    ran = tree.split_form()
+    tree.close()
+    assert ran == form, f"{wl.name}: form {ran}, not {form}"
+    return got
 
 
 # Pieces per row from 1 to some 40 (chunks of one page), head dims whose rows take 10 to 255 threads
@@ -301,13 +324,19 @@ def test_items_of_two_row_tiles_together_and_in_phases(make, more):
     assert_close(run_gpu(wl, kernel_mode=2), run_oracle_c(wl), wl.kv_dtype, wl.name)
 
 
-# More short items than run at a time (512 workgroups, 768 with heads of 64), which the form with one set of K and V
-# registers takes, and fewer; items of one page to 16 and beyond (the other form), of whole and of partial blocks; masks.
+# Short items of one page to 16, of whole and of partial blocks, fewer than run at a time (512 workgroups, 768 with heads of 64) and
+# more: as row tiles, with one set of K and V registers, through LDS and, of the last, in phases.
 @pytest.mark.parametrize("heads,kv_dtype", [((8, 2, 128), "fp8_e4m3"), ((8, 2, 64), "bf16"), ((12, 4, 64), "fp8_e4m3")])
 @pytest.mark.parametrize("trees", [20, 50])
 @pytest.mark.parametrize("step,chunk", [(1, 0), (33, 0), (250, 16), (280, 17), (100, 3)])
 def test_many_short_items(heads, kv_dtype, trees, step, chunk):
     wl = sw.bfs_tot(n_queries=trees, prompt=21, step=step, width=8, keep=8, depth=1, heads=heads, kv_dtype=kv_dtype)
+    form = ROW_TILES if trees == 20 and step <= 250 and step != 100 else ONE_REGISTER_SET
+    if (trees, step, kv_dtype) == (20, 280, "bf16"):
+        form = THROUGH_LDS
+    if (trees, step, heads) == (50, 100, (12, 4, 64)):
+        form = IN_PHASES
+    assert planned_form(wl, prefix_chunk_pages=chunk, suffix_chunk_pages=chunk) == form
     got = run_gpu(wl, kernel_mode=2, prefix_chunk_pages=chunk, suffix_chunk_pages=chunk)
     assert_close(got, run_oracle_c(wl), kv_dtype, f"{heads} {kv_dtype} {trees} {step}")
 
@@ -315,7 +344,35 @@ def test_many_short_items(heads, kv_dtype, trees, step, chunk):
 @pytest.mark.parametrize("heads,kv_dtype", [((8, 2, 128), "fp8_e4m3"), ((8, 2, 64), "bf16")])
 def test_many_short_items_with_draft_masks(heads, kv_dtype):
     wl = sw.tot_with_drafts(n_queries=100, prompt=40, step=19, depth=2, drafts=3, heads=heads, kv_dtype=kv_dtype, token_trees=True)
+    assert planned_form(wl) == ONE_REGISTER_SET
     assert_close(run_gpu(wl, kernel_mode=2), run_oracle_c(wl), kv_dtype, kv_dtype)
+
+
+# The forms on either side of their bounds.  One set of registers: more items than run at a time, none of more than 64 rows,
+# the longest of few rows and of branches 16 pages and not 17; row tiles of fp8: by number and length of the items; through LDS what is beyond, fp8
+# groups of up to 64 and of up to 128 rows, one and both of the lists, at lengths given and at the planner's.
+def _bfs(n, prompt, step, width, heads, kv_dtype="fp8_e4m3", keep=None, depth=1):
+    return sw.bfs_tot(n_queries=n, prompt=prompt, step=step, width=width, keep=keep or width, depth=depth, heads=heads, kv_dtype=kv_dtype)
+
+
+@pytest.mark.parametrize("make,chunks,form", [
+    (lambda: _bfs(20, 21, 256, 16, (8, 2, 128)), (0, 16), ONE_REGISTER_SET), (lambda: _bfs(20, 21, 265, 16, (8, 2, 128)), (0, 17), THROUGH_LDS),
+    (lambda: _bfs(13, 21, 256, 16, (12, 4, 64)), (0, 16), ONE_REGISTER_SET), (lambda: _bfs(13, 21, 265, 16, (12, 4, 64)), (0, 17), THROUGH_LDS),
+    (lambda: _bfs(25, 21, 256, 16, (8, 2, 64), "bf16"), (0, 16), ONE_REGISTER_SET),
+    (lambda: _bfs(25, 21, 265, 16, (8, 2, 64), "bf16"), (0, 17), THROUGH_LDS),
+    (lambda: _bfs(24, 21, 40, 16, (8, 2, 128)), (0, 0), ONE_REGISTER_SET), (lambda: _bfs(70, 300, 40, 4, (8, 2, 128)), (0, 0), ONE_REGISTER_SET),
+    (lambda: _bfs(30, 21, 100, 16, (8, 2, 64)), (0, 0), ONE_REGISTER_SET),
+    (lambda: _bfs(40, 700, 20, 30, (8, 2, 128)), (0, 0), THROUGH_LDS),
+    (lambda: _bfs(36, 200, 20, 32, (8, 2, 128), keep=2, depth=2), (0, 0), THROUGH_LDS),
+    (lambda: _bfs(36, 200, 20, 32, (8, 2, 64), keep=2, depth=2), (0, 0), THROUGH_LDS),
+    (lambda: _bfs(4, 6 * 384, 20, 24, (32, 8, 128)), (24, 0), ROW_TILES), (lambda: _bfs(4, 7 * 384, 20, 24, (32, 8, 128)), (24, 0), THROUGH_LDS),
+    (lambda: _bfs(24, 5 * 384, 20, 16, (8, 2, 64)), (24, 0), ROW_TILES),
+    (lambda: _bfs(24, 7 * 384, 20, 16, (8, 2, 64)), (24, 0), ONE_REGISTER_SET),
+    (lambda: _bfs(8, 16, 20, 16, (8, 2, 128)), (0, 0), ROW_TILES), (lambda: _bfs(16, 16, 20, 16, (8, 2, 128)), (0, 0), ONE_REGISTER_SET)])
+def test_forms_of_the_split_launch_at_their_bounds(make, chunks, form):
+    wl = make()
+    got = run_form(wl, form, prefix_chunk_pages=chunks[0], suffix_chunk_pages=chunks[1])
+    assert_close(got, run_oracle_c(wl), wl.kv_dtype, f"{wl.name} {chunks}")
 
 
 # Prompts shared by 17 to 128 rows and more, as row tiles of 16 and of 32 (20 heads a kv head) in a workgroup each: the last
@@ -326,12 +383,15 @@ def test_many_short_items_with_draft_masks(heads, kv_dtype):
 @pytest.mark.parametrize("prompt,chunk", [(21, 0), (160, 3), (70, 1), (3001, 0)])
 def test_items_of_many_rows_as_row_tiles(heads, kv_dtype, width, prompt, chunk):
     wl = sw.bfs_tot(n_queries=1, prompt=prompt, step=20, width=width, keep=width, depth=1, heads=heads, kv_dtype=kv_dtype)
+    few_rows, many_tiles = width * heads[0] // heads[1] <= 16, (heads[0], width, prompt) == (20, 33, 3001)
+    form = planned_form(wl, prefix_chunk_pages=chunk, suffix_chunk_pages=chunk)
+    assert form == (THROUGH_LDS if few_rows or many_tiles else ROW_TILES)
     got = run_gpu(wl, kernel_mode=2, prefix_chunk_pages=chunk, suffix_chunk_pages=chunk)
     assert_close(got, run_oracle_c(wl), kv_dtype, f"{heads} {kv_dtype} {width} {prompt}")
 
 
-# Either side of 512 row tiles (fp8 of 16 rows 2048, heads of 64 1536): a prompt of 16 leaves takes 4 tiles of 16 rows (two
-# of 32 with drafts' masks) a kv head and each leaf one or two, beyond which the items of many rows go through LDS.
+# Either side of 512 row tiles, and of 992 with fp8 items of 3 pages and heads of 64: a prompt of 16 leaves takes 4 tiles of 16 rows
+# a kv head and each leaf one, with drafts' masks the nodes of 4 leaves take 4 and 2 of 32 and each leaf one; beyond, the items go through LDS.
 @pytest.mark.parametrize("kv_dtype,dim", [("bf16", 128), ("fp8_e4m3", 64)])
 @pytest.mark.parametrize("drafts", [0, 5])
 @pytest.mark.parametrize("n_queries", [12, 13, 24, 26, 27, 38, 39])
@@ -341,6 +401,9 @@ def test_items_of_many_rows_as_row_tiles_and_through_lds(kv_dtype, dim, drafts, 
                                 token_trees=True)
     else:
         wl = sw.bfs_tot(n_queries=n_queries, prompt=40, step=20, width=16, keep=16, depth=1, heads=(8, 2, dim), kv_dtype=kv_dtype)
+    tiles = (24 if drafts else 40) * n_queries <= (992 if kv_dtype == "fp8_e4m3" and not drafts else 512)
+    form = ROW_TILES if tiles else (ONE_REGISTER_SET if kv_dtype == "fp8_e4m3" and not drafts else THROUGH_LDS)
+    assert planned_form(wl) == form
     assert_close(run_gpu(wl, kernel_mode=2), run_oracle_c(wl), kv_dtype, f"{kv_dtype} {drafts} {n_queries}")
 
 
