@@ -12,8 +12,8 @@
 //       private suffix) and a set of query rows.  Items of many rows stage operand images in LDS as
 //       the tree-walk kernel does; items of few rows split their pages between four wavefronts that
 //       stream them from memory to registers (S^T = K Q^T and O^T = V^T P^T with MFMA 16x16x32,
-//       fp32 accumulation).  Small launches, and fp8 ones of middle size, take the row tiles of the first kind the
-//       second way, a workgroup each.  Every item keeps an online softmax per row and emits the partial state
+//       fp32 accumulation).  Small launches, and fp8 ones of middle size whose items are long, take the row tiles of
+//       the first kind the second way, a workgroup each.  Every item keeps an online softmax per row and emits the partial state
 //       (m, l, o); a shared page is read from memory once for all rows below it.
 //   spex_wave_attn_kernel / spex_coop_attn_kernel
 //       The same items in launches of their own, few rows (a wavefront an item) and many, where there
@@ -988,7 +988,9 @@ __device__ __forceinline__ void coop_item(const AttnArgs &p, const Shape &sh, co
 // (heads of 64: five and three).
 // kSplitTiles: for launches that leave the chip room: items of many rows go as row tiles of 16 NT, a workgroup each that
 // splits the pages between its wavefronts, instead of one through LDS, whose blocks follow each other.  The tiles read the
-// pages again, from L2.
+// pages again, from L2 as far as the tiles of an item run on one XCD at one time: tile t of an item is workgroup item + t * items of
+// its list, which is one XCD where the list's items are a multiple of 8.  Bytes past L2 over KV bytes, prompts of 24000 tokens
+// under 63 or 64 rows, fp8: 120 items of 2 and of 4 kv heads 1.07 and 1.06, 96 of 8 kv heads 1.6, 188 of 2 kv heads of 64 2.1.
 template <int KV, int D, int NT, bool TREE, SplitForm FORM>
 __global__ __launch_bounds__(256, split_occupancy(D, FORM)) void spex_split_attn_kernel(AttnArgs p, Shape sh, SplitLists ls) {
   constexpr int kLds = FORM != kSplitTiles && coop_lds_floats<D>() > wave_fold_floats<D>() ? coop_lds_floats<D>() : wave_fold_floats<D>();
