@@ -32,7 +32,8 @@ def source_sha16():
     profiles/ names the hash it was measured at."""
     import hashlib
     h = hashlib.sha256()
-    for rel in ("paper_2605_10195_amd/csrc/kernels.hip", "paper_2605_10195_amd/csrc/planner.cpp"):
+    for rel in ("paper_2605_10195_amd/csrc/kernels.hip", "paper_2605_10195_amd/csrc/planner.cpp",
+                "paper_2605_10195_amd/csrc/launch_shape.hpp"):
         with open(os.path.join(ROOT, rel), "rb") as f:
             h.update(f.read())
     return h.hexdigest()[:16]
